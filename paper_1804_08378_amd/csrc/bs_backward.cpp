@@ -82,12 +82,27 @@ bool walks_rows(const bs_stack *s, const BwdStage &g)
            g.k.W / full <= 64 && g.k.Wo * p.sw == g.k.W && g.k.Ho == (g.k.H + 2 - 3) / p.sh + 1;
 }
 
+// Overlapping 3 x 3 max windows (stride 1 or 2, padding 0 or 1, any plane, any channel count) of channels-last tensors, no
+// Add in the stage: the kernel whose lanes walk strips of columns finds the picks itself.  Measured on MI355X against the
+// kernel that gathers recorded picks, the caller's picks at hand: ResNet stem bfloat16 87 -> 60 us, 192 x 71 x 71 / 2 without
+// padding binary16 55 -> 39 us.  (With Adds in the stage the strips would keep every residual's factors in registers.)
+bool walks_strips(const bs_stack *s, const BwdStage &g)
+{
+    const PoolK &p = g.k.pool;
+    return s->opts.layout == BS_LAYOUT_NHWC && s->opts.lane_exchange >= 0 && g.n_res == 0 &&
+           p.kind == OP_MAXPOOL && p.kh == 3 && p.kw == 3 && p.sh == p.sw && (p.sh == 1 || p.sh == 2) && p.ph == p.pw && p.ph <= 1;
+}
+
 // Stage g = [element-wise list without Add, average pooling 3 x 3 / 1 / 1 that keeps the plane's size] and the stage
 // behind it = [max pooling 3 x 3 / 2 / 1 alone, with the element-wise operations that joined it]: one kernel walks
 // both levels down the plane (rows of whole 4-cell blocks that fit one wave).
 bool walks_two_levels(const bs_stack *s, const BwdStage &g, const BwdStage &nx)
 {
     const PoolK &p = g.k.pool, &q = nx.k.pool;
+    if (s->opts.layout == BS_LAYOUT_NHWC)  // any width, any size of the max pooling's output
+        return g.n_res == 0 && g.k.n_post == 0 && nx.k.n_ew == 0 && g.k.n_ew + nx.k.n_post <= K_BWD_EW && p.kind == OP_AVGSUM &&
+               p.kh == 3 && p.kw == 3 && p.sh == 1 && p.sw == 1 && p.ph == 1 && p.pw == 1 && g.k.Ho == g.k.H && g.k.Wo == g.k.W &&
+               q.sh == 2 && q.ph == 1 && walks_strips(s, nx);
     return s->opts.layout != BS_LAYOUT_NHWC && s->opts.lane_exchange >= 0 && g.n_res == 0 && nx.n_res == 0 && g.k.n_post == 0 &&
            nx.k.n_ew == 0 && g.k.n_ew + nx.k.n_post <= K_BWD_EW && p.kind == OP_AVGSUM && p.kh == 3 && p.kw == 3 && p.sh == 1 &&
            p.sw == 1 && p.ph == 1 && p.pw == 1 && g.k.Ho == g.k.H && g.k.Wo == g.k.W && q.kind == OP_MAXPOOL && q.sh == 2 &&
@@ -183,7 +198,7 @@ extern "C" bs_status bs_stack_plan_backward(bs_stack *stack)
             BwdStage &g = plan->stages[j];
             const BwdStage &nx = plan->stages[j + 1];
             bool plain = nx.k.pool.kind == 0 && nx.n_res == 0 && g.k.n_ew + nx.k.n_ew <= K_BWD_EW;
-            if (!plain || g.k.pool.kind != OP_MAXPOOL || !walks_rows(stack, g)) continue;
+            if (!plain || g.k.pool.kind != OP_MAXPOOL || !(walks_rows(stack, g) || walks_strips(stack, g))) continue;
             for (int32_t q = 0; q < nx.k.n_ew; ++q) g.k.ew[g.k.n_ew + q] = nx.k.ew[q];
             g.k.n_post = nx.k.n_ew;
             g.n_layers += nx.n_layers;
@@ -222,7 +237,25 @@ extern "C" bs_status bs_stack_plan_backward(bs_stack *stack)
                                   g.k.H == 2 * g.k.Ho && g.k.W == 2 * g.k.Wo;
             uint64_t lanes;
             g.k.nhwc = nhwc ? 1 : 0;
-            if (nhwc) {
+            if (nhwc && (g.k.wave_rows == 2 || walks_strips(stack, g))) {
+                // a lane per channel, strip of columns and chunk of window rows; a chunk holds two window rows at least
+                BwdK &k = g.k;
+                const bool two = k.wave_rows == 2;
+                const int32_t q = two ? K_BWD_STRIP2_Q : K_BWD_STRIP_Q, s = two ? 2 : p.sh;
+                k.wave_rows = two ? 2 : 1;
+                g.vec = 1;
+                k.cbs = (k.W + q - 1) / q;
+                const int64_t per_chunk = g.in_shape[0] * k.cbs * k.C, rows = (k.H + s - 1) / s;
+                int64_t chunks = two ? (K_BWD_STRIP2_LANES + per_chunk - 1) / per_chunk : K_BWD_STRIP_LANES / per_chunk;
+                chunks = std::max<int64_t>(1, std::min(chunks, (rows + 1) / 2));
+                k.rc = (int32_t)((rows + chunks - 1) / chunks);
+                k.chunks = (int32_t)((rows + k.rc - 1) / k.rc);
+                k.units = 0;
+                k.div_wv = make_fastdiv((uint32_t)k.C);
+                k.div_cbs = make_fastdiv((uint32_t)k.cbs);
+                k.div_chunks = make_fastdiv((uint32_t)k.chunks);
+                lanes = (uint64_t)per_chunk * (uint64_t)k.chunks;
+            } else if (nhwc) {
                 // a lane per pixel (per window when 2 x 2 windows tile the plane) and channel vector
                 g.vec = g.k.C % full == 0 ? full : 1;
                 // (with two or more Adds in the stage the window-owning kernel would keep 4 pixels x vec channels of
@@ -289,7 +322,7 @@ extern "C" bs_status bs_stack_plan_backward(bs_stack *stack)
             g.k.div_c = make_fastdiv((uint32_t)g.k.C);
             g.threads = 256;
             g.grid = (int64_t)((lanes + 255) / 256);
-            if (g.k.wave_rows) g.grid = ((int64_t)g.k.units + 4 * g.k.spw - 1) / (4 * g.k.spw);  // whole segments per wave
+            if (g.k.wave_rows && !nhwc) g.grid = ((int64_t)g.k.units + 4 * g.k.spw - 1) / (4 * g.k.spw);  // whole segments per wave
             const bool is_max = p.kind == OP_MAXPOOL && !g.k.direct && !g.k.wave_rows;  // recorded picks needed
             // the buffers are sized by these shapes: a stage must end where the next one begins
             const int64_t *next = j + 1 < S ? plan->stages[j + 1].in_shape : stack->out_shape;

@@ -19,41 +19,10 @@
 // Traffic: the stage input and the gradients in and out move once; the upstream gradient and
 // the picks of overlapping windows are re-read from cache.
 #include "bs_xrows_device.h"
+#include "bs_bwd_device.h"
 #include "bs_internal.h"
 
 namespace bs {
-
-
-// Build with -DBS_BWD_AUDIT to check every element offset into the stage input, the upstream gradient and the
-// input gradient against the extents the host passes (k.audit_lim[0..2], in elements) before it is used: an
-// offset outside is counted in k.audit[site] and replaced by 0, so such a build cannot read or write outside
-// those tensors.  Without the macro the checks compile to nothing.
-#if defined(BS_BWD_AUDIT)
-BS_DEV uint32_t audited(const BwdK &k, int which, int site, uint32_t off, uint32_t n)
-{
-    if (k.audit && (uint64_t)off + n > k.audit_lim[which]) {
-        atomicAdd(&k.audit[site], 1u);
-        return 0u;
-    }
-    return off;
-}
-#else
-BS_DEV uint32_t audited(const BwdK &, int, int, uint32_t off, uint32_t) { return off; }
-#endif
-
-// float32 reciprocal of the divisor of the average pooling window (oh, ow): the forward
-// kernels' rule (0: in-range cells, 1: kh * kw, 2: cells inside the padded plane).
-BS_DEV float bwd_avg_inv(const PoolK &p, int32_t H, int32_t W, int32_t oh, int32_t ow)
-{
-    if (p.count_include_pad == 1) return p.inv_kk;
-    const int32_t h0 = oh * p.sh - p.ph, w0 = ow * p.sw - p.pw;
-    if (p.count_include_pad == 2) {
-        const int32_t nr = min(h0 + p.kh, H + p.ph) - h0, nc = min(w0 + p.kw, W + p.pw) - w0;
-        return 1.0f / (float)max(nr * nc, 1);
-    }
-    const int32_t nr = min(h0 + p.kh, H) - max(h0, 0), nc = min(w0 + p.kw, W) - max(w0, 0);
-    return 1.0f / (float)max(nr * nc, 1);
-}
 
 // Forward pass of the stage's element-wise list on R register rows of VEC cells each (row j
 // starts at element offset off[j] and lies in channel c[j]), collecting for every cell the
@@ -1146,6 +1115,7 @@ bs_status launch_backward_stage(const BwdK &k, int32_t dtype, int32_t vec, int64
     // a stage without Add gets the instances that keep no residual gradients in registers
     int32_t n_add = 0;
     for (int32_t j = 0; j < k.n_ew; ++j) n_add += k.ew[j].kind == OP_ADD;
+    if (k.nhwc && k.wave_rows) return launch_backward_strips(k, dtype, vec, grid, threads, stream);
     if (k.nhwc) {
         // a lane per (pixel or window, channel vector): the divisors must be the ones the kernels assume
         if ((vec != 1 && vec != full) || k.C % vec != 0 || (int64_t)k.div_wv.d * vec != k.C ||

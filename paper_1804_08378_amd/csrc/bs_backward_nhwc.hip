@@ -1,0 +1,752 @@
+// Backward kernels of channels-last (N, H, W, C in memory) stages with overlapping 3 x 3 pooling windows: no recorded
+// picks, no recomputation pass, nothing through the workspace.
+//
+// A lane owns V channels of a strip of Q pixel columns and walks down a chunk of rows.  The lanes of a wave are neighbouring
+// channels (then neighbouring strips), so every access of a wave is contiguous; the columns a strip's windows reach into
+// beside it are read and computed by the lane itself -- they come from the caches, and no lane waits for another one: no
+// LDS, no barrier, no lane exchange, any width and any channel count.  V = 1: two channels per lane (16-bit storage) measured
+// the same in the one-level kernel and spill in the two-level one.
+//
+// Work-groups are numbered so that each XCD gets one contiguous part of the image (xcd_contiguous): the strips that share
+// columns find them in one L2.
+#include <hip/hip_runtime.h>
+
+#include <algorithm>
+#include <type_traits>
+#include <utility>
+
+#include "bs_bwd_device.h"
+#include "bs_internal.h"
+
+namespace bs {
+namespace {
+
+template <int DT>
+constexpr int elem_bytes() { return DT == DT_F32 ? 4 : 2; }
+
+// f(integral_constant<0>), f(integral_constant<1>) ...
+template <int... B, typename F>
+BS_DEV void each_of(std::integer_sequence<int, B...>, F f)
+{
+    (f(std::integral_constant<int, B>{}), ...);
+}
+
+constexpr bool ends_in_relu(int code) { return code > 0 && ew_code_kind(code, ew_code_len(code) - 1) == OP_RELU; }
+
+// V elements at byte offset `off`.  OFF: uint32_t where every tensor of the launch is below 4 GiB (one address addition
+// per access: the base stays in scalar registers), else uint64_t.
+template <int DT, int V, typename OFF>
+BS_DEV void load_at(const BwdK &k, int which, int site, const void *base, OFF off, float *v)
+{
+#if defined(BS_BWD_AUDIT)
+    if constexpr (sizeof(OFF) == 4) off = audited(k, which, site, off / elem_bytes<DT>(), V) * elem_bytes<DT>();
+#endif
+    float u[V];
+    Raw<DT, V> r;
+    r.q = *reinterpret_cast<const typename Raw<DT, V>::type *>(static_cast<const char *>(base) + off);
+    unpack<DT, V>(r, u);
+#pragma unroll
+    for (int e = 0; e < V; ++e) v[e] = u[e];
+}
+
+template <int DT, int V, typename OFF>
+BS_DEV void store_at(const BwdK &k, int site, void *base, OFF off, const float (&v)[V])
+{
+#if defined(BS_BWD_AUDIT)
+    if constexpr (sizeof(OFF) == 4) off = audited(k, 2, site, off / elem_bytes<DT>(), V) * elem_bytes<DT>();
+#endif
+    store_elems<DT, V>(static_cast<char *>(base) + off, 0, v);
+}
+
+// N pixels of a row at byte offsets row + col[j].
+template <int DT, int V, int N, typename OFF>
+BS_DEV void load_row(const BwdK &k, int which, int site, const void *base, OFF row, const OFF (&col)[N], float *v)
+{
+#pragma unroll
+    for (int j = 0; j < N; ++j) load_at<DT, V, OFF>(k, which, site, base, row + col[j], v + j * V);
+}
+
+// N pixels of a row of the input gradient, `pitch` bytes apart; whole: all of them lie in the plane.
+template <int DT, int V, int N, typename OFF>
+BS_DEV void store_row(const BwdK &k, int site, OFF at, int32_t first, int32_t width, OFF pitch, bool whole, const float (&v)[N * V])
+{
+    auto pixel = [&](int j) __attribute__((always_inline)) {
+        float u[V];
+#pragma unroll
+        for (int e = 0; e < V; ++e) u[e] = v[j * V + e];
+        store_at<DT, V, OFF>(k, site, k.g_in, at + (OFF)j * pitch, u);
+    };
+    if (whole) {
+#pragma unroll
+        for (int j = 0; j < N; ++j) pixel(j);
+    } else {
+#pragma unroll
+        for (int j = 0; j < N; ++j)
+            if (first + j < width) pixel(j);
+    }
+}
+
+// The compare-and-select steps below are written out so that the comparison's lane mask stays in VCC: left to the compiler the
+// masks go through scalar register pairs, whose selects issue at half the rate and need wait states behind the compare.
+// max(x, 0): NaN and -0 give +0.  (The builtin first canonicalises values that come out of a conversion.)
+BS_DEV float relu(float x)
+{
+    float y;
+    asm("v_max_f32_e32 %0, 0, %1" : "=v"(y) : "v"(x));
+    return y;
+}
+// v > best: best = v, at = AT
+template <int AT>
+BS_DEV void take_if_more(float v, float &best, int32_t &at)
+{
+    asm("v_cmp_gt_f32_e32 vcc, %2, %0\n\tv_max_f32_e32 %0, %0, %2\n\tv_cndmask_b32_e64 %1, %1, %3, vcc"
+        : "+v"(best), "+v"(at)
+        : "v"(v), "n"(AT)
+        : "vcc");
+}
+// The first maximum of a, b, c (codes A, A + 1, A + 2).
+template <int A>
+BS_DEV void first_max3(float a, float b, float c, float &best, int32_t &at)
+{
+    asm("v_cmp_gt_f32_e32 vcc, %3, %2\n\tv_max_f32_e32 %0, %3, %2\n\tv_cndmask_b32_e64 %1, %5, %6, vcc\n\t"
+        "v_cmp_gt_f32_e32 vcc, %4, %0\n\tv_max_f32_e32 %0, %0, %4\n\tv_cndmask_b32_e64 %1, %1, %7, vcc"
+        : "=&v"(best), "=&v"(at)
+        : "v"(a), "v"(b), "v"(c), "n"(A), "n"(A + 1), "n"(A + 2)
+        : "vcc");
+}
+// v > best: best = v, at = c
+BS_DEV void take_if_more(float v, int32_t c, float &best, int32_t &at)
+{
+    asm("v_cmp_gt_f32_e32 vcc, %2, %0\n\tv_max_f32_e32 %0, %0, %2\n\tv_cndmask_b32_e32 %1, %1, %3, vcc"
+        : "+v"(best), "+v"(at)
+        : "v"(v), "v"(c)
+        : "vcc");
+}
+// at == AT: sum += g
+template <int AT, bool FIRST>
+BS_DEV void add_if_at(int32_t at, float g, float &sum)
+{
+    if constexpr (FIRST) {  // nothing there yet
+        asm("v_cmp_eq_u32_e32 vcc, %3, %1\n\tv_cndmask_b32_e32 %0, 0, %2, vcc" : "=&v"(sum) : "v"(at), "v"(g), "n"(AT) : "vcc");
+        return;
+    }
+    float t;
+    asm("v_cmp_eq_u32_e32 vcc, %4, %2\n\tv_cndmask_b32_e32 %1, 0, %3, vcc\n\tv_add_f32_e32 %0, %0, %1"
+        : "+v"(sum), "=&v"(t)
+        : "v"(at), "v"(g), "n"(AT)
+        : "vcc");
+}
+
+// An element-wise list on N pixels of V channels (pixel-major), with the product t of its derivatives: float32, rounded
+// to the storage type after every layer, as the forward kernels compute it.  CODE >= 0: the kinds are compile-time
+// (base-K_EW_BASE digits) and BatchNorm's parameters of the lane's channels are read once, in front of the row loop;
+// -1: kinds and parameters are read at every use.
+template <int DT, int V, int CODE>
+struct StripList {
+    static constexpr int L = CODE > 0 ? ew_code_len(CODE) : 0;
+    float sc[L ? L : 1][V], sh[L ? L : 1][V];
+    int32_t first, count, c0;
+
+    BS_DEV void load(const BwdK &k, int32_t c, int32_t f, int32_t n)
+    {
+        first = f;
+        count = n;
+        c0 = c;
+#pragma unroll
+        for (int q = 0; q < L; ++q)
+            if (ew_code_kind(CODE, q) == OP_BN)
+#pragma unroll
+                for (int e = 0; e < V; ++e) {
+                    sc[q][e] = k.params[k.ew[f + q].arg + c + e];
+                    sh[q][e] = k.params[k.ew[f + q].arg + k.C + c + e];
+                }
+    }
+
+    template <int N>
+    BS_DEV void one(const BwdK &k, int32_t kind, int32_t arg, const float (&a)[V], const float (&b)[V], float (&x)[N], float (&t)[N]) const
+    {
+        if (kind == OP_BN) {
+#pragma unroll
+            for (int i = 0; i < N; ++i) {
+                x[i] = __builtin_fmaf(x[i], a[i % V], b[i % V]);
+                t[i] *= a[i % V];
+            }
+            round_store_all<DT, N>(x);
+        } else if (kind == OP_RELU) {
+#pragma unroll
+            for (int i = 0; i < N; ++i) {
+                t[i] = x[i] > 0.0f ? t[i] : 0.0f;
+                x[i] = relu(x[i]);
+            }
+        } else if (kind == OP_LEAKY) {
+            const float slope = k.params[arg];
+#pragma unroll
+            for (int i = 0; i < N; ++i) {
+                t[i] *= x[i] > 0.0f ? 1.0f : slope;
+                x[i] = round_store<DT>(x[i] > 0.0f ? x[i] : x[i] * slope);
+            }
+        } else {  // OP_CLAMP: the gradient passes where lo <= x <= hi
+            const float lo = k.params[arg], hi = k.params[arg + 1];
+#pragma unroll
+            for (int i = 0; i < N; ++i) {
+                t[i] = x[i] >= lo && x[i] <= hi ? t[i] : 0.0f;
+                x[i] = round_store<DT>(__builtin_fminf(__builtin_fmaxf(x[i], lo), hi));
+            }
+        }
+    }
+
+    template <int N>
+    BS_DEV void apply(const BwdK &k, float (&x)[N], float (&t)[N]) const
+    {
+        static_assert(N % V == 0, "whole pixels");
+#pragma unroll
+        for (int i = 0; i < N; ++i) t[i] = 1.0f;
+        if constexpr (CODE >= 0) {
+#pragma unroll
+            for (int q = 0; q < L; ++q) one<N>(k, ew_code_kind(CODE, q), k.ew[first + q].arg, sc[q], sh[q], x, t);
+        } else {
+#pragma clang loop unroll(disable)
+            for (int32_t q = first; q < first + count; ++q) {
+                const int32_t kind = k.ew[q].kind, arg = k.ew[q].arg;
+                float a[V] = {}, b[V] = {};
+                if (kind == OP_BN)
+#pragma unroll
+                    for (int e = 0; e < V; ++e) {
+                        a[e] = k.params[arg + c0 + e];
+                        b[e] = k.params[arg + k.C + c0 + e];
+                    }
+                one<N>(k, kind, arg, a, b, x, t);
+            }
+        }
+    }
+};
+
+// The lane's place: total = images * chunks * strips * (C / V), channel vectors fastest.
+struct StripLane {
+    bool live;
+    uint32_t n;
+    int32_t chunk, q0, c0;
+};
+
+template <int V, int Q>
+BS_DEV StripLane strip_lane(const BwdK &k)
+{
+    StripLane L;
+    uint32_t i = xcd_contiguous(blockIdx.x, gridDim.x) * 256u + threadIdx.x;
+    L.live = i < k.total;
+    i = L.live ? i : 0u;
+    const uint32_t u = fdiv(i, k.div_wv);
+    L.c0 = (int32_t)(i - u * k.div_wv.d) * V;
+    const uint32_t v = fdiv(u, k.div_cbs);
+    L.q0 = (int32_t)(u - v * k.div_cbs.d) * Q;
+    L.n = fdiv(v, k.div_chunks);
+    L.chunk = (int32_t)(v - L.n * k.div_chunks.d);
+    return L;
+}
+
+// Row maxima of N adjacent windows (S columns apart) of window row DH: value and code 3 * DH + window column of the first
+// one.  A column outside the plane holds -infinity.  Window LEAD begins one column left of the plane when `lead` is set
+// (padding): its scan starts at column 1, so that a window of nothing but -infinity picks its first cell inside.  NaN is
+// never a maximum.
+// NONAN: no value is NaN (a ReLU stands in front).
+template <int V, int S, int N, int CW, int DH, int LEAD, bool NONAN>
+BS_DEV void row_maxima(const float (&y)[CW * V], bool lead, float (&m)[N * V], int32_t (&code)[N * V])
+{
+#pragma unroll
+    for (int b = 0; b < N; ++b)
+#pragma unroll
+        for (int e = 0; e < V; ++e) {
+            const float first = NONAN ? y[b * S * V + e] : __builtin_fmaxf(y[b * S * V + e], -INFINITY);
+            if (LEAD == b) {
+                float best = first;
+                int32_t at = lead ? 3 * DH + 1 : 3 * DH;
+                take_if_more<3 * DH + 1>(y[(b * S + 1) * V + e], best, at);
+                take_if_more<3 * DH + 2>(y[(b * S + 2) * V + e], best, at);
+                m[b * V + e] = best;
+                code[b * V + e] = at;
+            } else {
+                first_max3<3 * DH>(first, y[(b * S + 1) * V + e], y[(b * S + 2) * V + e], m[b * V + e], code[b * V + e]);
+            }
+        }
+}
+
+// The windows' picks from the row maxima of their three rows.  top: the first window row lies above the plane (padding, all
+// -infinity) and must not be picked, not even by a window of nothing but -infinity.
+template <int N>
+BS_DEV void combine_rows(const float (&m0)[N], const int32_t (&code0)[N], const float (&m1)[N], const int32_t (&code1)[N], const float (&m2)[N],
+                         const int32_t (&code2)[N], bool top, float (&best)[N], int32_t (&pick)[N])
+{
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+        best[i] = m0[i];
+        pick[i] = top ? code1[i] : code0[i];
+        take_if_more(m1[i], code1[i], best[i], pick[i]);
+        take_if_more(m2[i], code2[i], best[i], pick[i]);
+    }
+}
+
+// sum[window row][column] += the gradients of the windows that picked the cell, left windows first: window b begins at column
+// X0 + b * S of the strip's G columns.  Rows FRESH, FRESH + 1 ... hold nothing yet: their first window writes.
+template <int V, int S, int N, int X0, int G, int FRESH>
+BS_DEV void scatter(const int32_t (&pick)[N * V], const float (&g)[N * V], float (&sum0)[G * V], float (&sum1)[G * V], float (&sum2)[G * V])
+{
+    auto cell = [&](auto dh_tag, auto dw_tag, auto b_tag) __attribute__((always_inline)) {
+        constexpr int dh = decltype(dh_tag)::value, dw = decltype(dw_tag)::value, b = decltype(b_tag)::value, col = X0 + b * S + dw;
+        // the first window over this column: the smallest b with X0 + b * S + 2 >= col
+        constexpr int b0 = col - 2 - X0 <= 0 ? 0 : (col - 2 - X0 + S - 1) / S;
+        if constexpr (col >= 0 && col < G) {
+#pragma unroll
+            for (int e = 0; e < V; ++e)
+                add_if_at<3 * dh + dw, (dh >= FRESH && b == b0)>(pick[b * V + e], g[b * V + e],
+                                                                 (dh == 0 ? sum0 : dh == 1 ? sum1 : sum2)[col * V + e]);
+        }
+    };
+    auto window = [&](auto dh_tag, auto b_tag) __attribute__((always_inline)) {
+        cell(dh_tag, std::integral_constant<int, 0>{}, b_tag);
+        cell(dh_tag, std::integral_constant<int, 1>{}, b_tag);
+        cell(dh_tag, std::integral_constant<int, 2>{}, b_tag);
+    };
+    auto row = [&](auto dh_tag) __attribute__((always_inline)) {
+        each_of(std::make_integer_sequence<int, N>{}, [&](auto b_tag) __attribute__((always_inline)) { window(dh_tag, b_tag); });
+    };
+    row(std::integral_constant<int, 0>{});
+    row(std::integral_constant<int, 1>{});
+    row(std::integral_constant<int, 2>{});
+}
+
+// =============================================================================
+// bwd_strip_kernel: [list, max pooling 3 x 3 with stride S = 1 or 2 and padding P = 0 or 1, list] (the ResNet and Inception
+// stems, the pools of SqueezeNet and AlexNet).  Per window row the lane reads S new input rows, finds the row maxima
+// of its windows in each (a row two window rows share is scanned once), combines three of them into the windows' picks,
+// adds the windows' gradients -- times the trailing list's derivative at the maximum -- to the picked cells and writes
+// the S rows no later window reaches.  A cell sums its windows in row-major window order.
+// PRE, POST: codes of the lists, or -1.
+// Measured on MI355X, us of a call with the caller's picks at hand, gathering kernel -> this one: ResNet stem 64 x 64 x 112 x 112
+// float32 105 -> 98 (4.7 TB/s of input, gradients in and out: waits for memory), bfloat16 87 -> 60 (vector instructions: 34
+// per cell, 70 % of the time); 32 x 192 x 71 x 71 / 2 without padding binary16 55 -> 39; without kept picks the gathering
+// kernel needs a forward pass on top.
+// =============================================================================
+template <int DT, int V, int Q, int S, int P, int PRE, int POST, typename OFF>
+__global__ __launch_bounds__(256) void bwd_strip_kernel(const BwdK k)
+{
+    static_assert(Q % S == 0 && (S == 1 || S == 2) && (P == 0 || P == 1), "compiled windows");
+    constexpr int OW0 = -((2 - P) / S);            // first window over the strip: q0 / S + OW0 = ceil((q0 + P - 2) / S)
+    constexpr int NW = (Q + 1) / S + 1;            // windows over the strip
+    constexpr int X0 = OW0 * S - P;                // their first column, from q0
+    constexpr int CW = (NW - 1) * S + 3;           // their columns
+    constexpr int KEEP = 3 - S, ES = elem_bytes<DT>();
+    constexpr int OEND = (P + S - 1) / S;
+    const StripLane L = strip_lane<V, Q>(k);
+
+    const OFF pa = (OFF)(k.C + k.a_extra) * ES, pg = (OFF)(k.C + k.gout_extra) * ES, pi = (OFF)(k.C + k.gin_extra) * ES;
+    const OFF abase = (OFF)(L.n * (uint32_t)(k.H * k.W)) * pa + (OFF)L.c0 * ES;
+    const OFF gbase = (OFF)(L.n * (uint32_t)(k.Ho * k.Wo)) * pg + (OFF)L.c0 * ES;
+    const OFF ibase = ((OFF)(L.n * (uint32_t)(k.H * k.W)) + (OFF)L.q0) * pi + (OFF)L.c0 * ES;
+    const OFF arow = (OFF)k.W * pa, grow = (OFF)k.Wo * pg, irow = (OFF)k.W * pi;
+    const int32_t x0 = L.q0 + X0, ow0 = L.q0 / S + OW0;
+    constexpr int LEAD = P == 1 ? -OW0 : -1;
+    const bool lead = L.q0 == 0;
+    OFF acol[CW], gcol[NW];
+    bool win[NW];
+#pragma unroll
+    for (int j = 0; j < CW; ++j) acol[j] = (OFF)min(max(x0 + j, 0), k.W - 1) * pa;  // outside the plane: a safe column, replaced below
+#pragma unroll
+    for (int b = 0; b < NW; ++b) {
+        win[b] = ow0 + b >= 0 && ow0 + b < k.Wo;
+        gcol[b] = (OFF)min(max(ow0 + b, 0), k.Wo - 1) * pg;
+    }
+    const bool inside = x0 >= 0 && x0 + CW <= k.W, whole = L.q0 + Q <= k.W;
+
+    StripList<DT, V, PRE> pre;
+    StripList<DT, V, POST> post;
+    pre.load(k, L.c0, 0, k.n_ew);
+    post.load(k, L.c0, k.n_ew, k.n_post);
+
+    const int32_t r_lo = L.chunk * k.rc * S, r_hi = min(r_lo + k.rc * S, k.H);  // rows this chunk writes
+    const int32_t oh_first = L.chunk * k.rc + OW0;
+    float m[3][NW * V], s[3][Q * V], t[3][Q * V];
+    int32_t code[3][NW * V];
+    // rows are requested in order, `at` = the offset of row `next` (clamped to the plane)
+    int32_t next = oh_first * S - P;
+    OFF at = abase + (OFF)min(max(next, 0), k.H - 1) * arow;
+    OFF gat = gbase + (OFF)min(max(oh_first, 0), k.Ho - 1) * grow;
+    OFF iat = ibase + (OFF)r_lo * irow;
+    // the next N rows -> ring slots slots(0) .. slots(N - 1), scanned as window rows DH0, DH0 + 1 ...
+    auto take_rows = [&](auto n_tag, auto dh_tag, auto slot_of) __attribute__((always_inline)) {
+        constexpr int N = decltype(n_tag)::value, DH0 = decltype(dh_tag)::value;
+        float x[N * CW * V], d[N * CW * V];
+        bool ok[N];
+#pragma unroll
+        for (int j = 0; j < N; ++j) {
+            ok[j] = next >= 0 && next < k.H;
+            load_row<DT, V, CW, OFF>(k, 0, 40, k.a, at, acol, &x[j * CW * V]);
+            at += next >= 0 && next < k.H - 1 ? arow : (OFF)0;
+            ++next;
+        }
+        pre.template apply<N * CW * V>(k, x, d);
+        each_of(std::make_integer_sequence<int, N>{}, [&](auto j_tag) __attribute__((always_inline)) {
+            constexpr int j = decltype(j_tag)::value, dh = DH0 + j;
+            const int slot = slot_of(j);
+            float y[CW * V];
+#pragma unroll
+            for (int i = 0; i < CW * V; ++i) y[i] = x[j * CW * V + i];
+            if (!(inside && ok[j])) {
+#pragma unroll
+                for (int i = 0; i < CW * V; ++i) {
+                    const int32_t c = x0 + i / V;
+                    y[i] = ok[j] && c >= 0 && c < k.W ? y[i] : -INFINITY;
+                }
+            }
+            row_maxima<V, S, NW, CW, dh, LEAD, ends_in_relu(PRE)>(y, lead, m[slot], code[slot]);
+#pragma unroll
+            for (int i = 0; i < Q * V; ++i) {
+                t[slot][i] = d[(j * CW - X0) * V + i];
+                if (dh < KEEP) s[slot][i] = 0.0f;
+            }
+        });
+    };
+    if constexpr (KEEP > 0) take_rows(std::integral_constant<int, KEEP>{}, std::integral_constant<int, 0>{}, [](int j) { return j; });
+
+    int32_t oh = oh_first;
+    // one window row; its three rows are in ring slots R0 (stride 2: two rows are new, the third's slot and the first's change
+    // roles from one window row to the next; stride 1: the rows move up)
+    auto step = [&](auto par) __attribute__((always_inline)) {
+        constexpr int R0 = decltype(par)::value ? 2 : 0, R2 = 2 - R0;
+        const int32_t hA = oh * S - P;
+        const bool row_ok = oh >= 0 && oh < k.Ho;
+        float g[NW * V];
+        load_row<DT, V, NW, OFF>(k, 1, 41, k.g_out, gat, gcol, g);
+        gat += oh >= 0 && oh < k.Ho - 1 ? grow : (OFF)0;
+        take_rows(std::integral_constant<int, S>{}, std::integral_constant<int, KEEP>{}, [](int j) { return KEEP + j == 2 ? R2 : KEEP + j; });
+        float best[NW * V];
+        int32_t pick[NW * V];
+        combine_rows<NW * V>(m[R0], code[R0], m[1], code[1], m[R2], code[R2], hA < 0, best, pick);
+#pragma unroll
+        for (int i = 0; i < NW * V; ++i) g[i] = row_ok && win[i / V] ? g[i] : 0.0f;  // windows that do not exist give nothing
+        if constexpr (POST != 0) {
+            float tp[NW * V];
+            post.template apply<NW * V>(k, best, tp);
+#pragma unroll
+            for (int i = 0; i < NW * V; ++i) g[i] *= tp[i];
+        }
+        scatter<V, S, NW, X0, Q, KEEP>(pick, g, s[R0], s[1], s[R2]);
+        // the S rows no later window row holds are complete
+#pragma unroll
+        for (int d = 0; d < S; ++d) {
+            const int32_t row = hA + d;
+            const int slot = d == 0 ? R0 : 1;
+            if (L.live && row >= r_lo && row < r_hi) {
+                float v[Q * V];
+#pragma unroll
+                for (int i = 0; i < Q * V; ++i) v[i] = s[slot][i] * t[slot][i];
+                store_row<DT, V, Q, OFF>(k, 42, iat, L.q0, k.W, pi, whole, v);
+                iat += irow;
+            }
+        }
+        if constexpr (S == 2) {
+#pragma unroll
+            for (int i = 0; i < NW * V; ++i) code[R2][i] -= 6;
+        } else {
+#pragma unroll
+            for (int d = 0; d < KEEP; ++d) {
+#pragma unroll
+                for (int i = 0; i < NW * V; ++i) {
+                    m[d][i] = m[d + 1][i];
+                    code[d][i] = code[d + 1][i] - 3;
+                }
+#pragma unroll
+                for (int i = 0; i < Q * V; ++i) {
+                    s[d][i] = s[d + 1][i];
+                    t[d][i] = t[d + 1][i];
+                }
+            }
+        }
+        ++oh;
+    };
+    const int32_t oh_end = oh_first + k.rc + OEND - OW0;  // as many window rows for every lane
+    for (;;) {
+        step(std::integral_constant<int, 0>{});
+        if (oh == oh_end) break;
+        if constexpr (S == 2) {
+            step(std::integral_constant<int, 1>{});
+            if (oh == oh_end) break;
+        }
+    }
+}
+
+// =============================================================================
+// bwd_strip2_kernel: [list, average pooling 3 x 3 / 1 / 1] and [max pooling 3 x 3 / 2 / 1, list] in one kernel; the plane
+// between the poolings and its gradient (float32) stay in registers.  Per window row `oh` of the max pooling a lane
+//   1. reads the input rows 2 oh + 1, 2 oh + 2 and applies the leading list (values y, derivatives T),
+//   2. forms rows 2 oh, 2 oh + 1 of the average's output in the forward kernels' arithmetic (row-major sum from +0, times
+//      the divisor's reciprocal, rounded to storage) and their windows' row maxima,
+//   3. combines rows 2 oh - 1 .. 2 oh + 1 into the picks and adds the upstream gradients, scaled by the trailing list's
+//      derivative at the maximum, to the picked cells,
+//   4. average rows 2 oh - 1, 2 oh can get nothing more: their gradients times the divisor's reciprocal, summed over the
+//      three windows of the row that hold a cell (rows of hs),
+//   5. writes the input gradient of rows 2 oh - 2, 2 oh - 1: hs of the rows above, at and below, times T.
+// Q columns need Q + 2 of the average's gradient, Q / 2 + 2 windows, Q + 5 averages and Q + 7 inputs.
+// INC: every divisor is 9 (count_include_pad, nothing overhangs).
+// Measured on MI355X (halo_stress, us of a call): three stages with two forward passes through the workspace -> this kernel:
+// float32 510 -> 109, bfloat16 390 -> 116.  Bound by vector instructions (the 18 additions per average and their halo, the
+// scans); two waves per SIMD with 8 columns beat four with 4 columns, which compute 9 averages per 4 columns instead of
+// 13 per 8.
+// =============================================================================
+template <int DT, int V, int Q, bool INC, int PRE, int POST, typename OFF>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) void bwd_strip2_kernel(const BwdK k)
+{
+    static_assert(Q % 2 == 0, "whole windows");
+    constexpr int NW = Q / 2 + 2, CA = Q + 5, CX = Q + 7, CG = Q + 2, ES = elem_bytes<DT>();
+    const StripLane L = strip_lane<V, Q>(k);
+
+    const OFF pa = (OFF)(k.C + k.a_extra) * ES, pg = (OFF)(k.C + k.gout_extra) * ES, pi = (OFF)(k.C + k.gin_extra) * ES;
+    const OFF abase = (OFF)(L.n * (uint32_t)(k.H * k.W)) * pa + (OFF)L.c0 * ES;
+    const OFF gbase = (OFF)(L.n * (uint32_t)(k.Ho * k.Wo)) * pg + (OFF)L.c0 * ES;
+    const OFF ibase = ((OFF)(L.n * (uint32_t)(k.H * k.W)) + (OFF)L.q0) * pi + (OFF)L.c0 * ES;
+    const OFF arow = (OFF)k.W * pa, grow = (OFF)k.Wo * pg, irow = (OFF)k.W * pi;
+    const int32_t x0 = L.q0 - 4, ow0 = L.q0 / 2 - 1;
+    const bool lead = L.q0 == 0;
+    OFF acol[CX], gcol[NW];
+    bool win[NW];
+#pragma unroll
+    for (int j = 0; j < CX; ++j) acol[j] = (OFF)min(max(x0 + j, 0), k.W - 1) * pa;  // outside the plane: a safe column, replaced below
+#pragma unroll
+    for (int b = 0; b < NW; ++b) {
+        win[b] = ow0 + b >= 0 && ow0 + b < k.Wo;
+        gcol[b] = (OFF)min(max(ow0 + b, 0), k.Wo - 1) * pg;
+    }
+    const bool inside = x0 >= 0 && x0 + CX <= k.W, whole = L.q0 + Q <= k.W;
+
+    StripList<DT, V, PRE> pre;
+    StripList<DT, V, POST> post;
+    pre.load(k, L.c0, 0, k.n_ew);
+    post.load(k, L.c0, k.n_ew, k.n_post);
+
+    const int32_t r_lo = L.chunk * k.rc * 2, r_hi = min(r_lo + k.rc * 2, k.H);
+    const int32_t oh_first = L.chunk * k.rc - 1;
+
+    float y[4][CX * V], T[5][Q * V], m[3][NW * V], gt[3][CG * V], hs[4][Q * V];
+    int32_t code[3][NW * V];
+    // rows are requested in order, `at` = the offset of row `next` (clamped to the plane)
+    int32_t next = oh_first * 2 - 2;
+    OFF at = abase + (OFF)min(max(next, 0), k.H - 1) * arow;
+    OFF gat = gbase + (OFF)min(max(oh_first, 0), k.Ho - 1) * grow;
+    OFF iat = ibase + (OFF)r_lo * irow;
+    // the next N rows: leading list -> y (outside the plane +0, the average's padding), derivatives -> T
+    auto take_rows = [&](auto n_tag, int slot, int tslot) __attribute__((always_inline)) {
+        constexpr int N = decltype(n_tag)::value;
+        float x[N * CX * V], d[N * CX * V];
+        bool ok[N];
+#pragma unroll
+        for (int j = 0; j < N; ++j) {
+            ok[j] = next >= 0 && next < k.H;
+            load_row<DT, V, CX, OFF>(k, 0, 43, k.a, at, acol, &x[j * CX * V]);
+            at += next >= 0 && next < k.H - 1 ? arow : (OFF)0;
+            ++next;
+        }
+        pre.template apply<N * CX * V>(k, x, d);
+#pragma unroll
+        for (int j = 0; j < N; ++j) {
+#pragma unroll
+            for (int i = 0; i < CX * V; ++i) y[slot + j][i] = x[j * CX * V + i];
+            if (!(inside && ok[j])) {
+#pragma unroll
+                for (int i = 0; i < CX * V; ++i) {
+                    const int32_t c = x0 + i / V;
+                    y[slot + j][i] = ok[j] && c >= 0 && c < k.W ? y[slot + j][i] : 0.0f;
+                }
+            }
+#pragma unroll
+            for (int i = 0; i < Q * V; ++i) T[tslot + j][i] = d[(j * CX + 4) * V + i];
+        }
+    };
+    // row `row` of the average's output from three rows of y -> row maxima of the windows (outside the plane: -infinity),
+    // scanned as window row DH
+    auto average_row = [&](const float (&ya)[CX * V], const float (&yb)[CX * V], const float (&yc)[CX * V], auto dh_tag, int mslot, int32_t row) __attribute__((always_inline)) {
+        float a[CA * V];
+#pragma unroll
+        for (int i = 0; i < CA * V; ++i) {
+            // a list that ends in a ReLU has no -0, so the sum may start with the first cell instead of +0
+            float sum = ends_in_relu(PRE) ? ya[i] : 0.0f + ya[i];
+            sum = sum + ya[i + V];
+            sum = sum + ya[i + 2 * V];
+#pragma unroll
+            for (int dw = 0; dw < 3; ++dw) sum = sum + yb[i + dw * V];
+#pragma unroll
+            for (int dw = 0; dw < 3; ++dw) sum = sum + yc[i + dw * V];
+            a[i] = sum * (INC ? k.pool.inv_kk : bwd_avg_inv(k.pool, k.H, k.W, row, L.q0 - 3 + i / V));
+        }
+        round_store_all<DT, CA * V>(a);
+        const bool ok = row >= 0 && row < k.H;
+        if (!(inside && ok)) {
+#pragma unroll
+            for (int i = 0; i < CA * V; ++i) {
+                const int32_t c = L.q0 - 3 + i / V;
+                a[i] = ok && c >= 0 && c < k.W ? a[i] : -INFINITY;
+            }
+        }
+        row_maxima<V, 2, NW, CA, decltype(dh_tag)::value, 1, ends_in_relu(PRE)>(a, lead, m[mslot], code[mslot]);
+    };
+
+#pragma unroll
+    for (int i = 0; i < CG * V; ++i) gt[0][i] = 0.0f;
+#pragma unroll
+    for (int d = 0; d < 2; ++d)
+#pragma unroll
+        for (int i = 0; i < Q * V; ++i) hs[d][i] = 0.0f;
+    // y rows 2 oh - 2 .. 2 oh of the first window row -> average row 2 oh - 1; y rows 2 oh - 1, 2 oh stay
+    take_rows(std::integral_constant<int, 3>{}, 1, 0);
+    average_row(y[1], y[2], y[3], std::integral_constant<int, 0>{}, 0, oh_first * 2 - 1);
+#pragma unroll
+    for (int i = 0; i < CX * V; ++i) {
+        y[0][i] = y[2][i];
+        y[1][i] = y[3][i];
+    }
+
+    int32_t oh = oh_first;
+    // one window row of the max pooling.  The rows that stay (two of y, one of the average's windows and gradient sums, two of
+    // hs) and the new ones change roles from one window row to the next: PAR.
+    auto step = [&](auto par) __attribute__((always_inline)) {
+        constexpr int PAR = decltype(par)::value, K0 = 2 * PAR, N0 = 2 - K0, R0 = 2 * PAR, R2 = 2 - R0;
+        const int32_t hA = oh * 2 - 1;  // average rows hA .. hA + 2 under this window row
+        const bool row_ok = oh >= 0 && oh < k.Ho;
+        float g[NW * V];
+        load_row<DT, V, NW, OFF>(k, 1, 44, k.g_out, gat, gcol, g);
+        gat += oh >= 0 && oh < k.Ho - 1 ? grow : (OFF)0;
+        take_rows(std::integral_constant<int, 2>{}, N0, 3);
+        average_row(y[K0], y[K0 + 1], y[N0], std::integral_constant<int, 1>{}, 1, hA + 1);
+        average_row(y[K0 + 1], y[N0], y[N0 + 1], std::integral_constant<int, 2>{}, R2, hA + 2);
+        float best[NW * V];
+        int32_t pick[NW * V];
+        combine_rows<NW * V>(m[R0], code[R0], m[1], code[1], m[R2], code[R2], hA < 0, best, pick);
+#pragma unroll
+        for (int i = 0; i < NW * V; ++i) g[i] = row_ok && win[i / V] ? g[i] : 0.0f;  // windows that do not exist give nothing
+        if constexpr (POST != 0) {
+            float tp[NW * V];
+            post.template apply<NW * V>(k, best, tp);
+#pragma unroll
+            for (int i = 0; i < NW * V; ++i) g[i] *= tp[i];
+        }
+        scatter<V, 2, NW, -2, CG, 1>(pick, g, gt[R0], gt[1], gt[R2]);  // gt's columns begin at q0 - 1
+#pragma unroll
+        for (int d = 0; d < 2; ++d) {
+            const int32_t row = min(max(hA + d, 0), k.H - 1);  // rows and columns outside the plane hold zeros
+            float w[CG * V];
+#pragma unroll
+            for (int i = 0; i < CG * V; ++i)
+                w[i] = gt[d == 0 ? R0 : 1][i] *
+                       (INC ? k.pool.inv_kk : bwd_avg_inv(k.pool, k.H, k.W, row, min(max(L.q0 - 1 + i / V, 0), k.W - 1)));
+#pragma unroll
+            for (int i = 0; i < Q * V; ++i) hs[N0 + d][i] = (w[i] + w[i + V]) + w[i + 2 * V];
+        }
+#pragma unroll
+        for (int d = 0; d < 2; ++d) {
+            const int32_t row = hA - 1 + d;
+            if (L.live && row >= r_lo && row < r_hi) {
+                float v[Q * V];
+#pragma unroll
+                for (int i = 0; i < Q * V; ++i)
+                    v[i] = (d == 0 ? (hs[K0][i] + hs[K0 + 1][i]) + hs[N0][i] : (hs[K0 + 1][i] + hs[N0][i]) + hs[N0 + 1][i]) * T[d][i];
+                store_row<DT, V, Q, OFF>(k, 45, iat, L.q0, k.W, pi, whole, v);
+                iat += irow;
+            }
+        }
+#pragma unroll
+        for (int i = 0; i < NW * V; ++i) code[R2][i] -= 6;
+#pragma unroll
+        for (int i = 0; i < Q * V; ++i) {
+            T[0][i] = T[2][i];
+            T[1][i] = T[3][i];
+            T[2][i] = T[4][i];
+        }
+        ++oh;
+    };
+    const int32_t oh_end = oh_first + k.rc + 2;  // window rows rc * chunk - 1 .. rc * (chunk + 1): as many for every lane
+    for (;;) {
+        step(std::integral_constant<int, 0>{});
+        if (oh == oh_end) break;
+        step(std::integral_constant<int, 1>{});
+        if (oh == oh_end) break;
+    }
+}
+
+constexpr int BN_RELU = OP_BN + OP_RELU * K_EW_BASE;
+
+template <int DT, int S, int P>
+void launch1(const BwdK &k, bool wide, int32_t pre, dim3 g, hipStream_t st)
+{
+    constexpr int V = 1, Q = K_BWD_STRIP_Q;
+    if (wide) bwd_strip_kernel<DT, V, Q, S, P, -1, -1, uint64_t><<<g, 256, 0, st>>>(k);
+    else if (pre == BN_RELU && k.n_post == 0) bwd_strip_kernel<DT, V, Q, S, P, BN_RELU, 0, uint32_t><<<g, 256, 0, st>>>(k);
+    else if (k.n_post == 0) bwd_strip_kernel<DT, V, Q, S, P, -1, 0, uint32_t><<<g, 256, 0, st>>>(k);
+    else bwd_strip_kernel<DT, V, Q, S, P, -1, -1, uint32_t><<<g, 256, 0, st>>>(k);
+}
+
+template <int DT>
+void launch2(const BwdK &k, bool wide, int32_t pre, int32_t post, dim3 g, hipStream_t st)
+{
+    constexpr int V = 1, Q = K_BWD_STRIP2_Q;
+    const bool inc = k.pool.count_include_pad == 1;
+    if (wide) bwd_strip2_kernel<DT, V, Q, false, -1, -1, uint64_t><<<g, 256, 0, st>>>(k);
+    else if (pre == BN_RELU && post == BN_RELU && inc) bwd_strip2_kernel<DT, V, Q, true, BN_RELU, BN_RELU, uint32_t><<<g, 256, 0, st>>>(k);
+    else bwd_strip2_kernel<DT, V, Q, false, -1, -1, uint32_t><<<g, 256, 0, st>>>(k);
+}
+
+int32_t list_code(const BwdK &k, int32_t first, int32_t n)
+{
+    int32_t c = 0, digit = 1;
+    if (n > 6) return -1;
+    for (int32_t j = 0; j < n; ++j, digit *= K_EW_BASE) c += k.ew[first + j].kind * digit;
+    return c;
+}
+
+}  // namespace
+
+bs_status launch_backward_strips(const BwdK &k, int32_t dtype, int32_t vec, int64_t grid, int32_t threads, void *stream)
+{
+    const PoolK &p = k.pool, &q = k.pool2;
+    const bool two = k.wave_rows == 2;
+    const int32_t s = two ? 2 : p.sh, Q = two ? K_BWD_STRIP2_Q : K_BWD_STRIP_Q;
+    // what the kernels assume: no Add; 3 x 3 windows; strips and chunks that cover the plane; the divisors of the lane numbering
+    if (k.n_ew < 0 || k.n_post < 0 || k.n_ew + k.n_post > K_BWD_EW || threads != 256 || grid < 1) return BS_ERR_UNSUPPORTED;
+    for (int32_t j = 0; j < k.n_ew + k.n_post; ++j)
+        if (k.ew[j].kind == OP_ADD) return BS_ERR_UNSUPPORTED;
+    const PoolK &mx = two ? q : p;
+    if (!k.nhwc || k.direct || vec != 1 || mx.kind != OP_MAXPOOL || mx.kh != 3 || mx.kw != 3 || mx.sh != mx.sw || mx.ph != mx.pw ||
+        mx.ph < 0 || mx.ph > 1 || (mx.sh != 1 && mx.sh != 2) || (int64_t)k.div_wv.d != k.C || (int64_t)k.div_cbs.d != k.cbs ||
+        (int64_t)k.div_chunks.d != k.chunks || k.cbs != (k.W + Q - 1) / Q || k.rc < 1 || k.chunks < 1 ||
+        (int64_t)k.chunks * k.rc * s < k.H || k.total % ((uint32_t)k.cbs * (uint32_t)k.chunks * k.div_wv.d) != 0 ||
+        (uint64_t)grid * 256 < k.total || k.Ho < 1 || k.Wo < 1)
+        return BS_ERR_UNSUPPORTED;
+    if (two && (p.kind != OP_AVGSUM || p.kh != 3 || p.kw != 3 || p.sh != 1 || p.sw != 1 || p.ph != 1 || p.pw != 1 || mx.sh != 2 || mx.ph != 1))
+        return BS_ERR_UNSUPPORTED;
+    // 32-bit byte offsets where every tensor ends below 4 GiB
+    const uint64_t images = k.total / ((uint64_t)k.cbs * k.chunks * k.div_wv.d), es = dtype == BS_F32 ? 4 : 2;
+    const uint64_t in_px = images * k.H * k.W, out_px = images * k.Ho * k.Wo;
+    const uint64_t far = std::max(in_px * std::max((uint64_t)k.C + k.a_extra, (uint64_t)k.C + k.gin_extra), out_px * ((uint64_t)k.C + k.gout_extra)) * es;
+    const bool wide = far > 0xffffffffull;
+    const int32_t pre = list_code(k, 0, k.n_ew), post = list_code(k, k.n_ew, k.n_post);
+    hipStream_t st = static_cast<hipStream_t>(stream);
+    const dim3 g((uint32_t)grid);
+#define BS_STRIPS(DT)                                                          \
+    do {                                                                       \
+        if (two) launch2<DT>(k, wide, pre, post, g, st);                       \
+        else if (p.sh == 2 && p.ph == 1) launch1<DT, 2, 1>(k, wide, pre, g, st); \
+        else if (p.sh == 2) launch1<DT, 2, 0>(k, wide, pre, g, st);            \
+        else if (p.ph == 1) launch1<DT, 1, 1>(k, wide, pre, g, st);            \
+        else launch1<DT, 1, 0>(k, wide, pre, g, st);                           \
+    } while (0)
+    if (dtype == BS_F32) BS_STRIPS(DT_F32);
+    else if (dtype == BS_BF16) BS_STRIPS(DT_BF16);
+    else if (dtype == BS_F16) BS_STRIPS(DT_F16);
+    else return BS_ERR_UNSUPPORTED;
+#undef BS_STRIPS
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) {
+        set_hip_error((int32_t)e);
+        return BS_ERR_HIP;
+    }
+    return BS_OK;
+}
+
+}  // namespace bs

@@ -161,6 +161,81 @@ def test_overlapping_max_windows_without_recorded_picks(shape, dtype):
     check(layers, shape, dtype, "own picks/pool_bn_relu", seed=9)
 
 
+def _strip_stacks(c):
+    return {
+        "stem": [wl.bn_params(c, 90), wl.relu(), wl.maxpool(3, 2, 1)],
+        "incep": [wl.bn_params(c, 91), wl.relu(), wl.maxpool(3, 2, 0)],
+        "ceil": [wl.relu(), wl.maxpool(3, 2, 0, ceil_mode=True)],
+        "ceil_padded": [wl.maxpool(3, 2, 1, ceil_mode=True), wl.leaky_relu(0.2)],
+        "stride1": [wl.bn_params(c, 92), wl.relu(), wl.maxpool(3, 1, 1)],
+        "stride1_no_padding": [wl.clamp(-0.5, 0.5), wl.maxpool(3, 1, 0), wl.bn_params(c, 93), wl.relu()],
+        "pool_only": [wl.maxpool(3, 2, 1)],
+        "halo_stress": [wl.bn_params(c, 94), wl.relu(), wl.avgpool(3, 1, 1, True), wl.maxpool(3, 2, 1), wl.bn_params(c, 95), wl.relu()],
+        "halo_in_range_count": [wl.leaky_relu(0.1), wl.avgpool(3, 1, 1, False), wl.maxpool(3, 2, 1, ceil_mode=True)],
+    }
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16", "f16"])
+@pytest.mark.parametrize("shape", [(2, 5, 3, 3), (1, 64, 4, 4), (2, 8, 9, 5), (1, 3, 7, 8), (2, 16, 21, 9), (1, 70, 37, 17), (3, 2, 70, 16)])
+def test_channels_last_strips(shape, dtype):
+    """Channels-last 3 x 3 max pooling (alone, or behind a 3 x 3 / 1 average) in the kernels whose lanes walk strips of columns:
+    planes narrower than a strip, odd sizes, whole and ragged strips, one and several chunks of rows, ties.  Against the
+    oracle, and -- one pooling, nothing handed on in 16 bits -- bit for bit against the kernel that gathers recorded picks
+    (both sum a cell's windows in the same order).  Tolerance: test module."""
+    nhwc = dict(layout=bs.BS_LAYOUT_NHWC)
+    for name, layers in _strip_stacks(shape[1]).items():
+        label = f"strips/{name}"
+        x, res, dy = _inputs(layers, shape, 23, dtype)
+        x[:, :, ::2, 1::3] = 0.5
+        print(f"[backward] {label} shape={shape} dtype={dtype}", flush=True)
+        ref_x, _ = bw.backward_stack(layers, x, res, dy, dtype)
+        gx, _, stages = run_gpu(layers, x, res, dy, dtype, **nhwc)
+        assert stages == 1, label
+        _close(gx, ref_x, dtype, label)
+        if name in ("stem", "incep", "ceil", "stride1", "pool_only"):
+            hx, _, _ = run_gpu(layers, x, res, dy, dtype, lane_exchange=-1, **nhwc)
+            if dtype == "f16":
+                # float32 product, then binary16: the compiler may merge the two roundings into one (v_fma_mixlo_f16) in
+                # either kernel, which moves a value by at most one unit in its last place (11-bit significand; 2^-24
+                # between subnormal numbers)
+                assert (np.abs(gx - hx) <= 2.0 ** -10 * np.abs(hx) + 2.0 ** -24).all(), label
+            else:
+                assert np.array_equal(gx, hx), label
+
+
+def test_channels_last_strips_with_infinities_and_offsets_beyond_4_gib():
+    """Windows of nothing but -infinity hand their gradient to their first cell inside the plane (the recorded pick);
+    a channel slice whose pixels lie so far apart that byte offsets need more than 32 bits."""
+    nhwc = dict(layout=bs.BS_LAYOUT_NHWC)
+    for pool in (wl.maxpool(3, 2, 1), wl.maxpool(3, 2, 0), wl.maxpool(3, 1, 1)):
+        x = wl.activation((1, 6, 9, 11), 3)
+        x[:, ::2] = -np.inf
+        x[:, 1, :4, :5] = -np.inf
+        dy = wl.activation(wl.output_shape([pool], x.shape), 4)
+        gx, _, _ = run_gpu([pool], x, [], dy, "f32", **nhwc)
+        hx, _, _ = run_gpu([pool], x, [], dy, "f32", lane_exchange=-1, **nhwc)
+        assert np.isfinite(gx).all() and np.array_equal(gx, hx), pool
+    c, h, w, ct = 8, 9, 8, 1 << 24          # 72 pixels of 64 MiB: 4.5 GiB
+    if torch.cuda.mem_get_info()[0] < (12 << 30):
+        pytest.skip("needs 12 GiB of free device memory")
+    layers = [wl.bn_params(c, 1), wl.relu(), wl.maxpool(3, 2, 1)]
+    x, _, dy = _inputs(layers, (1, c, h, w), 5, "f32")
+    st = bs.Stack(layers, (1, c, h, w), "f32").plan(**nhwc).plan_backward()
+    put = lambda a: _dev(a, "f32").contiguous(memory_format=torch.channels_last)
+    xd, dyd = put(x), put(dy)
+    dense, _ = st.backward(xd, [], dyd)
+    big = torch.empty(h * w * ct, dtype=torch.float32, device="cuda")
+    big.view(h * w, ct)[:, ct - c:] = xd.permute(0, 2, 3, 1).reshape(h * w, c)
+    gx = torch.empty_like(xd, memory_format=torch.channels_last)
+    ws = st.workspace("cuda", backward=True)
+    bs.bs_stack_backward_strided(st.handle, big.data_ptr() + 4 * (ct - c), h * w * ct, [], None, dyd.data_ptr(), 0, gx.data_ptr(), 0, [],
+                                 ws.data_ptr() if ws is not None else 0, bs.bs_stack_backward_workspace_bytes(st.handle),
+                                 torch.cuda.current_stream().cuda_stream)
+    torch.cuda.synchronize()
+    assert torch.equal(gx, dense)
+    st.close()
+
+
 def _two_level_stacks(c):
     return {
         "halo_stress": [wl.bn_params(c, 70), wl.relu(), wl.avgpool(3, 1, 1, True), wl.maxpool(3, 2, 1), wl.bn_params(c, 71), wl.relu()],
