@@ -196,7 +196,11 @@ typedef enum bs_layout {
  *                           maximum with stride 1 or 2, no index output, images at most 64 pixels
  *                           wide -- runs as one BS_VARIANT_NHWC_ROWS sequence instead (rows in
  *                           registers, no LDS); tile_rows is then the number of output rows per
- *                           work-group.
+ *                           work-group.  With threads_per_group, tile_rows, tile_cols and
+ *                           planes_per_group all 0 and lane_exchange = 0, sequences of one 3 x 3 step
+ *                           or of a 3 x 3 / 1 / 1 step and a 3 x 3 maximum (no residual Add) run as strips
+ *                           of output columns in registers where that is faster; bs_stack_sequence_info
+ *                           keeps reporting the kernel and geometry those options would select.
  *   lane_exchange           sliding-window (BS_VARIANT_POOL_ROWS) sequences on planes whose rows fit one
  *                           wave as 128-bit column blocks (at most 64 of them): 0 = the lanes pass
  *                           their edge columns to their neighbours inside the wave (each input

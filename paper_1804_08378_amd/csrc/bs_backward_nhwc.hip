@@ -12,26 +12,13 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
-#include <type_traits>
-#include <utility>
 
 #include "bs_bwd_device.h"
+#include "bs_strip_device.h"
 #include "bs_internal.h"
 
 namespace bs {
 namespace {
-
-template <int DT>
-constexpr int elem_bytes() { return DT == DT_F32 ? 4 : 2; }
-
-// f(integral_constant<0>), f(integral_constant<1>) ...
-template <int... B, typename F>
-BS_DEV void each_of(std::integer_sequence<int, B...>, F f)
-{
-    (f(std::integral_constant<int, B>{}), ...);
-}
-
-constexpr bool ends_in_relu(int code) { return code > 0 && ew_code_kind(code, ew_code_len(code) - 1) == OP_RELU; }
 
 // V elements at byte offset `off`.  OFF: uint32_t where every tensor of the launch is below 4 GiB (one address addition
 // per access: the base stays in scalar registers), else uint64_t.
@@ -86,42 +73,6 @@ BS_DEV void store_row(const BwdK &k, int site, OFF at, int32_t first, int32_t wi
     }
 }
 
-// The compare-and-select steps below are written out so that the comparison's lane mask stays in VCC: left to the compiler the
-// masks go through scalar register pairs, whose selects issue at half the rate and need wait states behind the compare.
-// max(x, 0): NaN and -0 give +0.  (The builtin first canonicalises values that come out of a conversion.)
-BS_DEV float relu(float x)
-{
-    float y;
-    asm("v_max_f32_e32 %0, 0, %1" : "=v"(y) : "v"(x));
-    return y;
-}
-// v > best: best = v, at = AT
-template <int AT>
-BS_DEV void take_if_more(float v, float &best, int32_t &at)
-{
-    asm("v_cmp_gt_f32_e32 vcc, %2, %0\n\tv_max_f32_e32 %0, %0, %2\n\tv_cndmask_b32_e64 %1, %1, %3, vcc"
-        : "+v"(best), "+v"(at)
-        : "v"(v), "n"(AT)
-        : "vcc");
-}
-// The first maximum of a, b, c (codes A, A + 1, A + 2).
-template <int A>
-BS_DEV void first_max3(float a, float b, float c, float &best, int32_t &at)
-{
-    asm("v_cmp_gt_f32_e32 vcc, %3, %2\n\tv_max_f32_e32 %0, %3, %2\n\tv_cndmask_b32_e64 %1, %5, %6, vcc\n\t"
-        "v_cmp_gt_f32_e32 vcc, %4, %0\n\tv_max_f32_e32 %0, %0, %4\n\tv_cndmask_b32_e64 %1, %1, %7, vcc"
-        : "=&v"(best), "=&v"(at)
-        : "v"(a), "v"(b), "v"(c), "n"(A), "n"(A + 1), "n"(A + 2)
-        : "vcc");
-}
-// v > best: best = v, at = c
-BS_DEV void take_if_more(float v, int32_t c, float &best, int32_t &at)
-{
-    asm("v_cmp_gt_f32_e32 vcc, %2, %0\n\tv_max_f32_e32 %0, %0, %2\n\tv_cndmask_b32_e32 %1, %1, %3, vcc"
-        : "+v"(best), "+v"(at)
-        : "v"(v), "v"(c)
-        : "vcc");
-}
 // at == AT: sum += g
 template <int AT, bool FIRST>
 BS_DEV void add_if_at(int32_t at, float g, float &sum)
@@ -242,32 +193,6 @@ BS_DEV StripLane strip_lane(const BwdK &k)
     L.n = fdiv(v, k.div_chunks);
     L.chunk = (int32_t)(v - L.n * k.div_chunks.d);
     return L;
-}
-
-// Row maxima of N adjacent windows (S columns apart) of window row DH: value and code 3 * DH + window column of the first
-// one.  A column outside the plane holds -infinity.  Window LEAD begins one column left of the plane when `lead` is set
-// (padding): its scan starts at column 1, so that a window of nothing but -infinity picks its first cell inside.  NaN is
-// never a maximum.
-// NONAN: no value is NaN (a ReLU stands in front).
-template <int V, int S, int N, int CW, int DH, int LEAD, bool NONAN>
-BS_DEV void row_maxima(const float (&y)[CW * V], bool lead, float (&m)[N * V], int32_t (&code)[N * V])
-{
-#pragma unroll
-    for (int b = 0; b < N; ++b)
-#pragma unroll
-        for (int e = 0; e < V; ++e) {
-            const float first = NONAN ? y[b * S * V + e] : __builtin_fmaxf(y[b * S * V + e], -INFINITY);
-            if (LEAD == b) {
-                float best = first;
-                int32_t at = lead ? 3 * DH + 1 : 3 * DH;
-                take_if_more<3 * DH + 1>(y[(b * S + 1) * V + e], best, at);
-                take_if_more<3 * DH + 2>(y[(b * S + 2) * V + e], best, at);
-                m[b * V + e] = best;
-                code[b * V + e] = at;
-            } else {
-                first_max3<3 * DH>(first, y[(b * S + 1) * V + e], y[(b * S + 2) * V + e], m[b * V + e], code[b * V + e]);
-            }
-        }
 }
 
 // The windows' picks from the row maxima of their three rows.  top: the first window row lies above the plane (padding, all

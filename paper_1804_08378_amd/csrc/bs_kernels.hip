@@ -559,6 +559,19 @@ static void launch_stream(const StreamK &k, dim3 grid, dim3 block, hipStream_t s
     else stream_kernel<DT, VEC, K_STREAM_U><<<grid, block, 0, st>>>(k);
 }
 
+static bs_status run_strips(const bs_stack *s, const Sequence &q, const void *in, void *out, uint32_t in_extra, uint32_t out_extra,
+                            int32_t *idx, void *stream)
+{
+    StripK k = q.strip;
+    const uint32_t hw_in = (uint32_t)(q.in_shape[2] * q.in_shape[3]), hw_out = (uint32_t)(q.out_shape[2] * q.out_shape[3]);
+    if (in_extra % hw_in != 0 || out_extra % hw_out != 0) return BS_ERR_UNSUPPORTED;
+    k.in_xp = in_extra / hw_in;
+    k.out_xp = out_extra / hw_out;
+    k.in = in; k.out = out; k.params = s->dev_params;
+    k.idx = idx;
+    return launch_nhwc_strips(k, s->dtype, q.strip_grid, stream);
+}
+
 bs_status launch_sequence(const bs_stack *s, const Sequence &q, const void *in, void *out,
                           uint32_t in_extra, uint32_t out_extra, const void *const *res,
                           int32_t *const *idx, void *stream)
@@ -707,6 +720,11 @@ bs_status launch_sequence(const bs_stack *s, const Sequence &q, const void *in, 
     }
     case BS_VARIANT_NHWC_STREAM:
     case BS_VARIANT_NHWC_POOL: {
+        if (q.strip_grid > 0) {
+            const bs_status ls = run_strips(s, q, in, out, in_extra, out_extra, ip[0], stream);
+            if (ls != BS_OK) return ls;
+            break;
+        }
         NhwcK k = q.nhwc;
         // a channel slice of a channels-last tensor: the batch stride is a whole number of pixels
         // of the larger tensor (checked by the caller), the slice skips the same count per pixel
@@ -722,6 +740,11 @@ bs_status launch_sequence(const bs_stack *s, const Sequence &q, const void *in, 
         break;
     }
     case BS_VARIANT_NHWC_TILE: {
+        if (q.strip_grid > 0) {
+            const bs_status ls = run_strips(s, q, in, out, in_extra, out_extra, ip[0], stream);
+            if (ls != BS_OK) return ls;
+            break;
+        }
         NhwcTile2K k = q.nhwc2;
         const uint32_t hw_in = (uint32_t)(q.in_shape[2] * q.in_shape[3]), hw_out = (uint32_t)(q.out_shape[2] * q.out_shape[3]);
         if (in_extra % hw_in != 0 || out_extra % hw_out != 0) return BS_ERR_UNSUPPORTED;
@@ -735,6 +758,11 @@ bs_status launch_sequence(const bs_stack *s, const Sequence &q, const void *in, 
         break;
     }
     case BS_VARIANT_NHWC_ROWS: {
+        if (q.strip_grid > 0) {
+            const bs_status ls = run_strips(s, q, in, out, in_extra, out_extra, ip[0], stream);
+            if (ls != BS_OK) return ls;
+            break;
+        }
         NhwcTile2K k = q.nhwc2;
         const uint32_t hw_in = (uint32_t)(q.in_shape[2] * q.in_shape[3]), hw_out = (uint32_t)(q.out_shape[2] * q.out_shape[3]);
         if (in_extra % hw_in != 0 || out_extra % hw_out != 0) return BS_ERR_UNSUPPORTED;

@@ -453,8 +453,47 @@ static bool commutes_with_max(const bs_stack *s, const EwOp *ew, int32_t n, int3
     return monotone && relu;
 }
 
+// Strips unless an option asks for another kernel or its geometry.
+static bool strips_wanted(const bs_plan_options &o)
+{
+    return o.lane_exchange >= 0 && o.threads_per_group == 0 && o.tile_rows == 0 && o.tile_cols == 0 && o.planes_per_group == 0;
+}
+
+// A channels-last sequence of one or two pooling steps as strips of output columns, if the kernel exists for it.  The
+// sequence keeps the geometry of the kernel that options would select (bs_stack_sequence_info reports that one).
+static void plan_strips(const bs_stack *s, Sequence &q, const StripK &lists, const PoolK *first, const PoolK &second, int32_t H, int32_t W, int32_t Ho,
+                        int32_t Wo)
+{
+    StripK k = lists;
+    if (first) k.pool1 = *first;
+    k.pool2 = second;
+    k.C = (int32_t)q.in_shape[1];
+    k.H = H; k.W = W; k.Ho = Ho; k.Wo = Wo;
+    if (!nhwc_strips_supported(k)) return;
+    k.strips = (Wo + K_STRIP_QO - 1) / K_STRIP_QO;
+    const int64_t per_chunk = q.in_shape[0] * k.strips * k.C;
+    // chunks of rows: as many lanes as the chip holds, but two output rows at least (a chunk reads the rows around it again)
+    const int64_t chunks = std::max<int64_t>(1, std::min<int64_t>(K_STRIP_LANES / per_chunk, (Ho + 1) / 2));
+    k.rc = (int32_t)((Ho + chunks - 1) / chunks);
+    k.chunks = (Ho + k.rc - 1) / k.rc;
+    const int64_t total = per_chunk * k.chunks;
+    if (total > 0x7fffffffll) return;
+    k.total = (uint32_t)total;
+    k.div_c = make_fastdiv((uint32_t)k.C);
+    k.div_strips = make_fastdiv((uint32_t)k.strips);
+    k.div_chunks = make_fastdiv((uint32_t)k.chunks);
+    q.strip = k;
+    q.strip_grid = (total + 255) / 256;
+}
+
+static void copy_list(const EwOp *from, int32_t n, EwOp *to, int32_t &n_to)
+{
+    for (int32_t j = 0; j < n; ++j) to[j] = from[j];
+    n_to = n;
+}
+
 // Channels-last sequence: element-wise only, or one pooling step.
-static bs_status plan_nhwc(const bs_stack *s, Sequence &q)
+static bs_status plan_nhwc(const bs_stack *s, Sequence &q, const bs_plan_options &o)
 {
     NhwcK &k = q.nhwc;
     k = NhwcK{};
@@ -525,6 +564,17 @@ static bs_status plan_nhwc(const bs_stack *s, Sequence &q)
             q.n_levels = 1;
             return BS_OK;
         }
+    }
+    // 3 x 3 windows as strips.  Measured on MI355X, us, one block of outputs per lane -> strips: stride 1 (64 x 128 x 56 x 56,
+    // BatchNorm, ReLU, average) float32 78 -> 35, bfloat16 64 -> 23; stride 2 with indices (ResNet stem) float32 59 -> 52, bfloat16
+    // 61 -> 37; channels that are no whole vectors (64 x 30 x 112 x 112 / 2) bfloat16 34 -> 13; stride 2, whole vectors, no indices:
+    // maximum float32 48 -> 50, bfloat16 25 -> 26 and average float32 46 -> 50 stay, average bfloat16 29 -> 26.
+    if (seen && strips_wanted(o) &&
+        (k.pool.sh == 1 || k.pool.idx_slot >= 0 || vec == 1 || (k.pool.kind == OP_AVGSUM && s->dtype != BS_F32))) {
+        StripK lists{};
+        copy_list(k.pre, k.n_pre, lists.pre, lists.n_pre);
+        copy_list(k.post, k.n_post, lists.post, lists.n_post);
+        plan_strips(s, q, lists, nullptr, k.pool, k.H, k.W, k.Ho, k.Wo);
     }
     // a lane takes one channel vector of a block of ohb x owb output pixels (1 x 1: one pixel)
     int32_t ohb = 1, owb = 1;
@@ -599,6 +649,16 @@ static bs_status plan_nhwc_tile2(const bs_stack *s, Sequence &q, const bs_plan_o
         commutes_with_max(s, k.mid, k.n_mid, C))
         move_behind(k.mid, k.n_mid, k.post, k.n_post);
 
+    // A 3 x 3 / 1 / 1 step and a 3 x 3 maximum behind it as strips.  Measured on MI355X, us, halo_stress: float32 75 -> 53 (tiles in
+    // LDS), with indices 91 -> 66, bfloat16 55 -> 42 (rows in registers, lanes = columns); four max blocks 64 x 64 x 56 x 56 float32
+    // 294 -> 44, bfloat16 79 -> 35.
+    if (strips_wanted(o) && k.H1 == k.H && k.W1 == k.W) {
+        StripK lists{};
+        copy_list(k.pre, k.n_pre, lists.pre, lists.n_pre);
+        copy_list(k.mid, k.n_mid, lists.mid, lists.n_mid);
+        copy_list(k.post, k.n_post, lists.post, lists.n_post);
+        plan_strips(s, q, lists, &k.pool1, k.pool2, k.H, k.W, k.Ho, k.Wo);
+    }
     // The register kernel where it exists for this pair (plan option lane_exchange = -1: not used).
     // A work-group is the channel vectors that share a cache line and a chunk of output rows (tile_rows overrides its length).
     if (o.lane_exchange >= 0 && nhwc_rows2_supported(k, s->dtype)) {
@@ -1542,7 +1602,7 @@ bs_status group_sequences(bs_stack *s, const bs_plan_options &o, const Limits &l
         q.n_levels = pools;
         bs_status st = BS_OK;
         if (nhwc) {
-            st = q.n_steps == 2 ? plan_nhwc_tile2(s, q, o, lim) : plan_nhwc(s, q);
+            st = q.n_steps == 2 ? plan_nhwc_tile2(s, q, o, lim) : plan_nhwc(s, q, o);
         } else if (pools == 0) {
             plan_stream(s, q);
         } else if (direct_applicable(s, q.first_op, q.n_ops) && o.force_variant != BS_VARIANT_LDS_TILE) {

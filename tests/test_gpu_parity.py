@@ -973,6 +973,66 @@ def test_channels_last_two_pools_in_registers(shape, dtype):
         assert "nhwc_rows" not in [q["variant_name"] for q in info["sequences"]], name
 
 
+def _fwd_strip_stacks(c):
+    bn = lambda i: wl.bn_params(c, 200 + i)
+    return {
+        "avg31": [bn(0), wl.relu(), wl.avgpool(3, 1, 1, True)],
+        "avg31_bare": [wl.avgpool(3, 1, 1, True)],
+        "avg31_in_range": [wl.leaky_relu(0.1), wl.avgpool(3, 1, 1, False), bn(1)],
+        "avg32": [bn(2), wl.avgpool(3, 2, 1, True), wl.relu()],
+        "avg32_ceil": [wl.avgpool(3, 2, 0, True, True)],
+        "max31": [wl.maxpool(3, 1, 1), bn(3), wl.relu()],
+        "max30_idx": [bn(4), wl.relu(), wl.maxpool(3, 1, 0, True)],
+        "max32_idx": [bn(5), wl.relu(), wl.maxpool(3, 2, 1, True)],
+        "max32_idx_raw_ceil": [wl.maxpool(3, 2, 0, True, True), wl.clamp(-0.5, 1.0)],
+        "halo": [bn(6), wl.relu(), wl.avgpool(3, 1, 1, True), wl.maxpool(3, 2, 1), bn(7), wl.relu()],
+        "halo_idx": [bn(8), wl.relu(), wl.avgpool(3, 1, 1, True), wl.maxpool(3, 2, 1, True), bn(9), wl.relu()],
+        "halo_general": [wl.clamp(-1.0, 1.5), wl.avgpool(3, 1, 1, False), bn(10), wl.maxpool(3, 1, 1, True)],
+        "avg_max_ceil": [wl.avgpool(3, 1, 1, True), wl.maxpool(3, 2, 1, False, True)],
+        "max_max_idx": [wl.maxpool(3, 1, 1), wl.leaky_relu(0.2), wl.maxpool(3, 2, 1, True)],
+        "blocks3": sum(([wl.maxpool(3, 1, 1), bn(11 + i), wl.relu()] for i in range(3)), []),
+    }
+
+
+@pytest.mark.parametrize("shape", [(1, 8, 3, 3), (2, 5, 4, 6), (1, 16, 9, 8), (2, 8, 13, 11), (1, 70, 35, 17), (3, 3, 7, 66), (1, 64, 40, 40)])
+@pytest.mark.parametrize("dtype", ["f32", "bf16", "f16"])
+def test_channels_last_strips(shape, dtype):
+    """Channels-last 3 x 3 pooling, alone and behind a 3 x 3 / 1 / 1 step, as strips of output columns: planes narrower than a
+    strip, whole and ragged strips, one and several chunks of rows, ties; bit for bit the oracle's values and indices, and
+    those of the kernels that lane_exchange = -1 selects (no tolerance: every layer has one order of operations)."""
+    for name, layers in _fwd_strip_stacks(shape[1]).items():
+        x = wl.activation(shape, 220, dtype)
+        x[:, :, ::3, ::2] = 0.0
+        _check_nhwc(layers, x, [], dtype, f"strips/{name}{shape}")
+        _check_nhwc(layers, x, [], dtype, f"no strips/{name}{shape}", lane_exchange=-1)
+
+
+def test_channels_last_strips_with_infinities_and_offsets_beyond_4_gib():
+    """Windows of nothing but -infinity pick their first cell inside the plane; a channel slice whose pixels lie so far
+    apart that byte offsets need more than 32 bits."""
+    for pool in (wl.maxpool(3, 2, 1, True), wl.maxpool(3, 2, 0, True), wl.maxpool(3, 1, 1, True)):
+        x = wl.activation((1, 6, 9, 11), 221)
+        x[:, ::2] = -np.inf
+        x[:, 1, :4, :5] = -np.inf
+        _check_nhwc([pool], x, [], "f32", "strips/infinities")
+    if torch.cuda.mem_get_info()[0] < (12 << 30):
+        pytest.skip("needs 12 GiB of free device memory")
+    c, h, w, ct = 8, 9, 8, 1 << 24          # 72 pixels of 64 MiB: 4.5 GiB
+    layers = [wl.bn_params(c, 1), wl.relu(), wl.avgpool(3, 1, 1, True), wl.maxpool(3, 2, 1, True)]
+    x = wl.activation((1, c, h, w), 222)
+    st = bs.Stack(layers, x.shape, "f32").plan(layout=bs.BS_LAYOUT_NHWC)
+    xd = _dev(x, "f32").contiguous(memory_format=torch.channels_last)
+    dense, idx = st.run(xd)
+    big = torch.empty(h * w * ct, dtype=torch.float32, device="cuda")
+    big.view(h * w, ct)[:, ct - c:] = xd.permute(0, 2, 3, 1).reshape(h * w, c)
+    out, idx2 = st.alloc_outputs("cuda")
+    bs.bs_stack_run_strided(st.handle, big.data_ptr() + 4 * (ct - c), h * w * ct, [], out.data_ptr(), 0, [idx2[0].data_ptr()], 0, 0,
+                            torch.cuda.current_stream().cuda_stream)
+    torch.cuda.synchronize()
+    assert torch.equal(out, dense) and torch.equal(idx2[0], idx[0])
+    st.close()
+
+
 def test_channels_last_register_kernel_needs_rows_that_fit_a_wave():
     layers = [wl.avgpool(3, 1, 1, True), wl.maxpool(3, 2, 1)]
     for w, want in ((64, True), (65, False)):
