@@ -201,6 +201,9 @@ typedef enum bs_layout {
  *                           or of a 3 x 3 / 1 / 1 step and a 3 x 3 maximum (no residual Add) run as strips
  *                           of output columns in registers where that is faster; bs_stack_sequence_info
  *                           keeps reporting the kernel and geometry those options would select.
+ *                           Row-major plans (also max_lds_bytes and force_variant 0, jit not 1) do the same
+ *                           with such sequences, and with 2 x 2 / 2 steps, that would take
+ *                           BS_VARIANT_LDS_TILE: nothing is built for them at plan time.
  *   lane_exchange           sliding-window (BS_VARIANT_POOL_ROWS) sequences on planes whose rows fit one
  *                           wave as 128-bit column blocks (at most 64 of them): 0 = the lanes pass
  *                           their edge columns to their neighbours inside the wave (each input

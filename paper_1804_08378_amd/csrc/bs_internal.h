@@ -55,7 +55,7 @@ struct Sequence {
     LdsSeqK lds{};
     NhwcK nhwc{};
     NhwcTile2K nhwc2{};
-    StripK strip{};           // channels-last pooling sequences that run as strips (strip_grid > 0), whatever `variant` says
+    StripK strip{};           // pooling sequences that run as strips (strip_grid > 0), whatever `variant` says
     int64_t strip_grid = 0;
     // run-time build (hipFunction_t) without / with index outputs; null = pre-compiled kernel
     int32_t jit = 0;
@@ -181,9 +181,9 @@ bool nhwc_tile2_fits(const PoolK &p1, const PoolK &p2, int32_t th, int32_t tw, i
 uint64_t nhwc_tile2_lds(const PoolK &p1, const PoolK &p2, int32_t th, int32_t tw, int32_t cvb, int32_t n_bn, int32_t vec);
 bs_status launch_nhwc_tile2(const NhwcTile2K &k, int32_t dtype, int32_t vec, int64_t grid, int32_t threads, uint64_t lds_bytes,
                             void *stream);
-// bs_nhwc_strip.hip: channels-last, one or two pooling steps per sequence, lanes walk strips of output columns
-bool nhwc_strips_supported(const StripK &k);
-bs_status launch_nhwc_strips(const StripK &k, int32_t dtype, int64_t grid, void *stream);
+// bs_strip.hip: one or two pooling steps per sequence, lanes walk strips of output columns
+bool strips_supported(const StripK &k);
+bs_status launch_strips(const StripK &k, int32_t dtype, int64_t grid, void *stream);
 // bs_rows.hip: *_supported = the signature is in the pre-compiled table; *_buildable = the
 // kernel template can be instantiated for it at run time; *_expr = that instance's name
 bool rows_supported(const PoolK &pool, const EwOp *pre, int32_t n_pre, const EwOp *post, int32_t n_post);

@@ -295,7 +295,7 @@ struct NhwcTile2K {
     FastDiv div_cvgs, div_chunks;
 };
 
-// Channels-last strips (bs_nhwc_strip.hip): one pooling step (pool1.kind == 0), or two with the first 3 x 3 / 1 / 1; lists in
+// Strips of output columns (bs_strip.hip): one pooling step (pool1.kind == 0), or two with the first 3 x 3 / 1 / 1; lists in
 // front, between and behind.
 struct StripK {
     const void *in;
@@ -307,15 +307,23 @@ struct StripK {
     PoolK pool1, pool2;
     int32_t C, H, W, Ho, Wo;      // input plane (two steps: also the plane between them), output plane
     int32_t strips, chunks, rc;   // strips per output row, chunks per plane, output rows per chunk
-    uint32_t total;               // lanes = images * chunks * strips * C, channels fastest
+    uint32_t total;               // lanes = images * channels * chunks * strips
     FastDiv div_c, div_strips, div_chunks;
-    uint32_t in_xp, out_xp;       // as in NhwcK
+    int32_t nhwc;                 // 1: channels-last tensors
+    uint32_t in_xp, out_xp;       // channels-last: as in NhwcK; row-major: as StreamK::in_extra, out_extra
+    uint64_t in_bytes;            // (set at launch) bytes from the input's first to its last element
 };
 // Output columns per strip and the lanes the chunks of rows aim at, at most (7 waves on each of 1024 SIMDs).  Measured on MI355X, us,
 // strips of 2 / 4 / 8 columns at their best chunk length: halo_stress float32 53 / 53 / 55, bfloat16 46 / 42 / 49, ResNet stem with
 // indices bfloat16 36 / 37 / 38; two channels per lane (16-bit storage) 46 and 39 with 4 columns.  halo_stress bfloat16 with
 // 1 / 2 / 4 / 7 chunks (4 fit): 54 / 45 / 42 / 44; 192 x 71 x 71 3x3/2 with indices binary16, 1 / 2 / 4 / 7 (8 fit): 40 / 26 / 22 / 20.
 constexpr int32_t K_STRIP_QO = 4;
+// Row-major tensors: a lane's columns are consecutive elements, 16 bytes of input per lane and row at most -- longer strips leave
+// gaps between the lanes of a load (float32, stride 2, 32 x 64 x 147 x 147: 2 columns against 4, see bs_plan.cpp).
+constexpr int32_t strip_columns(bool nhwc, int32_t dtype, int32_t stride)
+{
+    return !nhwc && dtype == 0 && stride == 2 ? 2 : K_STRIP_QO;
+}
 constexpr int64_t K_STRIP_LANES = 7 * 1024 * 64;
 
 // Backward pass of one stage: element-wise operations followed by at most one pooling

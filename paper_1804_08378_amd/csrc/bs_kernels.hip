@@ -563,13 +563,17 @@ static bs_status run_strips(const bs_stack *s, const Sequence &q, const void *in
                             int32_t *idx, void *stream)
 {
     StripK k = q.strip;
-    const uint32_t hw_in = (uint32_t)(q.in_shape[2] * q.in_shape[3]), hw_out = (uint32_t)(q.out_shape[2] * q.out_shape[3]);
-    if (in_extra % hw_in != 0 || out_extra % hw_out != 0) return BS_ERR_UNSUPPORTED;
-    k.in_xp = in_extra / hw_in;
-    k.out_xp = out_extra / hw_out;
+    k.in_xp = in_extra;
+    k.out_xp = out_extra;
+    if (k.nhwc) {  // a slice skips the larger tensor's other channels in every pixel
+        const uint32_t hw_in = (uint32_t)(q.in_shape[2] * q.in_shape[3]), hw_out = (uint32_t)(q.out_shape[2] * q.out_shape[3]);
+        if (in_extra % hw_in != 0 || out_extra % hw_out != 0) return BS_ERR_UNSUPPORTED;
+        k.in_xp = in_extra / hw_in;
+        k.out_xp = out_extra / hw_out;
+    }
     k.in = in; k.out = out; k.params = s->dev_params;
     k.idx = idx;
-    return launch_nhwc_strips(k, s->dtype, q.strip_grid, stream);
+    return launch_strips(k, s->dtype, q.strip_grid, stream);
 }
 
 bs_status launch_sequence(const bs_stack *s, const Sequence &q, const void *in, void *out,
@@ -706,6 +710,11 @@ bs_status launch_sequence(const bs_stack *s, const Sequence &q, const void *in, 
         break;
     }
     case BS_VARIANT_LDS_TILE: {
+        if (q.strip_grid > 0) {
+            const bs_status ls = run_strips(s, q, in, out, in_extra, out_extra, ip[0], stream);
+            if (ls != BS_OK) return ls;
+            break;
+        }
         LdsSeqK k = q.lds;
         k.in = in; k.out = out; k.params = s->dev_params;
         k.in_extra = in_extra; k.out_extra = out_extra;

@@ -465,12 +465,14 @@ static void plan_strips(const bs_stack *s, Sequence &q, const StripK &lists, con
                         int32_t Wo)
 {
     StripK k = lists;
+    k.nhwc = s->opts.layout == BS_LAYOUT_NHWC ? 1 : 0;
     if (first) k.pool1 = *first;
     k.pool2 = second;
     k.C = (int32_t)q.in_shape[1];
     k.H = H; k.W = W; k.Ho = Ho; k.Wo = Wo;
-    if (!nhwc_strips_supported(k)) return;
-    k.strips = (Wo + K_STRIP_QO - 1) / K_STRIP_QO;
+    if (!strips_supported(k)) return;
+    const int32_t qo = strip_columns(k.nhwc != 0, s->dtype, second.sh);
+    k.strips = (Wo + qo - 1) / qo;
     const int64_t per_chunk = q.in_shape[0] * k.strips * k.C;
     // chunks of rows: as many lanes as the chip holds, but two output rows at least (a chunk reads the rows around it again)
     const int64_t chunks = std::max<int64_t>(1, std::min<int64_t>(K_STRIP_LANES / per_chunk, (Ho + 1) / 2));
@@ -490,6 +492,56 @@ static void copy_list(const EwOp *from, int32_t n, EwOp *to, int32_t &n_to)
 {
     for (int32_t j = 0; j < n; ++j) to[j] = from[j];
     n_to = n;
+}
+
+// A row-major sequence that would take the LDS tiles -- above all rows that are no whole vectors -- as strips, if the kernel exists
+// for it (one or two poolings, no Add; with jit = 1 the caller asks for built kernels).  Measured on MI355X, us, LDS tiles built for the
+// signature -> strips: BatchNorm, ReLU, max 3x3/2 on 32 x 64 x 147 x 147 binary16 65 -> 28, float32 87 -> 60 (4 columns per lane: 85);
+// max 2x2/2 on 32 x 64 x 111 x 111 binary16 35 -> 15, float32 45 -> 29; average 3x3/1 on 32 x 288 x 35 x 35 float32 45 -> 31, bfloat16
+// 38 -> 18; with indices 64 x 64 x 111 x 111 float32 112 -> 76; halo_stress's stack on 18 x 56 x 117 x 117 float32 42 -> 38, binary16
+// 37 -> 18.  The sequence keeps the tile plan's geometry (bs_stack_sequence_info) without a kernel being built for it.
+static void plan_row_strips(const bs_stack *s, Sequence &q, const bs_plan_options &o)
+{
+    if (!strips_wanted(o) || o.force_variant != BS_VARIANT_AUTO || o.max_lds_bytes != 0 || o.jit == 1 || q.n_res > 0) return;
+    StripK k{};
+    PoolK pools[2];
+    int32_t n = 0, H = 0, W = 0, Ho = 0, Wo = 0;
+    for (int32_t i = q.first_op; i < q.first_op + q.n_ops; ++i) {
+        const Op &op = s->ops[i];
+        if (!op_is_elementwise(op.kind)) {
+            if (n == 2 || (n == 1 && (op.in_h != H || op.in_w != W))) return;
+            Sequence none;
+            pools[n] = make_pool(op, nullptr, none);
+            pools[n].idx_slot = op.idx_slot >= 0 ? 0 : -1;
+            if (n == 0) { H = op.in_h; W = op.in_w; }
+            Ho = op.out_h; Wo = op.out_w;
+            ++n;
+        } else if (op.kind != OP_AVGNORM) {
+            EwOp *list = n == 0 ? k.pre : n == 1 ? k.mid : k.post;
+            int32_t &m = n == 0 ? k.n_pre : n == 1 ? k.n_mid : k.n_post;
+            if (op.kind == OP_ADD || m >= K_MAX_EW) return;
+            EwOp &e = list[m++];
+            e.kind = op.kind;
+            e.arg = op.param_off;
+        }
+    }
+    if (n == 0 || (n == 2 && pools[0].idx_slot >= 0)) return;
+    if (n == 1) {
+        copy_list(k.mid, k.n_mid, k.post, k.n_post);
+        k.n_mid = 0;
+    }
+    // maximum first: as in plan_nhwc
+    auto move_behind = [&](EwOp *from, int32_t &n_from, EwOp *to, int32_t &n_to) {
+        if (n_from == 0 || n_from + n_to > K_MAX_EW || !commutes_with_max(s, from, n_from, (int32_t)q.in_shape[1])) return;
+        for (int32_t j = n_to - 1; j >= 0; --j) to[j + n_from] = to[j];
+        for (int32_t j = 0; j < n_from; ++j) to[j] = from[j];
+        n_to += n_from;
+        n_from = 0;
+    };
+    if (n == 1 && pools[0].kind == OP_MAXPOOL && pools[0].idx_slot < 0) move_behind(k.pre, k.n_pre, k.post, k.n_post);
+    if (n == 2 && pools[0].kind == OP_MAXPOOL) move_behind(k.pre, k.n_pre, k.mid, k.n_mid);
+    if (n == 2 && pools[1].kind == OP_MAXPOOL && pools[1].idx_slot < 0) move_behind(k.mid, k.n_mid, k.post, k.n_post);
+    plan_strips(s, q, k, n == 2 ? &pools[0] : nullptr, pools[n - 1], H, W, Ho, Wo);
 }
 
 // Channels-last sequence: element-wise only, or one pooling step.
@@ -1619,7 +1671,8 @@ bs_status group_sequences(bs_stack *s, const bs_plan_options &o, const Limits &l
             st = plan_lds(s, q, o, lim);
         }
         if (st != BS_OK) return st;
-        if (!nhwc) st = prepare_jit(s, q, o.host_only != 0);
+        if (!nhwc && q.variant == BS_VARIANT_LDS_TILE) plan_row_strips(s, q, o);
+        if (!nhwc && q.strip_grid == 0) st = prepare_jit(s, q, o.host_only != 0);
         if (st != BS_OK) return st;
         if (di + 1 < drafts.size()) {
             uint64_t bytes = (uint64_t)q.out_shape[0] * q.out_shape[1] * q.out_shape[2] * q.out_shape[3] * es;

@@ -1,4 +1,4 @@
-// Device helpers shared by the channels-last kernels whose lanes walk strips of pixel columns (bs_nhwc_strip.hip,
+// Device helpers shared by the channels-last kernels whose lanes walk strips of pixel columns (bs_strip.hip,
 // bs_backward_nhwc.hip).
 #pragma once
 #include <hip/hip_runtime.h>

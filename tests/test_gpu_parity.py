@@ -1007,6 +1007,28 @@ def test_channels_last_strips(shape, dtype):
         _check_nhwc(layers, x, [], dtype, f"no strips/{name}{shape}", lane_exchange=-1)
 
 
+@pytest.mark.parametrize("shape", [(1, 1, 3, 3), (1, 2, 4, 5), (2, 3, 9, 7), (1, 2, 13, 11), (2, 5, 35, 17), (1, 1, 6, 261), (1, 3, 147, 30)])
+@pytest.mark.parametrize("dtype", ["f32", "bf16", "f16"])
+def test_row_major_strips(shape, dtype):
+    """Row-major 3 x 3 and 2 x 2 pooling on rows that are no whole vectors as strips of output columns: tensors shorter than
+    one lane's run of columns, the first and last rows of a tensor (read one element at a time), ragged strips, chunks of
+    rows, ties; bit for bit the oracle's values and indices (no tolerance: every layer has one order of operations)."""
+    c = shape[1]
+    stacks = dict(_fwd_strip_stacks(c))
+    stacks["max22"] = [wl.bn_params(c, 240), wl.relu(), wl.maxpool(2, 2)]
+    stacks["max22_idx"] = [wl.bn_params(c, 241), wl.relu(), wl.maxpool(2, 2, 0, True)]
+    stacks["max22_raw_idx_ceil"] = [wl.maxpool(2, 2, 0, True, True), wl.leaky_relu(0.1)]
+    stacks["avg22"] = [wl.bn_params(c, 242), wl.relu(), wl.avgpool(2, 2)]
+    stacks["avg22_ceil_in_range"] = [wl.avgpool(2, 2, 0, False, True)]
+    for name, layers in stacks.items():
+        x = wl.activation(shape, 243, dtype)
+        x[:, :, ::3, ::2] = 0.0
+        check(layers, x, [], dtype, f"row strips/{name}{shape}")
+    x = wl.activation(shape, 244, dtype)
+    x[:, :, :3] = -np.inf  # windows of nothing but -infinity: their first cell inside the plane
+    check([wl.maxpool(3, 2, 1, True), wl.relu()], x, [], dtype, f"row strips/infinities{shape}")
+
+
 def test_channels_last_strips_with_infinities_and_offsets_beyond_4_gib():
     """Windows of nothing but -infinity pick their first cell inside the plane; a channel slice whose pixels lie so far
     apart that byte offsets need more than 32 bits."""
