@@ -82,14 +82,15 @@ bool walks_rows(const bs_stack *s, const BwdStage &g)
            g.k.W / full <= 64 && g.k.Wo * p.sw == g.k.W && g.k.Ho == (g.k.H + 2 - 3) / p.sh + 1;
 }
 
-// Overlapping 3 x 3 max windows (stride 1 or 2, padding 0 or 1, any plane, any channel count) of channels-last tensors, no
-// Add in the stage: the kernel whose lanes walk strips of columns finds the picks itself.  Measured on MI355X against the
+// Overlapping 3 x 3 max windows (stride 1 or 2, padding 0 or 1) without Add in the stage, channels-last (any plane, any channel
+// count) or row-major where the rows are no whole vectors or the windows not padded: the kernel whose lanes walk strips of columns finds the picks itself.  Measured on MI355X against the
 // kernel that gathers recorded picks, the caller's picks at hand: ResNet stem bfloat16 87 -> 60 us, 192 x 71 x 71 / 2 without
 // padding binary16 55 -> 39 us.  (With Adds in the stage the strips would keep every residual's factors in registers.)
 bool walks_strips(const bs_stack *s, const BwdStage &g)
 {
     const PoolK &p = g.k.pool;
-    return s->opts.layout == BS_LAYOUT_NHWC && s->opts.lane_exchange >= 0 && g.n_res == 0 &&
+    if (s->opts.layout != BS_LAYOUT_NHWC && p.ph == 1 && g.k.W % (s->dtype == BS_F32 ? 4 : 8) == 0) return false;
+    return s->opts.lane_exchange >= 0 && g.n_res == 0 &&
            p.kind == OP_MAXPOOL && p.kh == 3 && p.kw == 3 && p.sh == p.sw && (p.sh == 1 || p.sh == 2) && p.ph == p.pw && p.ph <= 1;
 }
 
@@ -99,10 +100,10 @@ bool walks_strips(const bs_stack *s, const BwdStage &g)
 bool walks_two_levels(const bs_stack *s, const BwdStage &g, const BwdStage &nx)
 {
     const PoolK &p = g.k.pool, &q = nx.k.pool;
-    if (s->opts.layout == BS_LAYOUT_NHWC)  // any width, any size of the max pooling's output
-        return g.n_res == 0 && g.k.n_post == 0 && nx.k.n_ew == 0 && g.k.n_ew + nx.k.n_post <= K_BWD_EW && p.kind == OP_AVGSUM &&
+    if (walks_strips(s, nx))  // any size of the max pooling's output
+        return s->opts.lane_exchange >= 0 && g.n_res == 0 && g.k.n_post == 0 && nx.k.n_ew == 0 && g.k.n_ew + nx.k.n_post <= K_BWD_EW && p.kind == OP_AVGSUM &&
                p.kh == 3 && p.kw == 3 && p.sh == 1 && p.sw == 1 && p.ph == 1 && p.pw == 1 && g.k.Ho == g.k.H && g.k.Wo == g.k.W &&
-               q.sh == 2 && q.ph == 1 && walks_strips(s, nx);
+               q.sh == 2 && q.ph == 1;
     return s->opts.layout != BS_LAYOUT_NHWC && s->opts.lane_exchange >= 0 && g.n_res == 0 && nx.n_res == 0 && g.k.n_post == 0 &&
            nx.k.n_ew == 0 && g.k.n_ew + nx.k.n_post <= K_BWD_EW && p.kind == OP_AVGSUM && p.kh == 3 && p.kw == 3 && p.sh == 1 &&
            p.sw == 1 && p.ph == 1 && p.pw == 1 && g.k.Ho == g.k.H && g.k.Wo == g.k.W && q.kind == OP_MAXPOOL && q.sh == 2 &&
@@ -216,6 +217,7 @@ extern "C" bs_status bs_stack_plan_backward(bs_stack *stack)
             g.k.n_post = nx.k.n_post;
             g.k.pool2 = nx.k.pool;
             g.k.wave_rows = 2;
+            g.k.strips = walks_strips(stack, nx) ? 1 : 0;
             g.k.Ho = nx.k.Ho;
             g.k.Wo = nx.k.Wo;
             g.idx_slot = -1;
@@ -237,11 +239,13 @@ extern "C" bs_status bs_stack_plan_backward(bs_stack *stack)
                                   g.k.H == 2 * g.k.Ho && g.k.W == 2 * g.k.Wo;
             uint64_t lanes;
             g.k.nhwc = nhwc ? 1 : 0;
-            if (nhwc && (g.k.wave_rows == 2 || walks_strips(stack, g))) {
+            // (two levels: the stage's pooling is the average)
+            if (g.k.strips || walks_strips(stack, g)) {
                 // a lane per channel, strip of columns and chunk of window rows; a chunk holds two window rows at least
                 BwdK &k = g.k;
                 const bool two = k.wave_rows == 2;
-                const int32_t q = two ? K_BWD_STRIP2_Q : K_BWD_STRIP_Q, s = two ? 2 : p.sh;
+                const int32_t q = two ? bwd_strip2_columns(nhwc, stack->dtype) : K_BWD_STRIP_Q, s = two ? 2 : p.sh;
+                k.strips = 1;
                 k.wave_rows = two ? 2 : 1;
                 g.vec = 1;
                 k.cbs = (k.W + q - 1) / q;
@@ -322,7 +326,7 @@ extern "C" bs_status bs_stack_plan_backward(bs_stack *stack)
             g.k.div_c = make_fastdiv((uint32_t)g.k.C);
             g.threads = 256;
             g.grid = (int64_t)((lanes + 255) / 256);
-            if (g.k.wave_rows && !nhwc) g.grid = ((int64_t)g.k.units + 4 * g.k.spw - 1) / (4 * g.k.spw);  // whole segments per wave
+            if (g.k.wave_rows && !g.k.strips) g.grid = ((int64_t)g.k.units + 4 * g.k.spw - 1) / (4 * g.k.spw);  // whole segments per wave
             const bool is_max = p.kind == OP_MAXPOOL && !g.k.direct && !g.k.wave_rows;  // recorded picks needed
             // the buffers are sized by these shapes: a stage must end where the next one begins
             const int64_t *next = j + 1 < S ? plan->stages[j + 1].in_shape : stack->out_shape;
@@ -335,7 +339,8 @@ extern "C" bs_status bs_stack_plan_backward(bs_stack *stack)
                 g.g_off = off;
                 off += align256(numel(g.in_shape) * es);
             }
-            if (is_max) {
+            // (row-major strips find the picks themselves; the room for them stays in the size, which callers may have fixed)
+            if (is_max || (g.k.strips && !nhwc && g.k.wave_rows == 1)) {
                 g.idx_off = off;
                 off += align256(numel(g.out_shape) * 4);
             }

@@ -1115,7 +1115,7 @@ bs_status launch_backward_stage(const BwdK &k, int32_t dtype, int32_t vec, int64
     // a stage without Add gets the instances that keep no residual gradients in registers
     int32_t n_add = 0;
     for (int32_t j = 0; j < k.n_ew; ++j) n_add += k.ew[j].kind == OP_ADD;
-    if (k.nhwc && k.wave_rows) return launch_backward_strips(k, dtype, vec, grid, threads, stream);
+    if (k.strips) return launch_backward_strips(k, dtype, vec, grid, threads, stream);
     if (k.nhwc) {
         // a lane per (pixel or window, channel vector): the divisors must be the ones the kernels assume
         if ((vec != 1 && vec != full) || k.C % vec != 0 || (int64_t)k.div_wv.d * vec != k.C ||

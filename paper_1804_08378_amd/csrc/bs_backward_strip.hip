@@ -1,13 +1,14 @@
-// Backward kernels of channels-last (N, H, W, C in memory) stages with overlapping 3 x 3 pooling windows: no recorded
-// picks, no recomputation pass, nothing through the workspace.
+// Backward kernels of stages with overlapping 3 x 3 pooling windows whose lanes walk strips of columns: no recorded picks, no
+// recomputation pass, nothing through the workspace.
 //
-// A lane owns V channels of a strip of Q pixel columns and walks down a chunk of rows.  The lanes of a wave are neighbouring
-// channels (then neighbouring strips), so every access of a wave is contiguous; the columns a strip's windows reach into
-// beside it are read and computed by the lane itself -- they come from the caches, and no lane waits for another one: no
-// LDS, no barrier, no lane exchange, any width and any channel count.  V = 1: two channels per lane (16-bit storage) measured
-// the same in the one-level kernel and spill in the two-level one.
-//
-// Work-groups are numbered so that each XCD gets one contiguous part of the image (xcd_contiguous): the strips that share
+// A lane owns one channel of a strip of Q columns and walks down a chunk of rows; the columns a strip's windows reach into
+// beside it are read and computed by the lane itself -- they come from the caches, and no lane waits for another one: no LDS,
+// no barrier, no lane exchange, any width and any channel count.  (Two channels per lane, 16-bit storage, measured the same in
+// the one-level kernel and spill in the two-level one.)
+//   Channels-last tensors (CL): the lanes of a wave are neighbouring channels, then neighbouring strips; every access is contiguous.
+//   Row-major tensors: the lanes are neighbouring strips of a row; a lane reads and writes its columns as vectors at whatever
+//   address they begin.
+// Work-groups are numbered so that each XCD gets one contiguous part of the tensor (xcd_contiguous): the strips that share
 // columns find them in one L2.
 #include <hip/hip_runtime.h>
 
@@ -20,56 +21,77 @@
 namespace bs {
 namespace {
 
-// V elements at byte offset `off`.  OFF: uint32_t where every tensor of the launch is below 4 GiB (one address addition
-// per access: the base stays in scalar registers), else uint64_t.
-template <int DT, int V, typename OFF>
-BS_DEV void load_at(const BwdK &k, int which, int site, const void *base, OFF off, float *v)
+// OFF: the type of byte offsets -- uint32_t where every tensor of the launch ends below 4 GiB (one address addition per access:
+// the base stays in scalar registers), else uint64_t.  One element at byte offset `off`, as it lies in memory.
+template <int DT, typename OFF>
+BS_DEV uint32_t load_at(const BwdK &k, int which, int site, const void *base, OFF off)
 {
 #if defined(BS_BWD_AUDIT)
-    if constexpr (sizeof(OFF) == 4) off = audited(k, which, site, off / elem_bytes<DT>(), V) * elem_bytes<DT>();
+    if constexpr (sizeof(OFF) == 4) off = audited(k, which, site, off / elem_bytes<DT>(), 1) * elem_bytes<DT>();
 #endif
-    float u[V];
-    Raw<DT, V> r;
-    r.q = *reinterpret_cast<const typename Raw<DT, V>::type *>(static_cast<const char *>(base) + off);
-    unpack<DT, V>(r, u);
-#pragma unroll
-    for (int e = 0; e < V; ++e) v[e] = u[e];
+    uint32_t w[1];
+    load_run<DT, 1>(static_cast<const char *>(base) + off, w);
+    return w[0];
 }
 
-template <int DT, int V, typename OFF>
-BS_DEV void store_at(const BwdK &k, int site, void *base, OFF off, const float (&v)[V])
+template <int DT, typename OFF>
+BS_DEV void store_at(const BwdK &k, int site, void *base, OFF off, float v)
 {
 #if defined(BS_BWD_AUDIT)
-    if constexpr (sizeof(OFF) == 4) off = audited(k, 2, site, off / elem_bytes<DT>(), V) * elem_bytes<DT>();
+    if constexpr (sizeof(OFF) == 4) off = audited(k, 2, site, off / elem_bytes<DT>(), 1) * elem_bytes<DT>();
 #endif
-    store_elems<DT, V>(static_cast<char *>(base) + off, 0, v);
+    const float t[1] = {v};
+    store_elems<DT, 1>(static_cast<char *>(base) + off, 0, t);
 }
 
-// N pixels of a row at byte offsets row + col[j].
-template <int DT, int V, int N, typename OFF>
-BS_DEV void load_row(const BwdK &k, int which, int site, const void *base, OFF row, const OFF (&col)[N], float *v)
+// Words that hold N columns of a row: channels-last one per column, row-major the run as it lies in memory.
+template <int DT, bool CL, int N>
+constexpr int row_words() { return CL ? N : run_words<DT, N>(); }
+
+// N columns of a row at byte offset `row`, column j at + col[j] (outside the plane: a safe column, the caller replaces it).
+// Row-major: the run from column `first` is read whole if it begins at `last` at the latest (so that it ends inside the tensor;
+// columns beside the plane are other rows' elements then), else one by one.
+template <int DT, bool CL, int N, typename OFF>
+BS_DEV void load_row(const BwdK &k, int which, int site, const void *base, OFF row, const OFF (&col)[N], int32_t first, bool fits, OFF last,
+                     uint32_t (&w)[row_words<DT, CL, N>()])
+{
+    if constexpr (CL) {
+#pragma unroll
+        for (int j = 0; j < N; ++j) w[j] = load_at<DT, OFF>(k, which, site, base, row + col[j]);
+    } else {
+        const OFF from = row + (OFF)first * (OFF)elem_bytes<DT>();
+        if (fits && from <= last) {
+            load_run<DT, N>(static_cast<const char *>(base) + from, w);
+        } else {
+#pragma unroll
+            for (int j = 0; j < N; ++j) {
+                const uint32_t e = load_at<DT, OFF>(k, which, site, base, row + col[j]);
+                if constexpr (DT == DT_F32) w[j] = e;
+                else w[j / 2] = j % 2 ? w[j / 2] | e << 16 : e;
+            }
+        }
+    }
+}
+template <int DT, bool CL, int N>
+BS_DEV void unpack_row(const uint32_t (&w)[row_words<DT, CL, N>()], float *v)
 {
 #pragma unroll
-    for (int j = 0; j < N; ++j) load_at<DT, V, OFF>(k, which, site, base, row + col[j], v + j * V);
+    for (int j = 0; j < N; ++j) v[j] = CL ? run_element<DT>(&w[CL ? j : 0], 0) : run_element<DT>(w, j);
 }
 
-// N pixels of a row of the input gradient, `pitch` bytes apart; whole: all of them lie in the plane.
-template <int DT, int V, int N, typename OFF>
-BS_DEV void store_row(const BwdK &k, int site, OFF at, int32_t first, int32_t width, OFF pitch, bool whole, const float (&v)[N * V])
+// N columns of a row of the input gradient, `pitch` bytes apart; whole: all of them lie in the plane.
+template <int DT, bool CL, int N, typename OFF>
+BS_DEV void store_row(const BwdK &k, int site, OFF at, int32_t first, int32_t width, OFF pitch, bool whole, const float (&v)[N])
 {
-    auto pixel = [&](int j) __attribute__((always_inline)) {
-        float u[V];
+    if (!CL && whole) {
+        store_run<DT, N>(static_cast<char *>(k.g_in) + at, v);
+    } else if (whole) {
 #pragma unroll
-        for (int e = 0; e < V; ++e) u[e] = v[j * V + e];
-        store_at<DT, V, OFF>(k, site, k.g_in, at + (OFF)j * pitch, u);
-    };
-    if (whole) {
-#pragma unroll
-        for (int j = 0; j < N; ++j) pixel(j);
+        for (int j = 0; j < N; ++j) store_at<DT, OFF>(k, site, k.g_in, at + (OFF)j * pitch, v[j]);
     } else {
 #pragma unroll
         for (int j = 0; j < N; ++j)
-            if (first + j < width) pixel(j);
+            if (first + j < width) store_at<DT, OFF>(k, site, k.g_in, at + (OFF)j * pitch, v[j]);
     }
 }
 
@@ -172,28 +194,58 @@ struct StripList {
     }
 };
 
-// The lane's place: total = images * chunks * strips * (C / V), channel vectors fastest.
+// The lane's place.  Channels-last: (image, chunk, strip, channel), row-major: (image, channel, chunk, strip), the last one fastest.
 struct StripLane {
     bool live;
-    uint32_t n;
+    uint32_t n, plane;
     int32_t chunk, q0, c0;
 };
 
-template <int V, int Q>
+template <bool CL, int Q>
 BS_DEV StripLane strip_lane(const BwdK &k)
 {
     StripLane L;
     uint32_t i = xcd_contiguous(blockIdx.x, gridDim.x) * 256u + threadIdx.x;
     L.live = i < k.total;
     i = L.live ? i : 0u;
-    const uint32_t u = fdiv(i, k.div_wv);
-    L.c0 = (int32_t)(i - u * k.div_wv.d) * V;
-    const uint32_t v = fdiv(u, k.div_cbs);
-    L.q0 = (int32_t)(u - v * k.div_cbs.d) * Q;
-    L.n = fdiv(v, k.div_chunks);
-    L.chunk = (int32_t)(v - L.n * k.div_chunks.d);
+    uint32_t v = i;
+    L.plane = 0;
+    if constexpr (CL) {
+        v = fdiv(i, k.div_wv);
+        L.c0 = (int32_t)(i - v * k.div_wv.d);
+    }
+    const uint32_t u = fdiv(v, k.div_cbs);
+    L.q0 = (int32_t)(v - u * k.div_cbs.d) * Q;
+    const uint32_t p = fdiv(u, k.div_chunks);
+    L.chunk = (int32_t)(u - p * k.div_chunks.d);
+    L.n = p;
+    if constexpr (!CL) {
+        L.plane = p;
+        L.n = fdiv(p, k.div_c);
+        L.c0 = (int32_t)(p - L.n * k.div_c.d);
+    }
     return L;
 }
+
+// Where the lane's rows begin and how far columns and rows lie apart (bytes).
+template <int DT, bool CL, typename OFF>
+struct StripPlaces {
+    OFF pa, pg, pi, abase, gbase, ibase, arow, grow, irow;
+    BS_DEV StripPlaces(const BwdK &k, const StripLane &L)
+    {
+        constexpr int ES = elem_bytes<DT>();
+        pa = CL ? (OFF)(k.C + k.a_extra) * ES : (OFF)ES;
+        pg = CL ? (OFF)(k.C + k.gout_extra) * ES : (OFF)ES;
+        pi = CL ? (OFF)(k.C + k.gin_extra) * ES : (OFF)ES;
+        const uint32_t in_px = (uint32_t)(k.H * k.W), out_px = (uint32_t)(k.Ho * k.Wo);
+        abase = CL ? (OFF)(L.n * in_px) * pa + (OFF)L.c0 * ES : ((OFF)(L.plane * in_px) + (OFF)L.n * k.a_extra) * ES;
+        gbase = CL ? (OFF)(L.n * out_px) * pg + (OFF)L.c0 * ES : ((OFF)(L.plane * out_px) + (OFF)L.n * k.gout_extra) * ES;
+        ibase = (CL ? (OFF)(L.n * in_px) * pi + (OFF)L.c0 * ES : ((OFF)(L.plane * in_px) + (OFF)L.n * k.gin_extra) * ES) + (OFF)L.q0 * pi;
+        arow = (OFF)k.W * pa;
+        grow = (OFF)k.Wo * pg;
+        irow = (OFF)k.W * pi;
+    }
+};
 
 // The windows' picks from the row maxima of their three rows.  top: the first window row lies above the plane (padding, all
 // -infinity) and must not be picked, not even by a window of nothing but -infinity.
@@ -249,9 +301,11 @@ BS_DEV void scatter(const int32_t (&pick)[N * V], const float (&g)[N * V], float
 // Measured on MI355X, us of a call with the caller's picks at hand, gathering kernel -> this one: ResNet stem 64 x 64 x 112 x 112
 // float32 105 -> 98 (4.7 TB/s of input, gradients in and out: waits for memory), bfloat16 87 -> 60 (vector instructions: 34
 // per cell, 70 % of the time); 32 x 192 x 71 x 71 / 2 without padding binary16 55 -> 39; without kept picks the gathering
-// kernel needs a forward pass on top.
+// kernel needs a forward pass on top.  Row-major rows that are no whole vectors, with the forward pass for the picks -> this
+// kernel: 64 x 64 x 111 x 111 / 2 float32 385 -> 137, bfloat16 472 -> 72; 32 x 64 x 147 x 147 / 2 without padding binary16
+// 404 -> 62; whole vectors without padding (32 x 64 x 112 x 112 / 2) float32 180 -> 72.
 // =============================================================================
-template <int DT, int V, int Q, int S, int P, int PRE, int POST, typename OFF>
+template <int DT, bool CL, int Q, int S, int P, int PRE, int POST, typename OFF>
 __global__ __launch_bounds__(256) void bwd_strip_kernel(const BwdK k)
 {
     static_assert(Q % S == 0 && (S == 1 || S == 2) && (P == 0 || P == 1), "compiled windows");
@@ -259,15 +313,12 @@ __global__ __launch_bounds__(256) void bwd_strip_kernel(const BwdK k)
     constexpr int NW = (Q + 1) / S + 1;            // windows over the strip
     constexpr int X0 = OW0 * S - P;                // their first column, from q0
     constexpr int CW = (NW - 1) * S + 3;           // their columns
-    constexpr int KEEP = 3 - S, ES = elem_bytes<DT>();
+    constexpr int KEEP = 3 - S, V = 1, ES = elem_bytes<DT>();
     constexpr int OEND = (P + S - 1) / S;
-    const StripLane L = strip_lane<V, Q>(k);
+    const StripLane L = strip_lane<CL, Q>(k);
+    const StripPlaces<DT, CL, OFF> at0(k, L);
+    const OFF pa = at0.pa, pg = at0.pg, pi = at0.pi, arow = at0.arow, grow = at0.grow, irow = at0.irow;
 
-    const OFF pa = (OFF)(k.C + k.a_extra) * ES, pg = (OFF)(k.C + k.gout_extra) * ES, pi = (OFF)(k.C + k.gin_extra) * ES;
-    const OFF abase = (OFF)(L.n * (uint32_t)(k.H * k.W)) * pa + (OFF)L.c0 * ES;
-    const OFF gbase = (OFF)(L.n * (uint32_t)(k.Ho * k.Wo)) * pg + (OFF)L.c0 * ES;
-    const OFF ibase = ((OFF)(L.n * (uint32_t)(k.H * k.W)) + (OFF)L.q0) * pi + (OFF)L.c0 * ES;
-    const OFF arow = (OFF)k.W * pa, grow = (OFF)k.Wo * pg, irow = (OFF)k.W * pi;
     const int32_t x0 = L.q0 + X0, ow0 = L.q0 / S + OW0;
     constexpr int LEAD = P == 1 ? -OW0 : -1;
     const bool lead = L.q0 == 0;
@@ -280,6 +331,8 @@ __global__ __launch_bounds__(256) void bwd_strip_kernel(const BwdK k)
         win[b] = ow0 + b >= 0 && ow0 + b < k.Wo;
         gcol[b] = (OFF)min(max(ow0 + b, 0), k.Wo - 1) * pg;
     }
+    const bool a_fits = k.a_bytes >= (uint64_t)CW * ES, g_fits = k.g_bytes >= (uint64_t)NW * ES;
+    const OFF a_last = a_fits ? (OFF)(k.a_bytes - (uint64_t)CW * ES) : (OFF)0, g_last = g_fits ? (OFF)(k.g_bytes - (uint64_t)NW * ES) : (OFF)0;
     const bool inside = x0 >= 0 && x0 + CW <= k.W, whole = L.q0 + Q <= k.W;
 
     StripList<DT, V, PRE> pre;
@@ -293,21 +346,24 @@ __global__ __launch_bounds__(256) void bwd_strip_kernel(const BwdK k)
     int32_t code[3][NW * V];
     // rows are requested in order, `at` = the offset of row `next` (clamped to the plane)
     int32_t next = oh_first * S - P;
-    OFF at = abase + (OFF)min(max(next, 0), k.H - 1) * arow;
-    OFF gat = gbase + (OFF)min(max(oh_first, 0), k.Ho - 1) * grow;
-    OFF iat = ibase + (OFF)r_lo * irow;
+    OFF at = at0.abase + (OFF)min(max(next, 0), k.H - 1) * arow;
+    OFF gat = at0.gbase + (OFF)min(max(oh_first, 0), k.Ho - 1) * grow;
+    OFF iat = at0.ibase + (OFF)r_lo * irow;
     // the next N rows -> ring slots slots(0) .. slots(N - 1), scanned as window rows DH0, DH0 + 1 ...
     auto take_rows = [&](auto n_tag, auto dh_tag, auto slot_of) __attribute__((always_inline)) {
         constexpr int N = decltype(n_tag)::value, DH0 = decltype(dh_tag)::value;
         float x[N * CW * V], d[N * CW * V];
+        uint32_t w[N][row_words<DT, CL, CW>()];  // requested for all rows before the first is used
         bool ok[N];
 #pragma unroll
         for (int j = 0; j < N; ++j) {
             ok[j] = next >= 0 && next < k.H;
-            load_row<DT, V, CW, OFF>(k, 0, 40, k.a, at, acol, &x[j * CW * V]);
+            load_row<DT, CL, CW, OFF>(k, 0, 40, k.a, at, acol, x0, a_fits, a_last, w[j]);
             at += next >= 0 && next < k.H - 1 ? arow : (OFF)0;
             ++next;
         }
+#pragma unroll
+        for (int j = 0; j < N; ++j) unpack_row<DT, CL, CW>(w[j], &x[j * CW]);
         pre.template apply<N * CW * V>(k, x, d);
         each_of(std::make_integer_sequence<int, N>{}, [&](auto j_tag) __attribute__((always_inline)) {
             constexpr int j = decltype(j_tag)::value, dh = DH0 + j;
@@ -340,9 +396,11 @@ __global__ __launch_bounds__(256) void bwd_strip_kernel(const BwdK k)
         const int32_t hA = oh * S - P;
         const bool row_ok = oh >= 0 && oh < k.Ho;
         float g[NW * V];
-        load_row<DT, V, NW, OFF>(k, 1, 41, k.g_out, gat, gcol, g);
+        uint32_t gw[row_words<DT, CL, NW>()];
+        load_row<DT, CL, NW, OFF>(k, 1, 41, k.g_out, gat, gcol, ow0, g_fits, g_last, gw);
         gat += oh >= 0 && oh < k.Ho - 1 ? grow : (OFF)0;
         take_rows(std::integral_constant<int, S>{}, std::integral_constant<int, KEEP>{}, [](int j) { return KEEP + j == 2 ? R2 : KEEP + j; });
+        unpack_row<DT, CL, NW>(gw, g);
         float best[NW * V];
         int32_t pick[NW * V];
         combine_rows<NW * V>(m[R0], code[R0], m[1], code[1], m[R2], code[R2], hA < 0, best, pick);
@@ -364,7 +422,7 @@ __global__ __launch_bounds__(256) void bwd_strip_kernel(const BwdK k)
                 float v[Q * V];
 #pragma unroll
                 for (int i = 0; i < Q * V; ++i) v[i] = s[slot][i] * t[slot][i];
-                store_row<DT, V, Q, OFF>(k, 42, iat, L.q0, k.W, pi, whole, v);
+                store_row<DT, CL, Q, OFF>(k, 42, iat, L.q0, k.W, pi, whole, v);
                 iat += irow;
             }
         }
@@ -413,22 +471,19 @@ __global__ __launch_bounds__(256) void bwd_strip_kernel(const BwdK k)
 // Q columns need Q + 2 of the average's gradient, Q / 2 + 2 windows, Q + 5 averages and Q + 7 inputs.
 // INC: every divisor is 9 (count_include_pad, nothing overhangs).
 // Measured on MI355X (halo_stress, us of a call): three stages with two forward passes through the workspace -> this kernel:
-// float32 510 -> 109, bfloat16 390 -> 116.  Bound by vector instructions (the 18 additions per average and their halo, the
+// float32 510 -> 109, bfloat16 390 -> 116; row-major, 64 x 64 x 55 x 55 float32 291 -> 53, binary16 287 -> 41.  Bound by vector instructions (the 18 additions per average and their halo, the
 // scans); two waves per SIMD with 8 columns beat four with 4 columns, which compute 9 averages per 4 columns instead of
 // 13 per 8.
 // =============================================================================
-template <int DT, int V, int Q, bool INC, int PRE, int POST, typename OFF>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) void bwd_strip2_kernel(const BwdK k)
+template <int DT, bool CL, int Q, bool INC, int PRE, int POST, typename OFF>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(Q == 8 ? 2 : 3, Q == 8 ? 2 : 3))) void bwd_strip2_kernel(const BwdK k)
 {
     static_assert(Q % 2 == 0, "whole windows");
-    constexpr int NW = Q / 2 + 2, CA = Q + 5, CX = Q + 7, CG = Q + 2, ES = elem_bytes<DT>();
-    const StripLane L = strip_lane<V, Q>(k);
+    constexpr int NW = Q / 2 + 2, CA = Q + 5, CX = Q + 7, CG = Q + 2, V = 1, ES = elem_bytes<DT>();
+    const StripLane L = strip_lane<CL, Q>(k);
+    const StripPlaces<DT, CL, OFF> at0(k, L);
+    const OFF pa = at0.pa, pg = at0.pg, pi = at0.pi, arow = at0.arow, grow = at0.grow, irow = at0.irow;
 
-    const OFF pa = (OFF)(k.C + k.a_extra) * ES, pg = (OFF)(k.C + k.gout_extra) * ES, pi = (OFF)(k.C + k.gin_extra) * ES;
-    const OFF abase = (OFF)(L.n * (uint32_t)(k.H * k.W)) * pa + (OFF)L.c0 * ES;
-    const OFF gbase = (OFF)(L.n * (uint32_t)(k.Ho * k.Wo)) * pg + (OFF)L.c0 * ES;
-    const OFF ibase = ((OFF)(L.n * (uint32_t)(k.H * k.W)) + (OFF)L.q0) * pi + (OFF)L.c0 * ES;
-    const OFF arow = (OFF)k.W * pa, grow = (OFF)k.Wo * pg, irow = (OFF)k.W * pi;
     const int32_t x0 = L.q0 - 4, ow0 = L.q0 / 2 - 1;
     const bool lead = L.q0 == 0;
     OFF acol[CX], gcol[NW];
@@ -440,6 +495,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
         win[b] = ow0 + b >= 0 && ow0 + b < k.Wo;
         gcol[b] = (OFF)min(max(ow0 + b, 0), k.Wo - 1) * pg;
     }
+    const bool a_fits = k.a_bytes >= (uint64_t)CX * ES, g_fits = k.g_bytes >= (uint64_t)NW * ES;
+    const OFF a_last = a_fits ? (OFF)(k.a_bytes - (uint64_t)CX * ES) : (OFF)0, g_last = g_fits ? (OFF)(k.g_bytes - (uint64_t)NW * ES) : (OFF)0;
     const bool inside = x0 >= 0 && x0 + CX <= k.W, whole = L.q0 + Q <= k.W;
 
     StripList<DT, V, PRE> pre;
@@ -454,21 +511,24 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     int32_t code[3][NW * V];
     // rows are requested in order, `at` = the offset of row `next` (clamped to the plane)
     int32_t next = oh_first * 2 - 2;
-    OFF at = abase + (OFF)min(max(next, 0), k.H - 1) * arow;
-    OFF gat = gbase + (OFF)min(max(oh_first, 0), k.Ho - 1) * grow;
-    OFF iat = ibase + (OFF)r_lo * irow;
+    OFF at = at0.abase + (OFF)min(max(next, 0), k.H - 1) * arow;
+    OFF gat = at0.gbase + (OFF)min(max(oh_first, 0), k.Ho - 1) * grow;
+    OFF iat = at0.ibase + (OFF)r_lo * irow;
     // the next N rows: leading list -> y (outside the plane +0, the average's padding), derivatives -> T
     auto take_rows = [&](auto n_tag, int slot, int tslot) __attribute__((always_inline)) {
         constexpr int N = decltype(n_tag)::value;
         float x[N * CX * V], d[N * CX * V];
+        uint32_t w[N][row_words<DT, CL, CX>()];  // requested for all rows before the first is used
         bool ok[N];
 #pragma unroll
         for (int j = 0; j < N; ++j) {
             ok[j] = next >= 0 && next < k.H;
-            load_row<DT, V, CX, OFF>(k, 0, 43, k.a, at, acol, &x[j * CX * V]);
+            load_row<DT, CL, CX, OFF>(k, 0, 43, k.a, at, acol, x0, a_fits, a_last, w[j]);
             at += next >= 0 && next < k.H - 1 ? arow : (OFF)0;
             ++next;
         }
+#pragma unroll
+        for (int j = 0; j < N; ++j) unpack_row<DT, CL, CX>(w[j], &x[j * CX]);
         pre.template apply<N * CX * V>(k, x, d);
 #pragma unroll
         for (int j = 0; j < N; ++j) {
@@ -536,11 +596,13 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
         const int32_t hA = oh * 2 - 1;  // average rows hA .. hA + 2 under this window row
         const bool row_ok = oh >= 0 && oh < k.Ho;
         float g[NW * V];
-        load_row<DT, V, NW, OFF>(k, 1, 44, k.g_out, gat, gcol, g);
+        uint32_t gw[row_words<DT, CL, NW>()];
+        load_row<DT, CL, NW, OFF>(k, 1, 44, k.g_out, gat, gcol, ow0, g_fits, g_last, gw);
         gat += oh >= 0 && oh < k.Ho - 1 ? grow : (OFF)0;
         take_rows(std::integral_constant<int, 2>{}, N0, 3);
         average_row(y[K0], y[K0 + 1], y[N0], std::integral_constant<int, 1>{}, 1, hA + 1);
         average_row(y[K0 + 1], y[N0], y[N0 + 1], std::integral_constant<int, 2>{}, R2, hA + 2);
+        unpack_row<DT, CL, NW>(gw, g);
         float best[NW * V];
         int32_t pick[NW * V];
         combine_rows<NW * V>(m[R0], code[R0], m[1], code[1], m[R2], code[R2], hA < 0, best, pick);
@@ -572,7 +634,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
 #pragma unroll
                 for (int i = 0; i < Q * V; ++i)
                     v[i] = (d == 0 ? (hs[K0][i] + hs[K0 + 1][i]) + hs[N0][i] : (hs[K0 + 1][i] + hs[N0][i]) + hs[N0 + 1][i]) * T[d][i];
-                store_row<DT, V, Q, OFF>(k, 45, iat, L.q0, k.W, pi, whole, v);
+                store_row<DT, CL, Q, OFF>(k, 45, iat, L.q0, k.W, pi, whole, v);
                 iat += irow;
             }
         }
@@ -597,24 +659,24 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
 
 constexpr int BN_RELU = OP_BN + OP_RELU * K_EW_BASE;
 
-template <int DT, int S, int P>
+template <int DT, bool CL, int S, int P>
 void launch1(const BwdK &k, bool wide, int32_t pre, dim3 g, hipStream_t st)
 {
-    constexpr int V = 1, Q = K_BWD_STRIP_Q;
-    if (wide) bwd_strip_kernel<DT, V, Q, S, P, -1, -1, uint64_t><<<g, 256, 0, st>>>(k);
-    else if (pre == BN_RELU && k.n_post == 0) bwd_strip_kernel<DT, V, Q, S, P, BN_RELU, 0, uint32_t><<<g, 256, 0, st>>>(k);
-    else if (k.n_post == 0) bwd_strip_kernel<DT, V, Q, S, P, -1, 0, uint32_t><<<g, 256, 0, st>>>(k);
-    else bwd_strip_kernel<DT, V, Q, S, P, -1, -1, uint32_t><<<g, 256, 0, st>>>(k);
+    constexpr int Q = K_BWD_STRIP_Q;
+    if (wide) bwd_strip_kernel<DT, CL, Q, S, P, -1, -1, uint64_t><<<g, 256, 0, st>>>(k);
+    else if (pre == BN_RELU && k.n_post == 0) bwd_strip_kernel<DT, CL, Q, S, P, BN_RELU, 0, uint32_t><<<g, 256, 0, st>>>(k);
+    else if (k.n_post == 0) bwd_strip_kernel<DT, CL, Q, S, P, -1, 0, uint32_t><<<g, 256, 0, st>>>(k);
+    else bwd_strip_kernel<DT, CL, Q, S, P, -1, -1, uint32_t><<<g, 256, 0, st>>>(k);
 }
 
-template <int DT>
+template <int DT, bool CL>
 void launch2(const BwdK &k, bool wide, int32_t pre, int32_t post, dim3 g, hipStream_t st)
 {
-    constexpr int V = 1, Q = K_BWD_STRIP2_Q;
+    constexpr int Q = bwd_strip2_columns(CL, DT);
     const bool inc = k.pool.count_include_pad == 1;
-    if (wide) bwd_strip2_kernel<DT, V, Q, false, -1, -1, uint64_t><<<g, 256, 0, st>>>(k);
-    else if (pre == BN_RELU && post == BN_RELU && inc) bwd_strip2_kernel<DT, V, Q, true, BN_RELU, BN_RELU, uint32_t><<<g, 256, 0, st>>>(k);
-    else bwd_strip2_kernel<DT, V, Q, false, -1, -1, uint32_t><<<g, 256, 0, st>>>(k);
+    if (wide) bwd_strip2_kernel<DT, CL, Q, false, -1, -1, uint64_t><<<g, 256, 0, st>>>(k);
+    else if (pre == BN_RELU && post == BN_RELU && inc) bwd_strip2_kernel<DT, CL, Q, true, BN_RELU, BN_RELU, uint32_t><<<g, 256, 0, st>>>(k);
+    else bwd_strip2_kernel<DT, CL, Q, false, -1, -1, uint32_t><<<g, 256, 0, st>>>(k);
 }
 
 int32_t list_code(const BwdK &k, int32_t first, int32_t n)
@@ -627,45 +689,54 @@ int32_t list_code(const BwdK &k, int32_t first, int32_t n)
 
 }  // namespace
 
-bs_status launch_backward_strips(const BwdK &k, int32_t dtype, int32_t vec, int64_t grid, int32_t threads, void *stream)
+bs_status launch_backward_strips(const BwdK &arg, int32_t dtype, int32_t vec, int64_t grid, int32_t threads, void *stream)
 {
+    BwdK k = arg;
     const PoolK &p = k.pool, &q = k.pool2;
-    const bool two = k.wave_rows == 2;
-    const int32_t s = two ? 2 : p.sh, Q = two ? K_BWD_STRIP2_Q : K_BWD_STRIP_Q;
+    const bool two = k.wave_rows == 2, nhwc = k.nhwc != 0;
+    const int32_t s = two ? 2 : p.sh, Q = two ? bwd_strip2_columns(nhwc, dtype) : K_BWD_STRIP_Q;
     // what the kernels assume: no Add; 3 x 3 windows; strips and chunks that cover the plane; the divisors of the lane numbering
     if (k.n_ew < 0 || k.n_post < 0 || k.n_ew + k.n_post > K_BWD_EW || threads != 256 || grid < 1) return BS_ERR_UNSUPPORTED;
     for (int32_t j = 0; j < k.n_ew + k.n_post; ++j)
         if (k.ew[j].kind == OP_ADD) return BS_ERR_UNSUPPORTED;
     const PoolK &mx = two ? q : p;
-    if (!k.nhwc || k.direct || vec != 1 || mx.kind != OP_MAXPOOL || mx.kh != 3 || mx.kw != 3 || mx.sh != mx.sw || mx.ph != mx.pw ||
-        mx.ph < 0 || mx.ph > 1 || (mx.sh != 1 && mx.sh != 2) || (int64_t)k.div_wv.d != k.C || (int64_t)k.div_cbs.d != k.cbs ||
+    if (!k.strips || k.direct || vec != 1 || mx.kind != OP_MAXPOOL || mx.kh != 3 || mx.kw != 3 || mx.sh != mx.sw || mx.ph != mx.pw ||
+        mx.ph < 0 || mx.ph > 1 || (mx.sh != 1 && mx.sh != 2) || (int64_t)(nhwc ? k.div_wv.d : k.div_c.d) != k.C || (int64_t)k.div_cbs.d != k.cbs ||
         (int64_t)k.div_chunks.d != k.chunks || k.cbs != (k.W + Q - 1) / Q || k.rc < 1 || k.chunks < 1 ||
-        (int64_t)k.chunks * k.rc * s < k.H || k.total % ((uint32_t)k.cbs * (uint32_t)k.chunks * k.div_wv.d) != 0 ||
+        (int64_t)k.chunks * k.rc * s < k.H || k.total % ((uint64_t)k.cbs * k.chunks * k.C) != 0 ||
         (uint64_t)grid * 256 < k.total || k.Ho < 1 || k.Wo < 1)
         return BS_ERR_UNSUPPORTED;
     if (two && (p.kind != OP_AVGSUM || p.kh != 3 || p.kw != 3 || p.sh != 1 || p.sw != 1 || p.ph != 1 || p.pw != 1 || mx.sh != 2 || mx.ph != 1))
         return BS_ERR_UNSUPPORTED;
-    // 32-bit byte offsets where every tensor ends below 4 GiB
-    const uint64_t images = k.total / ((uint64_t)k.cbs * k.chunks * k.div_wv.d), es = dtype == BS_F32 ? 4 : 2;
-    const uint64_t in_px = images * k.H * k.W, out_px = images * k.Ho * k.Wo;
-    const uint64_t far = std::max(in_px * std::max((uint64_t)k.C + k.a_extra, (uint64_t)k.C + k.gin_extra), out_px * ((uint64_t)k.C + k.gout_extra)) * es;
-    const bool wide = far > 0xffffffffull;
+    // elements from the first to the last one of each tensor; 32-bit byte offsets where they all end below 4 GiB
+    const uint64_t images = k.total / ((uint64_t)k.cbs * k.chunks * k.C), es = dtype == BS_F32 ? 4 : 2;
+    auto reach = [&](uint64_t pixels, uint64_t extra) { return nhwc ? images * pixels * (k.C + extra) : images * pixels * k.C + (images - 1) * extra; };
+    const uint64_t in_px = (uint64_t)k.H * k.W, out_px = (uint64_t)k.Ho * k.Wo;
+    k.a_bytes = reach(in_px, k.a_extra) * es;
+    k.g_bytes = reach(out_px, k.gout_extra) * es;
+    const bool wide = std::max(std::max(k.a_bytes, k.g_bytes), reach(in_px, k.gin_extra) * es) > 0xffffffffull;
     const int32_t pre = list_code(k, 0, k.n_ew), post = list_code(k, k.n_ew, k.n_post);
     hipStream_t st = static_cast<hipStream_t>(stream);
     const dim3 g((uint32_t)grid);
-#define BS_STRIPS(DT)                                                          \
-    do {                                                                       \
-        if (two) launch2<DT>(k, wide, pre, post, g, st);                       \
-        else if (p.sh == 2 && p.ph == 1) launch1<DT, 2, 1>(k, wide, pre, g, st); \
-        else if (p.sh == 2) launch1<DT, 2, 0>(k, wide, pre, g, st);            \
-        else if (p.ph == 1) launch1<DT, 1, 1>(k, wide, pre, g, st);            \
-        else launch1<DT, 1, 0>(k, wide, pre, g, st);                           \
+#define BS_STRIPS_CL(DT, CL)                                                       \
+    do {                                                                           \
+        if (two) launch2<DT, CL>(k, wide, pre, post, g, st);                       \
+        else if (p.sh == 2 && p.ph == 1) launch1<DT, CL, 2, 1>(k, wide, pre, g, st); \
+        else if (p.sh == 2) launch1<DT, CL, 2, 0>(k, wide, pre, g, st);            \
+        else if (p.ph == 1) launch1<DT, CL, 1, 1>(k, wide, pre, g, st);            \
+        else launch1<DT, CL, 1, 0>(k, wide, pre, g, st);                           \
+    } while (0)
+#define BS_STRIPS(DT)                                                              \
+    do {                                                                           \
+        if (nhwc) BS_STRIPS_CL(DT, true);                                          \
+        else BS_STRIPS_CL(DT, false);                                              \
     } while (0)
     if (dtype == BS_F32) BS_STRIPS(DT_F32);
     else if (dtype == BS_BF16) BS_STRIPS(DT_BF16);
     else if (dtype == BS_F16) BS_STRIPS(DT_F16);
     else return BS_ERR_UNSUPPORTED;
 #undef BS_STRIPS
+#undef BS_STRIPS_CL
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) {
         set_hip_error((int32_t)e);

@@ -221,7 +221,7 @@ bs_status launch_lds(const LdsSeqK &k, int32_t dtype, int64_t grid, int32_t thre
 // bs_backward.cpp / bs_backward.hip
 void free_backward(bs_stack *s);
 bs_status launch_backward_stage(const BwdK &k, int32_t dtype, int32_t vec, int64_t grid, int32_t threads, void *stream);
-// bs_backward_nhwc.hip: channels-last stages with overlapping 3 x 3 max pooling (BwdK::wave_rows)
+// bs_backward_strip.hip: stages with overlapping 3 x 3 max pooling as strips of columns (BwdK::strips)
 bs_status launch_backward_strips(const BwdK &k, int32_t dtype, int32_t vec, int64_t grid, int32_t threads, void *stream);
 // bs_trace.cpp
 bool trace_enabled();

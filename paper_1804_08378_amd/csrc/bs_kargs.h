@@ -341,10 +341,12 @@ constexpr int K_BWD_MAXROWS_RC = BS_MAXROWS_RC;
 // ... of the kernel that walks two pooling levels at once (a chunk revisits two window rows).  Measured on MI355X, 56 x 56 planes
 // (28 window rows), float32: 7 -> 145 us, 14 -> 134 us, 28 -> 130 us; with the BatchNorm parameters read once per lane: 132, 122, 116 us.
 constexpr int K_BWD_ROWS2_RC = BS_ROWS2_RC;
-// Channels-last backward kernels that walk strips of pixel columns (bs_backward_nhwc.hip): columns per strip of the one- and the
+// Backward kernels that walk strips of columns (bs_backward_strip.hip): columns per strip of the one- and the
 // two-level kernel.  Measured on MI355X (us), ResNet stem bfloat16 / float32: 4 columns 60 / 98, 8 columns 58 / 97 (half the
 // waves for small planes); halo_stress float32 / bfloat16: 4 columns 115 / 117, 8 columns (two waves per SIMD) 109 / 116.
-constexpr int K_BWD_STRIP_Q = 4, K_BWD_STRIP2_Q = 8;
+constexpr int K_BWD_STRIP_Q = 4;
+// ... two-level, row-major float32: 4, 16 bytes of own columns per lane, so that a wave's load has no gaps
+constexpr int bwd_strip2_columns(bool nhwc, int dtype) { return !nhwc && dtype == 0 ? 4 : 8; }
 // ... and the lanes their chunks of rows aim at.  One level: at most what the chip holds at once (7 waves on each of 1024
 // SIMDs; ResNet stem bfloat16 with 1 / 2 / 3 / 4 / 7 chunks, of which 4 fit: 95 / 68 / 65 / 60 / 63 us).  Two levels: three quarters of
 // it (2 waves; a chunk computes the window rows above and below it again: halo_stress float32 with 1 / 2 / 3 / 4 chunks 109 / 116 /
@@ -385,8 +387,10 @@ struct BwdK {
     // audit builds (-DBS_BWD_AUDIT): elements reachable from a / g_out / g_in, and where offsets beyond them are counted
     uint32_t audit_lim[3];
     uint32_t *audit;
-    // Channels-last with wave_rows != 0: a lane owns one channel of a strip of columns and walks down a chunk of rc
+    // strips: a lane owns one channel of a strip of columns and walks down a chunk of rc
     // window rows; cbs = strips per row, total = images * chunks * strips * C, spw and units unused.
+    int32_t strips;       // 1: the kernels whose lanes walk strips of columns (wave_rows says which)
+    uint64_t a_bytes, g_bytes;  // strips (set at launch): bytes from a tensor's first to its last element
     int32_t wave_rows;    // 2: two stages in one kernel -- `pool` (average 3 x 3 / 1 / 1) behind ew[0 .. n_ew), then `pool2` (max
                           // 3 x 3 / 2 / 1) with ew[n_ew .. n_ew + n_post) behind it; H x W: the input plane, Ho x Wo: the max pooling's output
     PoolK pool2;

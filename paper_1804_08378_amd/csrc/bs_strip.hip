@@ -86,46 +86,6 @@ struct FwdList {
     }
 };
 
-// N consecutive elements at any multiple of the element size, as they lie in memory (128-, 64-, 32- and 16-bit loads).
-template <int DT, int N>
-constexpr int run_words() { return (N * elem_bytes<DT>() + 3) / 4; }
-template <int DT, int N>
-BS_DEV void load_run(const char *p, uint32_t (&w)[run_words<DT, N>()])
-{
-    constexpr int BYTES = N * elem_bytes<DT>();
-    constexpr int n16 = BYTES / 16, n8 = (BYTES % 16) / 8, n4 = (BYTES % 8) / 4, n2 = (BYTES % 4) / 2;
-#pragma unroll
-    for (int i = 0; i < n16; ++i) __builtin_memcpy(w + 4 * i, p + 16 * i, 16);
-    if constexpr (n8) __builtin_memcpy(w + 4 * n16, p + 16 * n16, 8);
-    if constexpr (n4) __builtin_memcpy(w + 4 * n16 + 2 * n8, p + 16 * n16 + 8 * n8, 4);
-    if constexpr (n2) {
-        uint16_t h;
-        __builtin_memcpy(&h, p + BYTES - 2, 2);
-        w[run_words<DT, N>() - 1] = h;
-    }
-}
-template <int DT>
-BS_DEV float run_element(const uint32_t *w, int i)
-{
-    if constexpr (DT == DT_F32) return __uint_as_float(w[i]);
-    else if constexpr (DT == DT_BF16) return __uint_as_float(i % 2 ? w[i / 2] & 0xffff0000u : w[i / 2] << 16);
-    else return half_up<DT>(i % 2 ? w[i / 2] >> 16 : w[i / 2] & 0xffffu);
-}
-
-// N (2 or 4) consecutive elements at any multiple of the element size.
-template <int DT, int N>
-BS_DEV void store_run(char *p, const float (&v)[N])
-{
-    if constexpr (DT == DT_F32) {
-        __builtin_memcpy(p, v, 4 * N);
-    } else {
-        uint32_t w[N / 2];
-#pragma unroll
-        for (int i = 0; i < N / 2; ++i) w[i] = pack2<DT>(v[2 * i], v[2 * i + 1]);
-        __builtin_memcpy(p, w, 2 * N);
-    }
-}
-
 // CL: channels-last tensors -- the lanes of a wave are channels, a column is one pixel further on.  Otherwise row-major -- the lanes
 // are neighbouring strips of a row, a lane's columns are consecutive elements, read as vectors that need no alignment.
 // K1: the first pooling (OP_MAXPOOL, OP_AVGSUM; 0: one pooling step only), 3 x 3, stride 1, padding 1; K2: the second (only) one,

@@ -203,6 +203,28 @@ def test_channels_last_strips(shape, dtype):
                 assert np.array_equal(gx, hx), label
 
 
+@pytest.mark.parametrize("dtype", ["f32", "bf16", "f16"])
+@pytest.mark.parametrize("shape", [(1, 1, 3, 3), (2, 3, 4, 5), (1, 2, 9, 7), (2, 5, 13, 11), (1, 3, 37, 35), (1, 1, 5, 261), (2, 2, 70, 18)])
+def test_row_major_strips(shape, dtype):
+    """The same kernels on row-major tensors whose rows are no whole vectors (and on windows without padding): tensors
+    shorter than one lane's run of columns, the first and last rows of a tensor, ragged strips, chunks of rows."""
+    for name, layers in _strip_stacks(shape[1]).items():
+        label = f"row strips/{name}"
+        x, res, dy = _inputs(layers, shape, 29, dtype)
+        x[:, :, ::2, 1::3] = 0.5
+        print(f"[backward] {label} shape={shape} dtype={dtype}", flush=True)
+        ref_x, _ = bw.backward_stack(layers, x, res, dy, dtype)
+        gx, _, stages = run_gpu(layers, x, res, dy, dtype)
+        assert stages == 1, label
+        _close(gx, ref_x, dtype, label)
+        if name in ("stem", "incep", "ceil", "stride1", "pool_only"):
+            hx, _, _ = run_gpu(layers, x, res, dy, dtype, lane_exchange=-1)
+            if dtype == "f16":  # as in test_channels_last_strips
+                assert (np.abs(gx - hx) <= 2.0 ** -10 * np.abs(hx) + 2.0 ** -24).all(), label
+            else:
+                assert np.array_equal(gx, hx), label
+
+
 def test_channels_last_strips_with_infinities_and_offsets_beyond_4_gib():
     """Windows of nothing but -infinity hand their gradient to their first cell inside the plane (the recorded pick);
     a channel slice whose pixels lie so far apart that byte offsets need more than 32 bits."""
