@@ -99,15 +99,8 @@ BS_DEV void store_row(const BwdK &k, int site, OFF at, int32_t first, int32_t wi
 template <int AT, bool FIRST>
 BS_DEV void add_if_at(int32_t at, float g, float &sum)
 {
-    if constexpr (FIRST) {  // nothing there yet
-        asm("v_cmp_eq_u32_e32 vcc, %3, %1\n\tv_cndmask_b32_e32 %0, 0, %2, vcc" : "=&v"(sum) : "v"(at), "v"(g), "n"(AT) : "vcc");
-        return;
-    }
-    float t;
-    asm("v_cmp_eq_u32_e32 vcc, %4, %2\n\tv_cndmask_b32_e32 %1, 0, %3, vcc\n\tv_add_f32_e32 %0, %0, %1"
-        : "+v"(sum), "=&v"(t)
-        : "v"(at), "v"(g), "n"(AT)
-        : "vcc");
+    const float t = at == AT ? g : 0.0f;
+    sum = FIRST ? t : sum + t;  // FIRST: nothing there yet
 }
 
 // An element-wise list on N pixels of V channels (pixel-major), with the product t of its derivatives: float32, rounded
@@ -249,7 +242,7 @@ struct StripPlaces {
 
 // The windows' picks from the row maxima of their three rows.  top: the first window row lies above the plane (padding, all
 // -infinity) and must not be picked, not even by a window of nothing but -infinity.
-template <int N>
+template <int N, bool BY_MAX>
 BS_DEV void combine_rows(const float (&m0)[N], const int32_t (&code0)[N], const float (&m1)[N], const int32_t (&code1)[N], const float (&m2)[N],
                          const int32_t (&code2)[N], bool top, float (&best)[N], int32_t (&pick)[N])
 {
@@ -257,8 +250,13 @@ BS_DEV void combine_rows(const float (&m0)[N], const int32_t (&code0)[N], const 
     for (int i = 0; i < N; ++i) {
         best[i] = m0[i];
         pick[i] = top ? code1[i] : code0[i];
-        take_if_more(m1[i], code1[i], best[i], pick[i]);
-        take_if_more(m2[i], code2[i], best[i], pick[i]);
+        if constexpr (BY_MAX) {
+            max_if_more(m1[i], code1[i], best[i], pick[i]);
+            max_if_more(m2[i], code2[i], best[i], pick[i]);
+        } else {
+            take_if_more(m1[i], code1[i], best[i], pick[i]);
+            take_if_more(m2[i], code2[i], best[i], pick[i]);
+        }
     }
 }
 
@@ -403,7 +401,7 @@ __global__ __launch_bounds__(256) void bwd_strip_kernel(const BwdK k)
         unpack_row<DT, CL, NW>(gw, g);
         float best[NW * V];
         int32_t pick[NW * V];
-        combine_rows<NW * V>(m[R0], code[R0], m[1], code[1], m[R2], code[R2], hA < 0, best, pick);
+        combine_rows<NW * V, false>(m[R0], code[R0], m[1], code[1], m[R2], code[R2], hA < 0, best, pick);
 #pragma unroll
         for (int i = 0; i < NW * V; ++i) g[i] = row_ok && win[i / V] ? g[i] : 0.0f;  // windows that do not exist give nothing
         if constexpr (POST != 0) {
@@ -570,7 +568,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(Q == 8 ? 2 
                 a[i] = ok && c >= 0 && c < k.W ? a[i] : -INFINITY;
             }
         }
-        row_maxima<V, 2, NW, CA, decltype(dh_tag)::value, 1, ends_in_relu(PRE)>(a, lead, m[mslot], code[mslot]);
+        row_maxima<V, 2, NW, CA, decltype(dh_tag)::value, 1, ends_in_relu(PRE), true>(a, lead, m[mslot], code[mslot]);
     };
 
 #pragma unroll
@@ -605,7 +603,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(Q == 8 ? 2 
         unpack_row<DT, CL, NW>(gw, g);
         float best[NW * V];
         int32_t pick[NW * V];
-        combine_rows<NW * V>(m[R0], code[R0], m[1], code[1], m[R2], code[R2], hA < 0, best, pick);
+        combine_rows<NW * V, true>(m[R0], code[R0], m[1], code[1], m[R2], code[R2], hA < 0, best, pick);
 #pragma unroll
         for (int i = 0; i < NW * V; ++i) g[i] = row_ok && win[i / V] ? g[i] : 0.0f;  // windows that do not exist give nothing
         if constexpr (POST != 0) {

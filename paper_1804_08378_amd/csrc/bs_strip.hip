@@ -279,7 +279,7 @@ __global__ __launch_bounds__(256) void strip_kernel(const StripK k)
                 for (int i = 0; i < QO; ++i) {
                     mx[i] = ends_in_relu(PRE) ? a[i * S] : __builtin_fmaxf(a[i * S], -INFINITY);
                     ix[i] = 0;
-                    take_if_more<1>(a[i * S + 1], mx[i], ix[i]);
+                    take_if_more(a[i * S + 1], 1, mx[i], ix[i]);
                 }
             }
 #pragma unroll

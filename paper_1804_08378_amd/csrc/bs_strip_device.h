@@ -61,8 +61,6 @@ BS_DEV void each_of(std::integer_sequence<int, B...>, F f)
 
 constexpr bool ends_in_relu(int code) { return code > 0 && ew_code_kind(code, ew_code_len(code) - 1) == OP_RELU; }
 
-// The compare-and-select steps below are written out so that the comparison's lane mask stays in VCC: left to the compiler the
-// masks go through scalar register pairs, whose selects issue at half the rate and need wait states behind the compare.
 // max(x, 0): NaN and -0 give +0.  (The builtin first canonicalises values that come out of a conversion.)
 BS_DEV float relu(float x)
 {
@@ -70,39 +68,30 @@ BS_DEV float relu(float x)
     asm("v_max_f32_e32 %0, 0, %1" : "=v"(y) : "v"(x));
     return y;
 }
-// v > best: best = v, at = AT
-template <int AT>
-BS_DEV void take_if_more(float v, float &best, int32_t &at)
-{
-    asm("v_cmp_gt_f32_e32 vcc, %2, %0\n\tv_max_f32_e32 %0, %0, %2\n\tv_cndmask_b32_e64 %1, %1, %3, vcc"
-        : "+v"(best), "+v"(at)
-        : "v"(v), "n"(AT)
-        : "vcc");
-}
-// The first maximum of a, b, c (codes A, A + 1, A + 2).
-template <int A>
-BS_DEV void first_max3(float a, float b, float c, float &best, int32_t &at)
-{
-    asm("v_cmp_gt_f32_e32 vcc, %3, %2\n\tv_max_f32_e32 %0, %3, %2\n\tv_cndmask_b32_e64 %1, %5, %6, vcc\n\t"
-        "v_cmp_gt_f32_e32 vcc, %4, %0\n\tv_max_f32_e32 %0, %0, %4\n\tv_cndmask_b32_e64 %1, %1, %7, vcc"
-        : "=&v"(best), "=&v"(at)
-        : "v"(a), "v"(b), "v"(c), "n"(A), "n"(A + 1), "n"(A + 2)
-        : "vcc");
-}
-// v > best: best = v, at = c
+// v > best: best = v, at = c.  NaN is never more; of zeros of both signs the first one stays.  Left to the compiler's
+// scheduler: between a vector compare and the select that reads its lane mask gfx950 needs two wait states, which it fills with the
+// neighbouring windows' work; inside an asm block nothing would.
 BS_DEV void take_if_more(float v, int32_t c, float &best, int32_t &at)
 {
-    asm("v_cmp_gt_f32_e32 vcc, %2, %0\n\tv_max_f32_e32 %0, %0, %2\n\tv_cndmask_b32_e32 %1, %1, %3, vcc"
-        : "+v"(best), "+v"(at)
-        : "v"(v), "v"(c)
-        : "vcc");
+    const bool more = v > best;
+    best = more ? v : best;
+    at = more ? c : at;
+}
+// The same where `best` only serves comparisons and derivatives, which the sign of a zero does not change: the value by the maximum
+// instruction, so that a lane mask is read once.  Measured on MI355X, us, this or take_if_more: two-level backward kernel (whose masks
+// then fit the scalar registers) halo_stress channels-last float32 114 / 120, bfloat16 121 / 126, binary16 113 / 121; one-level
+// kernel, ResNet stem channels-last bfloat16 57.6 / 54.1, binary16 55.6 / 52.7.
+BS_DEV void max_if_more(float v, int32_t c, float &best, int32_t &at)
+{
+    at = v > best ? c : at;
+    best = __builtin_fmaxf(best, v);
 }
 // Row maxima of N adjacent windows (S columns apart) of window row DH: value and code 3 * DH + window column of the first
 // one.  A column outside the plane holds -infinity.  Window LEAD begins one column left of the plane when `lead` is set
 // (padding): its scan starts at column 1, so that a window of nothing but -infinity picks its first cell inside.  NaN is
 // never a maximum.
-// NONAN: no value is NaN (a ReLU stands in front).
-template <int V, int S, int N, int CW, int DH, int LEAD, bool NONAN>
+// NONAN: no value is NaN (a ReLU stands in front).  BY_MAX: max_if_more instead of take_if_more.
+template <int V, int S, int N, int CW, int DH, int LEAD, bool NONAN, bool BY_MAX = false>
 BS_DEV void row_maxima(const float (&y)[CW * V], bool lead, float (&m)[N * V], int32_t (&code)[N * V])
 {
 #pragma unroll
@@ -110,16 +99,15 @@ BS_DEV void row_maxima(const float (&y)[CW * V], bool lead, float (&m)[N * V], i
 #pragma unroll
         for (int e = 0; e < V; ++e) {
             const float first = NONAN ? y[b * S * V + e] : __builtin_fmaxf(y[b * S * V + e], -INFINITY);
-            if (LEAD == b) {
-                float best = first;
-                int32_t at = lead ? 3 * DH + 1 : 3 * DH;
-                take_if_more<3 * DH + 1>(y[(b * S + 1) * V + e], best, at);
-                take_if_more<3 * DH + 2>(y[(b * S + 2) * V + e], best, at);
-                m[b * V + e] = best;
-                code[b * V + e] = at;
-            } else {
-                first_max3<3 * DH>(first, y[(b * S + 1) * V + e], y[(b * S + 2) * V + e], m[b * V + e], code[b * V + e]);
+            float best = first;
+            int32_t at = LEAD == b && lead ? 3 * DH + 1 : 3 * DH;
+#pragma unroll
+            for (int d = 1; d < 3; ++d) {
+                if constexpr (BY_MAX) max_if_more(y[(b * S + d) * V + e], 3 * DH + d, best, at);
+                else take_if_more(y[(b * S + d) * V + e], 3 * DH + d, best, at);
             }
+            m[b * V + e] = best;
+            code[b * V + e] = at;
         }
 }
 

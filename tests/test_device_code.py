@@ -1,0 +1,60 @@
+"""The machine code the build makes for gfx950: wait states between vector compares and the selects that read their masks."""
+import os
+import re
+import subprocess
+
+import pytest
+
+from paper_1804_08378_amd import build
+
+BIN = "/opt/rocm/lib/llvm/bin"
+WAIT_STATES = 2  # between a vector instruction that writes a lane mask (VCC or a scalar pair) and a vector instruction that reads it
+
+
+def disassemble(obj: str, tmp: str) -> str:
+    """Assembly of the device code inside an object that build() made."""
+    bundle, code = os.path.join(tmp, "bundle"), os.path.join(tmp, "code")
+    subprocess.run([f"{BIN}/llvm-objcopy", f"--dump-section=.hip_fatbin={bundle}", obj, os.path.join(tmp, "rest.o")], check=True)
+    subprocess.run([f"{BIN}/clang-offload-bundler", "--type=o", "--unbundle", f"--input={bundle}",
+                    "--targets=hipv4-amdgcn-amd-amdhsa--gfx950", f"--output={code}"], check=True)
+    return subprocess.run([f"{BIN}/llvm-objdump", "-d", "--no-show-raw-insn", "--no-leading-addr", code], check=True, capture_output=True,
+                          text=True).stdout
+
+
+def mask_reads(lines):
+    """(line, wait states since the vector compare that wrote its mask) of every select; straight-line code only: what a jump
+    lands on is not followed."""
+    written, now = {}, 0
+    for line in lines:
+        op, _, rest = line.partition(" ")
+        if not op or op.endswith(":") or op.startswith(("s_branch", "s_cbranch", "s_setpc", "s_swappc")):
+            written.clear()
+            continue
+        args = [a.strip() for a in rest.split("//")[0].split(",")]
+        if op.startswith("v_cndmask"):
+            mask = args[3] if len(args) > 3 else "vcc"
+            if mask in written:
+                yield line, now - written[mask] - 1
+        now += int(args[0], 0) + 1 if op == "s_nop" else 1
+        if op.startswith("v_cmp") and not op.startswith("v_cmpx"):
+            written[args[0]] = now - 1
+        elif args[0] in written:  # written by something else (a scalar instruction: no wait states)
+            del written[args[0]]
+
+
+@pytest.mark.parametrize("source", [s for s in build.SOURCES if s.endswith(".hip")])
+def test_selects_wait_for_the_compares_that_write_their_masks(source, tmp_path):
+    """The compiler keeps the wait states in its own code; it does not look inside asm blocks."""
+    build.build(force=False)
+    obj = os.path.join(build.HERE, "_build", source + ".o")
+    if not os.path.exists(obj) or not os.path.exists(BIN):
+        pytest.skip("needs the build's objects and the ROCm toolchain")
+    text = disassemble(obj, str(tmp_path))
+    lines = [re.sub(r"\s+", " ", l).strip() for l in text.split("\n")]
+    pairs, short = 0, []
+    for line, states in mask_reads(lines):
+        pairs += 1
+        if states < WAIT_STATES:
+            short.append((states, line))
+    print(f"{source}: {pairs} compare-select pairs")
+    assert not short, (len(short), short[:5])
