@@ -142,7 +142,7 @@ struct StripList {
 #pragma unroll
             for (int i = 0; i < N; ++i) {
                 t[i] = x[i] > 0.0f ? t[i] : 0.0f;
-                x[i] = relu(x[i]);
+                x[i] = __builtin_fmaxf(x[i], 0.0f);  // NaN, -0 -> +0
             }
         } else if (kind == OP_LEAKY) {
             const float slope = k.params[arg];

@@ -53,7 +53,7 @@ struct FwdList {
             round_store_all<DT, N>(x);
         } else if (kind == OP_RELU) {
 #pragma unroll
-            for (int i = 0; i < N; ++i) x[i] = relu(x[i]);
+            for (int i = 0; i < N; ++i) x[i] = __builtin_fmaxf(x[i], 0.0f);  // NaN, -0 -> +0
         } else if (kind == OP_LEAKY) {
             const float slope = k.params[arg];
 #pragma unroll

@@ -61,13 +61,6 @@ BS_DEV void each_of(std::integer_sequence<int, B...>, F f)
 
 constexpr bool ends_in_relu(int code) { return code > 0 && ew_code_kind(code, ew_code_len(code) - 1) == OP_RELU; }
 
-// max(x, 0): NaN and -0 give +0.  (The builtin first canonicalises values that come out of a conversion.)
-BS_DEV float relu(float x)
-{
-    float y;
-    asm("v_max_f32_e32 %0, 0, %1" : "=v"(y) : "v"(x));
-    return y;
-}
 // v > best: best = v, at = c.  NaN is never more; of zeros of both signs the first one stays.  Left to the compiler's
 // scheduler: between a vector compare and the select that reads its lane mask gfx950 needs two wait states, which it fills with the
 // neighbouring windows' work; inside an asm block nothing would.

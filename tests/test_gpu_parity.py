@@ -1029,6 +1029,30 @@ def test_row_major_strips(shape, dtype):
     check([wl.maxpool(3, 2, 1, True), wl.relu()], x, [], dtype, f"row strips/infinities{shape}")
 
 
+@pytest.mark.parametrize("dtype", ["f32", "bf16", "f16"])
+def test_strips_with_zeros_of_both_signs_and_nan(dtype):
+    """Poolings with indices in the strip kernels: of zeros of both signs the first one is stored, as its index says; NaN,
+    signalling ones included, is never a maximum, a window of nothing but NaN picks its first cell, ReLU makes it +0."""
+    for shape in ((2, 6, 9, 11), (1, 3, 13, 35)):
+        rng = np.random.default_rng(250)
+        zeros = np.where(rng.random(shape) < 0.5, np.float32(0.0), np.float32(-0.0)) * np.where(rng.random(shape) < 0.05, np.float32(0.0), np.float32(1.0))
+        zeros[rng.random(shape) < 0.1] = -1.0
+        nan = wl.activation(shape, 251, dtype)
+        nan[rng.random(shape) < 0.4] = np.nan
+        nan[:, 0, :4, :5] = np.nan
+        if dtype == "f32":  # a conversion to 16 bits would make them quiet
+            nan.view(np.uint32)[np.isnan(nan) & (rng.random(shape) < 0.5)] = 0x7f800001
+        pools = {"3s2p1": wl.maxpool(3, 2, 1, True), "3s2": wl.maxpool(3, 2, 0, True), "3s1p1": wl.maxpool(3, 1, 1, True), "2s2": wl.maxpool(2, 2, 0, True)}
+        for name, pool in pools.items():
+            for what, x, layers in (("zeros", zeros, [pool]), ("zeros behind a list", zeros, [wl.leaky_relu(0.5), pool]),
+                                    ("nan", nan, [pool, wl.relu()]), ("nan behind ReLU", nan, [wl.relu(), pool])):
+                check(layers, x, [], dtype, f"row strips/{what}/{name}")
+                _check_nhwc(layers, x, [], dtype, f"strips/{what}/{name}")
+        for front in ([wl.relu()], [wl.bn_params(shape[1], 252), wl.relu()]):
+            check(front + [wl.avgpool(3, 1, 1)], nan, [], dtype, "row strips/nan behind ReLU/average")
+            _check_nhwc(front + [wl.avgpool(3, 1, 1)], nan, [], dtype, "strips/nan behind ReLU/average")
+
+
 def test_channels_last_strips_with_infinities_and_offsets_beyond_4_gib():
     """Windows of nothing but -infinity pick their first cell inside the plane; a channel slice whose pixels lie so far
     apart that byte offsets need more than 32 bits."""
