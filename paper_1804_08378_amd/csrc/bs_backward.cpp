@@ -95,6 +95,20 @@ bool walks_strips(const bs_stack *s, const BwdStage &g)
            p.kind == OP_MAXPOOL && p.kh == 3 && p.kw == 3 && p.sh == p.sw && (p.sh == 1 || p.sh == 2) && p.ph == p.pw && p.ph <= 1;
 }
 
+// A one-level strip stage whose picks the caller kept may gather them instead: no pick has to be found, and the kernel is small.
+// Measured on MI355X with kept picks, us, gather / strips: lists read at run time (BatchNorm, leaky ReLU, max 3x3/2) channels-last
+// binary16 8 x 64 x 28 x 28 5.5 / 8.1, 64 x 64 x 55 x 55 25 / 29, 32 x 64 x 111 x 111 45 / 43, float32 8 x 192 x 35 x 35 7 / 9, 32 x 64 x 56 x 56 19 / 18,
+// 16 x 30 x 57 x 57 12 / 10; row-major bfloat16 1 x 64 x 14 x 14 5.5 / 8.6, 4 x 64 x 71 x 71 12 / 10; no list, stride 1, 4 x 64 x 71 x 71 channels-last 6.8 / 8.5,
+// row-major float32 12.8 / 15.3, bfloat16 13.9 / 8.9; other stages of the lists that are compiled in: strips.
+bool gathers_kept_picks(const bs_stack *s, const BwdStage &g)
+{
+    if (g.idx_slot < 0 || g.k.n_post > 0) return false;  // (the gathering kernel has no list behind the pooling)
+    const bool f32 = s->dtype == BS_F32, nhwc = s->opts.layout == BS_LAYOUT_NHWC, whole = nhwc && g.k.C % (f32 ? 4 : 8) == 0;
+    const uint64_t cells = numel(g.in_shape), M = 1 << 20;
+    if (!bwd_strip_compiled(g.k)) return cells < (whole ? (f32 ? 4 : 16) * M : M);
+    return g.k.pool.sh == 1 && (whole || (!nhwc && f32)) && cells < 2 * M;
+}
+
 // Stage g = [element-wise list without Add, average pooling 3 x 3 / 1 / 1 that keeps the plane's size] and the stage
 // behind it = [max pooling 3 x 3 / 2 / 1 alone, with the element-wise operations that joined it]: one kernel walks
 // both levels down the plane (rows of whole 4-cell blocks that fit one wave).
@@ -245,7 +259,7 @@ extern "C" bs_status bs_stack_plan_backward(bs_stack *stack)
                 // a lane per channel, strip of columns and chunk of window rows; a chunk holds two window rows at least
                 BwdK &k = g.k;
                 const bool two = k.wave_rows == 2;
-                const int32_t q = two ? bwd_strip2_columns(nhwc, stack->dtype) : K_BWD_STRIP_Q, s = two ? 2 : p.sh;
+                const int32_t q = two ? bwd_strip2_columns(nhwc, stack->dtype, bwd_strip2_compiled(k)) : K_BWD_STRIP_Q, s = two ? 2 : p.sh;
                 k.strips = 1;
                 k.wave_rows = two ? 2 : 1;
                 g.vec = 1;
@@ -260,6 +274,18 @@ extern "C" bs_status bs_stack_plan_backward(bs_stack *stack)
                 k.div_cbs = make_fastdiv((uint32_t)k.cbs);
                 k.div_chunks = make_fastdiv((uint32_t)k.chunks);
                 lanes = (uint64_t)per_chunk * (uint64_t)k.chunks;
+                if (!two && j + 1 == S && gathers_kept_picks(stack, g)) {
+                    const int32_t row = nhwc ? k.C : k.W;
+                    g.kept_vec = row % full == 0 ? full : (!nhwc && stack->dtype != BS_F32 && row % 4 == 0 ? 4 : 1);
+                    BwdK &t = g.kept = k;
+                    t.strips = t.wave_rows = t.cbs = t.rc = t.chunks = 0;
+                    t.total = (uint32_t)(numel(g.in_shape) / (uint64_t)g.kept_vec);
+                    t.div_wv = make_fastdiv((uint32_t)(row / g.kept_vec));
+                    t.div_w = make_fastdiv((uint32_t)t.W);
+                    t.div_h = make_fastdiv((uint32_t)t.H);
+                    t.div_c = make_fastdiv((uint32_t)t.C);
+                    g.kept_grid = ((int64_t)t.total + 255) / 256;
+                }
             } else if (nhwc) {
                 // a lane per pixel (per window when 2 x 2 windows tile the plane) and channel vector
                 g.vec = g.k.C % full == 0 ? full : 1;
@@ -476,12 +502,13 @@ extern "C" bs_status bs_stack_backward_strided(const bs_stack *stack, const void
     // ---- gradients, last stage first
     for (size_t j = S; j-- > 0;) {
         const BwdStage &g = plan.stages[j];
-        BwdK k = g.k;
+        const bool gathers = j + 1 == S && g.kept_grid > 0 && kept(g);
+        BwdK k = gathers ? g.kept : g.k;
         k.a = j == 0 ? in : ws + g.a_off;
         k.g_out = j + 1 == S ? grad_out : ws + plan.stages[j + 1].g_off;
         k.g_in = j == 0 ? grad_in : ws + g.g_off;
         k.idx = g.k.pool.kind == OP_MAXPOOL && !g.k.direct && !g.k.wave_rows ? reinterpret_cast<const int32_t *>(ws + g.idx_off) : nullptr;
-        if (k.idx && j + 1 == S && kept(g)) k.idx = kept(g);
+        if ((k.idx || gathers) && j + 1 == S && kept(g)) k.idx = kept(g);
         k.params = stack->dev_params;
         k.a_extra = j == 0 ? a_extra : 0;
         k.gin_extra = j == 0 ? gin_extra : 0;
@@ -502,7 +529,7 @@ extern "C" bs_status bs_stack_backward_strided(const bs_stack *stack, const void
             wanted = wanted || k.g_res[r] != nullptr;
         }
         if (!wanted) continue;  // first stage, and the caller asked for none of its gradients
-        const bs_status st = launch_backward_stage(k, stack->dtype, g.vec, g.grid, g.threads, stream);
+        const bs_status st = launch_backward_stage(k, stack->dtype, gathers ? g.kept_vec : g.vec, gathers ? g.kept_grid : g.grid, g.threads, stream);
         if (st != BS_OK) return st;
     }
     return BS_OK;

@@ -105,12 +105,14 @@ BS_DEV void add_if_at(int32_t at, float g, float &sum)
 
 // An element-wise list on N pixels of V channels (pixel-major), with the product t of its derivatives: float32, rounded
 // to the storage type after every layer, as the forward kernels compute it.  CODE >= 0: the kinds are compile-time
-// (base-K_EW_BASE digits) and BatchNorm's parameters of the lane's channels are read once, in front of the row loop;
-// -1: kinds and parameters are read at every use.
-template <int DT, int V, int CODE>
+// (base-K_EW_BASE digits) and load() reads the parameters of the lane's channels once, in front of the row loop; -1: kinds and
+// parameters are read at every use -- HOLD: those of the first HELD operations once per lane (two levels, 64 x 64 x 55 x 55 row-major
+// float32 with leaky ReLU 100 -> 75 us; one level: 4 % faster in float32, up to 6 % slower with 16-bit storage, so read at every use).
+template <int DT, int V, int CODE, bool HOLD>
 struct StripList {
-    static constexpr int L = CODE > 0 ? ew_code_len(CODE) : 0;
-    float sc[L ? L : 1][V], sh[L ? L : 1][V];
+    static constexpr int HELD = HOLD ? 4 : 0, L = CODE > 0 ? ew_code_len(CODE) : CODE == 0 ? 0 : HELD;
+    HeldParams<V> held[L ? L : 1];
+    uint32_t kinds;  // HOLD: K_EW_BASE digits
     int32_t first, count, c0;
 
     BS_DEV void load(const BwdK &k, int32_t c, int32_t f, int32_t n)
@@ -118,20 +120,27 @@ struct StripList {
         first = f;
         count = n;
         c0 = c;
+        kinds = 0;
 #pragma unroll
-        for (int q = 0; q < L; ++q)
-            if (ew_code_kind(CODE, q) == OP_BN)
-#pragma unroll
-                for (int e = 0; e < V; ++e) {
-                    sc[q][e] = k.params[k.ew[f + q].arg + c + e];
-                    sh[q][e] = k.params[k.ew[f + q].arg + k.C + c + e];
-                }
+        for (int q = 0; q < L; ++q) {
+            if constexpr (CODE >= 0) {
+                if (CODE == BN_RELU && q == 0 && n == 1) held[q].identity();  // ReLU alone
+                else held[q].load(k.params, ew_code_kind(CODE, q), k.ew[f + q].arg, c, k.C);
+            } else {
+                const bool there = q < n;
+                const int32_t kind = there ? k.ew[f + q].kind : (int32_t)OP_RELU;
+                kinds |= (uint32_t)kind << (4 * q);
+                held[q].load(k.params, kind, there ? k.ew[f + q].arg : 0, c, k.C);
+            }
+        }
     }
 
-    template <int N>
-    BS_DEV void one(const BwdK &k, int32_t kind, int32_t arg, const float (&a)[V], const float (&b)[V], float (&x)[N], float (&t)[N]) const
+    template <int N, typename P>
+    BS_DEV static void one(int32_t kind, const P &p, float (&x)[N], float (&t)[N])
     {
         if (kind == OP_BN) {
+            float a[V], b[V];
+            p.bn(a, b);
 #pragma unroll
             for (int i = 0; i < N; ++i) {
                 x[i] = __builtin_fmaf(x[i], a[i % V], b[i % V]);
@@ -145,14 +154,14 @@ struct StripList {
                 x[i] = __builtin_fmaxf(x[i], 0.0f);  // NaN, -0 -> +0
             }
         } else if (kind == OP_LEAKY) {
-            const float slope = k.params[arg];
+            const float slope = p.first();
 #pragma unroll
             for (int i = 0; i < N; ++i) {
                 t[i] *= x[i] > 0.0f ? 1.0f : slope;
                 x[i] = round_store<DT>(x[i] > 0.0f ? x[i] : x[i] * slope);
             }
         } else {  // OP_CLAMP: the gradient passes where lo <= x <= hi
-            const float lo = k.params[arg], hi = k.params[arg + 1];
+            const float lo = p.first(), hi = p.second();
 #pragma unroll
             for (int i = 0; i < N; ++i) {
                 t[i] = x[i] >= lo && x[i] <= hi ? t[i] : 0.0f;
@@ -169,23 +178,33 @@ struct StripList {
         for (int i = 0; i < N; ++i) t[i] = 1.0f;
         if constexpr (CODE >= 0) {
 #pragma unroll
-            for (int q = 0; q < L; ++q) one<N>(k, ew_code_kind(CODE, q), k.ew[first + q].arg, sc[q], sh[q], x, t);
+            for (int q = 0; q < L; ++q) one<N>(ew_code_kind(CODE, q), held[q], x, t);
         } else {
 #pragma clang loop unroll(disable)
             for (int32_t q = first; q < first + count; ++q) {
-                const int32_t kind = k.ew[q].kind, arg = k.ew[q].arg;
-                float a[V] = {}, b[V] = {};
-                if (kind == OP_BN)
+                if constexpr (HOLD) {
+                    const int32_t i = q - first;
+                    HeldParams<V> p;
+                    int32_t kind = k.ew[q].kind;
+                    if (i < HELD) {
+                        kind = (int32_t)(kinds >> (4 * i) & 15u);
 #pragma unroll
-                    for (int e = 0; e < V; ++e) {
-                        a[e] = k.params[arg + c0 + e];
-                        b[e] = k.params[arg + k.C + c0 + e];
+                        for (int e = 0; e < V; ++e) {
+                            p.a[e] = one_of(i, held[0].a[e], held[1].a[e], held[2].a[e], held[3].a[e]);
+                            p.b[e] = one_of(i, held[0].b[e], held[1].b[e], held[2].b[e], held[3].b[e]);
+                        }
+                    } else {
+                        p.load(k.params, kind, k.ew[q].arg, c0, k.C);
                     }
-                one<N>(k, kind, arg, a, b, x, t);
+                    one<N>(kind, p, x, t);
+                } else {
+                    one<N>(k.ew[q].kind, ReadParams<V>{k.params, k.ew[q].arg, c0, k.C}, x, t);
+                }
             }
         }
     }
 };
+static_assert(K_EW_BASE == 16, "a digit of `kinds` is four bits");
 
 // The lane's place.  Channels-last: (image, chunk, strip, channel), row-major: (image, channel, chunk, strip), the last one fastest.
 struct StripLane {
@@ -295,7 +314,7 @@ BS_DEV void scatter(const int32_t (&pick)[N * V], const float (&g)[N * V], float
 // of its windows in each (a row two window rows share is scanned once), combines three of them into the windows' picks,
 // adds the windows' gradients -- times the trailing list's derivative at the maximum -- to the picked cells and writes
 // the S rows no later window reaches.  A cell sums its windows in row-major window order.
-// PRE, POST: codes of the lists, or -1.
+// PRE, POST: codes of the lists, or -1 (small stages with such lists gather kept picks instead: bs_backward.cpp).
 // Measured on MI355X, us of a call with the caller's picks at hand, gathering kernel -> this one: ResNet stem 64 x 64 x 112 x 112
 // float32 105 -> 98 (4.7 TB/s of input, gradients in and out: waits for memory), bfloat16 87 -> 60 (vector instructions: 34
 // per cell, 70 % of the time); 32 x 192 x 71 x 71 / 2 without padding binary16 55 -> 39; without kept picks the gathering
@@ -333,8 +352,8 @@ __global__ __launch_bounds__(256) void bwd_strip_kernel(const BwdK k)
     const OFF a_last = a_fits ? (OFF)(k.a_bytes - (uint64_t)CW * ES) : (OFF)0, g_last = g_fits ? (OFF)(k.g_bytes - (uint64_t)NW * ES) : (OFF)0;
     const bool inside = x0 >= 0 && x0 + CW <= k.W, whole = L.q0 + Q <= k.W;
 
-    StripList<DT, V, PRE> pre;
-    StripList<DT, V, POST> post;
+    StripList<DT, V, PRE, false> pre;
+    StripList<DT, V, POST, false> post;
     pre.load(k, L.c0, 0, k.n_ew);
     post.load(k, L.c0, k.n_ew, k.n_post);
 
@@ -469,12 +488,19 @@ __global__ __launch_bounds__(256) void bwd_strip_kernel(const BwdK k)
 // Q columns need Q + 2 of the average's gradient, Q / 2 + 2 windows, Q + 5 averages and Q + 7 inputs.
 // INC: every divisor is 9 (count_include_pad, nothing overhangs).
 // Measured on MI355X (halo_stress, us of a call): three stages with two forward passes through the workspace -> this kernel:
-// float32 510 -> 109, bfloat16 390 -> 116; row-major, 64 x 64 x 55 x 55 float32 291 -> 53, binary16 287 -> 41.  Bound by vector instructions (the 18 additions per average and their halo, the
-// scans); two waves per SIMD with 8 columns beat four with 4 columns, which compute 9 averages per 4 columns instead of
-// 13 per 8.
+// float32 510 -> 114, bfloat16 390 -> 121; row-major, 64 x 64 x 55 x 55 float32 291 -> 55, binary16 287 -> 41.  Bound by vector
+// instructions (the 18 additions per average and their halo, the scans); two waves per SIMD with 8 columns beat four with 4
+// columns, which compute 9 averages per 4 columns instead of 13 per 8.
+// Lists read at run time (PRE, POST -1): 4 columns, so that nothing lies in scratch memory; three stages / 8 columns with scratch / 4
+// columns, 64 x 64 x 55 x 55 channels-last: BatchNorm, leaky ReLU, average, maximum, BatchNorm, leaky ReLU float32 143 / 65 / 63, bfloat16
+// 117 / 69 / 74; halo_stress's lists without padding counted float32 147 / 180 / 94, bfloat16 116 / 170 / 100; 8 x 64 x 28 x 28 27 / 53 / 25.
 // =============================================================================
+// Waves per SIMD: what the registers of an instance allow without scratch memory.
+constexpr int strip2_waves(int Q, int PRE, int off_bytes) { return off_bytes == 8 ? 1 : Q == 8 || PRE < 0 ? 2 : 3; }
+
 template <int DT, bool CL, int Q, bool INC, int PRE, int POST, typename OFF>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(Q == 8 ? 2 : 3, Q == 8 ? 2 : 3))) void bwd_strip2_kernel(const BwdK k)
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(strip2_waves(Q, PRE, sizeof(OFF)), strip2_waves(Q, PRE, sizeof(OFF)))))
+void bwd_strip2_kernel(const BwdK k)
 {
     static_assert(Q % 2 == 0, "whole windows");
     constexpr int NW = Q / 2 + 2, CA = Q + 5, CX = Q + 7, CG = Q + 2, V = 1, ES = elem_bytes<DT>();
@@ -497,8 +523,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(Q == 8 ? 2 
     const OFF a_last = a_fits ? (OFF)(k.a_bytes - (uint64_t)CX * ES) : (OFF)0, g_last = g_fits ? (OFF)(k.g_bytes - (uint64_t)NW * ES) : (OFF)0;
     const bool inside = x0 >= 0 && x0 + CX <= k.W, whole = L.q0 + Q <= k.W;
 
-    StripList<DT, V, PRE> pre;
-    StripList<DT, V, POST> post;
+    StripList<DT, V, PRE, true> pre;
+    StripList<DT, V, POST, true> post;
     pre.load(k, L.c0, 0, k.n_ew);
     post.load(k, L.c0, k.n_ew, k.n_post);
 
@@ -543,6 +569,18 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(Q == 8 ? 2 
             for (int i = 0; i < Q * V; ++i) T[tslot + j][i] = d[(j * CX + 4) * V + i];
         }
     };
+    // times the divisors' reciprocals of the average's windows around N cells of row `row`, from column `col` on (outside the
+    // plane: any).  A strip whose windows all lie inside the plane has one divisor: no division per cell.
+    auto scale = [&](auto n_tag, int32_t row, int32_t col, float *v) __attribute__((always_inline)) {
+        constexpr int N = decltype(n_tag)::value;
+        if (INC || k.pool.count_include_pad == 1 || (inside && row >= 1 && row < k.H - 1)) {
+#pragma unroll
+            for (int i = 0; i < N; ++i) v[i] *= k.pool.inv_kk;
+        } else {
+#pragma unroll
+            for (int i = 0; i < N; ++i) v[i] *= bwd_avg_inv(k.pool, k.H, k.W, row, min(max(col + i / V, 0), k.W - 1));
+        }
+    };
     // row `row` of the average's output from three rows of y -> row maxima of the windows (outside the plane: -infinity),
     // scanned as window row DH
     auto average_row = [&](const float (&ya)[CX * V], const float (&yb)[CX * V], const float (&yc)[CX * V], auto dh_tag, int mslot, int32_t row) __attribute__((always_inline)) {
@@ -557,8 +595,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(Q == 8 ? 2 
             for (int dw = 0; dw < 3; ++dw) sum = sum + yb[i + dw * V];
 #pragma unroll
             for (int dw = 0; dw < 3; ++dw) sum = sum + yc[i + dw * V];
-            a[i] = sum * (INC ? k.pool.inv_kk : bwd_avg_inv(k.pool, k.H, k.W, row, L.q0 - 3 + i / V));
+            a[i] = sum;
         }
+        scale(std::integral_constant<int, CA * V>{}, row, L.q0 - 3, a);
         round_store_all<DT, CA * V>(a);
         const bool ok = row >= 0 && row < k.H;
         if (!(inside && ok)) {
@@ -618,9 +657,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(Q == 8 ? 2 
             const int32_t row = min(max(hA + d, 0), k.H - 1);  // rows and columns outside the plane hold zeros
             float w[CG * V];
 #pragma unroll
-            for (int i = 0; i < CG * V; ++i)
-                w[i] = gt[d == 0 ? R0 : 1][i] *
-                       (INC ? k.pool.inv_kk : bwd_avg_inv(k.pool, k.H, k.W, row, min(max(L.q0 - 1 + i / V, 0), k.W - 1)));
+            for (int i = 0; i < CG * V; ++i) w[i] = gt[d == 0 ? R0 : 1][i];
+            scale(std::integral_constant<int, CG * V>{}, row, L.q0 - 1, w);
 #pragma unroll
             for (int i = 0; i < Q * V; ++i) hs[N0 + d][i] = (w[i] + w[i + V]) + w[i + 2 * V];
         }
@@ -655,44 +693,49 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(Q == 8 ? 2 
     }
 }
 
-constexpr int BN_RELU = OP_BN + OP_RELU * K_EW_BASE;
-
 template <int DT, bool CL, int S, int P>
 void launch1(const BwdK &k, bool wide, int32_t pre, dim3 g, hipStream_t st)
 {
     constexpr int Q = K_BWD_STRIP_Q;
     if (wide) bwd_strip_kernel<DT, CL, Q, S, P, -1, -1, uint64_t><<<g, 256, 0, st>>>(k);
     else if (pre == BN_RELU && k.n_post == 0) bwd_strip_kernel<DT, CL, Q, S, P, BN_RELU, 0, uint32_t><<<g, 256, 0, st>>>(k);
+    else if (pre == 0 && strip_list_code(k.ew + k.n_ew, k.n_post) == BN_RELU)  // the stacked pooling blocks
+        bwd_strip_kernel<DT, CL, Q, S, P, 0, BN_RELU, uint32_t><<<g, 256, 0, st>>>(k);
+    else if (pre == 0 && k.n_post == 0) bwd_strip_kernel<DT, CL, Q, S, P, 0, 0, uint32_t><<<g, 256, 0, st>>>(k);
     else if (k.n_post == 0) bwd_strip_kernel<DT, CL, Q, S, P, -1, 0, uint32_t><<<g, 256, 0, st>>>(k);
     else bwd_strip_kernel<DT, CL, Q, S, P, -1, -1, uint32_t><<<g, 256, 0, st>>>(k);
 }
 
 template <int DT, bool CL>
-void launch2(const BwdK &k, bool wide, int32_t pre, int32_t post, dim3 g, hipStream_t st)
+void launch2(const BwdK &k, bool wide, bool compiled, dim3 g, hipStream_t st)
 {
-    constexpr int Q = bwd_strip2_columns(CL, DT);
-    const bool inc = k.pool.count_include_pad == 1;
-    if (wide) bwd_strip2_kernel<DT, CL, Q, false, -1, -1, uint64_t><<<g, 256, 0, st>>>(k);
-    else if (pre == BN_RELU && post == BN_RELU && inc) bwd_strip2_kernel<DT, CL, Q, true, BN_RELU, BN_RELU, uint32_t><<<g, 256, 0, st>>>(k);
-    else bwd_strip2_kernel<DT, CL, Q, false, -1, -1, uint32_t><<<g, 256, 0, st>>>(k);
-}
-
-int32_t list_code(const BwdK &k, int32_t first, int32_t n)
-{
-    int32_t c = 0, digit = 1;
-    if (n > 6) return -1;
-    for (int32_t j = 0; j < n; ++j, digit *= K_EW_BASE) c += k.ew[first + j].kind * digit;
-    return c;
+    constexpr int Q = bwd_strip2_columns(CL, DT, true), QR = bwd_strip2_columns(CL, DT, false);
+    if (compiled && wide) bwd_strip2_kernel<DT, CL, Q, true, BN_RELU, BN_RELU, uint64_t><<<g, 256, 0, st>>>(k);
+    else if (compiled) bwd_strip2_kernel<DT, CL, Q, true, BN_RELU, BN_RELU, uint32_t><<<g, 256, 0, st>>>(k);
+    else if (wide) bwd_strip2_kernel<DT, CL, QR, false, -1, -1, uint64_t><<<g, 256, 0, st>>>(k);
+    else bwd_strip2_kernel<DT, CL, QR, false, -1, -1, uint32_t><<<g, 256, 0, st>>>(k);
 }
 
 }  // namespace
+
+bool bwd_strip_compiled(const BwdK &k)
+{
+    const int32_t pre = strip_list_code(k.ew, k.n_ew);
+    return k.n_post == 0 && (pre == BN_RELU || pre == 0);
+}
+
+bool bwd_strip2_compiled(const BwdK &k)
+{
+    return k.pool.count_include_pad == 1 && strip_list_code(k.ew, k.n_ew) == BN_RELU && strip_list_code(k.ew + k.n_ew, k.n_post) == BN_RELU;
+}
 
 bs_status launch_backward_strips(const BwdK &arg, int32_t dtype, int32_t vec, int64_t grid, int32_t threads, void *stream)
 {
     BwdK k = arg;
     const PoolK &p = k.pool, &q = k.pool2;
     const bool two = k.wave_rows == 2, nhwc = k.nhwc != 0;
-    const int32_t s = two ? 2 : p.sh, Q = two ? bwd_strip2_columns(nhwc, dtype) : K_BWD_STRIP_Q;
+    const bool compiled = two && bwd_strip2_compiled(k);
+    const int32_t s = two ? 2 : p.sh, Q = two ? bwd_strip2_columns(nhwc, dtype, compiled) : K_BWD_STRIP_Q;
     // what the kernels assume: no Add; 3 x 3 windows; strips and chunks that cover the plane; the divisors of the lane numbering
     if (k.n_ew < 0 || k.n_post < 0 || k.n_ew + k.n_post > K_BWD_EW || threads != 256 || grid < 1) return BS_ERR_UNSUPPORTED;
     for (int32_t j = 0; j < k.n_ew + k.n_post; ++j)
@@ -713,12 +756,12 @@ bs_status launch_backward_strips(const BwdK &arg, int32_t dtype, int32_t vec, in
     k.a_bytes = reach(in_px, k.a_extra) * es;
     k.g_bytes = reach(out_px, k.gout_extra) * es;
     const bool wide = std::max(std::max(k.a_bytes, k.g_bytes), reach(in_px, k.gin_extra) * es) > 0xffffffffull;
-    const int32_t pre = list_code(k, 0, k.n_ew), post = list_code(k, k.n_ew, k.n_post);
+    const int32_t pre = strip_list_code(k.ew, k.n_ew);
     hipStream_t st = static_cast<hipStream_t>(stream);
     const dim3 g((uint32_t)grid);
 #define BS_STRIPS_CL(DT, CL)                                                       \
     do {                                                                           \
-        if (two) launch2<DT, CL>(k, wide, pre, post, g, st);                       \
+        if (two) launch2<DT, CL>(k, wide, compiled, g, st);                       \
         else if (p.sh == 2 && p.ph == 1) launch1<DT, CL, 2, 1>(k, wide, pre, g, st); \
         else if (p.sh == 2) launch1<DT, CL, 2, 0>(k, wide, pre, g, st);            \
         else if (p.ph == 1) launch1<DT, CL, 1, 1>(k, wide, pre, g, st);            \

@@ -78,6 +78,9 @@ struct BwdStage {
     int32_t n_res = 0, res_map[K_MAX_RES] = {-1, -1, -1, -1};  // stack-wide residual numbers
     int32_t vec = 1, threads = 256;
     int64_t grid = 0;
+    BwdK kept{};                  // strips: where kept_grid > 0, what runs instead if the caller kept the picks (the gathering kernel)
+    int32_t kept_vec = 1;
+    int64_t kept_grid = 0;
     bs_stack *forward = nullptr;  // this stage alone as a forward stack (null: its output and picks are not needed)
     int32_t idx_slot = -1;        // the stack's index output that holds this stage's max-pooling picks, if it has one
     uint64_t a_off = 0;           // workspace offsets: the stage's input (stages >= 1),
@@ -222,6 +225,8 @@ bs_status launch_lds(const LdsSeqK &k, int32_t dtype, int64_t grid, int32_t thre
 void free_backward(bs_stack *s);
 bs_status launch_backward_stage(const BwdK &k, int32_t dtype, int32_t vec, int64_t grid, int32_t threads, void *stream);
 // bs_backward_strip.hip: stages with overlapping 3 x 3 max pooling as strips of columns (BwdK::strips)
+bool bwd_strip_compiled(const BwdK &k);   // the one-level kernel has this stage's lists compiled in,
+bool bwd_strip2_compiled(const BwdK &k);  // the two-level kernel its lists and divisors
 bs_status launch_backward_strips(const BwdK &k, int32_t dtype, int32_t vec, int64_t grid, int32_t threads, void *stream);
 // bs_trace.cpp
 bool trace_enabled();

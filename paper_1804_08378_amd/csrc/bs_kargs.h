@@ -345,8 +345,9 @@ constexpr int K_BWD_ROWS2_RC = BS_ROWS2_RC;
 // two-level kernel.  Measured on MI355X (us), ResNet stem bfloat16 / float32: 4 columns 60 / 98, 8 columns 58 / 97 (half the
 // waves for small planes); halo_stress float32 / bfloat16: 4 columns 115 / 117, 8 columns (two waves per SIMD) 109 / 116.
 constexpr int K_BWD_STRIP_Q = 4;
-// ... two-level, row-major float32: 4, 16 bytes of own columns per lane, so that a wave's load has no gaps
-constexpr int bwd_strip2_columns(bool nhwc, int dtype) { return !nhwc && dtype == 0 ? 4 : 8; }
+// ... two-level, row-major float32: 4, 16 bytes of own columns per lane, so that a wave's load has no gaps; 4 as well where the lists or
+// the divisors are not compiled in (registers)
+constexpr int bwd_strip2_columns(bool nhwc, int dtype, bool compiled) { return !compiled || (!nhwc && dtype == 0) ? 4 : 8; }
 // ... and the lanes their chunks of rows aim at.  One level: at most what the chip holds at once (7 waves on each of 1024
 // SIMDs; ResNet stem bfloat16 with 1 / 2 / 3 / 4 / 7 chunks, of which 4 fit: 95 / 68 / 65 / 60 / 63 us).  Two levels: three quarters of
 // it (2 waves; a chunk computes the window rows above and below it again: halo_stress float32 with 1 / 2 / 3 / 4 chunks 109 / 116 /

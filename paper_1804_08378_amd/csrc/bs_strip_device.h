@@ -61,6 +61,80 @@ BS_DEV void each_of(std::integer_sequence<int, B...>, F f)
 
 constexpr bool ends_in_relu(int code) { return code > 0 && ew_code_kind(code, ew_code_len(code) - 1) == OP_RELU; }
 
+// BatchNorm, ReLU: compiled into the strip kernels.  A ReLU alone runs in those instances as well, behind a BatchNorm with scale 1
+// and shift +0: x * 1 + 0 is x, but for -0, which the ReLU makes +0 in either case.
+constexpr int BN_RELU = OP_BN + OP_RELU * K_EW_BASE;
+inline int32_t strip_list_code(const EwOp *ew, int32_t n)
+{
+    if (n == 1 && ew[0].kind == OP_RELU) return BN_RELU;
+    int32_t c = 0, digit = 1;
+    if (n > 6) return -1;
+    for (int32_t j = 0; j < n; ++j, digit *= K_EW_BASE) c += ew[j].kind * digit;
+    return c;
+}
+
+// Where an element-wise operation's parameters come from: held in registers, or read at this use.  bn(): BatchNorm's scale and shift
+// of V channels from `c` on; first(), second(): leaky ReLU's slope, clamp's bounds.
+template <int V>
+struct HeldParams {
+    float a[V], b[V];
+    BS_DEV void bn(float (&scale)[V], float (&shift)[V]) const
+    {
+#pragma unroll
+        for (int e = 0; e < V; ++e) {
+            scale[e] = a[e];
+            shift[e] = b[e];
+        }
+    }
+    BS_DEV float first() const { return a[0]; }
+    BS_DEV float second() const { return b[0]; }
+    // of operation `kind` with argument `arg`, once per lane
+    BS_DEV void load(const float *params, int32_t kind, int32_t arg, int32_t c, int32_t C)
+    {
+#pragma unroll
+        for (int e = 0; e < V; ++e) {
+            a[e] = b[e] = 0.0f;
+            if (kind == OP_BN) {
+                a[e] = params[arg + c + e];
+                b[e] = params[arg + C + c + e];
+            } else if (kind != OP_RELU) {
+                a[e] = params[arg];
+                if (kind == OP_CLAMP) b[e] = params[arg + 1];
+            }
+        }
+    }
+    BS_DEV void identity()  // the BatchNorm in front of a ReLU alone
+    {
+#pragma unroll
+        for (int e = 0; e < V; ++e) {
+            a[e] = 1.0f;
+            b[e] = 0.0f;
+        }
+    }
+};
+template <int V>
+struct ReadParams {
+    const float *params;
+    int32_t arg, c, C;
+    BS_DEV void bn(float (&scale)[V], float (&shift)[V]) const
+    {
+#pragma unroll
+        for (int e = 0; e < V; ++e) {
+            scale[e] = params[arg + c + e];
+            shift[e] = params[arg + C + c + e];
+        }
+    }
+    BS_DEV float first() const { return params[arg]; }
+    BS_DEV float second() const { return params[arg + 1]; }
+};
+
+// The q-th of four values (taken by value: an index into an array would put the array into scratch memory).
+BS_DEV float one_of(int32_t q, float v0, float v1, float v2, float v3)
+{
+    const float low = q == 0 ? v0 : v1, high = q == 2 ? v2 : v3;
+    return q < 2 ? low : high;
+}
+
 // v > best: best = v, at = c.  NaN is never more; of zeros of both signs the first one stays.  Left to the compiler's
 // scheduler: between a vector compare and the select that reads its lane mask gfx950 needs two wait states, which it fills with the
 // neighbouring windows' work; inside an asm block nothing would.

@@ -258,6 +258,76 @@ def test_channels_last_strips_with_infinities_and_offsets_beyond_4_gib():
     st.close()
 
 
+def _run_time_lists(c):
+    six = [wl.bn_params(c, 96), wl.leaky_relu(0.3), wl.clamp(-1.5, 2.0), wl.bn_params(c, 97), wl.leaky_relu(0.1), wl.bn_params(c, 98)]
+    return {
+        "leaky": [wl.bn_params(c, 99), wl.leaky_relu(0.1), wl.maxpool(3, 2, 1, True)],
+        "six": six + [wl.maxpool(3, 2, 0, True)],
+        "six_stride1": six + [wl.maxpool(3, 1, 1, True)],
+        "six_behind": [wl.relu(), wl.maxpool(3, 2, 1, True)] + six,
+        "relu": [wl.relu(), wl.maxpool(3, 2, 1, True)],
+        "none": [wl.maxpool(3, 2, 0, True)],
+        "none_stride1": [wl.maxpool(3, 1, 1, True)],
+        "two_six": six + [wl.avgpool(3, 1, 1, False), wl.maxpool(3, 2, 1)] + six,
+        "two_relu": [wl.relu(), wl.avgpool(3, 1, 1, True), wl.maxpool(3, 2, 1), wl.relu()],
+        "two_counted": [wl.bn_params(c, 100), wl.relu(), wl.avgpool(3, 1, 1, False), wl.maxpool(3, 2, 1), wl.bn_params(c, 101), wl.relu()],
+        "two_none": [wl.avgpool(3, 1, 1, True), wl.maxpool(3, 2, 1)],
+    }
+
+
+@pytest.mark.parametrize("layout,shape,dtype", [(l, s, d) for d in ("f32", "bf16", "f16") for l, s in (
+    ("nhwc", (2, 6, 21, 19)), ("nhwc", (1, 16, 12, 24)), ("nhwc", (2, 3, 9, 61)), ("nchw", (2, 6, 21, 19)), ("nchw", (1, 2, 24, 13)),
+    ("nchw", (1, 6, 425, 431)), ("nhwc", (1, 7, 425, 431)))] + [("nhwc", (1, 24, 425, 431), "f32")])
+def test_strips_with_lists_read_at_run_time(layout, shape, dtype):
+    """Lists of any length (more operations than the kernels hold the parameters of), a ReLU alone and none, divisors that leave out
+    padding; with the picks of the forward pass and without: small stages gather kept picks, whose sums have the same order."""
+    opts = dict(layout=bs.BS_LAYOUT_NHWC) if layout == "nhwc" else {}
+    mf = torch.channels_last if opts else torch.contiguous_format
+    for name, layers in _run_time_lists(shape[1]).items():
+        label = f"run-time lists/{layout}/{name}"
+        x, _, dy = _inputs(layers, shape, 31, dtype)
+        x[:, :, ::2, 1::3] = 0.5
+        print(f"[backward] {label} shape={shape} dtype={dtype}", flush=True)
+        ref_x, _ = bw.backward_stack(layers, x, [], dy, dtype)
+        st = bs.Stack(layers, shape, dtype).plan(**opts).plan_backward()
+        assert bs.bs_stack_backward_num_stages(st.handle) == 1, label
+        xd, dyd = (_dev(a, dtype).contiguous(memory_format=mf) for a in (x, dy))
+        gx, _ = st.backward(xd, [], dyd)
+        _close(gx.float().cpu().numpy(), ref_x, dtype, label)
+        if st.n_idx:
+            _, idx = st.run(xd)
+            hx, _ = st.backward(xd, [], dyd, indices=idx)
+            if dtype == "f16":  # as in test_channels_last_strips
+                assert bool(((gx.float() - hx.float()).abs() <= 2.0 ** -10 * hx.float().abs() + 2.0 ** -24).all()), label
+            else:
+                assert torch.equal(gx, hx), label
+        st.close()
+
+
+def test_row_major_strips_with_offsets_beyond_4_gib():
+    """Images so far apart that byte offsets need more than 32 bits, one and two pooling levels, lists compiled in and not."""
+    n, c, h, w, stride = 3, 2, 9, 11, 700 << 20
+    if torch.cuda.mem_get_info()[0] < (12 << 30):
+        pytest.skip("needs 12 GiB of free device memory")
+    big = torch.empty(2 * stride + c * h * w, dtype=torch.float32, device="cuda")
+    for layers in ([wl.bn_params(c, 1), wl.relu(), wl.maxpool(3, 2, 1)], [wl.leaky_relu(0.1), wl.maxpool(3, 1, 1)],
+                   [wl.bn_params(c, 2), wl.relu(), wl.avgpool(3, 1, 1, True), wl.maxpool(3, 2, 1), wl.bn_params(c, 3), wl.relu()],
+                   [wl.avgpool(3, 1, 1, False), wl.maxpool(3, 2, 1)]):
+        x, _, dy = _inputs(layers, (n, c, h, w), 5, "f32")
+        st = bs.Stack(layers, (n, c, h, w), "f32").plan().plan_backward()
+        xd, dyd = _dev(x, "f32"), _dev(dy, "f32")
+        dense, _ = st.backward(xd, [], dyd)
+        big.as_strided((n, c * h * w), (stride, 1)).copy_(xd.reshape(n, -1))
+        gx = torch.empty_like(xd)
+        ws = st.workspace("cuda", backward=True)
+        bs.bs_stack_backward_strided(st.handle, big.data_ptr(), stride, [], None, dyd.data_ptr(), 0, gx.data_ptr(), 0, [],
+                                     ws.data_ptr() if ws is not None else 0, bs.bs_stack_backward_workspace_bytes(st.handle),
+                                     torch.cuda.current_stream().cuda_stream)
+        torch.cuda.synchronize()
+        assert torch.equal(gx, dense), [l["kind"] for l in layers]
+        st.close()
+
+
 def _two_level_stacks(c):
     return {
         "halo_stress": [wl.bn_params(c, 70), wl.relu(), wl.avgpool(3, 1, 1, True), wl.maxpool(3, 2, 1), wl.bn_params(c, 71), wl.relu()],
