@@ -56,7 +56,9 @@ struct Sequence {
     NhwcK nhwc{};
     NhwcTile2K nhwc2{};
     StripK strip{};           // pooling sequences that run as strips (strip_grid > 0), whatever `variant` says
+    StripK strip_plain{};     // the same for a call that asks for no index output: the list may run behind the maximum
     int64_t strip_grid = 0;
+    bool strip_first = false; // they run wherever possible (else only where the kernel of `variant` takes no such slice)
     // run-time build (hipFunction_t) without / with index outputs; null = pre-compiled kernel
     int32_t jit = 0;
     void *jit_fn[2] = {nullptr, nullptr};
@@ -186,6 +188,7 @@ bs_status launch_nhwc_tile2(const NhwcTile2K &k, int32_t dtype, int32_t vec, int
                             void *stream);
 // bs_strip.hip: one or two pooling steps per sequence, lanes walk strips of output columns
 bool strips_supported(const StripK &k);
+bool strips_lists_compiled(const StripK &k);  // no element-wise list is read at run time
 bs_status launch_strips(const StripK &k, int32_t dtype, int64_t grid, void *stream);
 // bs_rows.hip: *_supported = the signature is in the pre-compiled table; *_buildable = the
 // kernel template can be instantiated for it at run time; *_expr = that instance's name

@@ -562,7 +562,7 @@ static void launch_stream(const StreamK &k, dim3 grid, dim3 block, hipStream_t s
 static bs_status run_strips(const bs_stack *s, const Sequence &q, const void *in, void *out, uint32_t in_extra, uint32_t out_extra,
                             int32_t *idx, void *stream)
 {
-    StripK k = q.strip;
+    StripK k = idx ? q.strip : q.strip_plain;
     k.in_xp = in_extra;
     k.out_xp = out_extra;
     if (k.nhwc) {  // a slice skips the larger tensor's other channels in every pixel
@@ -589,6 +589,12 @@ bs_status launch_sequence(const bs_stack *s, const Sequence &q, const void *in, 
     int32_t *ip[K_MAX_IDX] = {nullptr, nullptr, nullptr, nullptr};
     for (int32_t j = 0; j < q.n_idx; ++j) ip[j] = idx ? idx[q.idx_map[j]] : nullptr;
 
+    if (q.strip_first) {
+        const bs_status ls = run_strips(s, q, in, out, in_extra, out_extra, ip[0], stream);
+        if (ls != BS_OK) return ls;
+        const hipError_t e = hipGetLastError();
+        return e != hipSuccess ? hip_fail(e) : BS_OK;
+    }
     switch (q.variant) {
     case BS_VARIANT_STREAM: {
         // vector widths the compiled instances exist for (guards against a plan / kernel mismatch)
@@ -710,11 +716,6 @@ bs_status launch_sequence(const bs_stack *s, const Sequence &q, const void *in, 
         break;
     }
     case BS_VARIANT_LDS_TILE: {
-        if (q.strip_grid > 0) {
-            const bs_status ls = run_strips(s, q, in, out, in_extra, out_extra, ip[0], stream);
-            if (ls != BS_OK) return ls;
-            break;
-        }
         LdsSeqK k = q.lds;
         k.in = in; k.out = out; k.params = s->dev_params;
         k.in_extra = in_extra; k.out_extra = out_extra;
@@ -729,11 +730,6 @@ bs_status launch_sequence(const bs_stack *s, const Sequence &q, const void *in, 
     }
     case BS_VARIANT_NHWC_STREAM:
     case BS_VARIANT_NHWC_POOL: {
-        if (q.strip_grid > 0) {
-            const bs_status ls = run_strips(s, q, in, out, in_extra, out_extra, ip[0], stream);
-            if (ls != BS_OK) return ls;
-            break;
-        }
         NhwcK k = q.nhwc;
         // a channel slice of a channels-last tensor: the batch stride is a whole number of pixels
         // of the larger tensor (checked by the caller), the slice skips the same count per pixel
@@ -749,11 +745,6 @@ bs_status launch_sequence(const bs_stack *s, const Sequence &q, const void *in, 
         break;
     }
     case BS_VARIANT_NHWC_TILE: {
-        if (q.strip_grid > 0) {
-            const bs_status ls = run_strips(s, q, in, out, in_extra, out_extra, ip[0], stream);
-            if (ls != BS_OK) return ls;
-            break;
-        }
         NhwcTile2K k = q.nhwc2;
         const uint32_t hw_in = (uint32_t)(q.in_shape[2] * q.in_shape[3]), hw_out = (uint32_t)(q.out_shape[2] * q.out_shape[3]);
         if (in_extra % hw_in != 0 || out_extra % hw_out != 0) return BS_ERR_UNSUPPORTED;
@@ -762,23 +753,20 @@ bs_status launch_sequence(const bs_stack *s, const Sequence &q, const void *in, 
         k.in = in; k.out = out; k.params = s->dev_params;
         for (int j = 0; j < K_MAX_RES; ++j) k.res[j] = rp[j];
         k.idx = ip[0];
-        const bs_status ls = launch_nhwc_tile2(k, dtype, q.vec, q.grid, q.threads, q.lds_bytes, stream);
+        bs_status ls = launch_nhwc_tile2(k, dtype, q.vec, q.grid, q.threads, q.lds_bytes, stream);
+        if (ls == BS_ERR_UNSUPPORTED && q.strip_grid > 0) ls = run_strips(s, q, in, out, in_extra, out_extra, ip[0], stream);
         if (ls != BS_OK) return ls;
         break;
     }
     case BS_VARIANT_NHWC_ROWS: {
-        if (q.strip_grid > 0) {
-            const bs_status ls = run_strips(s, q, in, out, in_extra, out_extra, ip[0], stream);
-            if (ls != BS_OK) return ls;
-            break;
-        }
         NhwcTile2K k = q.nhwc2;
         const uint32_t hw_in = (uint32_t)(q.in_shape[2] * q.in_shape[3]), hw_out = (uint32_t)(q.out_shape[2] * q.out_shape[3]);
         if (in_extra % hw_in != 0 || out_extra % hw_out != 0) return BS_ERR_UNSUPPORTED;
         k.in_xp = in_extra / hw_in;
         k.out_xp = out_extra / hw_out;
         k.in = in; k.out = out; k.params = s->dev_params;
-        const bs_status ls = launch_nhwc_rows2(k, dtype, q.vec, q.grid, q.threads, stream);
+        bs_status ls = launch_nhwc_rows2(k, dtype, q.vec, q.grid, q.threads, stream);
+        if (ls == BS_ERR_UNSUPPORTED && q.strip_grid > 0) ls = run_strips(s, q, in, out, in_extra, out_extra, ip[0], stream);
         if (ls != BS_OK) return ls;
         break;
     }

@@ -459,6 +459,43 @@ static bool strips_wanted(const bs_plan_options &o)
     return o.lane_exchange >= 0 && o.threads_per_group == 0 && o.tile_rows == 0 && o.tile_cols == 0 && o.planes_per_group == 0;
 }
 
+// Strips whose lists are read at run time (any list but BatchNorm -> ReLU or a ReLU alone where the kernels have it compiled in, none, or
+// divisors that leave out padding).  Their instances are larger: small calls wait for their code, pairs are bound by it.  Measured on
+// MI355X, us, the kernels the options would select / strips:
+//   pairs: an average and a 3x3/2 maximum stay (64 x 64 x 55 x 55, no padding counted, channels-last float32 26 / 51, binary16
+//   36 / 53; row-major binary16 42 / 62); with stride 1 (64 x 64 x 55 x 55 channels-last float32 136 / 45, bfloat16 48 / 34; 8 x 64 x 28 x 28
+//   7 / 8); behind a 3x3/1 maximum (64 x 64 x 55 x 55, leaky ReLU between: channels-last binary16 34 / 31, float32 27 / 30, 8 x 64 x 28 x 28
+//   9 / 11; row-major bfloat16 50 / 33, 1 x 192 x 35 x 35 9 / 11);
+//   one step, channels-last: stride 1 (8 x 64 x 28 x 28 average, leaky ReLU: 8 / 7; 1 x 30 x 33 x 33 5 / 6); stride 2, whole vectors, BatchNorm, leaky ReLU, with
+//   indices 64 x 64 x 55 x 55 binary16 20 / 19, float32 16 / 18, 8 x 64 x 28 x 28 binary16 7 / 8, average without padding counted binary16
+//   9 / 15; other channel counts 32 x 30 x 113 x 113 15 / 12, 16 x 30 x 57 x 57 6 / 8;
+//   one step, row-major: 1 x 64 x 14 x 14 5 / 7, 32 x 64 x 17 x 17 8 / 8, 64 x 64 x 55 x 55 average with leaky ReLU 42 / 32 (float32 4 x 64 x 71 x 71 8 / 9,
+//   3x3/2 average without padding counted binary16 7.0 / 7.6).
+static bool run_time_lists_pay(const bs_stack *s, const Sequence &q, const StripK &k)
+{
+    const bool f32 = s->dtype == BS_F32, idx = k.pool2.idx_slot >= 0, nhwc = k.nhwc != 0;
+    const int64_t cells = q.in_shape[0] * q.in_shape[1] * q.in_shape[2] * q.in_shape[3], M = 1 << 20;
+    if (k.pool1.kind != 0) {
+        if (k.pool2.sh == 1) return nhwc ? cells >= 4 * M : !f32 && cells >= 8 * M;
+        if (k.pool1.kind != OP_MAXPOOL) return false;
+        return nhwc ? !f32 && cells >= 4 * M : (!f32 || idx) && cells >= M / 2;
+    }
+    const bool avg = k.pool2.kind == OP_AVGSUM, whole = k.C % (f32 ? 4 : 8) == 0;
+    if (!nhwc) return (!avg && !idx) || cells >= (avg && k.pool2.sh == 2 ? 2 * M : avg && f32 ? 4 * M : M / 2);
+    if (k.pool2.sh == 1) return whole || cells >= M / 4;
+    return !(whole && (f32 || avg)) && cells >= 4 * M;
+}
+
+// Lists in front of a maximum go behind it where the values stay the same (plan_nhwc says when).
+static void move_behind_max(const bs_stack *s, int32_t C, EwOp *from, int32_t &n_from, EwOp *to, int32_t &n_to)
+{
+    if (n_from == 0 || n_from + n_to > K_MAX_EW || !commutes_with_max(s, from, n_from, C)) return;
+    for (int32_t j = n_to - 1; j >= 0; --j) to[j + n_from] = to[j];
+    for (int32_t j = 0; j < n_from; ++j) to[j] = from[j];
+    n_to += n_from;
+    n_from = 0;
+}
+
 // A channels-last sequence of one or two pooling steps as strips of output columns, if the kernel exists for it.  The
 // sequence keeps the geometry of the kernel that options would select (bs_stack_sequence_info reports that one).
 static void plan_strips(const bs_stack *s, Sequence &q, const StripK &lists, const PoolK *first, const PoolK &second, int32_t H, int32_t W, int32_t Ho,
@@ -471,6 +508,9 @@ static void plan_strips(const bs_stack *s, Sequence &q, const StripK &lists, con
     k.C = (int32_t)q.in_shape[1];
     k.H = H; k.W = W; k.Ho = Ho; k.Wo = Wo;
     if (!strips_supported(k)) return;
+    // pairs that stay with the channels-last tile kernel: it takes 32-bit byte offsets only, slices beyond them run as strips
+    const bool pays = strips_lists_compiled(k) || run_time_lists_pay(s, q, k);
+    if (!pays && !(first && k.nhwc)) return;
     const int32_t qo = strip_columns(k.nhwc != 0, s->dtype, second.sh);
     k.strips = (Wo + qo - 1) / qo;
     const int64_t per_chunk = q.in_shape[0] * k.strips * k.C;
@@ -485,7 +525,10 @@ static void plan_strips(const bs_stack *s, Sequence &q, const StripK &lists, con
     k.div_strips = make_fastdiv((uint32_t)k.strips);
     k.div_chunks = make_fastdiv((uint32_t)k.chunks);
     q.strip = k;
+    if (!first && k.pool2.kind == OP_MAXPOOL) move_behind_max(s, k.C, k.pre, k.n_pre, k.post, k.n_post);
+    q.strip_plain = k;
     q.strip_grid = (total + 255) / 256;
+    q.strip_first = pays;
 }
 
 static void copy_list(const EwOp *from, int32_t n, EwOp *to, int32_t &n_to)
@@ -531,16 +574,10 @@ static void plan_row_strips(const bs_stack *s, Sequence &q, const bs_plan_option
         k.n_mid = 0;
     }
     // maximum first: as in plan_nhwc
-    auto move_behind = [&](EwOp *from, int32_t &n_from, EwOp *to, int32_t &n_to) {
-        if (n_from == 0 || n_from + n_to > K_MAX_EW || !commutes_with_max(s, from, n_from, (int32_t)q.in_shape[1])) return;
-        for (int32_t j = n_to - 1; j >= 0; --j) to[j + n_from] = to[j];
-        for (int32_t j = 0; j < n_from; ++j) to[j] = from[j];
-        n_to += n_from;
-        n_from = 0;
-    };
-    if (n == 1 && pools[0].kind == OP_MAXPOOL && pools[0].idx_slot < 0) move_behind(k.pre, k.n_pre, k.post, k.n_post);
-    if (n == 2 && pools[0].kind == OP_MAXPOOL) move_behind(k.pre, k.n_pre, k.mid, k.n_mid);
-    if (n == 2 && pools[1].kind == OP_MAXPOOL && pools[1].idx_slot < 0) move_behind(k.mid, k.n_mid, k.post, k.n_post);
+    const int32_t C = (int32_t)q.in_shape[1];
+    if (n == 1 && pools[0].kind == OP_MAXPOOL && pools[0].idx_slot < 0) move_behind_max(s, C, k.pre, k.n_pre, k.post, k.n_post);
+    if (n == 2 && pools[0].kind == OP_MAXPOOL) move_behind_max(s, C, k.pre, k.n_pre, k.mid, k.n_mid);
+    if (n == 2 && pools[1].kind == OP_MAXPOOL && pools[1].idx_slot < 0) move_behind_max(s, C, k.mid, k.n_mid, k.post, k.n_post);
     plan_strips(s, q, k, n == 2 ? &pools[0] : nullptr, pools[n - 1], H, W, Ho, Wo);
 }
 
@@ -1672,7 +1709,7 @@ bs_status group_sequences(bs_stack *s, const bs_plan_options &o, const Limits &l
         }
         if (st != BS_OK) return st;
         if (!nhwc && q.variant == BS_VARIANT_LDS_TILE) plan_row_strips(s, q, o);
-        if (!nhwc && q.strip_grid == 0) st = prepare_jit(s, q, o.host_only != 0);
+        if (!nhwc && !q.strip_first) st = prepare_jit(s, q, o.host_only != 0);
         if (st != BS_OK) return st;
         if (di + 1 < drafts.size()) {
             uint64_t bytes = (uint64_t)q.out_shape[0] * q.out_shape[1] * q.out_shape[2] * q.out_shape[3] * es;

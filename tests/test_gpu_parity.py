@@ -1029,6 +1029,109 @@ def test_row_major_strips(shape, dtype):
     check([wl.maxpool(3, 2, 1, True), wl.relu()], x, [], dtype, f"row strips/infinities{shape}")
 
 
+def _six_ops(c, i):
+    """More operations than the strip kernels hold the parameters of."""
+    return [wl.bn_params(c, i), wl.leaky_relu(0.3), wl.clamp(-1.5, 2.0), wl.bn_params(c, i + 1), wl.leaky_relu(0.1), wl.bn_params(c, i + 2)]
+
+
+# Strips whose lists are read at run time, on tensors large enough for the planner to choose them: layout, shape, dtypes, stacks
+RUN_TIME_LISTS = [
+    ("nchw", (2, 5, 235, 251), ("f32", "bf16", "f16"), ("idx", "idx_six", "max31", "max30", "maxmid", "maxmid_idx", "avg32", "max22")),
+    ("nchw", (2, 9, 343, 347), ("f32", "bf16"), ("avg32", "avg32_ceil")),
+    ("nchw", (1, 24, 425, 431), ("f32",), ("avg31", "avg31_six")),
+    ("nchw", (1, 46, 425, 431), ("f16",), ("avgmax31",)),
+    ("nhwc", (2, 27, 80, 71), ("f32", "bf16", "f16"), ("avg31", "avg31_six", "max31", "max30", "idx31")),
+    ("nhwc", (1, 24, 425, 431), ("bf16",), ("idx", "idx_six", "maxmid", "maxmid_idx", "avgmax31")),
+    ("nhwc", (1, 24, 425, 431), ("f32",), ("avgmax31", "maxmax31")),
+    ("nhwc", (1, 27, 425, 403), ("f32", "f16"), ("idx", "avg32")),
+]
+
+
+@pytest.mark.parametrize("layout,shape,dtype,names", [(l, s, d, n) for l, s, ds, n in RUN_TIME_LISTS for d in ds])
+def test_strips_with_lists_read_at_run_time(layout, shape, dtype, names):
+    """Lists, divisors and combinations of them that the strip kernels have no instance for, bit for bit the oracle's values and
+    indices; a call that asks for no index output gives the same values."""
+    c = shape[1]
+    stacks = {
+        "idx": [wl.bn_params(c, 260), wl.leaky_relu(0.1), wl.maxpool(3, 2, 1, True)],
+        "idx_six": _six_ops(c, 261) + [wl.maxpool(3, 2, 0, True), wl.bn_params(c, 264)],
+        "idx31": [wl.clamp(-1.0, 1.0), wl.maxpool(3, 1, 1, True)],
+        "max31": [wl.maxpool(3, 1, 1), wl.bn_params(c, 265), wl.leaky_relu(0.2)],
+        "max30": [wl.bn_params(c, 266), wl.maxpool(3, 1, 0)],
+        "max22": [wl.bn_params(c, 267), wl.leaky_relu(0.1), wl.maxpool(2, 2, 0, True)],
+        "avg31": [wl.bn_params(c, 268), wl.leaky_relu(0.1), wl.avgpool(3, 1, 1, False), wl.bn_params(c, 269)],
+        "avg31_six": [wl.avgpool(3, 1, 1, True)] + _six_ops(c, 270),
+        "avg32": [wl.bn_params(c, 273), wl.relu(), wl.avgpool(3, 2, 1, False)],
+        "avg32_ceil": [wl.leaky_relu(0.1), wl.avgpool(3, 2, 0, True, True)],
+        "maxmid": [wl.maxpool(3, 1, 1), wl.bn_params(c, 274), wl.leaky_relu(0.1), wl.maxpool(3, 2, 1, dtype == "f32")],
+        "maxmid_idx": [wl.maxpool(3, 1, 1)] + _six_ops(c, 275) + [wl.maxpool(3, 2, 1, True), wl.relu()],
+        "maxmax31": [wl.maxpool(3, 1, 1), wl.leaky_relu(0.1), wl.maxpool(3, 1, 1)],
+        "avgmax31": [wl.bn_params(c, 278), wl.leaky_relu(0.1), wl.avgpool(3, 1, 1, False), wl.maxpool(3, 1, 1, True)],
+    }
+    for name in names:
+        layers = stacks[name]
+        x = wl.activation(shape, 279, dtype)
+        x[:, :, ::3, ::2] = 0.0
+        opts = dict(layout=bs.BS_LAYOUT_NHWC) if layout == "nhwc" else {}
+        (_check_nhwc if opts else check)(layers, x, [], dtype, f"run-time lists/{layout}/{name}")
+        _check_without_indices(layers, x, dtype, **opts)
+
+
+def _check_without_indices(layers, x, dtype, **opts):
+    st = bs.Stack(layers, x.shape, dtype).plan(**opts)
+    xd = _dev(x, dtype).contiguous(memory_format=torch.channels_last if opts else torch.contiguous_format)
+    with_idx, _ = st.run(xd)
+    without, _ = st.run(xd, indices=[])
+    torch.cuda.synchronize()
+    assert torch.equal(with_idx.view(torch.int32 if dtype == "f32" else torch.int16), without.view(torch.int32 if dtype == "f32" else torch.int16))
+    st.close()
+
+
+@pytest.mark.parametrize("layout", ["nchw", "nhwc"])
+@pytest.mark.parametrize("dtype", ["f32", "bf16", "f16"])
+def test_strips_with_a_relu_alone_or_no_list(layout, dtype):
+    """A ReLU alone runs in the instances compiled for BatchNorm and ReLU, poolings without any list in instances of their own; with
+    zeros of both signs and calls that ask for no index output."""
+    opts = dict(layout=bs.BS_LAYOUT_NHWC) if layout == "nhwc" else {}
+    for shape in ((2, 8, 13, 11), (1, 5, 9, 35)):
+        x = wl.activation(shape, 280, dtype)
+        x[:, :, ::3, ::2] = 0.0
+        x[:, :, 1::3, ::2] = -0.0
+        for pool in (wl.maxpool(3, 2, 1, True), wl.maxpool(3, 2, 0, True, True), wl.maxpool(3, 1, 1, True), wl.maxpool(3, 1, 1), wl.maxpool(3, 1, 0, True),
+                     wl.maxpool(2, 2, 0, True), wl.avgpool(3, 1, 1), wl.avgpool(3, 2, 1), wl.avgpool(3, 1, 0)):
+            for layers in ([wl.relu(), pool], [pool, wl.relu()], [pool], [wl.relu(), pool, wl.relu()]):
+                if pool["kind"] == "maxpool" and not pool["return_indices"] and layers[0] is pool and len(layers) == 1:
+                    continue  # max(-0, +0) without a list: either zero is a maximum
+                (_check_nhwc if opts else check)(layers, x, [], dtype, f"{layout}/{[l['kind'] for l in layers]}")
+                if layers[-1]["kind"] == "relu":
+                    _check_without_indices(layers, x, dtype, **opts)
+        for layers in ([wl.relu(), wl.avgpool(3, 1, 1), wl.maxpool(3, 2, 1, True), wl.relu()], [wl.maxpool(3, 1, 1), wl.relu(), wl.maxpool(3, 2, 1)]):
+            (_check_nhwc if opts else check)(layers, x, [], dtype, f"{layout}/pair")
+
+
+def test_row_major_strips_with_offsets_beyond_4_gib():
+    """Image slices so far apart that byte offsets need more than 32 bits; the tensor's first row begins with a run of columns that
+    would start in front of it."""
+    n, c, h, w, stride = 3, 2, 9, 11, 700 << 20
+    if torch.cuda.mem_get_info()[0] < (12 << 30):
+        pytest.skip("needs 12 GiB of free device memory")
+    for layers in ([wl.bn_params(c, 1), wl.relu(), wl.avgpool(3, 1, 1, True), wl.maxpool(3, 2, 1, True)],
+                   [wl.bn_params(c, 2), wl.relu(), wl.maxpool(3, 2, 1, True)]):
+        x = wl.activation((n, c, h, w), 281)
+        st = bs.Stack(layers, x.shape, "f32").plan()
+        xd = _dev(x, "f32")
+        dense, idx = st.run(xd)
+        big = torch.empty(2 * stride + c * h * w, dtype=torch.float32, device="cuda")
+        big.as_strided((n, c * h * w), (stride, 1)).copy_(xd.reshape(n, -1))
+        out, idx2 = st.alloc_outputs("cuda")
+        bs.bs_stack_run_strided(st.handle, big.data_ptr(), stride, [], out.data_ptr(), 0, [idx2[0].data_ptr()], 0, 0,
+                                torch.cuda.current_stream().cuda_stream)
+        torch.cuda.synchronize()
+        assert torch.equal(out, dense) and torch.equal(idx2[0], idx[0])
+        st.close()
+        del big
+
+
 @pytest.mark.parametrize("dtype", ["f32", "bf16", "f16"])
 def test_strips_with_zeros_of_both_signs_and_nan(dtype):
     """Poolings with indices in the strip kernels: of zeros of both signs the first one is stored, as its index says; NaN,
