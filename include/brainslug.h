@@ -140,6 +140,9 @@ typedef enum bs_variant {
     BS_VARIANT_NHWC_TILE = 8,   /* channels-last plans only: two pooling steps, tiles of both planes with halos staged in LDS */
     BS_VARIANT_ROWS_CHAIN = 9,  /* two and more identical max-pooling steps that keep the plane's size, each with the same
                                    kinds of element-wise operations behind it: rows ripple through all levels in registers */
+    BS_VARIANT_STRIPS = 11,     /* one 3 x 3 (row-major also 2 x 2 / 2) pooling step, or a 3 x 3 / 1 / 1 step and a 3 x 3 maximum, both layouts:
+                                   a lane walks down a strip of output columns in registers, no LDS (chosen by the planner,
+                                   force_variant does not take it)                                                        */
     BS_VARIANT_NHWC_ROWS = 10   /* channels-last plans only: two 3 x 3 pooling steps (the first with stride 1, the second a
                                    maximum) on images at most 64 pixels wide: rows slide in registers, a lane = one pixel
                                    column x one channel vector, no LDS */
@@ -198,9 +201,8 @@ typedef enum bs_layout {
  *                           registers, no LDS); tile_rows is then the number of output rows per
  *                           work-group.  With threads_per_group, tile_rows, tile_cols and
  *                           planes_per_group all 0 and lane_exchange = 0, sequences of one 3 x 3 step
- *                           or of a 3 x 3 / 1 / 1 step and a 3 x 3 maximum (no residual Add) run as strips
- *                           of output columns in registers where that is faster; bs_stack_sequence_info
- *                           keeps reporting the kernel and geometry those options would select.
+ *                           or of a 3 x 3 / 1 / 1 step and a 3 x 3 maximum (no residual Add) run as
+ *                           BS_VARIANT_STRIPS where that is faster.
  *                           Row-major plans (also max_lds_bytes and force_variant 0, jit not 1) do the same
  *                           with such sequences, and with 2 x 2 / 2 steps, that would take
  *                           BS_VARIANT_LDS_TILE: nothing is built for them at plan time.
@@ -247,7 +249,7 @@ typedef struct bs_sequence_info {
     int32_t first_layer, n_layers;
     int32_t variant;                 /* bs_variant                                         */
     int32_t n_levels;                /* pooling operations inside (LDS hand-offs + 1)      */
-    int32_t tile_rows, tile_cols;    /* final-output tile per work-group (LDS variant)     */
+    int32_t tile_rows, tile_cols;    /* final-output tile per work-group (LDS variant); strips: per lane */
     int32_t planes_per_group;
     int32_t halo_rows, halo_cols;    /* input rows/cols an interior tile loads beyond tile*stride */
     int32_t threads_per_group;

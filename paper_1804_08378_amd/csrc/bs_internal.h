@@ -55,7 +55,7 @@ struct Sequence {
     LdsSeqK lds{};
     NhwcK nhwc{};
     NhwcTile2K nhwc2{};
-    StripK strip{};           // pooling sequences that run as strips (strip_grid > 0), whatever `variant` says
+    StripK strip{};           // pooling sequences as strips (strip_grid > 0: planned); `variant`: the kernel without them
     StripK strip_plain{};     // the same for a call that asks for no index output: the list may run behind the maximum
     int64_t strip_grid = 0;
     bool strip_first = false; // they run wherever possible (else only where the kernel of `variant` takes no such slice)

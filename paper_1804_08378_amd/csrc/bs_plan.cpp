@@ -496,8 +496,8 @@ static void move_behind_max(const bs_stack *s, int32_t C, EwOp *from, int32_t &n
     n_from = 0;
 }
 
-// A channels-last sequence of one or two pooling steps as strips of output columns, if the kernel exists for it.  The
-// sequence keeps the geometry of the kernel that options would select (bs_stack_sequence_info reports that one).
+// A sequence of one or two pooling steps as strips of output columns, if the kernel exists for it and pays.  The plan for the kernel
+// that options would select stays beside it.
 static void plan_strips(const bs_stack *s, Sequence &q, const StripK &lists, const PoolK *first, const PoolK &second, int32_t H, int32_t W, int32_t Ho,
                         int32_t Wo)
 {
@@ -542,7 +542,7 @@ static void copy_list(const EwOp *from, int32_t n, EwOp *to, int32_t &n_to)
 // signature -> strips: BatchNorm, ReLU, max 3x3/2 on 32 x 64 x 147 x 147 binary16 65 -> 28, float32 87 -> 60 (4 columns per lane: 85);
 // max 2x2/2 on 32 x 64 x 111 x 111 binary16 35 -> 15, float32 45 -> 29; average 3x3/1 on 32 x 288 x 35 x 35 float32 45 -> 31, bfloat16
 // 38 -> 18; with indices 64 x 64 x 111 x 111 float32 112 -> 76; halo_stress's stack on 18 x 56 x 117 x 117 float32 42 -> 38, binary16
-// 37 -> 18.  The sequence keeps the tile plan's geometry (bs_stack_sequence_info) without a kernel being built for it.
+// 37 -> 18.  No kernel is built for the tile plan then.
 static void plan_row_strips(const bs_stack *s, Sequence &q, const bs_plan_options &o)
 {
     if (!strips_wanted(o) || o.force_variant != BS_VARIANT_AUTO || o.max_lds_bytes != 0 || o.jit == 1 || q.n_res > 0) return;
@@ -1881,6 +1881,21 @@ bs_status bs_stack_sequence_info(const bs_stack *stack, int32_t sequence, bs_seq
     r.redundancy = q.redundancy;
     r.run_time_build = q.jit;
     r.reserved = 0;
+    if (q.strip_first) {  // what is launched, not what the options would select without strips
+        const StripK &k = q.strip;
+        const int32_t qo = strip_columns(k.nhwc != 0, stack->dtype, k.pool2.sh), inner = k.pool1.kind != 0 ? 2 : 0;
+        r.variant = BS_VARIANT_STRIPS;
+        r.tile_rows = k.rc;
+        r.tile_cols = qo;
+        r.planes_per_group = 1;
+        r.halo_rows = k.pool2.kh - k.pool2.sh + inner;
+        r.halo_cols = k.pool2.kw - k.pool2.sw + inner;
+        r.threads_per_group = 256;
+        r.grid = q.strip_grid;
+        r.lds_bytes = 0;
+        r.redundancy = (double)k.total * (k.rc * k.pool2.sh + r.halo_rows) * (qo * k.pool2.sw + r.halo_cols) /
+                       ((double)q.in_shape[0] * q.in_shape[1] * q.in_shape[2] * q.in_shape[3]);
+    }
     *info = r;
     return BS_OK;
 }

@@ -53,6 +53,10 @@ const char *variant_name(int32_t v)
     case BS_VARIANT_PLANE_POOL: return "plane_pool";
     case BS_VARIANT_NHWC_STREAM: return "nhwc_stream";
     case BS_VARIANT_NHWC_POOL: return "nhwc_pool";
+    case BS_VARIANT_NHWC_TILE: return "nhwc_tile";
+    case BS_VARIANT_ROWS_CHAIN: return "rows_chain";
+    case BS_VARIANT_NHWC_ROWS: return "nhwc_rows";
+    case BS_VARIANT_STRIPS: return "strips";
     }
     return "?";
 }
@@ -64,7 +68,7 @@ bool trace_enabled() { return tracer().push != nullptr; }
 void trace_push_sequence(const Sequence &q, size_t index, size_t count)
 {
     char label[128];
-    std::snprintf(label, sizeof label, "bs seq %zu/%zu %s%s steps %d..%d", index + 1, count, variant_name(q.variant),
+    std::snprintf(label, sizeof label, "bs seq %zu/%zu %s%s steps %d..%d", index + 1, count, variant_name(q.strip_first ? BS_VARIANT_STRIPS : q.variant),
                   q.jit ? " (run-time build)" : "", q.first_step, q.first_step + q.n_steps - 1);
     (void)tracer().push(label);
 }

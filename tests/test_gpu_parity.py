@@ -810,12 +810,14 @@ def _check_nhwc(layers, x, res, dtype, label, **opts):
     for a, b in zip(idx, ref_idx):
         assert np.array_equal(a.cpu().numpy(), b), label
     names = [q["variant_name"] for q in info["sequences"]]
-    assert all(v in ("nhwc_stream", "nhwc_pool", "nhwc_tile", "nhwc_rows") for v in names)
-    assert sum(2 if v in ("nhwc_tile", "nhwc_rows") else 1 for v in names) == info["n_steps"]
+    assert all(v in ("nhwc_stream", "nhwc_pool", "nhwc_tile", "nhwc_rows", "strips") for v in names)
+    steps = [q["n_steps"] for q in info["sequences"]]
+    assert sum(steps) == info["n_steps"]
+    assert all(n == 2 if v in ("nhwc_tile", "nhwc_rows") else n in (1, 2) if v == "strips" else n == 1 for v, n in zip(names, steps))
     if opts.get("max_steps_per_sequence") == 1 or opts.get("breadth_first"):
-        assert "nhwc_tile" not in names and "nhwc_rows" not in names
+        assert all(n == 1 for n in steps)
     if opts.get("lane_exchange") == -1:
-        assert "nhwc_rows" not in names
+        assert "nhwc_rows" not in names and "strips" not in names
     return info
 
 
@@ -949,15 +951,16 @@ def _nhwc_rows_stacks(c):
 @pytest.mark.parametrize("dtype", ["f32", "bf16", "f16"])
 def test_channels_last_two_pools_in_registers(shape, dtype):
     """The channels-last kernel whose lanes are the pixel columns of an image row (neighbouring columns by lane
-    shifts, no LDS; 16-bit storage) against the oracle: the planner's chunk length, one output row per chunk, a ragged last chunk,
-    the whole image as one chunk; images wider than a wave and the pairs it is not compiled for take the tile kernel."""
+    shifts, no LDS; 16-bit storage) against the oracle: the planner's chunk length (rc 0; a tile width rules strips out), one output row
+    per chunk, a ragged last chunk, the whole image as one chunk; images wider than a wave and the pairs it is not compiled for take
+    the tile kernel."""
     mine, other = _nhwc_rows_stacks(shape[1])
     vec = 4 if dtype == "f32" else 8
     for name, layers in mine.items():
         x = wl.activation(shape, 189, dtype)
         x[:, :, ::3, ::2] = 0.0
         for rc in (0, 1, 3, 5, 1000):
-            info = _check_nhwc(layers, x, [], dtype, f"rows/{name}{shape}/rc{rc}", tile_rows=rc)
+            info = _check_nhwc(layers, x, [], dtype, f"rows/{name}{shape}/rc{rc}", **(dict(tile_rows=rc) if rc else dict(tile_cols=64)))
             names = [q["variant_name"] for q in info["sequences"]]
             if shape[1] % vec == 0 and dtype != "f32":  # compiled for 16-bit storage (float32 is faster through the tile kernel)
                 assert names == ["nhwc_rows"], name
@@ -971,6 +974,10 @@ def test_channels_last_two_pools_in_registers(shape, dtype):
         res = [wl.activation(sh, 191 + i, dtype) for i, sh in enumerate(wl.residual_shapes(layers, shape))]
         info = _check_nhwc(layers, x, res, dtype, f"rows-not/{name}{shape}")
         assert "nhwc_rows" not in [q["variant_name"] for q in info["sequences"]], name
+
+
+def _names(info):
+    return [q["variant_name"] for q in info["sequences"]]
 
 
 def _fwd_strip_stacks(c):
@@ -1003,7 +1010,9 @@ def test_channels_last_strips(shape, dtype):
     for name, layers in _fwd_strip_stacks(shape[1]).items():
         x = wl.activation(shape, 220, dtype)
         x[:, :, ::3, ::2] = 0.0
-        _check_nhwc(layers, x, [], dtype, f"strips/{name}{shape}")
+        info = _check_nhwc(layers, x, [], dtype, f"strips/{name}{shape}")
+        if name in ("avg31", "avg31_bare", "max31", "max32_idx") or (name in ("halo", "halo_idx") and shape[1] % 8 == 0):  # lists compiled in
+            assert _names(info) == ["strips"], name
         _check_nhwc(layers, x, [], dtype, f"no strips/{name}{shape}", lane_exchange=-1)
 
 
@@ -1023,7 +1032,9 @@ def test_row_major_strips(shape, dtype):
     for name, layers in stacks.items():
         x = wl.activation(shape, 243, dtype)
         x[:, :, ::3, ::2] = 0.0
-        check(layers, x, [], dtype, f"row strips/{name}{shape}")
+        info = check(layers, x, [], dtype, f"row strips/{name}{shape}")
+        if shape[3] % 2 and name in ("avg31", "avg31_bare", "max31", "max32_idx", "halo", "halo_idx", "max22", "max22_idx", "avg22"):  # lists compiled in
+            assert _names(info) == ["strips"], name
     x = wl.activation(shape, 244, dtype)
     x[:, :, :3] = -np.inf  # windows of nothing but -infinity: their first cell inside the plane
     check([wl.maxpool(3, 2, 1, True), wl.relu()], x, [], dtype, f"row strips/infinities{shape}")
@@ -1036,8 +1047,8 @@ def _six_ops(c, i):
 
 # Strips whose lists are read at run time, on tensors large enough for the planner to choose them: layout, shape, dtypes, stacks
 RUN_TIME_LISTS = [
-    ("nchw", (2, 5, 235, 251), ("f32", "bf16", "f16"), ("idx", "idx_six", "max31", "max30", "maxmid", "maxmid_idx", "avg32", "max22")),
-    ("nchw", (2, 9, 343, 347), ("f32", "bf16"), ("avg32", "avg32_ceil")),
+    ("nchw", (2, 5, 235, 251), ("f32", "bf16", "f16"), ("idx", "idx_six", "max31", "max30", "maxmid", "maxmid_idx", "max22")),
+    ("nchw", (2, 9, 343, 347), ("f32", "bf16", "f16"), ("avg32", "avg32_ceil")),
     ("nchw", (1, 24, 425, 431), ("f32",), ("avg31", "avg31_six")),
     ("nchw", (1, 46, 425, 431), ("f16",), ("avgmax31",)),
     ("nhwc", (2, 27, 80, 71), ("f32", "bf16", "f16"), ("avg31", "avg31_six", "max31", "max30", "idx31")),
@@ -1073,7 +1084,8 @@ def test_strips_with_lists_read_at_run_time(layout, shape, dtype, names):
         x = wl.activation(shape, 279, dtype)
         x[:, :, ::3, ::2] = 0.0
         opts = dict(layout=bs.BS_LAYOUT_NHWC) if layout == "nhwc" else {}
-        (_check_nhwc if opts else check)(layers, x, [], dtype, f"run-time lists/{layout}/{name}")
+        info = (_check_nhwc if opts else check)(layers, x, [], dtype, f"run-time lists/{layout}/{name}")
+        assert _names(info) == ["strips"], name
         _check_without_indices(layers, x, dtype, **opts)
 
 
@@ -1186,7 +1198,7 @@ def test_channels_last_register_kernel_needs_rows_that_fit_a_wave():
     layers = [wl.avgpool(3, 1, 1, True), wl.maxpool(3, 2, 1)]
     for w, want in ((64, True), (65, False)):
         shape = (1, 8, 5, w)
-        info = _check_nhwc(layers, wl.activation(shape, 192, "bf16"), [], "bf16", f"rows/width{w}")
+        info = _check_nhwc(layers, wl.activation(shape, 192, "bf16"), [], "bf16", f"rows/width{w}", tile_rows=2)
         assert ("nhwc_rows" in [q["variant_name"] for q in info["sequences"]]) == want
 
 
@@ -1243,6 +1255,8 @@ def test_channels_last_channel_slices(shape, dtype):
               "head": [wl.bn_params(c, 165), wl.relu(), wl.avgpool((h, w), (h, w), 0)],
               "two_pools": [wl.bn_params(c, 166), wl.relu(), wl.avgpool(3, 1, 1), wl.maxpool(3, 2, 1, True), wl.relu()],
               # without the index output: the register kernel with 16-bit storage
+              "two_pools_as_strips": [wl.bn_params(c, 166), wl.relu(), wl.avgpool(3, 1, 1, True), wl.maxpool(3, 2, 1),
+                                      wl.bn_params(c, 159), wl.relu()],
               "two_pools_in_registers": [wl.bn_params(c, 166), wl.relu(), wl.avgpool(3, 1, 1, True), wl.maxpool(3, 2, 1),
                                          wl.bn_params(c, 159), wl.relu()]}
     for name, layers in stacks.items():
@@ -1250,7 +1264,10 @@ def test_channels_last_channel_slices(shape, dtype):
         x = wl.activation(shape, 167, dtype)
         res = [wl.activation(sh, 168 + i, dtype) for i, sh in enumerate(wl.residual_shapes(layers, shape))]
         ref, ref_idx, _ = bf.run_stack(layers, x, res, dtype)
-        st = bs.Stack(layers, shape, dtype).plan(layout=bs.BS_LAYOUT_NHWC)
+        # (a tile size rules strips out)
+        st = bs.Stack(layers, shape, dtype).plan(layout=bs.BS_LAYOUT_NHWC, **(dict(tile_rows=3) if name == "two_pools_in_registers" else {}))
+        if name in ("stem", "avg3s1", "two_pools_as_strips"):
+            assert [q["variant_name"] for q in st.info()["sequences"]] == ["strips"]
         if name == "two_pools_in_registers" and dtype != "f32":
             assert [q["variant_name"] for q in st.info()["sequences"]] == ["nhwc_rows"]
         big_in = torch.full((n, c + 16, h, w), float("nan"), dtype=td, device="cuda").contiguous(memory_format=cl)

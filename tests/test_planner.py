@@ -281,7 +281,9 @@ def test_channels_last_plans_take_one_or_two_steps_per_sequence():
             info = st.info()
             assert info["n_sequences"] == info["n_steps"]
             names = [q["variant_name"] for q in info["sequences"]]
-            assert names == (["nhwc_pool"] * pools if pools else ["nhwc_stream"])
+            # 3 x 3 steps with stride 1 run as strips
+            alone = ["strips" if l["k"] == (3, 3) and l["s"] == (1, 1) else "nhwc_pool" for l in layers if l["kind"] in ("maxpool", "avgpool")]
+            assert names == (alone if pools else ["nhwc_stream"])
             assert (info["workspace_bytes"] > 0) == (pools > 1)
             for q in info["sequences"]:
                 assert q["run_time_build"] == 0 and q["lds_bytes"] == 0 and q["grid"] >= 1
@@ -289,10 +291,20 @@ def test_channels_last_plans_take_one_or_two_steps_per_sequence():
             st = bs.Stack(layers, shape, dtype).plan(host_only=1, layout=bs.BS_LAYOUT_NHWC)
             info = st.info()
             names = [q["variant_name"] for q in info["sequences"]]
-            # halo_stress (3 x 3 / 1 average, 3 x 3 / 2 maximum, 56 pixels per row) takes the register kernel with 16-bit storage
-            two = "nhwc_tile" if dtype == "f32" else "nhwc_rows"
-            assert names == ([two] if pools == 2 else ["nhwc_pool"] * pools if pools else ["nhwc_stream"])
+            assert names == (["strips"] if pools == 2 else ["nhwc_pool"] * pools if pools else ["nhwc_stream"])
             assert info["workspace_bytes"] == 0
+            if pools == 2:
+                # halo_stress as strips of 4 output columns and 28 or 14 output rows: what is launched
+                q = info["sequences"][0]
+                chunks = min(7 * 1024 * 64 // (shape[0] * 7 * shape[1]), 14)
+                assert (q["lds_bytes"], q["threads_per_group"], q["tile_rows"], q["tile_cols"]) == (0, 256, -(-28 // chunks), 4)
+                assert q["grid"] == -(-shape[0] * 7 * shape[1] * chunks // 256) and q["n_steps"] == 2 and 1.0 < q["redundancy"] < 2.5
+                # a tile size rules strips out: the pair (3 x 3 / 1 average, 3 x 3 / 2 maximum, 56 pixels per row) takes the register
+                # kernel with 16-bit storage
+                st.close()
+                st = bs.Stack(layers, shape, dtype).plan(host_only=1, layout=bs.BS_LAYOUT_NHWC, tile_cols=64)
+                info = st.info()
+                assert [q["variant_name"] for q in info["sequences"]] == ["nhwc_tile" if dtype == "f32" else "nhwc_rows"]
             for q in info["sequences"]:
                 if q["variant_name"] == "nhwc_rows":
                     assert q["lds_bytes"] == 0 and q["threads_per_group"] == 64 * 4 and q["tile_rows"] == 7
@@ -326,10 +338,10 @@ def test_channels_last_plans_take_one_or_two_steps_per_sequence():
     # pairs are taken from the front; windows outside the tile kernel's table, first pools with
     # an index output and channel counts that give no 128-bit vectors stay one step per sequence
     three = [wl.maxpool(3, 2, 1), wl.relu(), wl.avgpool(2, 2, 0), wl.maxpool(3, 1, 1, True)]
-    for layers, shape, want in ((three, (1, 8, 32, 32), ["nhwc_tile", "nhwc_pool"]),
-                                ([wl.maxpool(5, 1, 2), wl.avgpool(3, 1, 1)], (1, 8, 16, 16), ["nhwc_pool"] * 2),
-                                ([wl.maxpool(3, 1, 1, True), wl.avgpool(3, 1, 1)], (1, 8, 16, 16), ["nhwc_pool"] * 2),
-                                ([wl.maxpool(3, 1, 1), wl.avgpool(3, 1, 1)], (1, 6, 16, 16), ["nhwc_pool"] * 2),
+    for layers, shape, want in ((three, (1, 8, 32, 32), ["nhwc_tile", "strips"]),
+                                ([wl.maxpool(5, 1, 2), wl.avgpool(3, 1, 1)], (1, 8, 16, 16), ["nhwc_pool", "strips"]),
+                                ([wl.maxpool(3, 1, 1, True), wl.avgpool(3, 1, 1)], (1, 8, 16, 16), ["strips"] * 2),
+                                ([wl.maxpool(3, 1, 1), wl.avgpool(3, 1, 1)], (1, 6, 16, 16), ["strips"] * 2),
                                 ([wl.maxpool(3, 1, 1), wl.maxpool(3, 1, 1, True)], (1, 8, 16, 16), ["nhwc_tile"])):
         st = bs.Stack(layers, shape, "f32").plan(host_only=1, layout=bs.BS_LAYOUT_NHWC)
         assert [q["variant_name"] for q in st.info()["sequences"]] == want
