@@ -22,26 +22,31 @@ namespace bs {
 namespace {
 
 // OFF: the type of byte offsets -- uint32_t where every tensor of the launch ends below 4 GiB (one address addition per access:
-// the base stays in scalar registers), else uint64_t.  One element at byte offset `off`, as it lies in memory.
+// the base stays in scalar registers), else uint64_t.  Byte offset `off` of n elements, checked in audit builds.
+template <int DT, typename OFF>
+BS_DEV OFF audited_bytes(const BwdK &k, int which, int site, OFF off, uint32_t n)
+{
+#if defined(BS_BWD_AUDIT)
+    return audited<OFF>(k, which, site, off / elem_bytes<DT>(), n) * elem_bytes<DT>();
+#else
+    return off;
+#endif
+}
+
+// One element at byte offset `off`, as it lies in memory.
 template <int DT, typename OFF>
 BS_DEV uint32_t load_at(const BwdK &k, int which, int site, const void *base, OFF off)
 {
-#if defined(BS_BWD_AUDIT)
-    if constexpr (sizeof(OFF) == 4) off = audited(k, which, site, off / elem_bytes<DT>(), 1) * elem_bytes<DT>();
-#endif
     uint32_t w[1];
-    load_run<DT, 1>(static_cast<const char *>(base) + off, w);
+    load_run<DT, 1>(static_cast<const char *>(base) + audited_bytes<DT, OFF>(k, which, site, off, 1), w);
     return w[0];
 }
 
 template <int DT, typename OFF>
 BS_DEV void store_at(const BwdK &k, int site, void *base, OFF off, float v)
 {
-#if defined(BS_BWD_AUDIT)
-    if constexpr (sizeof(OFF) == 4) off = audited(k, 2, site, off / elem_bytes<DT>(), 1) * elem_bytes<DT>();
-#endif
     const float t[1] = {v};
-    store_elems<DT, 1>(static_cast<char *>(base) + off, 0, t);
+    store_elems<DT, 1>(static_cast<char *>(base) + audited_bytes<DT, OFF>(k, 2, site, off, 1), 0, t);
 }
 
 // Words that hold N columns of a row: channels-last one per column, row-major the run as it lies in memory.
@@ -61,7 +66,7 @@ BS_DEV void load_row(const BwdK &k, int which, int site, const void *base, OFF r
     } else {
         const OFF from = row + (OFF)first * (OFF)elem_bytes<DT>();
         if (fits && from <= last) {
-            load_run<DT, N>(static_cast<const char *>(base) + from, w);
+            load_run<DT, N>(static_cast<const char *>(base) + audited_bytes<DT, OFF>(k, which, site, from, N), w);
         } else {
 #pragma unroll
             for (int j = 0; j < N; ++j) {
@@ -84,7 +89,7 @@ template <int DT, bool CL, int N, typename OFF>
 BS_DEV void store_row(const BwdK &k, int site, OFF at, int32_t first, int32_t width, OFF pitch, bool whole, const float (&v)[N])
 {
     if (!CL && whole) {
-        store_run<DT, N>(static_cast<char *>(k.g_in) + at, v);
+        store_run<DT, N>(static_cast<char *>(k.g_in) + audited_bytes<DT, OFF>(k, 2, site, at, N), v);
     } else if (whole) {
 #pragma unroll
         for (int j = 0; j < N; ++j) store_at<DT, OFF>(k, site, k.g_in, at + (OFF)j * pitch, v[j]);

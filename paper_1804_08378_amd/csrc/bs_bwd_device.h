@@ -5,21 +5,23 @@
 
 namespace bs {
 
-// Build with -DBS_BWD_AUDIT to check every element offset into the stage input, the upstream gradient and the
-// input gradient against the extents the host passes (k.audit_lim[0..2], in elements) before it is used: an
-// offset outside is counted in k.audit[site] and replaced by 0, so such a build cannot read or write outside
-// those tensors.  Without the macro the checks compile to nothing.
+// Build with -DBS_BWD_AUDIT to check every element offset (32 or 64 bits) into the stage input, the upstream gradient and the
+// input gradient, with the number of elements read or written there, against the extents the host passes (k.audit_lim[0..2],
+// in elements) before it is used: an offset outside is counted in k.audit[site] and replaced by 0, so such a build cannot
+// read or write outside those tensors.  Without the macro the checks compile to nothing.
 #if defined(BS_BWD_AUDIT)
-BS_DEV uint32_t audited(const BwdK &k, int which, int site, uint32_t off, uint32_t n)
+template <typename OFF>
+BS_DEV OFF audited(const BwdK &k, int which, int site, OFF off, uint32_t n)
 {
-    if (k.audit && (uint64_t)off + n > k.audit_lim[which]) {
+    if (k.audit && (off > k.audit_lim[which] || (uint64_t)off + n > k.audit_lim[which])) {
         atomicAdd(&k.audit[site], 1u);
         return 0u;
     }
     return off;
 }
 #else
-BS_DEV uint32_t audited(const BwdK &, int, int, uint32_t off, uint32_t) { return off; }
+template <typename OFF>
+BS_DEV OFF audited(const BwdK &, int, int, OFF off, uint32_t) { return off; }
 #endif
 
 // float32 reciprocal of the divisor of the average pooling window (oh, ow): the forward

@@ -58,3 +58,18 @@ def test_selects_wait_for_the_compares_that_write_their_masks(source, tmp_path):
             short.append((states, line))
     print(f"{source}: {pairs} compare-select pairs")
     assert not short, (len(short), short[:5])
+
+
+def test_audit_builds_check_every_access_of_the_backward_strip_kernels():
+    """bs_bwd_device.h says that a build with -DBS_BWD_AUDIT checks every offset into the three tensors: each load and store of the
+    strip kernels passes its offset through the check, runs of elements with their length, and such a build compiles."""
+    text = open(os.path.join(build.CSRC, "bs_backward_strip.hip")).read()
+    accesses = re.findall(r"^.*\b(?:load_run|store_run|store_elems)<.*$", text, re.M)
+    assert len(accesses) >= 4
+    for line in accesses:
+        assert "audited_bytes<" in line, line.strip()
+    helpers = open(os.path.join(build.CSRC, "bs_bwd_device.h")).read()
+    assert "uint64_t)off + n" in helpers and "template <typename OFF>\nBS_DEV OFF audited" in helpers  # 64-bit offsets, too
+    # nothing else in the file reads or writes through a pointer of the argument block (k.params: the parameter table)
+    code = re.sub(r"//.*", "", text)
+    assert not re.search(r"k\.(?:a|g_out|g_in)\s*\[|\*\s*k\.(?:a|g_out|g_in)\b", code)
