@@ -366,8 +366,7 @@ extern "C" bs_status bs_stack_plan_backward(bs_stack *stack)
                 g.g_off = off;
                 off += align256(numel(g.in_shape) * es);
             }
-            // (row-major strips find the picks themselves; the room for them stays in the size, which callers may have fixed)
-            if (is_max || (g.k.strips && !nhwc && g.k.wave_rows == 1)) {
+            if (is_max) {
                 g.idx_off = off;
                 off += align256(numel(g.out_shape) * 4);
             }

@@ -213,6 +213,18 @@ def test_backward_stages_and_workspace():
     assert _backward_plan([wl.add()] * 5, shape)[0] == 2
 
 
+def test_backward_strips_need_no_workspace():
+    """Overlapping 3 x 3 max windows that run as strips of columns (rows that are no whole vectors, windows without padding,
+    channels-last) find their picks themselves: no room for them, alone or behind an average."""
+    c = 8
+    for layers in ([wl.bn_params(c, 0), wl.relu(), wl.maxpool(3, 2, 1)], [wl.maxpool(3, 1, 0), wl.leaky_relu(0.1)], [wl.maxpool(3, 2, 1, True)],
+                   [wl.avgpool(3, 1, 1), wl.maxpool(3, 2, 1)]):
+        for dtype in ("f32", "bf16"):
+            assert _backward_plan(layers, (2, c, 15, 15), dtype) == (1, 0)
+            assert _backward_plan(layers, (2, c, 15, 15), dtype, layout=bs.BS_LAYOUT_NHWC) == (1, 0)
+    assert _backward_plan([wl.maxpool(3, 2, 0)], (2, c, 16, 16)) == (1, 0)
+
+
 def test_index_outputs_may_share_bytes_with_nothing():
     """Index outputs are written by the kernels like the output itself: one that overlaps the
     input, the output, a residual operand, the workspace or another index output is refused
