@@ -86,7 +86,9 @@ bool walks_rows(const bs_stack *s, const BwdStage &g)
 // count) or row-major where the rows are no whole vectors or the windows not padded: the kernel whose lanes walk strips of
 // columns finds the picks itself.  Measured on MI355X against the kernel that gathers recorded picks: channels-last, the caller's
 // picks at hand, ResNet stem bfloat16 87 -> 60 us, 192 x 71 x 71 / 2 without padding binary16 55 -> 39 us; row-major, with the
-// forward pass for the picks, 64 x 64 x 111 x 111 / 2 float32 385 -> 137 us.  (With Adds in the stage the strips would keep every residual's factors in registers.)
+// forward pass for the picks, 64 x 64 x 111 x 111 / 2 float32 385 -> 137 us.  (With Adds in the stage the strips would keep every
+// residual's factors in registers.)  Row-major padded windows on rows of whole vectors stay with walks_rows; those it does not take (rows
+// wider than a wave, ceil-mode sizes) gather, strips were not measured there.
 bool walks_strips(const bs_stack *s, const BwdStage &g)
 {
     const PoolK &p = g.k.pool;

@@ -321,7 +321,7 @@ BS_DEV void scatter(const int32_t (&pick)[N * V], const float (&g)[N * V], float
 // the S rows no later window reaches.  A cell sums its windows in row-major window order.
 // PRE, POST: codes of the lists, or -1 (small stages with such lists gather kept picks instead: bs_backward.cpp).
 // Measured on MI355X, us of a call with the caller's picks at hand, gathering kernel -> this one: ResNet stem 64 x 64 x 112 x 112
-// float32 105 -> 98 (4.7 TB/s of input, gradients in and out: waits for memory), bfloat16 87 -> 60 (vector instructions: 34
+// float32 105 -> 98 (4.7 TB/s of input, gradients in and out: waits for memory), bfloat16 87 -> 60 (vector instructions: 36
 // per cell, 70 % of the time); 32 x 192 x 71 x 71 / 2 without padding binary16 55 -> 39; without kept picks the gathering
 // kernel needs a forward pass on top.  Row-major rows that are no whole vectors, with the forward pass for the picks -> this
 // kernel: 64 x 64 x 111 x 111 / 2 float32 385 -> 137, bfloat16 472 -> 72; 32 x 64 x 147 x 147 / 2 without padding binary16

@@ -343,7 +343,7 @@ constexpr int K_BWD_MAXROWS_RC = BS_MAXROWS_RC;
 constexpr int K_BWD_ROWS2_RC = BS_ROWS2_RC;
 // Backward kernels that walk strips of columns (bs_backward_strip.hip): columns per strip of the one- and the
 // two-level kernel.  Measured on MI355X (us), ResNet stem bfloat16 / float32: 4 columns 60 / 98, 8 columns 58 / 97 (half the
-// waves for small planes); halo_stress float32 / bfloat16: 4 columns 115 / 117, 8 columns (two waves per SIMD) 109 / 116.
+// waves for small planes); halo_stress float32 / bfloat16: 4 columns 115 / 117, 8 columns (two waves per SIMD) 109 / 116 (with the compare steps' wait states 114 / 121).
 constexpr int K_BWD_STRIP_Q = 4;
 // ... two-level, row-major float32: 4, 16 bytes of own columns per lane, so that a wave's load has no gaps; 4 as well where the lists or
 // the divisors are not compiled in (registers)

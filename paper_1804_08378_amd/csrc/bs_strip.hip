@@ -12,10 +12,10 @@
 // +0, the first maximum wins.  Where no index is asked for, an average in front of a maximum is rounded behind it (rounding
 // never decreases, so it commutes with the maximum).
 //
-// What bounds it on MI355X: halo_stress float32 53 us = 4.9 TB/s of input and output (memory, with vector instructions close
-// behind), bfloat16 42 us = 3.1 TB/s (vector instructions: conversions and the nine additions per average and its halo); one
-// step with indices 4.9 TB/s (ResNet stem bfloat16, 37 us).  Row-major 32 x 64 x 147 x 147 / 2 binary16: 28 us = 3.9 TB/s (one wave's
-// rows at a time in flight).  The kernels it takes over from: bs_plan.cpp has both sides.
+// What bounds it on MI355X (back to back; single launches take 3 to 7 us more): halo_stress float32 53 us = 4.9 TB/s of input and output
+// (memory, with vector instructions close behind), bfloat16 38 us = 3.4 TB/s (vector instructions, 27 per cell: conversions and the
+// nine additions per average and its halo); one step with indices 4.9 TB/s (ResNet stem bfloat16, 37 us).  Row-major 32 x 64 x 147 x 147
+// / 2 binary16: 28 us = 3.9 TB/s (one wave's rows at a time in flight).  The kernels it takes over from: bs_plan.cpp has both sides.
 #include <algorithm>
 
 #include "bs_nhwc_device.h"
