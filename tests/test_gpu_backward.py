@@ -534,9 +534,14 @@ def test_single_stage_stacks_need_no_workspace_and_max_pooling_does():
     st = bs.Stack([wl.bn_params(8, 1), wl.relu(), wl.maxpool(3, 2, 1)], (2, 8, 8, 8), "f32").plan().plan_backward()
     assert bs.bs_stack_backward_num_stages(st.handle) == 1 and bs.bs_stack_backward_workspace_bytes(st.handle) == 0
     st.close()
-    # ... and with recorded picks where that kernel does not apply or is switched off
+    # ... on other rows as well, as strips of columns
+    st = bs.Stack([wl.bn_params(8, 1), wl.relu(), wl.maxpool(3, 2, 1)], (2, 8, 8, 10), "f32").plan().plan_backward()
+    assert bs.bs_stack_backward_num_stages(st.handle) == 1 and bs.bs_stack_backward_workspace_bytes(st.handle) == 0
+    st.close()
+    # ... and with recorded picks where those kernels do not apply or are switched off
     for layers, shape, opts in (([wl.bn_params(8, 1), wl.relu(), wl.maxpool(3, 2, 1)], (2, 8, 8, 8), dict(lane_exchange=-1)),
-                                ([wl.bn_params(8, 1), wl.relu(), wl.maxpool(3, 2, 1)], (2, 8, 8, 10), {}),
+                                ([wl.bn_params(8, 1), wl.relu(), wl.maxpool(3, 2, 1)], (2, 8, 8, 10), dict(lane_exchange=-1)),
+                                ([wl.bn_params(8, 1), wl.add(), wl.relu(), wl.maxpool(3, 2, 1)], (2, 8, 8, 10), {}),
                                 ([wl.bn_params(8, 1), wl.relu(), wl.maxpool(5, 2, 2)], (2, 8, 8, 8), {})):
         st = bs.Stack(layers, shape, "f32").plan(**opts).plan_backward()
         out = wl.output_shape(layers, shape)
