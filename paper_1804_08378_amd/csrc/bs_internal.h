@@ -52,6 +52,7 @@ struct Sequence {
     PoolRowsK rows{};
     PoolRows2K rows2{};
     RowsChainK chain{};
+    ChainK blocks{};          // n_levels > 0: the chain as blocks of 3 x 3 maximum, BatchNorm, ReLU
     LdsSeqK lds{};
     NhwcK nhwc{};
     NhwcTile2K nhwc2{};
@@ -212,12 +213,15 @@ bool xrows_launchable(const PoolRowsK &k, int32_t dtype, int64_t grid, int32_t t
 bool xrows2_launchable(const PoolRows2K &k, int32_t dtype, int64_t grid, int32_t threads);
 bs_status launch_xrows(const PoolRowsK &k, int32_t dtype, int64_t grid, int32_t threads, void *stream);
 bs_status launch_xrows2(const PoolRows2K &k, int32_t dtype, int64_t grid, int32_t threads, void *stream);
-// the chain kernel: is there an instance for this pooling shape, list and depth / launch it
-bool xrows_chain_supported(const RowsChainK &k, int32_t dtype);
+// blocks of 3 x 3 maximum, BatchNorm, ReLU (pool_chain_kernel): compiled in (else a run-time build) / launch it
+bool blocks_compiled(int32_t dtype);
+bool blocks_launchable(const ChainK &k, int64_t planes, int64_t grid, int32_t threads);
+std::string blocks_expr(const ChainK &k, int32_t dtype);
+bs_status launch_blocks(const ChainK &k, int32_t dtype, int64_t grid, int32_t threads, void *stream);
+// the chain kernel for other lists and windows (always a run-time build)
 bool xrows_chain_buildable(const RowsChainK &k, int32_t vec);
 bool xrows_chain_launchable(const RowsChainK &k, int32_t dtype, int64_t grid, int32_t threads);
 std::string xrows_chain_expr(const RowsChainK &k, int32_t dtype);
-bs_status launch_xrows_chain(const RowsChainK &k, int32_t dtype, int64_t grid, int32_t threads, void *stream);
 // bs_lds.hip
 bool lds_fast_path(const LdsSeqK &k);
 bool lds_precompiled(const LdsSeqK &k, int32_t dtype);

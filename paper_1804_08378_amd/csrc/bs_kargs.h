@@ -242,6 +242,24 @@ struct RowsChainK {
     FastDiv div_cbs, div_chunks, div_c;
 };
 
+// The same chain with 3 x 3 windows and BatchNorm, ReLU behind each of them (pool_chain_kernel).  A lane owns two columns; a segment is
+// a plane or, of planes too wide for a wave, a column tile of it with halo_w columns on each inner side.
+constexpr int K_BLOCKS_MAX = 10;
+struct ChainK {
+    const void *in;
+    void *out;
+    const float *params;
+    uint32_t in_extra, out_extra;  // as above
+    int32_t n_levels;
+    int32_t bn[K_BLOCKS_MAX];      // offsets of the levels' parameters
+    int32_t C, H, W;
+    int32_t rc, chunks;            // output rows of a wave, chunks per plane
+    int32_t tile_w, tiles, halo_w; // columns a segment writes, segments per plane
+    int32_t pitch, spw;            // lanes from one segment of a wave to the next (the last one stays idle), segments per wave
+    uint32_t units;                // segments = planes * tiles
+    FastDiv div_chunks, div_pitch, div_tiles, div_c;
+};
+
 // Channels-last (N, H, W, C in memory) sequences: element-wise only (pool.kind == 0, the list
 // in `pre`) or one pooling operation with element-wise operations before and after it.
 struct NhwcK {

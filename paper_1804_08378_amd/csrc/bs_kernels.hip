@@ -707,11 +707,20 @@ bs_status launch_sequence(const bs_stack *s, const Sequence &q, const void *in, 
         break;
     }
     case BS_VARIANT_ROWS_CHAIN: {
+        if (q.blocks.n_levels > 0) {
+            ChainK k = q.blocks;
+            k.in = in; k.out = out; k.params = s->dev_params;
+            k.in_extra = in_extra; k.out_extra = out_extra;
+            if (!blocks_launchable(k, q.in_shape[0] * q.in_shape[1], q.grid, q.threads)) return BS_ERR_UNSUPPORTED;
+            const bs_status ls = q.jit ? launch_built(q, false, &k, sizeof k, stream) : launch_blocks(k, dtype, q.grid, q.threads, stream);
+            if (ls != BS_OK) return ls;
+            break;
+        }
         RowsChainK k = q.chain;
         k.in = in; k.out = out; k.params = s->dev_params;
         k.in_extra = in_extra; k.out_extra = out_extra;
-        if (!xrows_chain_launchable(k, dtype, q.grid, q.threads)) return BS_ERR_UNSUPPORTED;
-        const bs_status ls = q.jit ? launch_built(q, false, &k, sizeof k, stream) : launch_xrows_chain(k, dtype, q.grid, q.threads, stream);
+        if (!q.jit || !xrows_chain_launchable(k, dtype, q.grid, q.threads)) return BS_ERR_UNSUPPORTED;
+        const bs_status ls = launch_built(q, false, &k, sizeof k, stream);
         if (ls != BS_OK) return ls;
         break;
     }

@@ -261,6 +261,7 @@ static void min_tile(int32_t hl, int32_t wl, int32_t threads, int32_t &th, int32
     th = std::min(hl, std::max(1, threads / tw));
 }
 
+static bool chain_applicable(const bs_stack *s, int32_t first_op, int32_t n_ops, Sequence *fill);
 static bool seq_capacity_ok(const bs_stack *s, int32_t first_op, int32_t n_ops, bool allow_stream)
 {
     int32_t pools = 0, ew_level = 0, ew_total = 0, res = 0, idx = 0;
@@ -283,7 +284,8 @@ static bool seq_capacity_ok(const bs_stack *s, int32_t first_op, int32_t n_ops, 
         }
         if (pools > 0 && ew_level > K_MAX_EW) return false;
     }
-    if (pools > K_MAX_LEVELS || res > K_MAX_RES || idx > K_MAX_IDX) return false;
+    if (pools > K_MAX_LEVELS && !chain_applicable(s, first_op, n_ops, nullptr)) return false;
+    if (res > K_MAX_RES || idx > K_MAX_IDX) return false;
     if (pools == 0) return allow_stream && ew_total <= K_MAX_STREAM_EW;
     // level-0 element-wise operations
     int32_t ew0 = 0;
@@ -335,9 +337,8 @@ static bool direct_applicable(const bs_stack *s, int32_t first_op, int32_t n_ops
 // smallest useful tile, including the overlap that padding / k > s adds at every level.
 static bool rows_applicable(const bs_stack *s, int32_t first_op, int32_t n_ops, Sequence *fill);
 static bool plane_applicable(const bs_stack *s, int32_t first_op, int32_t n_ops);
-static bool chain_applicable(const bs_stack *s, int32_t first_op, int32_t n_ops, Sequence *fill);
-// Fewest identical pooling blocks the chain kernel is used for.  Measured on 64 x 64 x 56 x 56, float32: one block 25 us
-// (one-level sliding-window kernel: 22 us), two blocks 25 us (two-level kernel: 34 us), three 26 us, four 27 us.
+// Fewest identical pooling blocks the chain kernels are used for.  Measured on 64 x 64 x 56 x 56, float32: one block 25 us
+// (one-level sliding-window kernel: 22 us), two blocks 26 us (two-level kernel: 34 us), four 27 us.
 #if !defined(BS_CHAIN_MIN)
 #define BS_CHAIN_MIN 2
 #endif
@@ -1084,14 +1085,16 @@ static void plan_exchange(Sequence &q, K &k, int64_t planes, int32_t rc, int32_t
 
 // Two and more identical max-pooling steps that keep the plane's size (odd window, stride 1, padding (k - 1) / 2,
 // no index output), each followed by element-wise operations of the same kinds (no Add), nothing in front of the
-// first: the blocks of Section 5.1.  The chain kernel exists for the shapes and lists compiled into the library, on
-// planes whose rows fit one wave; anything else takes the LDS tiles.
+// first: the blocks of Section 5.1.  3 x 3 windows with BatchNorm, ReLU behind each: pool_chain_kernel, up to ten levels and any width.
+// Other windows and lists: run-time builds of pool_xrows_chain_kernel on planes whose rows fit one wave; anything else takes the LDS tiles.
 static bool chain_applicable(const bs_stack *s, int32_t first_op, int32_t n_ops, Sequence *fill)
 {
     if (s->opts.layout == BS_LAYOUT_NHWC || s->opts.force_variant == BS_VARIANT_LDS_TILE) return false;
     Sequence tmp;
     Sequence &q = fill ? *fill : tmp;
     RowsChainK k{};
+    ChainK b{};
+    bool blocks = true;  // every level: 3 x 3 maximum, BatchNorm, ReLU
     int32_t level = -1, n_here = 0;
     for (int32_t i = first_op; i < first_op + n_ops; ++i) {
         const Op &op = s->ops[i];
@@ -1100,7 +1103,8 @@ static bool chain_applicable(const bs_stack *s, int32_t first_op, int32_t n_ops,
                 op.kw != 2 * op.pw + 1 || op.out_h != op.in_h || op.out_w != op.in_w)
                 return false;
             if (level >= 0 && n_here != k.n_ew) return false;  // every level has the same list length
-            if (++level >= K_CHAIN_MAX) return false;
+            if (++level >= K_BLOCKS_MAX) return false;
+            blocks = blocks && op.kh == 3 && op.kw == 3;
             const PoolK p = make_pool(op, nullptr, q);
             if (level == 0) {
                 k.pool = p;
@@ -1112,8 +1116,12 @@ static bool chain_applicable(const bs_stack *s, int32_t first_op, int32_t n_ops,
             n_here = 0;
         } else if (op.kind != OP_AVGNORM) {
             if (level < 0 || op.kind == OP_ADD || n_here >= K_MAX_EW) return false;
-            fill_ew(s, op, q, k.ew[level][n_here]);
-            if (level > 0 && k.ew[level][n_here].kind != k.ew[0][n_here].kind) return false;
+            EwOp e{};
+            fill_ew(s, op, q, e);
+            if (level == 0) k.ew[0][n_here] = e;
+            if (e.kind != k.ew[0][n_here].kind) return false;
+            if (level < K_CHAIN_MAX) k.ew[level][n_here] = e;
+            if (e.kind == OP_BN) b.bn[level] = e.arg;
             ++n_here;
             if (level == 0) k.n_ew = n_here;
         }
@@ -1121,19 +1129,102 @@ static bool chain_applicable(const bs_stack *s, int32_t first_op, int32_t n_ops,
     if (level < BS_CHAIN_MIN - 1 || n_here != k.n_ew) return false;
     k.n_levels = level + 1;
     const int32_t vec = xrows_vec(s->dtype);
+    blocks = blocks && k.n_ew == 2 && k.ew[0][0].kind == OP_BN && k.ew[0][1].kind == OP_RELU;
+    // Any width from two columns up to what a wave's 128-bit vectors cover (wider rows: not measured).  Against the kernel for other lists (rows of
+    // whole vectors) and the LDS tiles (other rows), us: 64 x 64 x 56 x 56 float32, two / ten levels 26.8 / 65 -> 26.3 / 33.5; 55 columns 52 / 153
+    // -> 30 / 38; 1 x 32 x 224 x 224 bfloat16 43 / 186 -> 6.3 / 14.3; 35 x 72 x 13 x 13 11.3 / 42 -> 4.4 / 10.7.
+    if (blocks && s->opts.lane_exchange >= 0 && k.W >= 2 && k.W <= 64 * vec && (blocks_compiled(s->dtype) || jit_allowed(s))) {
+        b.n_levels = k.n_levels;
+        b.H = k.H;
+        b.W = k.W;
+        if (fill) fill->blocks = b;
+        return true;
+    }
+    if (k.n_levels > K_CHAIN_MAX) return false;
     if (!exchange_fits(s, k.W, vec)) return false;
-    if (!xrows_chain_supported(k, s->dtype) && !(jit_allowed(s) && xrows_chain_buildable(k, vec))) return false;
+    if (!jit_allowed(s) || !xrows_chain_buildable(k, vec)) return false;
     k.cbs = k.W / vec;
     k.spw = 64 / k.cbs;
     if (fill) fill->chain = k;
     return true;
 }
 
-static void plan_chain(const bs_stack *s, Sequence &q, const bs_plan_options &o)
+// Columns, lanes, chunks and grid of pool_chain_kernel.
+static void plan_blocks(const bs_stack *s, Sequence &q, const bs_plan_options &o, const Limits &lim)
+{
+    ChainK &k = q.blocks;
+    const int64_t planes = q.in_shape[0] * q.in_shape[1];
+    const int32_t L = k.n_levels;
+    k.C = (int32_t)q.in_shape[1];
+    q.vec = 2;
+    // A segment is a whole plane, or the fewest column tiles that fit a wave's 64 lanes; inner sides of a tile recompute L columns
+    // (rounded up to whole lanes, so that tiles begin at even columns).
+    k.halo_w = (L + 1) / 2 * 2;
+    int32_t columns = 0;
+    for (k.tiles = 1;; ++k.tiles) {
+        k.tile_w = ((k.W + k.tiles - 1) / k.tiles + 1) / 2 * 2;
+        columns = k.tile_w + k.halo_w * std::min(k.tiles - 1, 2);
+        if (columns <= 128) break;
+    }
+    k.tiles = (k.W + k.tile_w - 1) / k.tile_w;
+    k.pitch = columns / 2 + 1;
+    k.spw = 65 / k.pitch;  // the wave's last segment needs no idle lane behind it
+    k.units = (uint32_t)(planes * k.tiles);
+    // Rows per chunk.  A whole plane recomputes nothing (a chunk walks L rows above and below its own), more chunks give more waves.  Cycles of a
+    // launch: rows walked x (7 L + 12) instructions x cycles per instruction of a wave, which depend on the waves of its SIMD (measured: one
+    // 10, four 18), plus the bytes at 2600 per cycle.  Longer chunks unless shorter ones save 3 %; none below half a plane, or 20 rows, or the
+    // rows they recompute.  Measured (us, float32, rows of the chunks): 64 x 64 x 56 x 56, ten levels 56: 33.9, 28: 38.5; two levels 25.9, 28.0;
+    // 7 x 208 x 128 x 128, ten levels 128: 61, 64: 51, 43: 59, 32: 57; 6 x 86 x 104 x 104, ten levels 104: 35, 35: 24, 26: 26, 13: 32.
+    const int64_t groups = ((int64_t)k.units + k.spw - 1) / k.spw;
+    const double bytes = (double)planes * k.H * k.W * (s->dtype == BS_F32 ? 4 : 2);
+    double best = 0.0;
+    int32_t rc = k.H;
+    for (int32_t chunks = 1; chunks <= k.H; ++chunks) {
+        const int32_t r = (k.H + chunks - 1) / chunks;
+        if (chunks > 1 && r < std::max(2 * L, std::min(20, (k.H + 1) / 2))) break;
+        const int64_t n = (k.H + r - 1) / r, resident = ((groups * n + 3) / 4 + lim.num_cus - 1) / lim.num_cus;
+        const double walked = r + (chunks > 1 ? 2 : 1) * L, again = chunks > 1 ? 2.0 * L / r : 0.0;
+        const double cycles = walked * (7 * L + 12) * (double)std::max<int64_t>(10, 6 + 3 * resident) + bytes * (2.0 + again) / 2600.0;
+        if (chunks == 1 || cycles < 0.97 * best) {
+            best = cycles;
+            rc = r;
+        }
+    }
+    if (o.tile_rows > 0) rc = std::min(o.tile_rows, k.H);
+    k.chunks = (k.H + rc - 1) / rc;
+    k.rc = (k.H + k.chunks - 1) / k.chunks;
+    k.chunks = (k.H + k.rc - 1) / k.rc;
+    k.div_chunks = make_fastdiv((uint32_t)k.chunks);
+    k.div_pitch = make_fastdiv((uint32_t)k.pitch);
+    k.div_tiles = make_fastdiv((uint32_t)k.tiles);
+    k.div_c = make_fastdiv((uint32_t)k.C);
+    q.threads = 256;
+    q.grid = (groups * k.chunks + 3) / 4;
+    q.lds_bytes = 0;
+    q.tile_rows = k.rc;
+    q.tile_cols = k.tile_w;
+    q.planes_per_group = 0;
+    q.n_levels = L;
+    q.halo_rows = 2 * L;
+    q.halo_cols = k.tiles > 1 ? 2 * L : 0;
+    double cells = 0;
+    for (int32_t ch = 0; ch < k.chunks; ++ch)
+        for (int32_t t = 0; t < k.tiles; ++t) {
+            const int32_t a = ch * k.rc, b = std::min(k.H, a + k.rc), c = t * k.tile_w, d = std::min(k.W, c + k.tile_w);
+            cells += (double)(std::min(k.H, b + L) - std::max(0, a - L)) * (std::min(k.W, d + k.halo_w) - std::max(0, c - k.halo_w));
+        }
+    q.redundancy = cells / ((double)k.H * k.W);
+}
+
+static void plan_chain(const bs_stack *s, Sequence &q, const bs_plan_options &o, const Limits &lim)
 {
     q.variant = BS_VARIANT_ROWS_CHAIN;
     q.n_idx = 0;
     chain_applicable(s, q.first_op, q.n_ops, &q);
+    if (q.blocks.n_levels > 0) {
+        plan_blocks(s, q, o, lim);
+        return;
+    }
     RowsChainK &k = q.chain;
     q.vec = xrows_vec(s->dtype);
     k.C = (int32_t)q.in_shape[1];
@@ -1500,6 +1591,10 @@ static bool audit_lds(const Sequence &q)
 static const char *jit_names(const bs_stack *s, const Sequence &q, std::string (&expr)[2])
 {
     if (q.variant == BS_VARIANT_ROWS_CHAIN) {
+        if (q.blocks.n_levels > 0) {
+            expr[0] = expr[1] = blocks_expr(q.blocks, s->dtype);
+            return "bs_chain_device.h";
+        }
         expr[0] = expr[1] = xrows_chain_expr(q.chain, s->dtype);
         return "bs_xrows_device.h";
     }
@@ -1536,8 +1631,11 @@ static bs_status prepare_jit(bs_stack *s, Sequence &q, bool host_only)
         const PoolRowsK &k = q.rows;
         if (tables && rows_supported(k.pool, k.pre, k.n_pre, k.post, k.n_post)) return BS_OK;
     } else if (q.variant == BS_VARIANT_ROWS_CHAIN) {
-        if (q.vec != xrows_vec(s->dtype)) return BS_ERR_UNSUPPORTED;
-        if (xrows_chain_supported(q.chain, s->dtype)) return BS_OK;
+        if (q.blocks.n_levels > 0) {
+            if (blocks_compiled(s->dtype)) return BS_OK;
+        } else if (q.vec != xrows_vec(s->dtype)) {
+            return BS_ERR_UNSUPPORTED;
+        }
     } else if (q.variant == BS_VARIANT_LDS_TILE) {
         if (lds_precompiled(q.lds, s->dtype) || !jit_allowed(s) || !lds_buildable(q.lds)) return BS_OK;
     } else {
@@ -1645,20 +1743,21 @@ bs_status group_sequences(bs_stack *s, const bs_plan_options &o, const Limits &l
         // memory, once a few steps are fused -- measured on MI355X, four to five steps per
         // sequence are fastest.  Cap sequences at K_AUTO_STEPS steps, then even out their
         // lengths (8 steps run as 4 + 4 rather than 5 + 3).
-        // Chains of identical blocks that the register kernel takes are the exception: it has no LDS
-        // traffic and measured fastest with as many levels as it is compiled for (64 x 64 x 56 x 56,
-        // float32: 9.0 / 7.1 / 6.3 / 6.0 / 5.6 us per block with 3 / 4 / 5 / 6 / 8 levels).
+        // Chains of identical blocks that the register kernels take are the exception: they have no LDS
+        // traffic and measured fastest with as many levels as they are built for (pool_chain_kernel, 64 x 64 x 56 x 56,
+        // float32: 13.2 / 6.8 / 4.3 / 3.4 us per block with 2 / 4 / 7 / 10 levels).
         int32_t cap = K_AUTO_STEPS;
         {
             std::vector<SeqDraft> longer;
-            bool all_chains = fill(K_CHAIN_MAX, longer) == BS_OK && !longer.empty();
+            bool all_chains = fill(K_BLOCKS_MAX, longer) == BS_OK && !longer.empty();
             for (const SeqDraft &d : longer) {
                 int32_t fo, no;
                 range_ops(d, fo, no);
                 all_chains = all_chains && (d.n_steps < BS_CHAIN_MIN || chain_applicable(s, fo, no, nullptr));
                 all_chains = all_chains && (d.n_steps >= BS_CHAIN_MIN || longer.size() > 1);
             }
-            if (all_chains) cap = K_CHAIN_MAX;
+            // nine or ten steps are one sequence; longer stacks are cut into sequences of at most eight
+            if (all_chains) cap = longer.size() == 1 ? K_BLOCKS_MAX : K_CHAIN_MAX;
         }
         bs_status fs = fill(cap, drafts);
         if (fs != BS_OK) return fs;
@@ -1697,13 +1796,13 @@ bs_status group_sequences(bs_stack *s, const bs_plan_options &o, const Limits &l
         } else if (direct_applicable(s, q.first_op, q.n_ops) && o.force_variant != BS_VARIANT_LDS_TILE) {
             plan_direct(s, q);
         } else if (BS_CHAIN_MIN < 3 && o.force_variant == BS_VARIANT_AUTO && chain_applicable(s, q.first_op, q.n_ops, nullptr)) {
-            plan_chain(s, q, o);
+            plan_chain(s, q, o, lim);
         } else if (rows_applicable(s, q.first_op, q.n_ops, nullptr) && o.force_variant != BS_VARIANT_LDS_TILE) {
             plan_rows(s, q, o, lim);
         } else if (plane_applicable(s, q.first_op, q.n_ops) && o.force_variant != BS_VARIANT_LDS_TILE) {
             plan_direct(s, q, true);
         } else if (chain_applicable(s, q.first_op, q.n_ops, nullptr)) {
-            plan_chain(s, q, o);
+            plan_chain(s, q, o, lim);
         } else {
             st = plan_lds(s, q, o, lim);
         }

@@ -678,7 +678,8 @@ struct IntTag {
 
 // =============================================================================
 // pool_xrows_chain_kernel: L identical max-pooling steps that keep the plane's size, each followed by
-// the element-wise list EW (the blocks of Section 5.1's stacked-pooling experiment), in registers.
+// the element-wise list EW, in registers (3 x 3 with BatchNorm, ReLU -- the blocks of Section 5.1's experiment -- runs in
+// pool_chain_kernel; this one is built at plan time for any other odd window and list).
 // One new input row per step ripples through all L levels: level l's row h - l * PH needs level
 // l - 1's rows up to h - (l - 1) * PH, the one the same step has just produced.  Per level the lane
 // keeps the KH newest rows of the level below (own columns only: the maximum goes down the window's

@@ -379,6 +379,36 @@ def test_chains_of_identical_pooling_blocks_in_registers(shape, dtype):
         assert all(q["variant_name"] != "rows_chain" for q in info["sequences"])
 
 
+@pytest.mark.parametrize("shape,levels", [((1, 3, 7, 7), 10), ((2, 2, 1, 2), 2), ((1, 2, 3, 3), 9), ((3, 5, 30, 31), 4), ((1, 2, 20, 63), 3),
+                                          ((1, 2, 40, 126), 10), ((1, 2, 33, 127), 5), ((1, 2, 9, 128), 2), ((1, 2, 31, 129), 9),
+                                          ((1, 1, 64, 224), 10), ((2, 1, 12, 255), 6), ((7, 3, 56, 56), 10)])
+@pytest.mark.parametrize("dtype", ["f32", "bf16", "f16"])
+def test_stacked_blocks_of_any_width(shape, levels, dtype):
+    """Blocks <MaxPool 3/1/1, BatchNorm, ReLU> in one sequence on rows of any width: odd rows, rows that fill a wave or go one column
+    beyond it (column tiles), several planes in a wave with some left over, chunks of one row, ragged chunks and whole planes; zeros of
+    both signs, equal cells, infinities of both signs and BatchNorm scales of both signs and zero.  Bit for bit: every operation is
+    exact or rounds once per layer, as in the oracle."""
+    c = shape[1]
+    layers = []
+    for i in range(levels):
+        bn = wl.bn_params(c, 500 + i)
+        bn["gamma"] = bn["gamma"] * np.where(np.arange(c) % 3 == i % 3, -1.0, 1.0).astype(np.float32)
+        if i == 1:
+            bn["gamma"][0] = 0.0
+        layers += [wl.maxpool(3, 1, 1), bn, wl.relu()]
+    x = wl.activation(shape, 75, dtype)
+    x[:, :, ::2, 1::3] = 0.5
+    x[:, :, ::3, ::4] = -np.inf
+    if shape[2] > 8:
+        x[0, -1, 5, 2] = np.inf
+    ref, _, _ = bf.run_stack(layers, x, [], dtype)
+    for rc in (0, 1, 5, 1000):
+        out, _, info = run_gpu(layers, x, [], dtype, tile_rows=rc, max_steps_per_sequence=levels)
+        assert [q["variant_name"] for q in info["sequences"]] == ["rows_chain"], rc
+        same = (out == ref) | (np.isnan(out) & np.isnan(ref))
+        assert same.all(), (rc, np.argwhere(~same)[:4])
+
+
 # ------------------------------------------------------------------ run-time builds
 def _built_stacks(c):
     """Signatures with no instance compiled into the library."""
