@@ -261,18 +261,23 @@ extern "C" bs_status bs_stack_plan_backward(bs_stack *stack)
                 // a lane per channel, strip of columns and chunk of window rows; a chunk holds two window rows at least
                 BwdK &k = g.k;
                 const bool two = k.wave_rows == 2;
-                const int32_t q = two ? bwd_strip2_columns(nhwc, stack->dtype, bwd_strip2_compiled(k)) : K_BWD_STRIP_Q, s = two ? 2 : p.sh;
-                k.strips = 1;
+                const int32_t s = two ? 2 : p.sh;
+                int32_t q = two ? bwd_strip2_columns(nhwc, stack->dtype, bwd_strip2_compiled(k)) : K_BWD_STRIP_Q;
                 k.wave_rows = two ? 2 : 1;
-                g.vec = 1;
+                g.vec = bwd_strip_channels(k, nhwc, stack->dtype);
+                // Two columns per lane where strips of four, in the shortest chunks, would be less than a wave per SIMD.  Measured, us, four / two
+                // columns: 9 x 88 x 42 x 42 bfloat16 channels-last 6.3 / 5.6 (748 waves), float32 6.3 / 5.6; 11 x 104 x 20 x 20 6.0 / 5.0 (224 waves);
+                // 16 x 64 x 56 x 57 bfloat16 7.2 / 7.3 (1680 waves).
+                if (bwd_strip_keys(k) && numel(g.in_shape) / (uint64_t)g.vec / 4 / (2 * s) < 1024 * 64) q = 2;
+                k.strips = q;
                 k.cbs = (k.W + q - 1) / q;
-                const int64_t per_chunk = g.in_shape[0] * k.cbs * k.C, rows = (k.H + s - 1) / s;
+                const int64_t per_chunk = g.in_shape[0] * k.cbs * (k.C / g.vec), rows = (k.H + s - 1) / s;
                 int64_t chunks = two ? (K_BWD_STRIP2_LANES + per_chunk - 1) / per_chunk : K_BWD_STRIP_LANES / per_chunk;
                 chunks = std::max<int64_t>(1, std::min(chunks, (rows + 1) / 2));
                 k.rc = (int32_t)((rows + chunks - 1) / chunks);
                 k.chunks = (int32_t)((rows + k.rc - 1) / k.rc);
                 k.units = 0;
-                k.div_wv = make_fastdiv((uint32_t)k.C);
+                k.div_wv = make_fastdiv((uint32_t)(k.C / g.vec));
                 k.div_cbs = make_fastdiv((uint32_t)k.cbs);
                 k.div_chunks = make_fastdiv((uint32_t)k.chunks);
                 lanes = (uint64_t)per_chunk * (uint64_t)k.chunks;

@@ -14,91 +14,11 @@
 
 #include <algorithm>
 
-#include "bs_bwd_device.h"
-#include "bs_strip_device.h"
+#include "bs_bwd_strip_device.h"
 #include "bs_internal.h"
 
 namespace bs {
 namespace {
-
-// OFF: the type of byte offsets -- uint32_t where every tensor of the launch ends below 4 GiB (one address addition per access:
-// the base stays in scalar registers), else uint64_t.  Byte offset `off` of n elements, checked in audit builds.
-template <int DT, typename OFF>
-BS_DEV OFF audited_bytes(const BwdK &k, int which, int site, OFF off, uint32_t n)
-{
-#if defined(BS_BWD_AUDIT)
-    return audited<OFF>(k, which, site, off / elem_bytes<DT>(), n) * elem_bytes<DT>();
-#else
-    return off;
-#endif
-}
-
-// One element at byte offset `off`, as it lies in memory.
-template <int DT, typename OFF>
-BS_DEV uint32_t load_at(const BwdK &k, int which, int site, const void *base, OFF off)
-{
-    uint32_t w[1];
-    load_run<DT, 1>(static_cast<const char *>(base) + audited_bytes<DT, OFF>(k, which, site, off, 1), w);
-    return w[0];
-}
-
-template <int DT, typename OFF>
-BS_DEV void store_at(const BwdK &k, int site, void *base, OFF off, float v)
-{
-    const float t[1] = {v};
-    store_elems<DT, 1>(static_cast<char *>(base) + audited_bytes<DT, OFF>(k, 2, site, off, 1), 0, t);
-}
-
-// Words that hold N columns of a row: channels-last one per column, row-major the run as it lies in memory.
-template <int DT, bool CL, int N>
-constexpr int row_words() { return CL ? N : run_words<DT, N>(); }
-
-// N columns of a row at byte offset `row`, column j at + col[j] (outside the plane: a safe column, the caller replaces it).
-// Row-major: the run from column `first` is read whole if it begins at `last` at the latest (so that it ends inside the tensor;
-// columns beside the plane are other rows' elements then), else one by one.
-template <int DT, bool CL, int N, typename OFF>
-BS_DEV void load_row(const BwdK &k, int which, int site, const void *base, OFF row, const OFF (&col)[N], int32_t first, bool fits, OFF last,
-                     uint32_t (&w)[row_words<DT, CL, N>()])
-{
-    if constexpr (CL) {
-#pragma unroll
-        for (int j = 0; j < N; ++j) w[j] = load_at<DT, OFF>(k, which, site, base, row + col[j]);
-    } else {
-        const OFF from = row + (OFF)first * (OFF)elem_bytes<DT>();
-        if (fits && from <= last) {
-            load_run<DT, N>(static_cast<const char *>(base) + audited_bytes<DT, OFF>(k, which, site, from, N), w);
-        } else {
-#pragma unroll
-            for (int j = 0; j < N; ++j) {
-                const uint32_t e = load_at<DT, OFF>(k, which, site, base, row + col[j]);
-                if constexpr (DT == DT_F32) w[j] = e;
-                else w[j / 2] = j % 2 ? w[j / 2] | e << 16 : e;
-            }
-        }
-    }
-}
-template <int DT, bool CL, int N>
-BS_DEV void unpack_row(const uint32_t (&w)[row_words<DT, CL, N>()], float *v)
-{
-#pragma unroll
-    for (int j = 0; j < N; ++j) v[j] = CL ? run_element<DT>(&w[CL ? j : 0], 0) : run_element<DT>(w, j);
-}
-
-// N columns of a row of the input gradient, `pitch` bytes apart; whole: all of them lie in the plane.
-template <int DT, bool CL, int N, typename OFF>
-BS_DEV void store_row(const BwdK &k, int site, OFF at, int32_t first, int32_t width, OFF pitch, bool whole, const float (&v)[N])
-{
-    if (!CL && whole) {
-        store_run<DT, N>(static_cast<char *>(k.g_in) + audited_bytes<DT, OFF>(k, 2, site, at, N), v);
-    } else if (whole) {
-#pragma unroll
-        for (int j = 0; j < N; ++j) store_at<DT, OFF>(k, site, k.g_in, at + (OFF)j * pitch, v[j]);
-    } else {
-#pragma unroll
-        for (int j = 0; j < N; ++j)
-            if (first + j < width) store_at<DT, OFF>(k, site, k.g_in, at + (OFF)j * pitch, v[j]);
-    }
-}
 
 // at == AT: sum += g
 template <int AT, bool FIRST>
@@ -211,59 +131,6 @@ struct StripList {
 };
 static_assert(K_EW_BASE == 16, "a digit of `kinds` is four bits");
 
-// The lane's place.  Channels-last: (image, chunk, strip, channel), row-major: (image, channel, chunk, strip), the last one fastest.
-struct StripLane {
-    bool live;
-    uint32_t n, plane;
-    int32_t chunk, q0, c0;
-};
-
-template <bool CL, int Q>
-BS_DEV StripLane strip_lane(const BwdK &k)
-{
-    StripLane L;
-    uint32_t i = xcd_contiguous(blockIdx.x, gridDim.x) * 256u + threadIdx.x;
-    L.live = i < k.total;
-    i = L.live ? i : 0u;
-    uint32_t v = i;
-    L.plane = 0;
-    if constexpr (CL) {
-        v = fdiv(i, k.div_wv);
-        L.c0 = (int32_t)(i - v * k.div_wv.d);
-    }
-    const uint32_t u = fdiv(v, k.div_cbs);
-    L.q0 = (int32_t)(v - u * k.div_cbs.d) * Q;
-    const uint32_t p = fdiv(u, k.div_chunks);
-    L.chunk = (int32_t)(u - p * k.div_chunks.d);
-    L.n = p;
-    if constexpr (!CL) {
-        L.plane = p;
-        L.n = fdiv(p, k.div_c);
-        L.c0 = (int32_t)(p - L.n * k.div_c.d);
-    }
-    return L;
-}
-
-// Where the lane's rows begin and how far columns and rows lie apart (bytes).
-template <int DT, bool CL, typename OFF>
-struct StripPlaces {
-    OFF pa, pg, pi, abase, gbase, ibase, arow, grow, irow;
-    BS_DEV StripPlaces(const BwdK &k, const StripLane &L)
-    {
-        constexpr int ES = elem_bytes<DT>();
-        pa = CL ? (OFF)(k.C + k.a_extra) * ES : (OFF)ES;
-        pg = CL ? (OFF)(k.C + k.gout_extra) * ES : (OFF)ES;
-        pi = CL ? (OFF)(k.C + k.gin_extra) * ES : (OFF)ES;
-        const uint32_t in_px = (uint32_t)(k.H * k.W), out_px = (uint32_t)(k.Ho * k.Wo);
-        abase = CL ? (OFF)(L.n * in_px) * pa + (OFF)L.c0 * ES : ((OFF)(L.plane * in_px) + (OFF)L.n * k.a_extra) * ES;
-        gbase = CL ? (OFF)(L.n * out_px) * pg + (OFF)L.c0 * ES : ((OFF)(L.plane * out_px) + (OFF)L.n * k.gout_extra) * ES;
-        ibase = (CL ? (OFF)(L.n * in_px) * pi + (OFF)L.c0 * ES : ((OFF)(L.plane * in_px) + (OFF)L.n * k.gin_extra) * ES) + (OFF)L.q0 * pi;
-        arow = (OFF)k.W * pa;
-        grow = (OFF)k.Wo * pg;
-        irow = (OFF)k.W * pi;
-    }
-};
-
 // The windows' picks from the row maxima of their three rows.  top: the first window row lies above the plane (padding, all
 // -infinity) and must not be picked, not even by a window of nothing but -infinity.
 template <int N, bool BY_MAX>
@@ -319,13 +186,12 @@ BS_DEV void scatter(const int32_t (&pick)[N * V], const float (&g)[N * V], float
 // of its windows in each (a row two window rows share is scanned once), combines three of them into the windows' picks,
 // adds the windows' gradients -- times the trailing list's derivative at the maximum -- to the picked cells and writes
 // the S rows no later window reaches.  A cell sums its windows in row-major window order.
-// PRE, POST: codes of the lists, or -1 (small stages with such lists gather kept picks instead: bs_backward.cpp).
-// Measured on MI355X, us of a call with the caller's picks at hand, gathering kernel -> this one: ResNet stem 64 x 64 x 112 x 112
-// float32 105 -> 98 (4.7 TB/s of input, gradients in and out: waits for memory), bfloat16 87 -> 60 (vector instructions: 36
-// per cell, 70 % of the time); 32 x 192 x 71 x 71 / 2 without padding binary16 55 -> 39; without kept picks the gathering
-// kernel needs a forward pass on top.  Row-major rows that are no whole vectors, with the forward pass for the picks -> this
-// kernel: 64 x 64 x 111 x 111 / 2 float32 385 -> 137, bfloat16 472 -> 72; 32 x 64 x 147 x 147 / 2 without padding binary16
-// 404 -> 62; whole vectors without padding (32 x 64 x 112 x 112 / 2) float32 180 -> 72.
+// PRE, POST: codes of the lists, or -1 (small stages with such lists gather kept picks instead: bs_backward.cpp).  BatchNorm -> ReLU or ReLU
+// alone in front and nothing behind: bwd_keys_kernel.
+// Measured on MI355X with BatchNorm -> ReLU in front (before bwd_keys_kernel took that list over), us of a call with the caller's picks at
+// hand, gathering kernel -> this one: ResNet stem 64 x 64 x 112 x 112 float32 105 -> 98 (waits for memory), bfloat16 87 -> 60 (vector
+// instructions: 36 per cell, 70 % of the time); without kept picks the gathering kernel needs a forward pass on top (row-major 64 x 64 x 111 x
+// 111 / 2 float32 385 -> 145; whole vectors without padding, 32 x 64 x 112 x 112 / 2, 180 -> 72).
 // =============================================================================
 template <int DT, bool CL, int Q, int S, int P, int PRE, int POST, typename OFF>
 __global__ __launch_bounds__(256) void bwd_strip_kernel(const BwdK k)
@@ -703,7 +569,6 @@ void launch1(const BwdK &k, bool wide, int32_t pre, dim3 g, hipStream_t st)
 {
     constexpr int Q = K_BWD_STRIP_Q;
     if (wide) bwd_strip_kernel<DT, CL, Q, S, P, -1, -1, uint64_t><<<g, 256, 0, st>>>(k);
-    else if (pre == BN_RELU && k.n_post == 0) bwd_strip_kernel<DT, CL, Q, S, P, BN_RELU, 0, uint32_t><<<g, 256, 0, st>>>(k);
     else if (pre == 0 && strip_list_code(k.ew + k.n_ew, k.n_post) == BN_RELU)  // the stacked pooling blocks
         bwd_strip_kernel<DT, CL, Q, S, P, 0, BN_RELU, uint32_t><<<g, 256, 0, st>>>(k);
     else if (pre == 0 && k.n_post == 0) bwd_strip_kernel<DT, CL, Q, S, P, 0, 0, uint32_t><<<g, 256, 0, st>>>(k);
@@ -723,6 +588,13 @@ void launch2(const BwdK &k, bool wide, bool compiled, dim3 g, hipStream_t st)
 
 }  // namespace
 
+int32_t bwd_strip_channels(const BwdK &k, bool nhwc, int32_t dtype)
+{
+    return bwd_strip_keys(k) && nhwc && dtype != BS_F32 && k.C % 2 == 0 ? 2 : 1;
+}
+
+bool bwd_strip_keys(const BwdK &k) { return k.wave_rows != 2 && k.n_post == 0 && strip_list_code(k.ew, k.n_ew) == BN_RELU; }
+
 bool bwd_strip_compiled(const BwdK &k)
 {
     const int32_t pre = strip_list_code(k.ew, k.n_ew);
@@ -740,22 +612,23 @@ bs_status launch_backward_strips(const BwdK &arg, int32_t dtype, int32_t vec, in
     const PoolK &p = k.pool, &q = k.pool2;
     const bool two = k.wave_rows == 2, nhwc = k.nhwc != 0;
     const bool compiled = two && bwd_strip2_compiled(k);
-    const int32_t s = two ? 2 : p.sh, Q = two ? bwd_strip2_columns(nhwc, dtype, compiled) : K_BWD_STRIP_Q;
+    const int32_t s = two ? 2 : p.sh, Q = k.strips;
+    if (Q != (two ? bwd_strip2_columns(nhwc, dtype, compiled) : K_BWD_STRIP_Q) && !(Q == 2 && bwd_strip_keys(k))) return BS_ERR_UNSUPPORTED;
     // what the kernels assume: no Add; 3 x 3 windows; strips and chunks that cover the plane; the divisors of the lane numbering
     if (k.n_ew < 0 || k.n_post < 0 || k.n_ew + k.n_post > K_BWD_EW || threads != 256 || grid < 1) return BS_ERR_UNSUPPORTED;
     for (int32_t j = 0; j < k.n_ew + k.n_post; ++j)
         if (k.ew[j].kind == OP_ADD) return BS_ERR_UNSUPPORTED;
     const PoolK &mx = two ? q : p;
-    if (!k.strips || k.direct || vec != 1 || mx.kind != OP_MAXPOOL || mx.kh != 3 || mx.kw != 3 || mx.sh != mx.sw || mx.ph != mx.pw ||
-        mx.ph < 0 || mx.ph > 1 || (mx.sh != 1 && mx.sh != 2) || (int64_t)(nhwc ? k.div_wv.d : k.div_c.d) != k.C || (int64_t)k.div_cbs.d != k.cbs ||
+    if (k.direct || vec != bwd_strip_channels(k, nhwc, dtype) || mx.kind != OP_MAXPOOL || mx.kh != 3 || mx.kw != 3 || mx.sh != mx.sw || mx.ph != mx.pw ||
+        mx.ph < 0 || mx.ph > 1 || (mx.sh != 1 && mx.sh != 2) || (int64_t)(nhwc ? k.div_wv.d * (uint32_t)vec : k.div_c.d) != k.C || (int64_t)k.div_cbs.d != k.cbs ||
         (int64_t)k.div_chunks.d != k.chunks || k.cbs != (k.W + Q - 1) / Q || k.rc < 1 || k.chunks < 1 ||
-        (int64_t)k.chunks * k.rc * s < k.H || k.total % ((uint64_t)k.cbs * k.chunks * k.C) != 0 ||
+        (int64_t)k.chunks * k.rc * s < k.H || k.total % ((uint64_t)k.cbs * k.chunks * (k.C / vec)) != 0 ||
         (uint64_t)grid * 256 < k.total || k.Ho < 1 || k.Wo < 1)
         return BS_ERR_UNSUPPORTED;
     if (two && (p.kind != OP_AVGSUM || p.kh != 3 || p.kw != 3 || p.sh != 1 || p.sw != 1 || p.ph != 1 || p.pw != 1 || mx.sh != 2 || mx.ph != 1))
         return BS_ERR_UNSUPPORTED;
     // elements from the first to the last one of each tensor; 32-bit byte offsets where they all end below 4 GiB
-    const uint64_t images = k.total / ((uint64_t)k.cbs * k.chunks * k.C), es = dtype == BS_F32 ? 4 : 2;
+    const uint64_t images = k.total / ((uint64_t)k.cbs * k.chunks * (k.C / vec)), es = dtype == BS_F32 ? 4 : 2;
     auto reach = [&](uint64_t pixels, uint64_t extra) { return nhwc ? images * pixels * (k.C + extra) : images * pixels * k.C + (images - 1) * extra; };
     const uint64_t in_px = (uint64_t)k.H * k.W, out_px = (uint64_t)k.Ho * k.Wo;
     k.a_bytes = reach(in_px, k.a_extra) * es;
@@ -777,10 +650,11 @@ bs_status launch_backward_strips(const BwdK &arg, int32_t dtype, int32_t vec, in
         if (nhwc) BS_STRIPS_CL(DT, true);                                          \
         else BS_STRIPS_CL(DT, false);                                              \
     } while (0)
-    if (dtype == BS_F32) BS_STRIPS(DT_F32);
+    if (dtype != BS_F32 && dtype != BS_BF16 && dtype != BS_F16) return BS_ERR_UNSUPPORTED;
+    if (bwd_strip_keys(k)) launch_backward_keys(k, dtype, vec, wide, grid, stream);
+    else if (dtype == BS_F32) BS_STRIPS(DT_F32);
     else if (dtype == BS_BF16) BS_STRIPS(DT_BF16);
-    else if (dtype == BS_F16) BS_STRIPS(DT_F16);
-    else return BS_ERR_UNSUPPORTED;
+    else BS_STRIPS(DT_F16);
 #undef BS_STRIPS
 #undef BS_STRIPS_CL
     const hipError_t e = hipGetLastError();

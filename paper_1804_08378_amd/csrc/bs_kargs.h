@@ -408,7 +408,7 @@ struct BwdK {
     uint32_t *audit;
     // strips: a lane owns one channel of a strip of columns and walks down a chunk of rc
     // window rows; cbs = strips per row, total = images * chunks * strips * C, spw and units unused.
-    int32_t strips;       // 1: the kernels whose lanes walk strips of columns (wave_rows says which)
+    int32_t strips;       // the kernels whose lanes walk strips of columns: columns of a strip (wave_rows says which kernel; 0: others)
     uint64_t a_bytes, g_bytes;  // strips (set at launch): bytes from a tensor's first to its last element
     int32_t wave_rows;    // 2: two stages in one kernel -- `pool` (average 3 x 3 / 1 / 1) behind ew[0 .. n_ew), then `pool2` (max
                           // 3 x 3 / 2 / 1) with ew[n_ew .. n_ew + n_post) behind it; H x W: the input plane, Ho x Wo: the max pooling's output

@@ -178,4 +178,48 @@ BS_DEV void row_maxima(const float (&y)[CW * V], bool lead, float (&m)[N * V], i
         }
 }
 
+// A value that is not negative (behind a ReLU: never NaN, no -0) and the order of its cell among those it is compared with, in one word that
+// orders like the pair: the greatest key is the greatest value and, among equal ones, the greatest code.  Codes grow towards the first cell
+// in row-major order, so a maximum of keys is the first maximum -- one instruction where a compare and two selects (with their wait
+// states) take three.  16-bit storage: value bits above 16 bits of code.  float32: the value's bits above the code's in a double (at most
+// 0x7f800000 above: never a NaN; the maximum keeps denormals).  Key 0: no cell.
+template <int DT>
+struct PickKey {
+    uint32_t k;
+    static constexpr int BITS = 16;
+    BS_DEV static PickKey none() { return {0u}; }
+    // v: rounded to the storage type
+    BS_DEV static PickKey of(float v, uint32_t code)
+    {
+        if constexpr (DT == DT_BF16) return {__float_as_uint(v) | code};
+        else return {(uint32_t)half_bits<DT>(v) << 16 | code};
+    }
+    BS_DEV uint32_t code() const { return k & 0xffffu; }
+    BS_DEV bool positive() const { return k > 0xffffu; }
+    BS_DEV float value() const { return half_up<DT>(k >> 16); }
+    BS_DEV PickKey bumped(uint32_t by) const { return {k + by}; }
+    BS_DEV static PickKey max(PickKey a, PickKey b) { return {a.k > b.k ? a.k : b.k}; }
+    BS_DEV static PickKey choose(bool c, PickKey a, PickKey b) { return {c ? a.k : b.k}; }
+};
+template <>
+struct PickKey<DT_F32> {
+    uint32_t lo, hi;
+    static constexpr int BITS = 32;
+    BS_DEV static PickKey none() { return {0u, 0u}; }
+    BS_DEV static PickKey of(float v, uint32_t code) { return {code, __float_as_uint(v)}; }
+    BS_DEV uint32_t code() const { return lo; }
+    BS_DEV bool positive() const { return hi != 0u; }
+    BS_DEV float value() const { return __uint_as_float(hi); }
+    BS_DEV PickKey bumped(uint32_t by) const { return {lo + by, hi}; }
+    // (the instruction: fmax would first make both operands canonical)
+    BS_DEV static PickKey max(PickKey a, PickKey b)
+    {
+        const uint64_t x = (uint64_t)a.hi << 32 | a.lo, y = (uint64_t)b.hi << 32 | b.lo;
+        uint64_t d;
+        asm("v_max_f64 %0, %1, %2" : "=v"(d) : "v"(x), "v"(y));
+        return {(uint32_t)d, (uint32_t)(d >> 32)};
+    }
+    BS_DEV static PickKey choose(bool c, PickKey a, PickKey b) { return {c ? a.lo : b.lo, c ? a.hi : b.hi}; }
+};
+
 }  // namespace bs

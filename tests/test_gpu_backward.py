@@ -753,3 +753,27 @@ def test_benchmark_sizes_on_sampled_images(name, dtype, layout):
         for i, r in enumerate(ref_res):
             _close(gres[i][sl].float().cpu().numpy(), r, dtype, f"{name} image {n} grad_residual[{i}]")
     st.close()
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16", "f16"])
+@pytest.mark.parametrize("shape", [(2, 3, 7, 5), (1, 6, 3, 3), (1, 2, 4, 1), (3, 16, 30, 9), (5, 7, 191, 170), (9, 64, 65, 62)])
+def test_picks_found_as_greatest_keys(shape, dtype):
+    """[BatchNorm -> ReLU or ReLU, max pooling 3 x 3] in the strip kernels whose maxima are keys of value and place: one and two channels per
+    lane (odd and even channel counts), strips of two and of four columns (the small and the large shapes), planes narrower than a strip,
+    equal maxima (the first in row-major order gets the gradient), windows of nothing but zeros (no gradient), infinite maxima."""
+    c = shape[1]
+    big = int(np.prod(shape)) > 100000
+    for (s, p), lead in zip(((2, 1), (2, 0), (1, 1), (1, 0)), ([wl.bn_params(c, 41), wl.relu()], [wl.relu()], [wl.relu()], [wl.bn_params(c, 42), wl.relu()])):
+        if shape[2] + 2 * p < 3 or shape[3] + 2 * p < 3 or (big and (s, p) in ((2, 0), (1, 0))):
+            continue
+        layers = lead + [wl.maxpool(3, s, p)]
+        rng = np.random.default_rng(7)
+        x = rng.choice(np.array([-2.0, -0.5, 0.0, 0.5, 0.5, 1.5], np.float32), shape)
+        x[:, :, : shape[2] // 3] = -1.0  # ReLU cuts off whole windows
+        x.flat[:: 97] = np.inf
+        dy = rng.integers(-8, 9, wl.output_shape(layers, shape)).astype(np.float32)  # sums of these are exact
+        ref, _ = bw.backward_stack(layers, x, [], dy, dtype)
+        for opts in (dict(layout=bs.BS_LAYOUT_NHWC), dict()):
+            gx, _, stages = run_gpu(layers, x, [], dy, dtype, **opts)
+            assert stages == 1
+            _close(gx, ref, dtype, f"keys {shape} {dtype} s{s} p{p} {opts}")
