@@ -9,7 +9,7 @@ ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libbrainslug_hip.so")
 SOURCES = ["bs_stack.cpp", "bs_plan.cpp", "bs_run.cpp", "bs_jit.cpp", "bs_trace.cpp", "bs_kernels.hip", "bs_lds.hip", "bs_rows.hip",
-           "bs_rows2.hip", "bs_xrows.hip", "bs_chain.hip", "bs_nhwc.hip", "bs_nhwc_tile.hip", "bs_nhwc_rows.hip", "bs_strip.hip", "bs_backward.cpp", "bs_backward.hip", "bs_backward_strip.hip", "bs_backward_keys.hip", "bs_probe.hip"]
+           "bs_rows2.hip", "bs_xrows.hip", "bs_chain.hip", "bs_nhwc.hip", "bs_nhwc_tile.hip", "bs_nhwc_rows.hip", "bs_strip.hip", "bs_backward.cpp", "bs_backward.hip", "bs_backward_strip.hip", "bs_probe.hip"]
 # device headers whose text is embedded in the library for run-time (hipRTC) kernel builds
 JIT_HEADERS = ["bs_kargs.h", "bs_device.h", "bs_lds_device.h", "bs_rows_device.h", "bs_xrows_device.h", "bs_chain_device.h"]
 
@@ -32,7 +32,7 @@ def up_to_date() -> bool:
     if not os.path.exists(LIB):
         return False
     t = os.path.getmtime(LIB)
-    deps = sources() + [os.path.join(CSRC, h) for h in JIT_HEADERS + ["bs_internal.h", "bs_rows_tables.h", "bs_nhwc_device.h", "bs_bwd_device.h", "bs_strip_device.h", "bs_bwd_strip_device.h"]]
+    deps = sources() + [os.path.join(CSRC, h) for h in JIT_HEADERS + ["bs_internal.h", "bs_rows_tables.h", "bs_nhwc_device.h", "bs_bwd_device.h", "bs_strip_device.h", "bs_backward_keys.h"]]
     deps.append(os.path.join(ROOT, "include", "brainslug.h"))
     return all(os.path.getmtime(d) <= t for d in deps)
 

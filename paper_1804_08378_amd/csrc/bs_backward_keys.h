@@ -10,13 +10,8 @@
 // What bounds it: memory -- 231 MB of the ResNet stem 64 x 64 x 112 x 112 bfloat16 in 46 us = 5.0 TB/s (the kernel that compares and selects: 60 us, 36
 // vector instructions per cell); float32 94 us = 4.9 TB/s (98).  32 x 192 x 71 x 71 / 2 without padding binary16 38 -> 35 us.  Row-major rows that are no whole
 // vectors, 64 x 64 x 111 x 111: float32 145 -> 143, bfloat16 78 -> 76.5.  Strips of 8 columns measured 5 % slower, 2 10 % (large tensors).
-#include <hip/hip_runtime.h>
-
-#include "bs_bwd_strip_device.h"
-#include "bs_internal.h"
-
-namespace bs {
-namespace {
+// Part of bs_backward_strip.hip (its lanes, places, loads and stores).
+#pragma once
 
 // keys of N columns x V channels (column-major: all channels of a column share its code): BatchNorm, rounded, ReLU
 template <int DT, int V, int N>
@@ -240,7 +235,7 @@ __global__ __launch_bounds__(256) void bwd_keys_kernel(const BwdK k)
 }
 
 template <int DT, bool CL, int V, int Q>
-void launch_windows(const BwdK &k, bool wide, dim3 g, hipStream_t st)
+void launch_keys_windows(const BwdK &k, bool wide, dim3 g, hipStream_t st)
 {
 #define BS_KEYS(S, P)                                                              \
     do {                                                                           \
@@ -255,32 +250,26 @@ void launch_windows(const BwdK &k, bool wide, dim3 g, hipStream_t st)
 }
 
 template <int DT, bool CL, int V>
-void launch_columns(const BwdK &k, bool wide, dim3 g, hipStream_t st)
+void launch_keys_columns(const BwdK &k, bool wide, dim3 g, hipStream_t st)
 {
-    if (k.strips == 2) launch_windows<DT, CL, V, 2>(k, wide, g, st);
-    else launch_windows<DT, CL, V, K_BWD_STRIP_Q>(k, wide, g, st);
+    if (k.strips == 2) launch_keys_windows<DT, CL, V, 2>(k, wide, g, st);
+    else launch_keys_windows<DT, CL, V, K_BWD_STRIP_Q>(k, wide, g, st);
 }
-
-}  // namespace
 
 // (launch_backward_strips has checked the arguments; vec: channels per lane)
-void launch_backward_keys(const BwdK &k, int32_t dtype, int32_t vec, bool wide, int64_t grid, void *stream)
+void launch_keys(const BwdK &k, int32_t dtype, int32_t vec, bool wide, dim3 g, hipStream_t st)
 {
-    hipStream_t st = static_cast<hipStream_t>(stream);
-    const dim3 g((uint32_t)grid);
     if (!k.nhwc) {
-        if (dtype == BS_F32) launch_columns<DT_F32, false, 1>(k, wide, g, st);
-        else if (dtype == BS_BF16) launch_columns<DT_BF16, false, 1>(k, wide, g, st);
-        else launch_columns<DT_F16, false, 1>(k, wide, g, st);
+        if (dtype == BS_F32) launch_keys_columns<DT_F32, false, 1>(k, wide, g, st);
+        else if (dtype == BS_BF16) launch_keys_columns<DT_BF16, false, 1>(k, wide, g, st);
+        else launch_keys_columns<DT_F16, false, 1>(k, wide, g, st);
     } else if (dtype == BS_F32) {
-        launch_columns<DT_F32, true, 1>(k, wide, g, st);
+        launch_keys_columns<DT_F32, true, 1>(k, wide, g, st);
     } else if (vec == 2) {
-        if (dtype == BS_BF16) launch_columns<DT_BF16, true, 2>(k, wide, g, st);
-        else launch_columns<DT_F16, true, 2>(k, wide, g, st);
+        if (dtype == BS_BF16) launch_keys_columns<DT_BF16, true, 2>(k, wide, g, st);
+        else launch_keys_columns<DT_F16, true, 2>(k, wide, g, st);
     } else {
-        if (dtype == BS_BF16) launch_columns<DT_BF16, true, 1>(k, wide, g, st);
-        else launch_columns<DT_F16, true, 1>(k, wide, g, st);
+        if (dtype == BS_BF16) launch_keys_columns<DT_BF16, true, 1>(k, wide, g, st);
+        else launch_keys_columns<DT_F16, true, 1>(k, wide, g, st);
     }
 }
-
-}  // namespace bs

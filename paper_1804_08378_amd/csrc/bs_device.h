@@ -277,4 +277,15 @@ BS_DEV void store_elems(void *base, uint32_t elem, const float (&v)[N])
     }
 }
 
+// The same for one or two elements as non-temporal stores (whole cache lines of a wave, written once and not read again).
+struct NonTemporal {};
+template <int DT, int N>
+BS_DEV void store_elems(NonTemporal, void *p, const float *v)
+{
+    static_assert(N == 1 || (N == 2 && DT != DT_F32), "one register");
+    if constexpr (DT == DT_F32) __builtin_nontemporal_store(v[0], static_cast<float *>(p));
+    else if constexpr (N == 2) __builtin_nontemporal_store(pack2<DT>(v[0], v[1]), static_cast<uint32_t *>(p));
+    else __builtin_nontemporal_store(half_bits<DT>(v[0]), static_cast<uint16_t *>(p));
+}
+
 }  // namespace bs

@@ -235,8 +235,7 @@ bs_status launch_backward_stage(const BwdK &k, int32_t dtype, int32_t vec, int64
 bool bwd_strip_compiled(const BwdK &k);   // the one-level kernel has this stage's lists compiled in,
 bool bwd_strip2_compiled(const BwdK &k);  // the two-level kernel its lists and divisors
 bool bwd_strip_keys(const BwdK &k);       // one level, BatchNorm -> ReLU or ReLU in front, nothing behind: the kernel whose maxima are keys,
-int32_t bwd_strip_channels(const BwdK &k, bool nhwc, int32_t dtype);  // and the channels a lane owns
-void launch_backward_keys(const BwdK &k, int32_t dtype, int32_t vec, bool wide, int64_t grid, void *stream);  // (arguments checked by:)
+int32_t bwd_strip_channels(const BwdK &k, bool nhwc, int32_t dtype);  // and the channels a lane of it owns
 bs_status launch_backward_strips(const BwdK &k, int32_t dtype, int32_t vec, int64_t grid, int32_t threads, void *stream);
 // bs_trace.cpp
 bool trace_enabled();
