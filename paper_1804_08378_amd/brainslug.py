@@ -491,17 +491,45 @@ class Stack:
         self._fast = None
         self._bwd_workspace = None
         self._bwd_planned = False
+        self._native = None
         self.layout = BS_LAYOUT_NCHW
 
     def close(self):
-        # also runs as __del__, possibly while the interpreter shuts down and module globals are gone
+        if getattr(self, "_native", None) is not None:
+            self._native.release()
+            self._native = None
         if getattr(self, "handle", None) and bs_stack_destroy is not None:
             bs_stack_destroy(self.handle)
             self.handle = None
 
-    __del__ = close
+    def __del__(self):
+        # possibly while the interpreter shuts down and module globals are gone
+        if getattr(self, "_native", None) is not None:
+            self._native = self.handle = None  # graph nodes may still hold the handle: the last owner destroys it
+        else:
+            self.close()
+
+    def native(self):
+        """The plan's native calls (`csrc/bs_torch.cpp`): every method takes the plain case -- dense torch tensors of the plan's
+        shapes, type, memory layout and device, torch's current stream -- and returns None for any other."""
+        if self._native is None:
+            import torch  # noqa: F401 (the module links against it)
+            from . import _bs_torch
+            _bs_torch.set_error(BrainSlugError)
+            lib = load()
+            fns = tuple(C.cast(f, C.c_void_p).value for f in (lib.bs_stack_run_strided, lib.bs_stack_backward_strided, lib.bs_stack_destroy))
+            code = (torch.float32, torch.bfloat16, torch.float16).index(self.torch_dtype())
+            n = _bs_torch.Plan(fns, self.handle or 0, self.in_shape, self.out_shape, code, self.layout == BS_LAYOUT_NHWC, self.res_shapes,
+                               self.idx_shapes, self._workspace_bytes)
+            if self._bwd_planned:
+                n.set_backward(self._bwd_workspace_bytes)
+            self._native = n
+        return self._native
 
     def plan(self, **opts):
+        if self._native is not None:  # bound to the plan that goes
+            self._native.release()
+            self._native = None
         bs_stack_plan(self.handle, **opts)
         self.layout = int(opts.get("layout", BS_LAYOUT_NCHW))
         self._workspace = None
@@ -517,6 +545,8 @@ class Stack:
         self._bwd_planned = True
         self._bwd_workspace = None
         self._bwd_workspace_bytes = bs_stack_backward_workspace_bytes(self.handle)
+        if self._native is not None:
+            self._native.set_backward(self._bwd_workspace_bytes)
         return self
 
     def backward(self, x, residuals, grad_out, need_input_grad=True, need_residual_grads=None, stream=None, indices=None):
@@ -526,9 +556,13 @@ class Stack:
         `x` and `residuals` are the forward pass's operands, `grad_out` the gradient with respect
         to its output; all dense tensors of the stack's dtype in the plan's memory layout (the
         gradients come back in that layout)."""
-        import torch
-        if not getattr(self, "_bwd_planned", False):
+        if not self._bwd_planned:
             self.plan_backward()
+        if need_input_grad and need_residual_grads is None and stream is None:
+            done = self.native().backward(x, residuals, grad_out, indices)
+            if done is not None:
+                return done
+        import torch
         dt = self.torch_dtype()
         mf = torch.channels_last if self.layout == BS_LAYOUT_NHWC else torch.contiguous_format
         if tuple(x.shape) != self.in_shape or x.dtype != dt or not x.is_contiguous(memory_format=mf):
@@ -609,6 +643,10 @@ class Stack:
         """Enqueue on `stream` (default: torch's current stream); returns (out, indices).
         `x` and `out` may be channel slices (t[:, a:b]) of larger contiguous tensors: they are
         read and written in place."""
+        if out is None and indices is None and stream is None:
+            done = self.native().run(x, residuals)
+            if done is not None:
+                return done
         import torch
         if self.layout == BS_LAYOUT_NHWC:
             return self._run_nhwc(x, residuals, out, indices, stream)

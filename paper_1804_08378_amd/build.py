@@ -8,6 +8,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libbrainslug_hip.so")
+TORCH_EXT = os.path.join(HERE, "_bs_torch.so")  # the binding's native calls (csrc/bs_torch.cpp, host code only)
 SOURCES = ["bs_stack.cpp", "bs_plan.cpp", "bs_run.cpp", "bs_jit.cpp", "bs_trace.cpp", "bs_kernels.hip", "bs_lds.hip", "bs_rows.hip",
            "bs_rows2.hip", "bs_xrows.hip", "bs_chain.hip", "bs_nhwc.hip", "bs_nhwc_tile.hip", "bs_nhwc_rows.hip", "bs_strip.hip", "bs_backward.cpp", "bs_backward.hip", "bs_backward_strip.hip", "bs_probe.hip"]
 # device headers whose text is embedded in the library for run-time (hipRTC) kernel builds
@@ -29,7 +30,9 @@ def sources():
 
 
 def up_to_date() -> bool:
-    if not os.path.exists(LIB):
+    if not os.path.exists(LIB) or not os.path.exists(TORCH_EXT):
+        return False
+    if os.path.getmtime(TORCH_EXT) < os.path.getmtime(os.path.join(CSRC, "bs_torch.cpp")):
         return False
     t = os.path.getmtime(LIB)
     deps = sources() + [os.path.join(CSRC, h) for h in JIT_HEADERS + ["bs_internal.h", "bs_rows_tables.h", "bs_nhwc_device.h", "bs_bwd_device.h", "bs_strip_device.h", "bs_backward_keys.h"]]
@@ -57,6 +60,24 @@ def write_embedded_headers(path: str) -> None:
             f.write(new)
 
 
+def build_torch_ext() -> None:
+    """Compile csrc/bs_torch.cpp against the installed torch (its headers and libraries; nothing of it runs on the device)."""
+    import sysconfig
+
+    import torch
+    from torch.utils import cpp_extension
+
+    lib = os.path.join(os.path.dirname(torch.__file__), "lib")
+    tmp = TORCH_EXT + ".tmp.%d" % os.getpid()
+    cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-fvisibility=hidden", "-Wall", "-Wno-unused-parameter",
+           "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1", "-D_GLIBCXX_USE_CXX11_ABI=%d" % int(torch._C._GLIBCXX_USE_CXX11_ABI)]
+    for d in [*cpp_extension.include_paths(), "/opt/rocm/include", sysconfig.get_paths()["include"]]:
+        cmd += ["-isystem", d]
+    cmd += [os.path.join(CSRC, "bs_torch.cpp"), "-o", tmp, "-L" + lib, "-ltorch_python", "-ltorch_cpu", "-lc10_hip", "-lc10"]
+    subprocess.run(cmd, check=True)
+    os.replace(tmp, TORCH_EXT)
+
+
 def build(force: bool = True, verbose: bool = False) -> str:
     if not force and up_to_date():
         return LIB
@@ -79,7 +100,9 @@ def build(force: bool = True, verbose: bool = False) -> str:
 
     from concurrent.futures import ThreadPoolExecutor
     with ThreadPoolExecutor(max_workers=min(8, len(SOURCES) + 1)) as ex:
+        ext = ex.submit(build_torch_ext)
         objs = list(ex.map(compile_one, sources() + [embed]))
+        ext.result()
     tmp = LIB + ".tmp.%d" % os.getpid()
     subprocess.run([hipcc, "--offload-arch=gfx950", "-shared", "-fPIC", "-fvisibility=hidden", *objs, "-lhiprtc", "-ldl",
                     "-o", tmp], check=True)

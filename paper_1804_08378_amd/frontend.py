@@ -149,6 +149,11 @@ class _StackFunction(torch.autograd.Function):
         # (saves recomputing them)
         picks = [torch.empty(sh, dtype=torch.int32, device=x.device, memory_format=mf) for sh in st.idx_shapes] or None
         st.run_unchecked(x, list(residuals), out, stride, 0, picks)
+        if not st._bwd_planned:
+            try:
+                st.plan_backward()  # the next call takes the native node
+            except bs.BrainSlugError:
+                pass  # the backward pass, if it comes to one, says so
         ctx.save_for_backward(x, *residuals)
         ctx.stack, ctx.mf, ctx.picks, ctx.stride, ctx.nhwc = st, mf, picks, stride, nhwc
         return out
@@ -281,6 +286,10 @@ class BrainSlugStack(nn.Module):
         where to write the result -- a tensor of the output's shape, dense in the input's memory
         format or a channel slice of such a tensor (a concatenation buffer); when it does not fit
         (shape, type, alignment) it is ignored and a new tensor is returned."""
+        if out is None and not self.training:
+            done = self._native_forward(x, residuals)
+            if done is not None:
+                return done
         if self.training:
             raise RuntimeError("BrainSlugStack implements inference-mode layers only (BatchNorm with running "
                                "statistics): call model.eval(); gradients still flow in that mode")
@@ -339,6 +348,24 @@ class BrainSlugStack(nn.Module):
                 out, ostride = torch.empty(st.out_shape, dtype=x.dtype, device=x.device, memory_format=mf), 0
             st.run_unchecked(x, res, out, stride, ostride)
         return out
+
+    def _native_forward(self, x, residuals):
+        """The call through the plan's native binding where there is a plan and the operands are dense; else None."""
+        if self._bn_seen:
+            self.sync_parameters()
+        record = torch.is_grad_enabled() and (x.requires_grad or any(r.requires_grad for r in residuals))
+        try:
+            st = self._plans.get((x.shape, x.dtype, not x.is_contiguous(), record))
+        except RuntimeError:  # a tensor without strides
+            return None
+        if st is None:
+            return None
+        if not record:
+            return st.native().infer(x, residuals)
+        # what records or transforms Python calls sees the autograd function
+        if not st._bwd_planned or torch.jit.is_tracing() or torch.compiler.is_compiling():
+            return None
+        return st.native().record(x, residuals)
 
     @staticmethod
     def _input_slice(x):
