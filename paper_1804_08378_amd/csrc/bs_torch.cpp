@@ -13,6 +13,7 @@
 #include <ATen/core/PythonFallbackKernel.h>
 #include <c10/core/impl/TorchDispatchModeTLS.h>
 #include <c10/hip/HIPStream.h>
+#include <c10/util/SmallVector.h>
 #include <torch/csrc/Exceptions.h>
 #include <torch/csrc/autograd/custom_function.h>
 #include <torch/csrc/autograd/python_variable.h>
@@ -134,11 +135,11 @@ void run_forward(Plan &p, const at::Tensor &x, const std::vector<at::Tensor> &re
     for (const Shape &s : p.idx) picks.push_back(at::empty(at::IntArrayRef(s.data(), 4), p.options(x).dtype(at::kInt).memory_format(p.mf)));
     void *stream = c10::hip::getCurrentHIPStream(x.device().index()).stream();
     const at::Tensor ws = p.workspace(false, x.device(), stream);
-    const void *rp[8];
-    int32_t *ip[8];
-    for (size_t i = 0; i < res.size(); ++i) rp[i] = res[i].data_ptr();
-    for (size_t i = 0; i < picks.size(); ++i) ip[i] = static_cast<int32_t *>(picks[i].data_ptr());
-    const int rc = p.run(p.handle, x.data_ptr(), 0, res.empty() ? nullptr : rp, out.data_ptr(), 0, picks.empty() ? nullptr : ip,
+    c10::SmallVector<const void *, 4> rp;
+    c10::SmallVector<int32_t *, 4> ip;
+    for (const at::Tensor &r : res) rp.push_back(r.data_ptr());
+    for (const at::Tensor &t : picks) ip.push_back(static_cast<int32_t *>(t.data_ptr()));
+    const int rc = p.run(p.handle, x.data_ptr(), 0, res.empty() ? nullptr : rp.data(), out.data_ptr(), 0, picks.empty() ? nullptr : ip.data(),
                          ws.defined() ? ws.data_ptr() : nullptr, p.ws_bytes, stream);
     if (rc != 0) throw CallFailed(rc, "bs_stack_run");
 }
@@ -153,16 +154,16 @@ void run_backward(Plan &p, const at::Tensor &x, const std::vector<at::Tensor> &r
         if (need[i + 1]) gres[i] = at::empty(at::IntArrayRef(p.res[i].data(), 4), p.options(x).memory_format(p.mf));
     void *stream = c10::hip::getCurrentHIPStream(x.device().index()).stream();
     const at::Tensor ws = p.workspace(true, x.device(), stream);
-    const void *rp[8];
-    void *gp[8];
-    const int32_t *ip[8];
+    c10::SmallVector<const void *, 4> rp;
+    c10::SmallVector<void *, 4> gp;
+    c10::SmallVector<const int32_t *, 4> ip;
     for (size_t i = 0; i < res.size(); ++i) {
-        rp[i] = res[i].data_ptr();
-        gp[i] = gres[i].defined() ? gres[i].data_ptr() : nullptr;
+        rp.push_back(res[i].data_ptr());
+        gp.push_back(gres[i].defined() ? gres[i].data_ptr() : nullptr);
     }
-    for (size_t i = 0; i < picks.size(); ++i) ip[i] = picks[i].defined() ? static_cast<const int32_t *>(picks[i].data_ptr()) : nullptr;
-    const int rc = p.backward(p.handle, x.data_ptr(), 0, res.empty() ? nullptr : rp, picks.empty() ? nullptr : ip, dy.data_ptr(), dy_stride,
-                              gx.defined() ? gx.data_ptr() : nullptr, 0, res.empty() ? nullptr : gp, ws.defined() ? ws.data_ptr() : nullptr,
+    for (const at::Tensor &t : picks) ip.push_back(t.defined() ? static_cast<const int32_t *>(t.data_ptr()) : nullptr);
+    const int rc = p.backward(p.handle, x.data_ptr(), 0, res.empty() ? nullptr : rp.data(), picks.empty() ? nullptr : ip.data(), dy.data_ptr(), dy_stride,
+                              gx.defined() ? gx.data_ptr() : nullptr, 0, res.empty() ? nullptr : gp.data(), ws.defined() ? ws.data_ptr() : nullptr,
                               p.bwd_ws_bytes, stream);
     if (rc != 0) throw CallFailed(rc, "bs_stack_backward");
 }
@@ -269,10 +270,6 @@ PyObject *plan_new(PyTypeObject *type, PyObject *args, PyObject *)
     p->mf = nhwc ? at::MemoryFormat::ChannelsLast : at::MemoryFormat::Contiguous;
     p->ws_bytes = ws;
     if (!read_shape(in, p->in) || !read_shape(out, p->out) || !read_shapes(res, p->res) || !read_shapes(idx, p->idx)) return nullptr;
-    if (p->res.size() > 8 || p->idx.size() > 8) {
-        PyErr_SetString(PyExc_ValueError, "more operands than the native calls take");
-        return nullptr;
-    }
     PlanObject *self = reinterpret_cast<PlanObject *>(type->tp_alloc(type, 0));
     if (!self) return nullptr;
     p->handle = reinterpret_cast<void *>(handle);
