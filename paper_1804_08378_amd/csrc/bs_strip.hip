@@ -91,6 +91,12 @@ __global__ __launch_bounds__(256) void strip_kernel(const StripK k)
     constexpr int ES = elem_bytes<DT>(), KEEP = K - S, KEPT = KEEP ? KEEP : 1;
     constexpr bool MAX2 = K2 == OP_MAXPOOL, GENERAL = PRE < 0;
     constexpr bool DEFER = K1 == OP_AVGSUM && MAX2 && !IDX && !GENERAL;  // the average is rounded behind the maximum
+    // Non-temporal stores (a wave writes whole cache lines of channels; float32 indices plainly) where the output is hardly ever the next launch's input:
+    // training, and the average-maximum pair.  Measured, us, plain / non-temporal: ResNet stem with indices 64 x 64 x 112 x 112 bfloat16 39.5 / 31.9, float32 62.2 / 60.9;
+    // 32 x 192 x 71 x 71 / 2 with indices binary16 23.7 / 18.8, float32 36.9 / 31.6; halo_stress float32 56.3 / 52.7, bfloat16 40.3 / 38.6, with indices 50.9 / 44.8, 33 x 40
+    // x 17 x 55 (0.7 MB) 6.8 / 7.1.  Two maxima between two launches, 32 x 64 x 56 x 56 float32, four blocks: 29.7 / 31.6 (plain).  float32 indices, forward and backward:
+    // 146.8 / 149.6 (plain).  A flag read in the loop instead: stem 37.4.
+    constexpr bool STREAMED = CL && (IDX || K1 == OP_AVGSUM);
     constexpr float PAD1 = K1 == OP_MAXPOOL ? -INFINITY : 0.0f, PAD2 = MAX2 ? -INFINITY : 0.0f;
     uint32_t i0 = xcd_contiguous(blockIdx.x, gridDim.x) * 256u + threadIdx.x;
     const bool live = i0 < k.total;
@@ -356,6 +362,17 @@ __global__ __launch_bounds__(256) void strip_kernel(const StripK k)
             if (!CL && whole) {
                 store_run<DT, QO>(out, o);
                 if constexpr (IDX) __builtin_memcpy(k.idx + iat, pick, 4 * QO);
+            } else if constexpr (STREAMED) {
+#pragma unroll
+                for (int j = 0; j < QO; ++j)
+                    if (whole || ow0 + j < k.Wo) {
+                        store_elems<DT, 1>(NonTemporal{}, out + (OFF)j * po, o + j);
+                        if constexpr (IDX) {
+                            int32_t *at = k.idx + (iat + (uint32_t)j * (uint32_t)k.C);
+                            if constexpr (DT == DT_F32) *at = pick[j];
+                            else __builtin_nontemporal_store(pick[j], at);
+                        }
+                    }
             } else {
 #pragma unroll
                 for (int j = 0; j < QO; ++j)
