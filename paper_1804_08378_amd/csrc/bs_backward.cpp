@@ -307,6 +307,10 @@ extern "C" bs_status bs_stack_plan_backward(bs_stack *stack)
                 g.vec = g.k.W % full == 0 ? full : (stack->dtype != BS_F32 && g.k.W % 4 == 0 ? 4 : 1);
                 // disjoint 2 x 2 windows that tile the plane: the kernel that owns whole windows
                 g.k.direct = tiles2x2 && g.vec > 1;
+                // Its two rows share cache lines where they are no whole lines: read through the caches below 256 bytes.  Measured, us, streaming / cached:
+                // rows of 56 bytes 26.6 / 22.5 (64 x 512 x 28 x 28 bfloat16), 112 bytes 57.0 / 53.5, 120 bytes 17.3 / 15.1, 224 bytes 44.2 / 42.4 and 80.1 / 79.1,
+                // 448 bytes 73.2 / 73.4, 896 bytes 71.2 / 73.9.
+                g.k.cached = (uint64_t)g.k.W * es < 256;
                 // no pooling and rows that are no whole vectors (the 28 x 28, 14 x 14, 7 x 7 planes of
                 // 16-bit networks): vectors over the whole tensor, which may straddle two planes
                 const int64_t hw = (int64_t)g.k.H * g.k.W;
@@ -315,6 +319,9 @@ extern "C" bs_status bs_stack_plan_backward(bs_stack *stack)
                     g.k.flat = 1;
                     g.k.div_w = make_fastdiv((uint32_t)hw);
                 }
+                // without pooling: as the forward kernel left it, up to half of the last cache (forward and backward, 64 x 512 x 28 x 28 float32, BatchNorm ->
+                // Add -> ReLU 125.8 / 120.4 us, BatchNorm -> ReLU 64 x 256 x 56 x 56 bfloat16 81.1 / 76.4, float32, 206 MB, 156 / 159)
+                if (p.kind == 0) g.k.cached = numel(g.in_shape) * es <= 128u << 20;
                 lanes = numel(g.in_shape) / (uint64_t)g.vec / (g.k.direct ? 2 : 1);
                 g.k.div_wv = make_fastdiv((uint32_t)(g.k.flat ? 1 : g.k.W / g.vec));
                 if (g.k.wave_rows == 2) {

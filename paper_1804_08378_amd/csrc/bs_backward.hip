@@ -431,7 +431,9 @@ __global__ __launch_bounds__(256) void bwd_ew_kernel(const BwdK k)
         }
         imgs[u] = fdiv(plane, k.div_c);  // a vector lies in one image (checked at launch when the tensors are slices)
         cs[u] = (int32_t)(plane - imgs[u] * (uint32_t)k.C);
-        ar[u] = load_raw<DT, VEC, true>(k.a, audited(k, 0, 2, offs[u] + imgs[u] * k.a_extra, VEC));
+        const uint32_t in_off = audited(k, 0, 2, offs[u] + imgs[u] * k.a_extra, VEC);
+        if (k.cached) ar[u] = load_raw<DT, VEC>(k.a, in_off);  // the same for every lane
+        else ar[u] = load_raw<DT, VEC, true>(k.a, in_off);
         gr[u] = load_raw<DT, VEC, true>(k.g_out, audited(k, 1, 16, offs[u] + imgs[u] * k.gout_extra, VEC));
     }
     float x[U][VEC], t[U][VEC], r[NR ? NR : 1][U][VEC], s[U][VEC];
@@ -476,7 +478,15 @@ __global__ __launch_bounds__(256) void bwd_direct2_kernel(const BwdK k)
     const uint32_t out_off = rowo * (uint32_t)k.Wo + cv * NO;  // Wo = W / 2: NO outputs of row oh
 
     const uint32_t ash = img * k.a_extra;
-    const Raw<DT, VEC> a0 = load_raw<DT, VEC, true>(k.a, audited(k, 0, 3, offs[0] + ash, VEC)), a1 = load_raw<DT, VEC, true>(k.a, audited(k, 0, 4, offs[1] + ash, VEC));
+    const uint32_t in0 = audited(k, 0, 3, offs[0] + ash, VEC), in1 = audited(k, 0, 4, offs[1] + ash, VEC);
+    Raw<DT, VEC> a0, a1;
+    if (k.cached) {  // the same for every lane
+        a0 = load_raw<DT, VEC>(k.a, in0);
+        a1 = load_raw<DT, VEC>(k.a, in1);
+    } else {
+        a0 = load_raw<DT, VEC, true>(k.a, in0);
+        a1 = load_raw<DT, VEC, true>(k.a, in1);
+    }
     const Raw<DT, NO> gr = load_raw<DT, NO, true>(k.g_out, audited(k, 1, 17, out_off + img * k.gout_extra, NO));
     float x[2][VEC], t[2][VEC], r[NR ? NR : 1][2][VEC], g[NO];
     unpack<DT, VEC>(a0, x[0]);

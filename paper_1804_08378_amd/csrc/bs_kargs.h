@@ -162,6 +162,7 @@ struct StreamK {
     FastDiv div_plane;  // by H*W/vec (flat: by H*W)
     FastDiv div_c;
     int32_t flat;       // 1: H*W is no multiple of vec; vectors run over the whole tensor and may straddle two planes
+    int32_t cached;     // 1: input read through the caches, 0: streamed
 };
 
 struct PoolDirectK {
@@ -179,6 +180,7 @@ struct PoolDirectK {
     FastDiv div_wv;      // by W / vec (whole-plane kernel staged through LDS: by H * W)
     FastDiv div_ho;      // by Ho
     FastDiv div_c;
+    int32_t cached;      // 1: input read through the caches, 0: streamed
     int32_t ppg, pitch;  // whole-plane kernel staged through LDS: planes per work-group, LDS floats per plane (odd)
 };
 
@@ -271,6 +273,7 @@ struct NhwcK {
     int32_t n_pre, n_post;
     EwOp pre[K_MAX_STREAM_EW], post[K_MAX_EW];
     PoolK pool;
+    int32_t cached;   // element-wise sequences: 1: input read through the caches, 0: streamed
     int32_t C, H, W, Ho, Wo;
     uint32_t total;   // lanes with work: (output) pixels * channel vectors
     FastDiv div_cv;   // by channel vectors per pixel = C / vec
@@ -386,6 +389,7 @@ struct BwdK {
     uint32_t total;       // lanes with work = planes * H * (W / vec); direct: planes * Ho * (W / vec)
     FastDiv div_wv;       // by W / vec
     FastDiv div_h, div_c; // by H (direct: by Ho), by C
+    int32_t cached;       // row-major stages without pooling, or direct: 1: the stage input is read through the caches, 0: streamed
     int32_t direct;       // 1: disjoint 2 x 2 windows that tile the plane; a lane owns whole windows and
                           // finds the max-pooling picks itself (idx unused)
     int32_t nhwc;         // 1: channels-last tensors.  A lane owns `vec` consecutive channels of one pixel (direct:

@@ -122,7 +122,13 @@ __global__ __launch_bounds__(512) void stream_kernel(const StreamK k)
         const uint32_t plane = fdiv(i, k.div_plane);
         img[u] = fdiv(plane, k.div_c);
         c[u] = (int32_t)(plane - img[u] * (uint32_t)k.C);
-        raw[u] = load_raw<DT, VEC, true>(image_base<DT>(k.in, img[u], k.in_extra), off[u]);
+    }
+    if (k.cached) {  // the same for every lane
+#pragma unroll
+        for (int u = 0; u < U; ++u) raw[u] = load_raw<DT, VEC>(image_base<DT>(k.in, img[u], k.in_extra), off[u]);
+    } else {
+#pragma unroll
+        for (int u = 0; u < U; ++u) raw[u] = load_raw<DT, VEC, true>(image_base<DT>(k.in, img[u], k.in_extra), off[u]);
     }
     float x[U][VEC];
 #pragma unroll
@@ -158,7 +164,7 @@ __global__ __launch_bounds__(512) void stream_flat_kernel(const StreamK k)
         const uint32_t c0 = plane - fdiv(plane, k.div_c) * (uint32_t)k.C;
         const uint32_t c1 = c0 + 1 == (uint32_t)k.C ? 0u : c0 + 1;
         float x[VEC];
-        unpack<DT, VEC>(load_raw<DT, VEC, true>(k.in, off), x);
+        unpack<DT, VEC>(k.cached ? load_raw<DT, VEC>(k.in, off) : load_raw<DT, VEC, true>(k.in, off), x);
 #pragma clang loop unroll(disable)
         for (int32_t j = 0; j < k.n_ew; ++j) {
             const int32_t kind = k.ew[j].kind, arg = k.ew[j].arg;
@@ -230,8 +236,13 @@ __global__ __launch_bounds__(512) void pool_direct_kernel(const PoolDirectK k)
         in_off[u] = plane * (uint32_t)(k.H * k.W) + idx0[u];
         out_off[u] = (plane * (uint32_t)k.Ho + oh) * (uint32_t)k.Wo + cv * NO;
         const void *inp = image_base<DT>(k.in, img[u], k.in_extra);
+        if (k.cached) {  // the same for every lane
 #pragma unroll
-        for (int dh = 0; dh < KH; ++dh) raw[u][dh] = load_raw<DT, VEC, true>(inp, in_off[u] + dh * (uint32_t)k.W);
+            for (int dh = 0; dh < KH; ++dh) raw[u][dh] = load_raw<DT, VEC>(inp, in_off[u] + dh * (uint32_t)k.W);
+        } else {
+#pragma unroll
+            for (int dh = 0; dh < KH; ++dh) raw[u][dh] = load_raw<DT, VEC, true>(inp, in_off[u] + dh * (uint32_t)k.W);
+        }
     }
     float sc[U], sh[U];
     if constexpr (SIG == 1) {
@@ -595,12 +606,21 @@ bs_status launch_sequence(const bs_stack *s, const Sequence &q, const void *in, 
         const hipError_t e = hipGetLastError();
         return e != hipSuccess ? hip_fail(e) : BS_OK;
     }
+    // Element-wise sequences: the input through the caches where it is at most half of the chip's last cache (256 MiB), or where the stack's
+    // backward pass reads it again and it fits; else streamed.  Measured, us, streamed / cached: BatchNorm -> Add -> ReLU, 64 x 256 x 56 x 56
+    // channels-last bfloat16 (103 MB) 48.4 / 44.6, float32 (206 MB) 96 / 98; BatchNorm -> ReLU, bfloat16 33.8 / 29.5, float32 65 / 69, 64 x 256 x 28 x 28
+    // float32 18.3 / 15.6; forward and backward together, float32 (206 MB) 268 / 251 and 163 / 156.
+    const uint64_t in_bytes = (uint64_t)q.in_shape[0] * q.in_shape[1] * q.in_shape[2] * q.in_shape[3] * dtype_size(dtype);
+    const bool read_again = s->backward && q.first_op == 0 && in_bytes <= 256u << 20;
+    // (With residual operands from 32 MB on: 16 x 512 x 28 x 28 bfloat16, 13 MB, 8.3 / 8.6, 64 x 512 x 28 x 28, 51 MB, 25.2 / 24.6.)
+    const int32_t cached = (in_bytes <= 128u << 20 && (q.n_res == 0 || in_bytes > 32u << 20)) || read_again ? 1 : 0;
     switch (q.variant) {
     case BS_VARIANT_STREAM: {
         // vector widths the compiled instances exist for (guards against a plan / kernel mismatch)
         if (q.vec != 1 && q.vec != (dtype == BS_F32 ? 4 : 8)) return BS_ERR_UNSUPPORTED;
         StreamK k = q.stream;
         k.in = in; k.out = out; k.params = s->dev_params;
+        k.cached = cached;
         k.in_extra = in_extra; k.out_extra = out_extra;
         for (int j = 0; j < K_MAX_RES; ++j) k.res[j] = rp[j];
         if (k.flat) {
@@ -646,6 +666,11 @@ bs_status launch_sequence(const bs_stack *s, const Sequence &q, const void *in, 
         k.in_extra = in_extra; k.out_extra = out_extra;
         for (int j = 0; j < K_MAX_RES; ++j) k.res[j] = rp[j];
         k.idx = ip[0];
+        // Cached loads instead of streaming ones where two of a lane's rows lie in one cache line (rows below 128 bytes), and where the
+        // stack's backward pass finds it again.  Measured, us, streaming / cached:
+        // 64 x 256 x 56 x 56 bfloat16 23.9 / 22.8, 28 x 28 float32 23.1 / 22.3 (rows of 112 bytes; 224 bytes: 21.5 / 22.5); forward and
+        // backward together, 64 x 512 x 28 x 28 float32 71.5 / 62.9, 64 x 256 x 56 x 56 bfloat16 75.9 / 67.5, float32 (206 MB) 118.7 / 114.2.
+        k.cached = (uint64_t)k.W * dtype_size(dtype) < 128 || read_again;
         if (dtype == BS_BF16) {
             if (q.vec == 8) launch_direct<DT_BF16, 8>(k, grid, block, st);
             else launch_direct<DT_BF16, 4>(k, grid, block, st);
@@ -740,6 +765,7 @@ bs_status launch_sequence(const bs_stack *s, const Sequence &q, const void *in, 
     case BS_VARIANT_NHWC_STREAM:
     case BS_VARIANT_NHWC_POOL: {
         NhwcK k = q.nhwc;
+        k.cached = cached;
         // a channel slice of a channels-last tensor: the batch stride is a whole number of pixels
         // of the larger tensor (checked by the caller), the slice skips the same count per pixel
         const uint32_t hw_in = (uint32_t)(q.in_shape[2] * q.in_shape[3]), hw_out = (uint32_t)(q.out_shape[2] * q.out_shape[3]);

@@ -47,7 +47,13 @@ __global__ __launch_bounds__(512) void nhwc_stream_kernel(const NhwcK k)
             i = valid[u] ? i : base % cvn;  // a vector of the same channels at the start of the tensor
             off[u] = i * VEC;
             pixel[u] = fdiv(i, k.div_cv);
-            raw[u] = load_raw<DT, VEC, true>(k.in, off[u] + pixel[u] * k.in_xp);
+        }
+        if (k.cached) {  // the same for every lane
+#pragma unroll
+            for (int u = 0; u < U; ++u) raw[u] = load_raw<DT, VEC>(k.in, off[u] + pixel[u] * k.in_xp);
+        } else {
+#pragma unroll
+            for (int u = 0; u < U; ++u) raw[u] = load_raw<DT, VEC, true>(k.in, off[u] + pixel[u] * k.in_xp);
         }
         float x[U][VEC];
 #pragma unroll
