@@ -426,6 +426,9 @@ BS_API bs_status bs_stack_plan_backward(bs_stack *stack);
 BS_API uint64_t bs_stack_backward_workspace_bytes(const bs_stack *stack);
 /* Stages of the backward plan (-1 without one). */
 BS_API int32_t bs_stack_backward_num_stages(const bs_stack *stack);
+/* Does bs_stack_backward read the forward pass's index outputs where the caller hands them over (1), or find every pick itself (0; then a
+ * caller that keeps them for nothing else need not ask the forward pass for them)?  -1 without a backward plan. */
+BS_API int32_t bs_stack_backward_reads_indices(const bs_stack *stack);
 
 /*
  * Enqueue the backward pass on `stream`: given the stack's input and residual operands of the

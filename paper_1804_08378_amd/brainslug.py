@@ -110,6 +110,7 @@ _SIGNATURES = {
     "bs_stack_plan_backward": (C.c_int, [C.c_void_p]),
     "bs_stack_backward_workspace_bytes": (C.c_uint64, [C.c_void_p]),
     "bs_stack_backward_num_stages": (C.c_int32, [C.c_void_p]),
+    "bs_stack_backward_reads_indices": (C.c_int32, [C.c_void_p]),
     "bs_stack_backward": (C.c_int, [C.c_void_p, C.c_void_p, C.POINTER(C.c_void_p), C.POINTER(C.c_void_p), C.c_void_p,
                                     C.c_void_p, C.POINTER(C.c_void_p), C.c_void_p, C.c_uint64, C.c_void_p]),
     "bs_stack_backward_strided": (C.c_int, [C.c_void_p, C.c_void_p, C.c_int64, C.POINTER(C.c_void_p), C.POINTER(C.c_void_p),
@@ -382,6 +383,10 @@ def bs_stack_backward_workspace_bytes(handle) -> int:
     return int(load().bs_stack_backward_workspace_bytes(C.c_void_p(handle)))
 
 
+def bs_stack_backward_reads_indices(handle) -> int:
+    return int(load().bs_stack_backward_reads_indices(C.c_void_p(handle)))
+
+
 def bs_stack_backward_num_stages(handle) -> int:
     return int(load().bs_stack_backward_num_stages(C.c_void_p(handle)))
 
@@ -522,7 +527,7 @@ class Stack:
             n = _bs_torch.Plan(fns, self.handle or 0, self.in_shape, self.out_shape, code, self.layout == BS_LAYOUT_NHWC, self.res_shapes,
                                self.idx_shapes, self._workspace_bytes)
             if self._bwd_planned:
-                n.set_backward(self._bwd_workspace_bytes)
+                n.set_backward(self._bwd_workspace_bytes, self.backward_reads_indices)
             self._native = n
         return self._native
 
@@ -545,8 +550,9 @@ class Stack:
         self._bwd_planned = True
         self._bwd_workspace = None
         self._bwd_workspace_bytes = bs_stack_backward_workspace_bytes(self.handle)
+        self.backward_reads_indices = bs_stack_backward_reads_indices(self.handle) == 1
         if self._native is not None:
-            self._native.set_backward(self._bwd_workspace_bytes)
+            self._native.set_backward(self._bwd_workspace_bytes, self.backward_reads_indices)
         return self
 
     def backward(self, x, residuals, grad_out, need_input_grad=True, need_residual_grads=None, stream=None, indices=None):

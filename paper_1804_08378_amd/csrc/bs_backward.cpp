@@ -427,6 +427,14 @@ extern "C" int32_t bs_stack_backward_num_stages(const bs_stack *stack)
     return stack && stack->backward ? (int32_t)stack->backward->stages.size() : -1;
 }
 
+extern "C" int32_t bs_stack_backward_reads_indices(const bs_stack *stack)
+{
+    if (!stack || !stack->backward) return -1;
+    for (const BwdStage &g : stack->backward->stages)
+        if (g.idx_slot >= 0 && (g.kept_grid > 0 || (g.k.pool.kind == OP_MAXPOOL && !g.k.direct && !g.k.wave_rows))) return 1;
+    return 0;
+}
+
 extern "C" bs_status bs_stack_backward(const bs_stack *stack, const void *in, const void *const *residuals,
                                        const int32_t *const *indices, const void *grad_out, void *grad_in,
                                        void *const *grad_residuals, void *workspace, uint64_t workspace_bytes,

@@ -69,7 +69,7 @@ struct Plan {
     at::ScalarType dtype = at::kFloat;
     at::MemoryFormat mf = at::MemoryFormat::Contiguous;
     uint64_t ws_bytes = 0, bwd_ws_bytes = 0;
-    bool bwd_planned = false;
+    bool bwd_planned = false, bwd_reads_picks = true;
     std::mutex mutex;
     // one workspace per (device, stream) and direction: runs on different streams may overlap
     std::map<std::pair<int, void *>, at::Tensor> ws[2];
@@ -127,12 +127,13 @@ int64_t slice_stride(const Plan &p, const at::Tensor &t)
 
 bool modes_active() { return c10::impl::dispatch_mode_enabled(); }
 
-// out and picks for x; the launch.  The caller has checked the operands.
-void run_forward(Plan &p, const at::Tensor &x, const std::vector<at::Tensor> &res, at::Tensor &out, std::vector<at::Tensor> &picks)
+// out and (if wanted) picks for x; the launch.  The caller has checked the operands.
+void run_forward(Plan &p, const at::Tensor &x, const std::vector<at::Tensor> &res, at::Tensor &out, std::vector<at::Tensor> &picks, bool want_picks = true)
 {
     out = at::empty(at::IntArrayRef(p.out.data(), 4), p.options(x).memory_format(p.mf));
     picks.clear();
-    for (const Shape &s : p.idx) picks.push_back(at::empty(at::IntArrayRef(s.data(), 4), p.options(x).dtype(at::kInt).memory_format(p.mf)));
+    if (want_picks)
+        for (const Shape &s : p.idx) picks.push_back(at::empty(at::IntArrayRef(s.data(), 4), p.options(x).dtype(at::kInt).memory_format(p.mf)));
     void *stream = c10::hip::getCurrentHIPStream(x.device().index()).stream();
     const at::Tensor ws = p.workspace(false, x.device(), stream);
     c10::SmallVector<const void *, 4> rp;
@@ -182,7 +183,7 @@ struct StackNode : torch::autograd::Function<StackNode> {
         at::Tensor out;
         {
             pybind11::gil_scoped_release no_gil;
-            run_forward(*plan, x, res, out, held->picks);
+            run_forward(*plan, x, res, out, held->picks, plan->bwd_reads_picks);
         }
         torch::autograd::variable_list saved{x};
         saved.insert(saved.end(), res.begin(), res.end());
@@ -441,15 +442,17 @@ PyObject *plan_record(PyObject *self, PyObject *const *args, Py_ssize_t n)
     END_HANDLE_TH_ERRORS
 }
 
-// set_backward(workspace bytes): the backward pass is planned
-PyObject *plan_set_backward(PyObject *self, PyObject *arg)
+// set_backward(workspace bytes, reads picks): the backward pass is planned
+PyObject *plan_set_backward(PyObject *self, PyObject *args)
 {
-    const unsigned long long n = PyLong_AsUnsignedLongLong(arg);
-    if (PyErr_Occurred()) return nullptr;
+    unsigned long long n;
+    int reads;
+    if (!PyArg_ParseTuple(args, "Kp", &n, &reads)) return nullptr;
     Plan &p = plan_of(self);
     std::lock_guard<std::mutex> lock(p.mutex);
     p.bwd_ws_bytes = n;
     p.bwd_planned = true;
+    p.bwd_reads_picks = reads != 0;
     p.ws[1].clear();
     Py_RETURN_NONE;
 }
@@ -470,7 +473,7 @@ PyMethodDef plan_methods[] = {
     {"backward", reinterpret_cast<PyCFunction>(reinterpret_cast<void (*)()>(plan_backward)), METH_FASTCALL,
      "(x, residuals, grad_out, indices or None) -> (grad_x, residual gradients) or None"},
     {"record", reinterpret_cast<PyCFunction>(reinterpret_cast<void (*)()>(plan_record)), METH_FASTCALL, "(x, residuals) -> out in the autograd graph, or None"},
-    {"set_backward", plan_set_backward, METH_O, "(workspace bytes)"},
+    {"set_backward", plan_set_backward, METH_VARARGS, "(workspace bytes, reads picks)"},
     {"release", plan_release, METH_NOARGS, "-> handle"},
     {nullptr, nullptr, 0, nullptr}};
 

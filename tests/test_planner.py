@@ -382,3 +382,23 @@ def test_threads_per_group_is_honoured_by_the_register_kernels():
             assert -(-waves // (threads // 64)) - 1 <= q["grid"] <= -(-waves // (threads // 64))
         q = plan(layers, shape, dtype, threads_per_group=512)["sequences"][0]
         assert q["threads_per_group"] == 256 and q["grid"] == base["grid"]
+
+
+@pytest.mark.parametrize("layers,shape,opts,reads", [
+    ([wl.bn_params(8, 1), wl.relu(), wl.maxpool(3, 2, 1, True)], (2, 8, 30, 30), dict(layout=bs.BS_LAYOUT_NHWC), 0),   # strips find the picks
+    ([wl.bn_params(8, 1), wl.relu(), wl.maxpool(3, 2, 1, True)], (2, 8, 32, 32), {}, 0),                               # so does the row-walking kernel
+    ([wl.bn_params(8, 1), wl.relu(), wl.maxpool(2, 2, 0, True)], (2, 8, 32, 32), {}, 0),                               # and the one that owns its windows
+    ([wl.relu(), wl.avgpool(3, 1, 1, True), wl.maxpool(3, 2, 1, True), wl.relu()], (2, 8, 31, 31), {}, 0),             # two levels
+    ([wl.bn_params(8, 1), wl.relu(), wl.maxpool(5, 2, 2, True)], (2, 8, 32, 32), {}, 1),                               # gathered
+    ([wl.bn_params(8, 1), wl.leaky_relu(0.1), wl.maxpool(3, 2, 1, True)], (2, 8, 30, 30), dict(layout=bs.BS_LAYOUT_NHWC), 1),  # a small stage: kept picks are gathered
+    ([wl.bn_params(8, 1), wl.relu(), wl.maxpool(5, 2, 2)], (2, 8, 32, 32), {}, 0),                                     # no index output to read
+    ([wl.bn_params(8, 1), wl.relu()], (2, 8, 32, 32), {}, 0)])
+def test_backward_says_whether_it_reads_the_index_outputs(layers, shape, opts, reads):
+    h = bs.bs_stack_create(layers, shape, "f32")
+    try:
+        assert bs.bs_stack_backward_reads_indices(h) == -1
+        bs.bs_stack_plan(h, host_only=1, **opts)
+        bs.bs_stack_plan_backward(h)
+        assert bs.bs_stack_backward_reads_indices(h) == reads
+    finally:
+        bs.bs_stack_destroy(h)
