@@ -13,30 +13,14 @@
 // Part of bs_backward_strip.hip (its lanes, places, loads and stores).
 #pragma once
 
-// keys of N columns x V channels (column-major: all channels of a column share its code): BatchNorm, rounded, ReLU
+// keys of N columns x V channels behind BatchNorm and ReLU
 template <int DT, int V, int N>
 BS_DEV void strip_keys(const float (&x)[N * V], const float (&a)[V], const float (&b)[V], uint32_t first_code, PickKey<DT> (&key)[N * V])
 {
     float y[N * V];
 #pragma unroll
     for (int i = 0; i < N * V; ++i) y[i] = __builtin_fmaxf(__builtin_fmaf(x[i], a[i % V], b[i % V]), 0.0f);  // (rounding keeps sign and zero)
-    if constexpr (DT == DT_BF16) {
-        constexpr int E = N * V / 2 * 2;
-#pragma unroll
-        for (int i = 0; i < E; i += 2) {
-            uint32_t w = pack2<DT>(y[i], y[i + 1]);
-            asm("" : "+v"(w));  // one conversion for both halves
-            key[i].k = w << 16 | (first_code - (uint32_t)(i / V));
-            key[i + 1].k = (w & 0xffff0000u) | (first_code - (uint32_t)((i + 1) / V));
-        }
-        if constexpr (E < N * V) key[E] = PickKey<DT>::of(round_store<DT>(y[E]), first_code - (uint32_t)(E / V));
-    } else {
-#pragma unroll
-        for (int i = 0; i < N * V; ++i) {
-            if constexpr (DT == DT_F16) asm("" : "+v"(y[i]));  // two roundings: float32, then binary16 (round_store)
-            key[i] = PickKey<DT>::of(y[i], first_code - (uint32_t)(i / V));
-        }
-    }
+    column_keys<DT, V, N>(y, first_code, key);
 }
 
 template <int DT, bool CL, int V, int Q, int S, int P, typename OFF>

@@ -292,7 +292,8 @@ BS_DEV void combine_rows(const float (&m0)[N], const int32_t (&code0)[N], const 
 
 // sum[window row][column] += the gradients of the windows that picked the cell, left windows first: window b begins at column
 // X0 + b * S of the strip's G columns.  Rows FRESH, FRESH + 1 ... hold nothing yet: their first window writes.
-template <int V, int S, int N, int X0, int G, int FRESH>
+// KEYS: picks are codes of keys, (2 - row) * 16 + 15 - strip column; else 3 * row + window column.
+template <int V, int S, int N, int X0, int G, int FRESH, bool KEYS = false>
 BS_DEV void scatter(const int32_t (&pick)[N * V], const float (&g)[N * V], float (&sum0)[G * V], float (&sum1)[G * V], float (&sum2)[G * V])
 {
     auto cell = [&](auto dh_tag, auto dw_tag, auto b_tag) __attribute__((always_inline)) {
@@ -302,7 +303,7 @@ BS_DEV void scatter(const int32_t (&pick)[N * V], const float (&g)[N * V], float
         if constexpr (col >= 0 && col < G) {
 #pragma unroll
             for (int e = 0; e < V; ++e)
-                add_if_at<3 * dh + dw, (dh >= FRESH && b == b0)>(pick[b * V + e], g[b * V + e],
+                add_if_at<KEYS ? (2 - dh) * 16 + 15 - (b * S + dw) : 3 * dh + dw, (dh >= FRESH && b == b0)>(pick[b * V + e], g[b * V + e],
                                                                  (dh == 0 ? sum0 : dh == 1 ? sum1 : sum2)[col * V + e]);
         }
     };
@@ -498,7 +499,7 @@ __global__ __launch_bounds__(256) void bwd_strip_kernel(const BwdK k)
 // Q columns need Q + 2 of the average's gradient, Q / 2 + 2 windows, Q + 5 averages and Q + 7 inputs.
 // INC: every divisor is 9 (count_include_pad, nothing overhangs).
 // Measured on MI355X (halo_stress, us of a call): three stages with two forward passes through the workspace -> this kernel:
-// float32 510 -> 114, bfloat16 390 -> 121; row-major, 64 x 64 x 55 x 55 float32 291 -> 55, binary16 287 -> 41.  Bound by vector
+// float32 510 -> 106, bfloat16 390 -> 101; row-major, 64 x 64 x 55 x 55 float32 291 -> 65, binary16 287 -> 43.  Bound by vector
 // instructions (the 18 additions per average and their halo, the scans); two waves per SIMD with 8 columns beat four with 4
 // columns, which compute 9 averages per 4 columns instead of 13 per 8.
 // Lists read at run time (PRE, POST -1): 4 columns, so that nothing lies in scratch memory; three stages / 8 columns with scratch / 4
@@ -541,8 +542,14 @@ void bwd_strip2_kernel(const BwdK k)
     const int32_t r_lo = L.chunk * k.rc * 2, r_hi = min(r_lo + k.rc * 2, k.H);
     const int32_t oh_first = L.chunk * k.rc - 1;
 
-    float y[4][CX * V], T[5][Q * V], m[3][NW * V], gt[3][CG * V], hs[4][Q * V];
-    int32_t code[3][NW * V];
+    // KEYS: averages of values that are not negative, 16-bit storage -- window maxima as keys of value and place (PickKey; a code is
+    // (2 - window row) * 16 + 15 - column).  halo_stress, us, compares / keys: bfloat16 116 / 101, binary16 102 / 98; float32 106 / 116 (its keys are doubles).
+    constexpr bool KEYS = ends_in_relu(PRE) && DT != DT_F32;
+    static_assert(CA <= 15, "a code holds four bits of column");
+    using Key = PickKey<DT>;
+    float y[4][CX * V], T[5][Q * V], m[3][KEYS ? 1 : NW * V], gt[3][CG * V], hs[4][Q * V];
+    int32_t code[3][KEYS ? 1 : NW * V];
+    Key km[3][KEYS ? NW * V : 1];
     // rows are requested in order, `at` = the offset of row `next` (clamped to the plane)
     int32_t next = oh_first * 2 - 2;
     OFF at = at0.abase + (OFF)min(max(next, 0), k.H - 1) * arow;
@@ -608,16 +615,31 @@ void bwd_strip2_kernel(const BwdK k)
             a[i] = sum;
         }
         scale(std::integral_constant<int, CA * V>{}, row, L.q0 - 3, a);
-        round_store_all<DT, CA * V>(a);
         const bool ok = row >= 0 && row < k.H;
-        if (!(inside && ok)) {
+        if constexpr (KEYS) {
+            Key key[CA * V];
+            column_keys<DT, V, CA>(a, (uint32_t)((2 - decltype(dh_tag)::value) * 16 + 15), key);
+            if (!(inside && ok)) {
 #pragma unroll
-            for (int i = 0; i < CA * V; ++i) {
-                const int32_t c = L.q0 - 3 + i / V;
-                a[i] = ok && c >= 0 && c < k.W ? a[i] : -INFINITY;
+                for (int i = 0; i < CA * V; ++i) {
+                    const int32_t c = L.q0 - 3 + i / V;
+                    key[i] = Key::choose(ok && c >= 0 && c < k.W, key[i], Key::none());
+                }
             }
+#pragma unroll
+            for (int b = 0; b < NW; ++b) km[mslot][b] = Key::max(Key::max(key[2 * b], key[2 * b + 1]), key[2 * b + 2]);
         }
-        row_maxima<V, 2, NW, CA, decltype(dh_tag)::value, 1, ends_in_relu(PRE), true>(a, lead, m[mslot], code[mslot]);
+        if constexpr (!KEYS) {
+            round_store_all<DT, CA * V>(a);
+            if (!(inside && ok)) {
+#pragma unroll
+                for (int i = 0; i < CA * V; ++i) {
+                    const int32_t c = L.q0 - 3 + i / V;
+                    a[i] = ok && c >= 0 && c < k.W ? a[i] : -INFINITY;
+                }
+            }
+            row_maxima<V, 2, NW, CA, decltype(dh_tag)::value, 1, ends_in_relu(PRE), true>(a, lead, m[mslot], code[mslot]);
+        }
     };
 
 #pragma unroll
@@ -652,7 +674,16 @@ void bwd_strip2_kernel(const BwdK k)
         unpack_row<DT, CL, NW>(gw, g);
         float best[NW * V];
         int32_t pick[NW * V];
-        combine_rows<NW * V, true>(m[R0], code[R0], m[1], code[1], m[R2], code[R2], hA < 0, best, pick);
+        if constexpr (KEYS) {
+#pragma unroll
+            for (int i = 0; i < NW * V; ++i) {
+                const Key key = Key::max(Key::max(km[R0][i], km[1][i]), km[R2][i]);
+                best[i] = key.value();
+                pick[i] = (int32_t)key.code();
+            }
+        } else {
+            combine_rows<NW * V, true>(m[R0], code[R0], m[1], code[1], m[R2], code[R2], hA < 0, best, pick);
+        }
 #pragma unroll
         for (int i = 0; i < NW * V; ++i) g[i] = row_ok && win[i / V] ? g[i] : 0.0f;  // windows that do not exist give nothing
         if constexpr (POST != 0) {
@@ -661,7 +692,7 @@ void bwd_strip2_kernel(const BwdK k)
 #pragma unroll
             for (int i = 0; i < NW * V; ++i) g[i] *= tp[i];
         }
-        scatter<V, 2, NW, -2, CG, 1>(pick, g, gt[R0], gt[1], gt[R2]);  // gt's columns begin at q0 - 1
+        scatter<V, 2, NW, -2, CG, 1, KEYS>(pick, g, gt[R0], gt[1], gt[R2]);  // gt's columns begin at q0 - 1
 #pragma unroll
         for (int d = 0; d < 2; ++d) {
             const int32_t row = min(max(hA + d, 0), k.H - 1);  // rows and columns outside the plane hold zeros
@@ -685,7 +716,10 @@ void bwd_strip2_kernel(const BwdK k)
             }
         }
 #pragma unroll
-        for (int i = 0; i < NW * V; ++i) code[R2][i] -= 6;
+        for (int i = 0; i < NW * V; ++i) {
+            if constexpr (KEYS) km[R2][i] = km[R2][i].bumped(32u);  // the last row is the next window row's first
+            else code[R2][i] -= 6;
+        }
 #pragma unroll
         for (int i = 0; i < Q * V; ++i) {
             T[0][i] = T[2][i];

@@ -222,4 +222,28 @@ struct PickKey<DT_F32> {
     BS_DEV static PickKey choose(bool c, PickKey a, PickKey b) { return {c ? a.lo : b.lo, c ? a.hi : b.hi}; }
 };
 
+// Keys of N columns x V channels (all channels of a column share its code, one less per column) from values that are not negative, rounded
+// to the storage type here.
+template <int DT, int V, int N>
+BS_DEV void column_keys(float (&y)[N * V], uint32_t first_code, PickKey<DT> (&key)[N * V])
+{
+    if constexpr (DT == DT_BF16) {
+        constexpr int E = N * V / 2 * 2;
+#pragma unroll
+        for (int i = 0; i < E; i += 2) {
+            uint32_t w = pack2<DT>(y[i], y[i + 1]);
+            asm("" : "+v"(w));  // one conversion for both halves
+            key[i].k = w << 16 | (first_code - (uint32_t)(i / V));
+            key[i + 1].k = (w & 0xffff0000u) | (first_code - (uint32_t)((i + 1) / V));
+        }
+        if constexpr (E < N * V) key[E] = PickKey<DT>::of(round_store<DT>(y[E]), first_code - (uint32_t)(E / V));
+    } else {
+#pragma unroll
+        for (int i = 0; i < N * V; ++i) {
+            if constexpr (DT == DT_F16) asm("" : "+v"(y[i]));  // two roundings: float32, then binary16 (round_store)
+            key[i] = PickKey<DT>::of(y[i], first_code - (uint32_t)(i / V));
+        }
+    }
+}
+
 }  // namespace bs
