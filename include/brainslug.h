@@ -139,7 +139,8 @@ typedef enum bs_variant {
     BS_VARIANT_NHWC_POOL = 7,   /* channels-last plans only: one pooling step, a lane = one output pixel x one channel vector */
     BS_VARIANT_NHWC_TILE = 8,   /* channels-last plans only: two pooling steps, tiles of both planes with halos staged in LDS */
     BS_VARIANT_ROWS_CHAIN = 9,  /* two and more identical max-pooling steps that keep the plane's size, each with the same
-                                   kinds of element-wise operations behind it: rows ripple through all levels in registers */
+                                   kinds of element-wise operations behind it: rows ripple through all levels in registers
+                                   (channels-last: 3 x 3 with BatchNorm, ReLU, four and more) */
     BS_VARIANT_STRIPS = 11,     /* one 3 x 3 (row-major also 2 x 2 / 2) pooling step, or a 3 x 3 / 1 / 1 step and a 3 x 3 maximum, both layouts:
                                    a lane walks down a strip of output columns in registers, no LDS (chosen by the planner,
                                    force_variant does not take it)                                                        */
@@ -202,7 +203,9 @@ typedef enum bs_layout {
  *                           work-group.  With threads_per_group, tile_rows, tile_cols and
  *                           planes_per_group all 0 and lane_exchange = 0, sequences of one 3 x 3 step
  *                           or of a 3 x 3 / 1 / 1 step and a 3 x 3 maximum (no residual Add) run as
- *                           BS_VARIANT_STRIPS where that is faster.
+ *                           BS_VARIANT_STRIPS where that is faster, and four and more blocks of a 3 x 3 / 1 / 1
+ *                           maximum without indices, BatchNorm and ReLU (max_steps_per_sequence 0) as
+ *                           BS_VARIANT_ROWS_CHAIN sequences.
  *                           Row-major plans (also max_lds_bytes and force_variant 0, jit not 1) do the same
  *                           with such sequences, and with 2 x 2 / 2 steps, that would take
  *                           BS_VARIANT_LDS_TILE: nothing is built for them at plan time.

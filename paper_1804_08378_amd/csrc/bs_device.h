@@ -283,15 +283,11 @@ template <int DT, int N>
 BS_DEV void store_elems(NonTemporal, void *p, const float *v)
 {
     static_assert(N == 1 || (N == 2 && DT != DT_F32), "one register");
-    float t[N];
-#pragma unroll
-    for (int i = 0; i < N; ++i) {
-        t[i] = v[i];
-        if constexpr (DT == DT_F16) asm("" : "+v"(t[i]));  // rounded to float32 before it is rounded to binary16 (round_store)
-    }
-    if constexpr (DT == DT_F32) __builtin_nontemporal_store(t[0], static_cast<float *>(p));
-    else if constexpr (N == 2) __builtin_nontemporal_store(pack2<DT>(t[0], t[1]), static_cast<uint32_t *>(p));
-    else __builtin_nontemporal_store(half_bits<DT>(t[0]), static_cast<uint16_t *>(p));
+    if constexpr (DT == DT_F32) __builtin_nontemporal_store(v[0], static_cast<float *>(p));
+    else if constexpr (N == 2 && DT == DT_BF16) __builtin_nontemporal_store(pack2<DT>(v[0], v[1]), static_cast<uint32_t *>(p));
+    else if constexpr (N == 2)  // one by one: a product in front of the conversion is rounded once, as where one element is stored
+        __builtin_nontemporal_store((uint32_t)half_bits<DT>(v[0]) | (uint32_t)half_bits<DT>(v[1]) << 16, static_cast<uint32_t *>(p));
+    else __builtin_nontemporal_store(half_bits<DT>(v[0]), static_cast<uint16_t *>(p));
 }
 
 }  // namespace bs

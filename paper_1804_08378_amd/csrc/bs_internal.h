@@ -53,6 +53,7 @@ struct Sequence {
     PoolRows2K rows2{};
     RowsChainK chain{};
     ChainK blocks{};          // n_levels > 0: the chain as blocks of 3 x 3 maximum, BatchNorm, ReLU
+    ChainNhwcK blocks_cl{};   // n_levels > 0: the same channels-last
     LdsSeqK lds{};
     NhwcK nhwc{};
     NhwcTile2K nhwc2{};
@@ -218,6 +219,10 @@ bool blocks_compiled(int32_t dtype);
 bool blocks_launchable(const ChainK &k, int64_t planes, int64_t grid, int32_t threads);
 std::string blocks_expr(const ChainK &k, int32_t dtype);
 bs_status launch_blocks(const ChainK &k, int32_t dtype, int64_t grid, int32_t threads, void *stream);
+// ... channels-last (pool_chain_nhwc_kernel)
+bool chain_nhwc_geometry(ChainNhwcK &k, int64_t images, int32_t dtype, int32_t num_cus, int64_t *grid);
+uint64_t chain_nhwc_lds_bytes(const ChainNhwcK &k);
+bs_status launch_chain_nhwc(const ChainNhwcK &k, int64_t images, int32_t dtype, int64_t grid, void *stream);
 // the chain kernel for other lists and windows (always a run-time build)
 bool xrows_chain_buildable(const RowsChainK &k, int32_t vec);
 bool xrows_chain_launchable(const RowsChainK &k, int32_t dtype, int64_t grid, int32_t threads);

@@ -262,6 +262,22 @@ struct ChainK {
     FastDiv div_chunks, div_pitch, div_tiles, div_c;
 };
 
+// ... of a channels-last tensor (pool_chain_nhwc_kernel): a work-group takes `cols` columns of `cg` channels, a segment is a channel.
+struct ChainNhwcK {
+    const void *in;
+    void *out;
+    const float *params;
+    uint32_t in_xp, out_xp;        // elements to skip per pixel beyond the C channels
+    int32_t n_levels;
+    int32_t bn[K_BLOCKS_MAX];
+    int32_t C, H, W;
+    int32_t rc, chunks;
+    int32_t tile_w, tiles, halo_w;
+    int32_t pitch, spw, cols;
+    int32_t cg, lp, vec;           // channels per work-group, LDS floats per channel and row, channels per memory access
+    FastDiv div_groups, div_tiles, div_chunks, div_pitch, div_cv, div_nv;
+};
+
 // Channels-last (N, H, W, C in memory) sequences: element-wise only (pool.kind == 0, the list
 // in `pre`) or one pooling operation with element-wise operations before and after it.
 struct NhwcK {

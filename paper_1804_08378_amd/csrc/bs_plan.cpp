@@ -343,6 +343,12 @@ static bool plane_applicable(const bs_stack *s, int32_t first_op, int32_t n_ops)
 #define BS_CHAIN_MIN 2
 #endif
 
+// ... and the fewest blocks pool_chain_nhwc_kernel is used for (two and three run as strips).
+#if !defined(BS_BLOCKS_NHWC_MIN)
+#define BS_BLOCKS_NHWC_MIN 4
+#endif
+constexpr int32_t K_BLOCKS_NHWC_MIN = BS_BLOCKS_NHWC_MIN;
+
 static uint64_t seq_min_lds(const bs_stack *s, int32_t first_op, int32_t n_ops, int32_t threads)
 {
     if (count_pools(s, first_op, n_ops) == 0) return 0;
@@ -1262,6 +1268,51 @@ static void plan_chain(const bs_stack *s, Sequence &q, const bs_plan_options &o,
     q.redundancy = rows_loaded / (double)k.H;
 }
 
+// Channels-last: blocks <max pooling 3 x 3 / 1 / 1 without index output, BatchNorm, ReLU> in one sequence (pool_chain_nhwc_kernel).
+static bool plan_blocks_nhwc(const bs_stack *s, Sequence &q, const bs_plan_options &o, const Limits &lim)
+{
+    if (o.lane_exchange < 0 || o.threads_per_group > 0 || o.tile_rows > 0 || o.tile_cols > 0 || o.planes_per_group > 0) return false;
+    ChainNhwcK k{};
+    int32_t at = 0;  // place in the block
+    for (int32_t i = q.first_op; i < q.first_op + q.n_ops; ++i) {
+        const Op &op = s->ops[i];
+        if (at == 0) {
+            if (op.kind != OP_MAXPOOL || op.idx_slot >= 0 || op.kh != 3 || op.kw != 3 || op.sh != 1 || op.sw != 1 || op.ph != 1 || op.pw != 1 ||
+                op.out_h != op.in_h || op.out_w != op.in_w || k.n_levels >= K_BLOCKS_MAX)
+                return false;
+            k.H = op.in_h;
+            k.W = op.in_w;
+        } else if (at == 1) {
+            if (op.kind != OP_BN) return false;
+            k.bn[k.n_levels] = op.param_off;
+        } else {
+            if (op.kind != OP_RELU) return false;
+            ++k.n_levels;
+        }
+        at = (at + 1) % 3;
+    }
+    k.C = (int32_t)s->in_shape[1];
+    int64_t grid = 0;
+    if (at != 0 || k.n_levels < 2 || (uint64_t)k.W * k.C * dtype_size(s->dtype) > 0x7fffffffull || !chain_nhwc_geometry(k, s->in_shape[0], s->dtype, lim.num_cus, &grid)) return false;
+    q.blocks_cl = k;
+    q.variant = BS_VARIANT_ROWS_CHAIN;
+    q.threads = 512;
+    q.vec = k.vec;
+    q.grid = grid;
+    q.lds_bytes = chain_nhwc_lds_bytes(k);
+    q.tile_rows = k.rc;
+    q.tile_cols = k.tile_w;
+    q.planes_per_group = k.cg;
+    q.n_levels = k.n_levels;
+    q.halo_rows = 2 * k.n_levels;
+    q.halo_cols = k.tiles > 1 ? 2 * k.n_levels : 0;
+    double rows = 0, cols = 0;
+    for (int32_t c = 0; c < k.chunks; ++c) rows += std::min(k.H, (c + 1) * k.rc + k.n_levels) - std::max(0, c * k.rc - k.n_levels);
+    for (int32_t t = 0; t < k.tiles; ++t) cols += std::min(k.W, (t + 1) * k.tile_w + k.halo_w) - std::max(0, t * k.tile_w - k.halo_w);
+    q.redundancy = rows * cols / ((double)k.H * k.W);
+    return true;
+}
+
 static void plan_rows2(const bs_stack *s, Sequence &q, const bs_plan_options &o)
 {
     PoolRows2K &k = q.rows2;
@@ -1718,6 +1769,20 @@ bs_status group_sequences(bs_stack *s, const bs_plan_options &o, const Limits &l
         if (!per_layer && o.max_steps_per_sequence != 1) {
             std::vector<SeqDraft> paired;
             for (size_t i = 0; i < drafts.size(); ++i) {
+                // runs of stacked blocks: up to ten in a sequence, longer runs in even parts of at most eight
+                auto blocks = [&](size_t from, int32_t n) {
+                    Sequence trial;
+                    range_ops(SeqDraft{drafts[from].first_step, n}, trial.first_op, trial.n_ops);
+                    return plan_blocks_nhwc(s, trial, o, lim);
+                };
+                if (o.max_steps_per_sequence == 0 && i + K_BLOCKS_NHWC_MIN <= drafts.size() && blocks(i, K_BLOCKS_NHWC_MIN)) {
+                    int32_t run = K_BLOCKS_NHWC_MIN;
+                    while (i + run < drafts.size() && blocks(i + run - 1, 2)) ++run;
+                    const int32_t parts = run <= K_BLOCKS_MAX ? 1 : (run + K_CHAIN_MAX - 1) / K_CHAIN_MAX, each = (run + parts - 1) / parts;
+                    for (int32_t done = 0; done < run; done += each) paired.push_back(SeqDraft{drafts[i + done].first_step, std::min(each, run - done)});
+                    i += (size_t)run - 1;
+                    continue;
+                }
                 if (i + 1 < drafts.size()) {
                     Sequence trial;
                     trial.in_shape[0] = s->in_shape[0];
@@ -1790,7 +1855,8 @@ bs_status group_sequences(bs_stack *s, const bs_plan_options &o, const Limits &l
         q.n_levels = pools;
         bs_status st = BS_OK;
         if (nhwc) {
-            st = q.n_steps == 2 ? plan_nhwc_tile2(s, q, o, lim) : plan_nhwc(s, q, o);
+            if (q.n_steps >= K_BLOCKS_NHWC_MIN && o.max_steps_per_sequence == 0 && plan_blocks_nhwc(s, q, o, lim)) st = BS_OK;
+            else st = q.n_steps == 2 ? plan_nhwc_tile2(s, q, o, lim) : plan_nhwc(s, q, o);
         } else if (pools == 0) {
             plan_stream(s, q);
         } else if (direct_applicable(s, q.first_op, q.n_ops) && o.force_variant != BS_VARIANT_LDS_TILE) {

@@ -409,6 +409,42 @@ def test_stacked_blocks_of_any_width(shape, levels, dtype):
         assert same.all(), (rc, np.argwhere(~same)[:4])
 
 
+@pytest.mark.parametrize("shape,levels", [((1, 8, 7, 7), 10), ((2, 3, 1, 2), 4), ((1, 5, 3, 3), 9), ((2, 24, 30, 31), 4), ((1, 16, 20, 63), 6), ((3, 40, 13, 13), 8),
+                                          ((1, 16, 40, 126), 10), ((1, 12, 33, 127), 5), ((1, 8, 9, 128), 4), ((1, 33, 31, 129), 9), ((1, 8, 64, 224), 10),
+                                          ((2, 24, 56, 56), 12)])
+@pytest.mark.parametrize("dtype", ["f32", "bf16", "f16"])
+def test_stacked_blocks_channels_last(shape, levels, dtype):
+    """The same blocks channels-last, handed to the lanes through LDS: channel counts that are whole vectors, that are not, and that leave lanes
+    of a work-group without a channel; odd rows, column tiles, several chunks of rows (64 and 56 rows), runs longer than a sequence; channel
+    slices of a larger tensor.  Bit for bit, as row-major."""
+    n, c, h, w = shape
+    layers = []
+    for i in range(levels):
+        bn = wl.bn_params(c, 600 + i)
+        bn["gamma"] = bn["gamma"] * np.where(np.arange(c) % 3 == i % 3, -1.0, 1.0).astype(np.float32)
+        layers += [wl.maxpool(3, 1, 1), bn, wl.relu()]
+    x = wl.activation(shape, 76, dtype)
+    x[:, :, ::2, 1::3] = 0.5
+    x[:, :, ::3, ::4] = -np.inf
+    ref, _, _ = bf.run_stack(layers, x, [], dtype)
+    out, _, info = run_gpu(layers, x, [], dtype, layout=bs.BS_LAYOUT_NHWC)
+    assert [q["variant_name"] for q in info["sequences"]] == ["rows_chain"] * (1 if levels <= 10 else 2)
+    same = (out == ref) | (np.isnan(out) & np.isnan(ref))
+    assert same.all(), np.argwhere(~same)[:4]
+    wide = torch.zeros((n, 2 * c + 8, h, w), dtype=TORCH_DTYPE[dtype], device="cuda").contiguous(memory_format=torch.channels_last)
+    if (2 * c + 8) * wide.element_size() % 16 == 0 and c * wide.element_size() % 16 == 0:
+        wide[:, c:2 * c] = _dev(x, dtype)
+        st = bs.Stack(layers, shape, dtype).plan(layout=bs.BS_LAYOUT_NHWC)
+        dst = torch.zeros_like(wide)
+        o = dst[:, 8:8 + c]
+        bs.bs_stack_run_strided(st.handle, wide[:, c:2 * c].data_ptr(), h * w * (2 * c + 8), [], o.data_ptr(), h * w * (2 * c + 8), None,
+                                *((lambda t: (t.data_ptr(), t.numel()) if t is not None else (0, 0))(st.workspace("cuda"))), torch.cuda.current_stream().cuda_stream)
+        got = o.float().cpu().numpy()
+        assert ((got == ref) | (np.isnan(got) & np.isnan(ref))).all()
+        assert not dst[:, :8].any() and not dst[:, 8 + c:].any()
+        st.close()
+
+
 # ------------------------------------------------------------------ run-time builds
 def _built_stacks(c):
     """Signatures with no instance compiled into the library."""
