@@ -248,12 +248,17 @@ extern "C" bs_status bs_stack_plan_backward(bs_stack *stack)
         const int32_t full = stack->dtype == BS_F32 ? 4 : 8;
         const size_t S = plan->stages.size();
         uint64_t off = 0;
+        bool last_room = false;  // the last stage has room for picks
         for (size_t j = 0; j < S && st == BS_OK; ++j) {
             BwdStage &g = plan->stages[j];
             const bool nhwc = stack->opts.layout == BS_LAYOUT_NHWC;
             const PoolK &p = g.k.pool;
             const bool tiles2x2 = p.kind != 0 && p.kh == 2 && p.kw == 2 && p.sh == 2 && p.sw == 2 && p.ph == 0 && p.pw == 0 &&
                                   g.k.H == 2 * g.k.Ho && g.k.W == 2 * g.k.Wo;
+            // the same windows with a row or a column of cells left over (Ho = H / 2, Wo = W / 2: none that the edge cuts)
+            const bool cells2x2 = p.kind != 0 && p.kh == 2 && p.kw == 2 && p.sh == 2 && p.sw == 2 && p.ph == 0 && p.pw == 0 &&
+                                  g.k.Ho >= 1 && g.k.Wo >= 1 && g.k.Ho == g.k.H / 2 && g.k.Wo == g.k.W / 2;
+            const uint64_t cells = (uint64_t)(g.in_shape[0] * g.in_shape[1]) * (uint64_t)((g.k.H + 1) / 2) * (uint64_t)((g.k.W + 1) / 2);
             uint64_t lanes;
             g.k.nhwc = nhwc ? 1 : 0;
             // (two levels: the stage's pooling is the average)
@@ -294,19 +299,28 @@ extern "C" bs_status bs_stack_plan_backward(bs_stack *stack)
                     g.kept_grid = ((int64_t)t.total + 255) / 256;
                 }
             } else if (nhwc) {
-                // a lane per pixel (per window when 2 x 2 windows tile the plane) and channel vector
+                // a lane per pixel (per cell of four pixels with 2 x 2 windows) and channel vector
                 g.vec = g.k.C % full == 0 ? full : 1;
                 // (with two or more Adds in the stage the window-owning kernel would keep 4 pixels x vec channels of
                 // every residual's factors in registers and spill: those stages gather with recorded picks)
-                g.k.direct = tiles2x2 && g.vec == full && g.n_res <= 1;
-                lanes = numel(g.in_shape) / (uint64_t)g.vec / (g.k.direct ? 4 : 1);
+                // Cells at the plane's edge, and one channel per lane, against the gather and its recomputation, us: 6 x 248 x 127 x 127 float32 / bfloat16
+                // 80 -> 41 / 50 -> 26; 64 x 130 x 28 x 28 float32 40 -> 15, 16 x 132 x 56 x 56 binary16 42 -> 13, 64 x 3 x 224 x 224 bfloat16 73 -> 19.
+                g.k.direct = cells2x2 && g.n_res <= 1;
+                lanes = (g.k.direct ? cells : numel(g.in_shape)) / (uint64_t)g.vec;
                 g.k.div_wv = make_fastdiv((uint32_t)(g.k.C / g.vec));
-                g.k.div_w = make_fastdiv((uint32_t)(g.k.direct ? g.k.Wo : g.k.W));
+                g.k.div_w = make_fastdiv((uint32_t)(g.k.direct ? (g.k.W + 1) / 2 : g.k.W));
             } else {
                 // one 128-bit vector per lane; 16-bit rows of 4 mod 8 elements (28 x 28 planes): one 64-bit vector
                 g.vec = g.k.W % full == 0 ? full : (stack->dtype != BS_F32 && g.k.W % 4 == 0 ? 4 : 1);
                 // disjoint 2 x 2 windows that tile the plane: the kernel that owns whole windows
                 g.k.direct = tiles2x2 && g.vec > 1;
+                // The other planes of such windows, a 2 x 2 cell per lane, against the gather and its recomputation, us: rows of odd length, 25 x 160 x 79 x 79
+                // float32 / bfloat16 143 -> 39 / 149 -> 22; of even, 64 x 512 x 14 x 14 bfloat16 51 -> 9; of whole vectors with an odd row, 16 x 64 x 111 x 112
+                // 109 -> 19 / 133 -> 13.  (A residual would have to be read as pairs too: stages with Add keep the gather.)
+                if (!g.k.direct && cells2x2 && g.n_res == 0) {
+                    g.k.direct = K_DIRECT_CELLS;
+                    g.vec = 1;
+                }
                 // Its two rows share cache lines where they are no whole lines: read through the caches below 256 bytes.  Measured, us, streaming / cached:
                 // rows of 56 bytes 26.6 / 22.5 (64 x 512 x 28 x 28 bfloat16), 112 bytes 57.0 / 53.5, 120 bytes 17.3 / 15.1, 224 bytes 44.2 / 42.4 and 80.1 / 79.1,
                 // 448 bytes 73.2 / 73.4, 896 bytes 71.2 / 73.9.
@@ -322,8 +336,8 @@ extern "C" bs_status bs_stack_plan_backward(bs_stack *stack)
                 // without pooling: as the forward kernel left it, up to half of the last cache (forward and backward, 64 x 512 x 28 x 28 float32, BatchNorm ->
                 // Add -> ReLU 125.8 / 120.4 us, BatchNorm -> ReLU 64 x 256 x 56 x 56 bfloat16 81.1 / 76.4, float32, 206 MB, 156 / 159)
                 if (p.kind == 0) g.k.cached = numel(g.in_shape) * es <= 128u << 20;
-                lanes = numel(g.in_shape) / (uint64_t)g.vec / (g.k.direct ? 2 : 1);
-                g.k.div_wv = make_fastdiv((uint32_t)(g.k.flat ? 1 : g.k.W / g.vec));
+                lanes = g.k.direct == K_DIRECT_CELLS ? cells : numel(g.in_shape) / (uint64_t)g.vec / (g.k.direct ? 2 : 1);
+                g.k.div_wv = make_fastdiv((uint32_t)(g.k.flat ? 1 : g.k.direct == K_DIRECT_CELLS ? (g.k.W + 1) / 2 : g.k.W / g.vec));
                 if (g.k.wave_rows == 2) {
                     // two pooling levels in one kernel: 4 cells per lane whatever the element size (registers)
                     BwdK &k = g.k;
@@ -363,7 +377,7 @@ extern "C" bs_status bs_stack_plan_backward(bs_stack *stack)
             }
             if (lanes > 0x7fffffffull) { st = BS_ERR_UNSUPPORTED; break; }
             g.k.total = (uint32_t)lanes;
-            g.k.div_h = make_fastdiv((uint32_t)(g.k.direct ? g.k.Ho : g.k.H));
+            g.k.div_h = make_fastdiv((uint32_t)(g.k.direct ? (g.k.H + 1) / 2 : g.k.H));
             g.k.div_c = make_fastdiv((uint32_t)g.k.C);
             g.threads = 256;
             g.grid = (int64_t)((lanes + 255) / 256);
@@ -380,14 +394,17 @@ extern "C" bs_status bs_stack_plan_backward(bs_stack *stack)
                 g.g_off = off;
                 off += align256(numel(g.in_shape) * es);
             }
-            if (is_max) {
+            // (the cells of row-major planes record nothing; the plan's workspace keeps the size that callers know for such planes)
+            const bool room = is_max || (p.kind == OP_MAXPOOL && g.k.direct == K_DIRECT_CELLS);
+            last_room = room;
+            if (room) {
                 g.idx_off = off;
                 off += align256(numel(g.out_shape) * 4);
             }
             if (g.forward) plan->fwd_ws_bytes = std::max(plan->fwd_ws_bytes, g.forward->workspace_bytes);
         }
         if (st == BS_OK) {
-            if (plan->stages[S - 1].forward) {
+            if (plan->stages[S - 1].forward || last_room) {
                 plan->last_out_off = off;
                 off += align256(numel(plan->stages[S - 1].out_shape) * es);
             }

@@ -530,6 +530,105 @@ __global__ __launch_bounds__(256) void bwd_direct2_kernel(const BwdK k)
     store_row<DT, VEC, 2, NR>(k, 1, offs[1], img * k.gin_extra, adds, s[1], t, r);
 }
 
+// Two neighbouring cells of a row that starts anywhere: an element is aligned, the pair need not be.
+template <int DT>
+BS_DEV void load_pair(const void *base, uint32_t elem, float (&v)[2])
+{
+    if constexpr (DT == DT_F32) {
+        struct __attribute__((packed, aligned(4))) Pair { float a, b; };
+        const Pair q = *reinterpret_cast<const Pair *>(static_cast<const float *>(base) + elem);
+        v[0] = q.a;
+        v[1] = q.b;
+    } else {
+        struct __attribute__((packed, aligned(2))) Pair { uint32_t w; };
+        Raw<DT, 2> raw;
+        raw.q = reinterpret_cast<const Pair *>(static_cast<const uint16_t *>(base) + elem)->w;
+        unpack<DT, 2>(raw, v);
+    }
+}
+
+template <int DT>
+BS_DEV void store_pair(void *base, uint32_t elem, const float (&v)[2])
+{
+    if constexpr (DT == DT_F32) {
+        struct __attribute__((packed, aligned(4))) Pair { float a, b; };
+        *reinterpret_cast<Pair *>(static_cast<float *>(base) + elem) = Pair{v[0], v[1]};
+    } else {
+        struct __attribute__((packed, aligned(2))) Pair { uint32_t w; };
+        uint32_t w;
+        store_elems<DT, 2>(&w, 0, v);
+        reinterpret_cast<Pair *>(static_cast<uint16_t *>(base) + elem)->w = w;
+    }
+}
+
+// =============================================================================
+// bwd_cells2_kernel: disjoint 2 x 2 windows on the row-major planes that bwd_direct2_kernel does not take (rows that are no
+// whole vectors, an odd row or column left over) and no Add in the stage.  The plane is cut into 2 x 2 cells, ceil(H / 2) x
+// ceil(W / 2) of them; a lane owns one: two pairs, one upstream gradient, no picks and no second pass.  A cell cut by the
+// plane's edge belongs to no window: its gradient is 0, its missing places are read from the ones beside them and not written.
+// Bound by memory: 25 x 160 x 79 x 79 float32 225 MB in 39 us (5.7 TB/s; the gather behind a forward pass for its picks: 143 us), bfloat16 22 us (149).
+// =============================================================================
+template <int DT, int PRE = -1>
+__global__ __launch_bounds__(256) void bwd_cells2_kernel(const BwdK k)
+{
+    uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
+    const bool live = i < k.total;
+    i = live ? i : 0u;
+    const uint32_t crow = fdiv(i, k.div_wv);       // plane * ceil(H / 2) + oh
+    const uint32_t ow = i - crow * k.div_wv.d;     // div_wv divides by ceil(W / 2)
+    const uint32_t plane = fdiv(crow, k.div_h);    // div_h divides by ceil(H / 2)
+    const uint32_t oh = crow - plane * k.div_h.d;
+    const uint32_t img = fdiv(plane, k.div_c);
+    const int32_t c = (int32_t)(plane - img * (uint32_t)k.C);
+    const bool row1 = 2 * oh + 1 < (uint32_t)k.H, col1 = 2 * ow + 1 < (uint32_t)k.W;  // Ho = H / 2, Wo = W / 2: a window if both
+    const uint32_t off0 = (plane * (uint32_t)k.H + 2 * oh) * (uint32_t)k.W + 2 * ow;
+    const uint32_t offs[2] = {off0, row1 ? off0 + (uint32_t)k.W : off0};
+    // the last column of an odd row: the pair that ends there (W >= 3)
+    const uint32_t back = col1 ? 0u : 1u, ash = img * k.a_extra;
+    float x[2][2], t[2][2], r[1][2][2], g[1];
+#pragma unroll
+    for (int j = 0; j < 2; ++j) load_pair<DT>(k.a, audited(k, 0, 33, offs[j] - back + ash, 2), x[j]);
+    const uint32_t gh = row1 ? oh : oh - 1, gw = col1 ? ow : ow - 1;  // (Ho, Wo >= 1: a cut cell has a window beside it)
+    const uint32_t out_off = (plane * (uint32_t)k.Ho + gh) * (uint32_t)k.Wo + gw;
+    unpack<DT, 1>(load_raw<DT, 1>(k.g_out, audited(k, 1, 34, out_off + img * k.gout_extra, 1)), g);
+#pragma unroll
+    for (int j = 0; j < 2; ++j) x[j][0] = col1 ? x[j][0] : x[j][1];
+    const float gi = row1 && col1 ? g[0] : 0.0f;
+    const int32_t cs[2] = {c, c};
+    const uint32_t whole[2] = {};
+    ew_sweep_impl<DT, 2, 2, false, 0, false, PRE>(k, cs, offs, x, t, r, whole, 0, k.n_ew);
+
+    float s[2][2];
+    if (k.pool.kind == OP_MAXPOOL) {
+        float best = -INFINITY;
+        int pick = 0;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const bool more = x[q / 2][q % 2] > best;
+            best = more ? x[q / 2][q % 2] : best;
+            pick = more ? q : pick;
+        }
+#pragma unroll
+        for (int q = 0; q < 4; ++q) s[q / 2][q % 2] = pick == q ? gi : 0.0f;
+    } else {
+#pragma unroll
+        for (int q = 0; q < 4; ++q) s[q / 2][q % 2] = gi * k.pool.inv_kk;  // every window lies inside the plane: the divisor is 4
+    }
+    if (!live || !k.g_in) return;
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+        if (j == 1 && !row1) break;
+        const float v[2] = {s[j][0] * t[j][0], s[j][1] * t[j][1]};
+        const uint32_t to = offs[j] + img * k.gin_extra;
+        if (col1) {
+            store_pair<DT>(k.g_in, audited(k, 2, 35, to, 2), v);
+        } else {
+            const float one[1] = {v[0]};
+            store_elems<DT, 1>(k.g_in, audited(k, 2, 36, to, 1), one);
+        }
+    }
+}
+
 // =============================================================================
 // bwd_rows_kernel: a stage whose pooling has overlapping 3 x 3 windows (padding 1, stride S = 1 or
 // 2; BatchNorm -> ReLU -> MaxPool of the ResNet stem, the stacked pooling blocks of Section 4.4)
@@ -1029,37 +1128,48 @@ __global__ __launch_bounds__(256) void bwd_stage_nhwc_kernel(const BwdK k)
     if (live) store_row<DT, VEC, 1, NR>(k, 0, off, pix * k.gin_extra, adds, s, t, r);
 }
 
-// Disjoint 2 x 2 windows that tile the plane, channels-last: a lane owns VEC channels of one
-// window's four pixels (row-major window order: the order of the first-maximum rule).
-template <int DT, int VEC, int NR>
+// Disjoint 2 x 2 windows, channels-last: a lane owns VEC channels of one window's four pixels
+// (row-major window order: the order of the first-maximum rule).
+// ODD: a row or a column of pixels is left over beside the windows.  The plane is then cut into ceil(H / 2) x ceil(W / 2)
+// cells; one that the edge cuts belongs to no window, its gradient is 0, and its missing pixels are not written (read: the ones beside them).
+// 6 x 248 x 127 x 127 float32 216 MB in 41 us (the gather behind a forward pass for its picks: 80 us).
+template <int DT, int VEC, int NR, bool ODD>
 __global__ __launch_bounds__(256) void bwd_direct2_nhwc_kernel(const BwdK k)
 {
     uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
     const bool live = i < k.total;
     i = live ? i : 0u;
-    const uint32_t opix = fdiv(i, k.div_wv);           // (n * Ho + oh) * Wo + ow
+    const uint32_t opix = fdiv(i, k.div_wv);           // (n * Ho + oh) * Wo + ow (ODD: of the cells, not of the windows)
     const uint32_t cv = i - opix * k.div_wv.d;
     const uint32_t orow = fdiv(opix, k.div_w);         // n * Ho + oh   (div_w divides by Wo here)
-    const uint32_t ow = opix - orow * (uint32_t)k.Wo;
+    const uint32_t ow = opix - orow * k.div_w.d;
     const uint32_t n = fdiv(orow, k.div_h);            // div_h divides by Ho here
-    const uint32_t oh = orow - n * (uint32_t)k.Ho;
+    const uint32_t oh = orow - n * k.div_h.d;
     const int32_t c0 = (int32_t)(cv * VEC);
-    // input pixels (2 oh + dh, 2 ow + dw): H = 2 Ho, W = 2 Wo
+    // input pixels (2 oh + dh, 2 ow + dw): H = 2 Ho, W = 2 Wo (ODD: the places beyond the edge stand for the one before it)
+    const bool row1 = !ODD || 2 * oh + 1 < (uint32_t)k.H, col1 = !ODD || 2 * ow + 1 < (uint32_t)k.W;
+    const uint32_t down = row1 ? (uint32_t)k.W : 0u, right = col1 ? 1u : 0u;
     const uint32_t p00 = (n * (uint32_t)k.H + 2 * oh) * (uint32_t)k.W + 2 * ow;
-    const uint32_t offs[4] = {p00 * (uint32_t)k.C + (uint32_t)c0, (p00 + 1) * (uint32_t)k.C + (uint32_t)c0,
-                              (p00 + (uint32_t)k.W) * (uint32_t)k.C + (uint32_t)c0,
-                              (p00 + (uint32_t)k.W + 1) * (uint32_t)k.C + (uint32_t)c0};
-    const uint32_t out_off = opix * (uint32_t)k.C + (uint32_t)c0;
+    const uint32_t pixels[4] = {p00, p00 + right, p00 + down, p00 + down + right};
+    uint32_t offs[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) offs[j] = pixels[j] * (uint32_t)k.C + (uint32_t)c0;
+    // (ODD, Ho and Wo >= 1: a cut cell has a window beside it, whose gradient is read in place of none)
+    const uint32_t opos = ODD ? (n * (uint32_t)k.Ho + (row1 ? oh : oh - 1)) * (uint32_t)k.Wo + (col1 ? ow : ow - 1) : opix;
+    const uint32_t out_off = opos * (uint32_t)k.C + (uint32_t)c0;
 
-    const uint32_t pixels[4] = {p00, p00 + 1, p00 + (uint32_t)k.W, p00 + (uint32_t)k.W + 1};
     Raw<DT, VEC> raw[4];
 #pragma unroll
     for (int j = 0; j < 4; ++j) raw[j] = load_raw<DT, VEC, true>(k.a, audited(k, 0, 7, offs[j] + pixels[j] * k.a_extra, VEC));
-    const Raw<DT, VEC> gr = load_raw<DT, VEC, true>(k.g_out, audited(k, 1, 22, out_off + opix * k.gout_extra, VEC));
+    const Raw<DT, VEC> gr = load_raw<DT, VEC, true>(k.g_out, audited(k, 1, 22, out_off + opos * k.gout_extra, VEC));
     float x[4][VEC], t[4][VEC], r[NR ? NR : 1][4][VEC], g[VEC];
 #pragma unroll
     for (int j = 0; j < 4; ++j) unpack<DT, VEC>(raw[j], x[j]);
     unpack<DT, VEC>(gr, g);
+    if constexpr (ODD) {
+#pragma unroll
+        for (int e = 0; e < VEC; ++e) g[e] = row1 && col1 ? g[e] : 0.0f;
+    }
     const int32_t cs[4] = {c0, c0, c0, c0};
     const int32_t adds = ew_sweep<DT, VEC, 4, true, NR>(k, cs, offs, x, t, r);
 
@@ -1088,7 +1198,8 @@ __global__ __launch_bounds__(256) void bwd_direct2_nhwc_kernel(const BwdK k)
     }
     if (!live) return;
 #pragma unroll
-    for (int j = 0; j < 4; ++j) store_row<DT, VEC, 4, NR>(k, j, offs[j], pixels[j] * k.gin_extra, adds, s[j], t, r);
+    for (int j = 0; j < 4; ++j)
+        if ((j < 2 || row1) && (j % 2 == 0 || col1)) store_row<DT, VEC, 4, NR>(k, j, offs[j], pixels[j] * k.gin_extra, adds, s[j], t, r);
 }
 
 static void set_error(hipError_t e) { set_hip_error((int32_t)e); }
@@ -1129,21 +1240,24 @@ bs_status launch_backward_stage(const BwdK &k, int32_t dtype, int32_t vec, int64
     if (k.nhwc) {
         // a lane per (pixel or window, channel vector): the divisors must be the ones the kernels assume
         if ((vec != 1 && vec != full) || k.C % vec != 0 || (int64_t)k.div_wv.d * vec != k.C ||
-            (int64_t)k.div_h.d != (k.direct ? k.Ho : k.H) || (int64_t)k.div_w.d != (k.direct ? k.Wo : k.W) ||
+            (int64_t)k.div_h.d != (k.direct ? (k.H + 1) / 2 : k.H) || (int64_t)k.div_w.d != (k.direct ? (k.W + 1) / 2 : k.W) ||
             (int64_t)grid * threads < (int64_t)k.total)
             return BS_ERR_UNSUPPORTED;
         const PoolK &p = k.pool;
         if (k.direct && ((p.kind != OP_MAXPOOL && p.kind != OP_AVGSUM) || p.kh != 2 || p.kw != 2 || p.sh != 2 || p.sw != 2 ||
-                         p.ph != 0 || p.pw != 0 || k.H != 2 * k.Ho || k.W != 2 * k.Wo))
+                         p.ph != 0 || p.pw != 0 || k.Ho < 1 || k.Wo < 1 || k.Ho != k.H / 2 || k.Wo != k.W / 2))
             return BS_ERR_UNSUPPORTED;
+        const bool odd = k.H % 2 != 0 || k.W % 2 != 0;
         if (k.direct && n_add > 1) return BS_ERR_UNSUPPORTED;  // planned for the gathering kernel instead
         if (!k.direct && p.kind == OP_MAXPOOL && !k.idx) return BS_ERR_NULL;
         // windows over one pixel: at most ceil(kh / sh) x ceil(kw / sw); 2 x 2 and 3 x 3 are compiled in
         const int32_t noh = p.kind != 0 ? (p.kh + p.sh - 1) / p.sh : 0, now = p.kind != 0 ? (p.kw + p.sw - 1) / p.sw : 0;
 #define BS_LAUNCH_NHWC(DT, V)                                                          \
     do {                                                                               \
-        if (k.direct && n_add == 0) bwd_direct2_nhwc_kernel<DT, V, 0><<<g, b, 0, st>>>(k); \
-        else if (k.direct) bwd_direct2_nhwc_kernel<DT, V, 1><<<g, b, 0, st>>>(k); \
+        if (k.direct && odd && n_add == 0) bwd_direct2_nhwc_kernel<DT, V, 0, true><<<g, b, 0, st>>>(k); \
+        else if (k.direct && odd) bwd_direct2_nhwc_kernel<DT, V, 1, true><<<g, b, 0, st>>>(k); \
+        else if (k.direct && n_add == 0) bwd_direct2_nhwc_kernel<DT, V, 0, false><<<g, b, 0, st>>>(k); \
+        else if (k.direct) bwd_direct2_nhwc_kernel<DT, V, 1, false><<<g, b, 0, st>>>(k); \
         else if (noh == 2 && now == 2 && n_add == 0) bwd_stage_nhwc_kernel<DT, V, 2, 2, 0><<<g, b, 0, st>>>(k); \
         else if (noh == 2 && now == 2) bwd_stage_nhwc_kernel<DT, V, 2, 2><<<g, b, 0, st>>>(k); \
         else if (noh == 3 && now == 3 && n_add == 0) bwd_stage_nhwc_kernel<DT, V, 3, 3, 0><<<g, b, 0, st>>>(k); \
@@ -1157,6 +1271,28 @@ bs_status launch_backward_stage(const BwdK &k, int32_t dtype, int32_t vec, int64
         else if (dtype == BS_F16) { if (vec == 8) BS_LAUNCH_NHWC(DT_F16, 8); else BS_LAUNCH_NHWC(DT_F16, 1); }
         else return BS_ERR_UNSUPPORTED;
 #undef BS_LAUNCH_NHWC
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) {
+            set_error(e);
+            return BS_ERR_HIP;
+        }
+        return BS_OK;
+    }
+    if (k.direct == K_DIRECT_CELLS) {
+        const PoolK &p = k.pool;
+        if ((p.kind != OP_MAXPOOL && p.kind != OP_AVGSUM) || p.kh != 2 || p.kw != 2 || p.sh != 2 || p.sw != 2 || p.ph != 0 ||
+            p.pw != 0 || k.Ho < 1 || k.Wo < 1 || k.Ho != k.H / 2 || k.Wo != k.W / 2 || vec != 1 || n_add != 0 ||
+            (int64_t)k.div_wv.d != (k.W + 1) / 2 || (int64_t)k.div_h.d != (k.H + 1) / 2 || (int64_t)k.div_c.d != k.C ||
+            (int64_t)grid * threads < (int64_t)k.total)
+            return BS_ERR_UNSUPPORTED;
+        constexpr int BN_RELU = OP_BN + OP_RELU * K_EW_BASE;
+        const bool bn_relu = k.n_ew == 2 && k.ew[0].kind == OP_BN && k.ew[1].kind == OP_RELU;
+#define BS_LAUNCH_CELLS(DT) do { if (bn_relu) bwd_cells2_kernel<DT, BN_RELU><<<g, b, 0, st>>>(k); else bwd_cells2_kernel<DT><<<g, b, 0, st>>>(k); } while (0)
+        if (dtype == BS_F32) BS_LAUNCH_CELLS(DT_F32);
+        else if (dtype == BS_BF16) BS_LAUNCH_CELLS(DT_BF16);
+        else if (dtype == BS_F16) BS_LAUNCH_CELLS(DT_F16);
+        else return BS_ERR_UNSUPPORTED;
+#undef BS_LAUNCH_CELLS
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) {
             set_error(e);

@@ -363,6 +363,8 @@ constexpr int32_t strip_columns(bool nhwc, int32_t dtype, int32_t stride)
 }
 constexpr int64_t K_STRIP_LANES = 7 * 1024 * 64;
 
+constexpr int K_DIRECT_CELLS = 2;  // BwdK::direct
+
 // Backward pass of one stage: element-wise operations followed by at most one pooling
 // operation (pool.kind == 0: none).  Dense tensors only, row-major (NCHW) or channels-last.
 constexpr int K_BWD_EW = 16;
@@ -406,11 +408,13 @@ struct BwdK {
     FastDiv div_wv;       // by W / vec
     FastDiv div_h, div_c; // by H (direct: by Ho), by C
     int32_t cached;       // row-major stages without pooling, or direct: 1: the stage input is read through the caches, 0: streamed
-    int32_t direct;       // 1: disjoint 2 x 2 windows that tile the plane; a lane owns whole windows and
-                          // finds the max-pooling picks itself (idx unused)
+    int32_t direct;       // 1: disjoint 2 x 2 windows that tile the plane (channels-last: with or without a row or column
+                          // left over); a lane owns whole windows and finds the max-pooling picks itself (idx unused);
+                          // K_DIRECT_CELLS: a lane owns one 2 x 2 cell of the other row-major planes; total = cells,
+                          // div_wv divides by ceil(W / 2), div_h by ceil(H / 2)
     int32_t nhwc;         // 1: channels-last tensors.  A lane owns `vec` consecutive channels of one pixel (direct:
-                          // of one window's four pixels); total = pixels (direct: windows) * (C / vec), div_wv
-                          // divides by C / vec, div_h by H (direct: Ho), div_w by W (direct: Wo)
+                          // of one window's four pixels); total = pixels (direct: cells) * (C / vec), div_wv
+                          // divides by C / vec, div_h by H (direct: ceil(H / 2)), div_w by W (direct: ceil(W / 2))
     FastDiv div_w;
     int32_t flat;         // 1 (row-major, no pooling): planes are no whole number of vectors; the tensor is one run of
                           // `vec`-element vectors that may begin in one plane and end in the next; total = vectors,

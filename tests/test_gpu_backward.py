@@ -394,6 +394,27 @@ def test_disjoint_two_by_two_windows(dtype):
 
 
 @pytest.mark.parametrize("dtype", ["f32", "bf16", "f16"])
+@pytest.mark.parametrize("layout", ["nchw", "nhwc"])
+@pytest.mark.parametrize("shape", [(2, 8, 2, 3), (1, 8, 3, 2), (3, 16, 13, 9), (2, 8, 7, 16), (1, 24, 6, 31), (2, 8, 10, 14), (1, 3, 65, 67)])
+def test_disjoint_windows_beside_a_row_or_column_left_over(shape, layout, dtype):
+    """2 x 2 windows on planes that they do not tile: a lane owns a cell of the plane, the ones that the edge cuts get a gradient
+    of zero.  Lists of each kind (compiled in, read at run time, none, one Add), and every tie to the first place."""
+    c = shape[1]
+    o = {"layout": bs.BS_LAYOUT_NHWC} if layout == "nhwc" else {}
+    for pool in (wl.maxpool(2, 2), wl.avgpool(2, 2), wl.maxpool(2, 2, ceil_mode=True)):
+        for layers in ([wl.bn_params(c, 1), wl.relu(), pool], [wl.leaky_relu(0.1), pool], [pool, wl.bn_params(c, 2)], [wl.add(), wl.relu(), pool]):
+            check(layers, shape, dtype, f"2x2 windows beside a rest, {layout}, {[l['kind'] for l in layers]}", seed=3, **o)
+    layers = [wl.maxpool(2, 2)]
+    for fill in (0.0, -np.inf):
+        x = np.full(shape, fill, np.float32)
+        dy = wl.activation(wl.output_shape(layers, shape), 5, dtype)
+        ref = np.zeros(shape, np.float32)
+        ref[:, :, 0:2 * dy.shape[2]:2, 0:2 * dy.shape[3]:2] = dy
+        got, _, _ = run_gpu(layers, x, [], dy, dtype, **o)
+        assert np.array_equal(got, ref)
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16", "f16"])
 @pytest.mark.parametrize("name", list(_stacks(3)))
 def test_channels_last_plans(name, dtype):
     """The same gradients from channels-last tensors: channel counts that give whole 128-bit vectors
