@@ -96,7 +96,15 @@ BS_DEV int32_t ew_sweep_impl(const BwdK &k, const int32_t (&c)[R], const uint32_
             if constexpr (CL) {
                 // tables start at multiples of 8 floats and c[0], C are multiples of VEC: 128-bit loads
                 float sc[VEC], sh[VEC];
-                if constexpr (VEC % 4 == 0) {
+                if constexpr (FLAT) {  // elements of the whole tensor: the channels go round
+                    int32_t ch = c[0];
+#pragma unroll
+                    for (int e = 0; e < VEC; ++e) {
+                        sc[e] = k.params[arg + ch];
+                        sh[e] = k.params[arg + k.C + ch];
+                        ch = ch + 1 == k.C ? 0 : ch + 1;
+                    }
+                } else if constexpr (VEC % 4 == 0) {
 #pragma unroll
                     for (int q = 0; q < VEC / 4; ++q) {
                         const float4 a = *reinterpret_cast<const float4 *>(k.params + arg + c[0] + 4 * q);
@@ -1128,6 +1136,38 @@ __global__ __launch_bounds__(256) void bwd_stage_nhwc_kernel(const BwdK k)
     if (live) store_row<DT, VEC, 1, NR>(k, 0, off, pix * k.gin_extra, adds, s, t, r);
 }
 
+// An element-wise stage on dense channels-last tensors whose channels are no whole vectors: the tensor is one run of elements,
+// a lane takes VEC of them, each with the parameters of its own channel (from the caches); the elements behind the last whole
+// vector one at a time.  BatchNorm -> Add -> ReLU, one element per lane / this: 10 x 30 x 193 x 193 bfloat16 74 / 28 us (112 MB), float32
+// 75 / 37 (224 MB, 6 TB/s); BatchNorm -> ReLU 16 x 132 x 56 x 56 binary16 33 / 22 (40 MB: the 16 parameter requests per BatchNorm).
+template <int DT, int VEC, int NR, int PRE>
+BS_DEV void ew_nhwc_flat(const BwdK &k, uint32_t off)
+{
+    const int32_t c0[1] = {(int32_t)(off - fdiv(off, k.div_c) * (uint32_t)k.C)};
+    const uint32_t offs[1] = {off}, whole[1] = {VEC};
+    float x[1][VEC], t[1][VEC], r[NR ? NR : 1][1][VEC], s[VEC];
+    const Raw<DT, VEC> ar = load_raw<DT, VEC, true>(k.a, audited(k, 0, 37, off, VEC));
+    const Raw<DT, VEC> gr = load_raw<DT, VEC, true>(k.g_out, audited(k, 1, 38, off, VEC));
+    unpack<DT, VEC>(ar, x[0]);
+    unpack<DT, VEC>(gr, s);
+    const int32_t adds = ew_sweep_impl<DT, VEC, 1, true, NR, true, PRE>(k, c0, offs, x, t, r, whole, 0, k.n_ew);
+    store_row<DT, VEC, 1, NR>(k, 0, off, 0, adds, s, t, r);
+}
+
+template <int DT, int VEC, int NR, int PRE = -1>
+__global__ __launch_bounds__(256) void bwd_ew_nhwc_flat_kernel(const BwdK k)
+{
+    const uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
+    if (i > (k.total - 1) / VEC) return;  // total = elements of the tensor
+    const uint32_t off = i * VEC;
+    if (k.total - off >= VEC) {
+        ew_nhwc_flat<DT, VEC, NR, PRE>(k, off);
+    } else {
+#pragma clang loop unroll(disable)
+        for (uint32_t e = off; e < k.total; ++e) ew_nhwc_flat<DT, 1, NR, -1>(k, e);
+    }
+}
+
 // Disjoint 2 x 2 windows, channels-last: a lane owns VEC channels of one window's four pixels
 // (row-major window order: the order of the first-maximum rule).
 // ODD: a row or a column of pixels is left over beside the windows.  The plane is then cut into ceil(H / 2) x ceil(W / 2)
@@ -1250,6 +1290,33 @@ bs_status launch_backward_stage(const BwdK &k, int32_t dtype, int32_t vec, int64
         const bool odd = k.H % 2 != 0 || k.W % 2 != 0;
         if (k.direct && n_add > 1) return BS_ERR_UNSUPPORTED;  // planned for the gathering kernel instead
         if (!k.direct && p.kind == OP_MAXPOOL && !k.idx) return BS_ERR_NULL;
+        // element-wise and dense: one run of elements (slices leave a gap behind every pixel: one element per lane)
+        if (p.kind == 0 && vec == 1 && !k.a_extra && !k.gin_extra && !k.gout_extra) {
+            if (k.total == 0 || k.total % (uint32_t)k.C != 0 || (int64_t)k.div_c.d != k.C) return BS_ERR_UNSUPPORTED;
+            const dim3 gf((uint32_t)(((uint64_t)k.total + 256 * full - 1) / (256 * (uint64_t)full)));
+            constexpr int C_BN_RELU = OP_BN + OP_RELU * K_EW_BASE, C_BN_ADD_RELU = OP_BN + OP_ADD * K_EW_BASE + OP_RELU * K_EW_BASE * K_EW_BASE;
+            const bool bn_relu = k.n_ew == 2 && k.ew[0].kind == OP_BN && k.ew[1].kind == OP_RELU;
+            const bool bn_add_relu = k.n_ew == 3 && k.ew[0].kind == OP_BN && k.ew[1].kind == OP_ADD && k.ew[2].kind == OP_RELU;
+#define BS_LAUNCH_FLAT(DT, V)                                                                       \
+    do {                                                                                            \
+        if (bn_relu) bwd_ew_nhwc_flat_kernel<DT, V, 0, C_BN_RELU><<<gf, b, 0, st>>>(k);             \
+        else if (bn_add_relu) bwd_ew_nhwc_flat_kernel<DT, V, 1, C_BN_ADD_RELU><<<gf, b, 0, st>>>(k); \
+        else if (n_add == 0) bwd_ew_nhwc_flat_kernel<DT, V, 0><<<gf, b, 0, st>>>(k);                \
+        else if (n_add == 1) bwd_ew_nhwc_flat_kernel<DT, V, 1><<<gf, b, 0, st>>>(k);                \
+        else bwd_ew_nhwc_flat_kernel<DT, V, K_MAX_RES><<<gf, b, 0, st>>>(k);                        \
+    } while (0)
+            if (dtype == BS_F32) BS_LAUNCH_FLAT(DT_F32, 4);
+            else if (dtype == BS_BF16) BS_LAUNCH_FLAT(DT_BF16, 8);
+            else if (dtype == BS_F16) BS_LAUNCH_FLAT(DT_F16, 8);
+            else return BS_ERR_UNSUPPORTED;
+#undef BS_LAUNCH_FLAT
+            const hipError_t e = hipGetLastError();
+            if (e != hipSuccess) {
+                set_error(e);
+                return BS_ERR_HIP;
+            }
+            return BS_OK;
+        }
         // windows over one pixel: at most ceil(kh / sh) x ceil(kw / sw); 2 x 2 and 3 x 3 are compiled in
         const int32_t noh = p.kind != 0 ? (p.kh + p.sh - 1) / p.sh : 0, now = p.kind != 0 ? (p.kw + p.sw - 1) / p.sw : 0;
 #define BS_LAUNCH_NHWC(DT, V)                                                          \

@@ -394,6 +394,17 @@ def test_disjoint_two_by_two_windows(dtype):
 
 
 @pytest.mark.parametrize("dtype", ["f32", "bf16", "f16"])
+@pytest.mark.parametrize("shape", [(1, 1, 1, 1), (1, 3, 1, 2), (2, 5, 3, 3), (1, 7, 13, 11), (3, 9, 1, 19), (2, 30, 29, 37), (1, 51, 64, 65), (2, 1, 33, 3)])
+def test_channels_last_elementwise_over_the_whole_tensor(shape, dtype):
+    """Channels that are no whole vectors: vectors over the whole tensor whose elements take their own channels' parameters, a rest
+    of single elements; fewer channels than a vector holds, tensors smaller than one vector; lists of every kind, up to four Adds."""
+    c = shape[1]
+    for layers in ([wl.bn_params(c, 1), wl.relu()], [wl.bn_params(c, 2), wl.add(), wl.relu()], [wl.add(), wl.bn_params(c, 3)],
+                   [wl.leaky_relu(0.1), wl.bn_params(c, 4), wl.clamp(-1.0, 1.0)], [wl.add(), wl.bn_params(c, 5), wl.add(), wl.relu(), wl.add(), wl.add()]):
+        check(layers, shape, dtype, f"channels-last, flat, {[l['kind'] for l in layers]}", seed=6, layout=bs.BS_LAYOUT_NHWC)
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16", "f16"])
 @pytest.mark.parametrize("layout", ["nchw", "nhwc"])
 @pytest.mark.parametrize("shape", [(2, 8, 2, 3), (1, 8, 3, 2), (3, 16, 13, 9), (2, 8, 7, 16), (1, 24, 6, 31), (2, 8, 10, 14), (1, 3, 65, 67)])
 def test_disjoint_windows_beside_a_row_or_column_left_over(shape, layout, dtype):
