@@ -79,6 +79,36 @@ __global__ __launch_bounds__(512) void nhwc_stream_kernel(const NhwcK k)
     }
 }
 
+// Element-wise only, dense tensors whose channels are no whole vectors: the tensor is one run of elements, a lane takes VEC of
+// them, each with its own channel's parameters (from the caches); the elements behind the last whole vector one at a time.
+// BatchNorm -> Add -> ReLU, one element per lane / this, us: 10 x 30 x 193 x 193 bfloat16 52 / 22, float32 50 / 24 (134 MB, 5.6 TB/s); BatchNorm ->
+// ReLU 16 x 132 x 56 x 56 binary16 24 / 22 (the parameter requests).
+template <int DT, int VEC, int CODE>
+BS_DEV void stream_flat(const NhwcK &k, uint32_t off)
+{
+    const uint32_t c0 = off - fdiv(off, k.div_cv) * k.div_cv.d;  // one element per vector in the plan: div_cv divides by C
+    const uint32_t offs[1] = {off};
+    float x[1][VEC];
+    if (k.cached) unpack<DT, VEC>(load_raw<DT, VEC>(k.in, off), x[0]);  // the same for every lane
+    else unpack<DT, VEC>(load_raw<DT, VEC, true>(k.in, off), x[0]);
+    apply_ew_nhwc<DT, VEC, 1, CODE, true>(x, c0, offs, k.pre, k.n_pre, k.params, k.C, k.res);
+    store_elems<DT, VEC>(k.out, off, x[0]);
+}
+
+template <int DT, int VEC, int CODE = -1>
+__global__ __launch_bounds__(512) void nhwc_stream_flat_kernel(const NhwcK k)
+{
+    const uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
+    if (i > (k.total - 1) / VEC) return;  // total = elements of the tensor
+    const uint32_t off = i * VEC;
+    if (k.total - off >= VEC) {
+        stream_flat<DT, VEC, CODE>(k, off);
+    } else {
+#pragma clang loop unroll(disable)
+        for (uint32_t e = off; e < k.total; ++e) stream_flat<DT, 1, -1>(k, e);
+    }
+}
+
 // What a lane adds to its running maximum / sum for one window cell.
 template <int VEC, bool IDX>
 BS_DEV void take_cell(bool is_max, const float (&v)[VEC], int32_t cell_index, float (&acc)[VEC], int32_t (&bi)[VEC])
@@ -481,6 +511,18 @@ static bs_status launch_nhwc_t(const NhwcK &k, int32_t dtype, dim3 grid, dim3 bl
             }
             if (code == BN_ADD_RELU) {
                 nhwc_stream_kernel<DT, VEC, K_STREAM_U, BN_ADD_RELU><<<grid, block, 0, st>>>(k);
+                return BS_OK;
+            }
+        }
+        if constexpr (VEC == 1) {
+            // dense: one run of elements (slices leave a gap behind every pixel: one element per lane)
+            if (!k.in_xp && !k.out_xp && k.total > 0 && (int64_t)k.div_cv.d == k.C && k.total % (uint32_t)k.C == 0) {
+                constexpr int V = DT == DT_F32 ? 4 : 8;
+                const dim3 gf((uint32_t)(((uint64_t)k.total + 256 * V - 1) / (256 * V)));
+                const int32_t code = list_code(k.pre, k.n_pre);
+                if (code == BN_RELU) nhwc_stream_flat_kernel<DT, V, BN_RELU><<<gf, dim3(256), 0, st>>>(k);
+                else if (code == BN_ADD_RELU) nhwc_stream_flat_kernel<DT, V, BN_ADD_RELU><<<gf, dim3(256), 0, st>>>(k);
+                else nhwc_stream_flat_kernel<DT, V><<<gf, dim3(256), 0, st>>>(k);
                 return BS_OK;
             }
         }

@@ -27,7 +27,8 @@ BS_DEV void load_params(const float *__restrict__ params, uint32_t off, float (&
 //           element res_base (the same for all lanes)
 //   CODE    >= 0: the list's kinds as a code of base-K_EW_BASE digits (n_ew is ignored): the list unrolls into
 //           straight code and only the arguments come from `ew`; -1: kinds and length are read at run time
-template <int DT, int VEC, int U, int CODE = -1>
+//   FLAT    the vectors are runs of the whole tensor: element i holds channel c0 + i, starting again at 0 behind the last one
+template <int DT, int VEC, int U, int CODE = -1, bool FLAT = false>
 BS_DEV void apply_ew_nhwc(float (&x)[U][VEC], uint32_t c0, const uint32_t (&off)[U], const EwOp *ew,
                           int32_t n_ew, const float *__restrict__ params, int32_t C, const void *const *res,
                           uint32_t res_base = 0)
@@ -35,8 +36,18 @@ BS_DEV void apply_ew_nhwc(float (&x)[U][VEC], uint32_t c0, const uint32_t (&off)
     auto one = [&](const int32_t kind, const int32_t arg) {
         if (kind == OP_BN) {
             float sc[VEC], sh[VEC];
-            load_params<VEC>(params, (uint32_t)arg + c0, sc);
-            load_params<VEC>(params, (uint32_t)(arg + C) + c0, sh);
+            if constexpr (FLAT) {
+                uint32_t ch = c0;
+#pragma unroll
+                for (int i = 0; i < VEC; ++i) {
+                    sc[i] = params[(uint32_t)arg + ch];
+                    sh[i] = params[(uint32_t)(arg + C) + ch];
+                    ch = ch + 1 == (uint32_t)C ? 0u : ch + 1;
+                }
+            } else {
+                load_params<VEC>(params, (uint32_t)arg + c0, sc);
+                load_params<VEC>(params, (uint32_t)(arg + C) + c0, sh);
+            }
 #pragma unroll
             for (int u = 0; u < U; ++u) {
 #pragma unroll

@@ -891,6 +891,19 @@ NHWC_SHAPES = [(2, 8, 13, 11), (1, 16, 9, 16), (2, 12, 12, 10), (3, 5, 7, 9), (1
                (1, 1, 6, 5)]
 
 
+@pytest.mark.parametrize("dtype", ["f32", "bf16", "f16"])
+@pytest.mark.parametrize("shape", [(1, 1, 1, 1), (1, 3, 1, 2), (2, 5, 3, 3), (1, 7, 13, 11), (3, 9, 1, 19), (2, 30, 29, 37), (1, 51, 64, 65), (2, 1, 33, 3)])
+def test_channels_last_elementwise_over_the_whole_tensor(shape, dtype):
+    """Channels that are no whole vectors: vectors over the whole tensor whose elements take their own channels' parameters, a rest
+    of single elements; fewer channels than a vector holds, tensors smaller than one vector."""
+    c = shape[1]
+    for layers in ([wl.bn_params(c, 1), wl.relu()], [wl.bn_params(c, 2), wl.add(), wl.relu()], [wl.add(), wl.bn_params(c, 3)],
+                   [wl.leaky_relu(0.1), wl.bn_params(c, 4), wl.clamp(-1.0, 1.0)], [wl.add(), wl.bn_params(c, 5), wl.add(), wl.relu()]):
+        x = wl.activation(shape, 7, dtype)
+        res = [wl.activation(r, 8 + i, dtype) for i, r in enumerate(wl.residual_shapes(layers, shape))]
+        check(layers, x, res, dtype, f"channels-last, flat, {[l['kind'] for l in layers]}", layout=bs.BS_LAYOUT_NHWC)
+
+
 @pytest.mark.parametrize("shape", NHWC_SHAPES)
 @pytest.mark.parametrize("dtype", ["f32", "bf16", "f16"])
 def test_channels_last_plans_match_the_oracle(shape, dtype):
