@@ -10,6 +10,7 @@ from __future__ import annotations
 
 import ctypes as C
 import os
+import threading
 
 import numpy as np
 
@@ -479,6 +480,9 @@ def batch_stride_nhwc(t):
 
 
 # ---- convenience wrapper -----------------------------------------------------------------
+_native_lock = threading.Lock()  # held while a stack's native object is made
+
+
 class Stack:
     """A planned stack bound to torch tensors (device memory and streams only)."""
 
@@ -517,19 +521,23 @@ class Stack:
     def native(self):
         """The plan's native calls (`csrc/bs_torch.cpp`): every method takes the plain case -- dense torch tensors of the plan's
         shapes, type, memory layout and device, torch's current stream -- and returns None for any other."""
-        if self._native is None:
+        native = self._native
+        if native is None:
             import torch  # noqa: F401 (the module links against it)
             from . import _bs_torch
-            _bs_torch.set_error(BrainSlugError)
-            lib = load()
-            fns = tuple(C.cast(f, C.c_void_p).value for f in (lib.bs_stack_run_strided, lib.bs_stack_backward_strided, lib.bs_stack_destroy))
-            code = (torch.float32, torch.bfloat16, torch.float16).index(self.torch_dtype())
-            n = _bs_torch.Plan(fns, self.handle or 0, self.in_shape, self.out_shape, code, self.layout == BS_LAYOUT_NHWC, self.res_shapes,
-                               self.idx_shapes, self._workspace_bytes)
-            if self._bwd_planned:
-                n.set_backward(self._bwd_workspace_bytes, self.backward_reads_indices)
-            self._native = n
-        return self._native
+            with _native_lock:  # one object per plan: it owns the handle, a second one would destroy it when it goes
+                native = self._native
+                if native is None:
+                    _bs_torch.set_error(BrainSlugError)
+                    lib = load()
+                    fns = tuple(C.cast(f, C.c_void_p).value for f in (lib.bs_stack_run_strided, lib.bs_stack_backward_strided, lib.bs_stack_destroy))
+                    code = (torch.float32, torch.bfloat16, torch.float16).index(self.torch_dtype())
+                    native = _bs_torch.Plan(fns, self.handle or 0, self.in_shape, self.out_shape, code, self.layout == BS_LAYOUT_NHWC,
+                                            self.res_shapes, self.idx_shapes, self._workspace_bytes)
+                    if self._bwd_planned:
+                        native.set_backward(self._bwd_workspace_bytes, self.backward_reads_indices)
+                    self._native = native
+        return native
 
     def plan(self, **opts):
         if self._native is not None:  # bound to the plan that goes

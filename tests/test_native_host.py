@@ -1,0 +1,54 @@
+"""The native calls' object (csrc/bs_torch.cpp) without a GPU: who owns a stack's handle, and the buffers it keeps."""
+import ctypes as C
+import threading
+import time
+
+import pytest
+import torch  # noqa: F401 (the native module links against it)
+
+from paper_1804_08378_amd import _bs_torch
+from paper_1804_08378_amd import brainslug as bs
+from paper_1804_08378_amd import workloads as wl
+
+SHAPE = (2, 8, 12, 12)
+
+
+class _Library:
+    """The library with a destroy function that also counts."""
+
+    def __init__(self, lib):
+        self._lib, self.destroyed = lib, []
+        self.bs_stack_destroy = C.CFUNCTYPE(None, C.c_void_p)(lambda h: self.destroyed.append(h))
+
+    def __getattr__(self, name):
+        return getattr(self._lib, name)
+
+
+def _stack(layers=None, **opts):
+    return bs.Stack(layers or [wl.bn_params(8, 1), wl.relu(), wl.maxpool(3, 2, 1)], SHAPE, "f32").plan(host_only=1, **opts)
+
+
+def test_threads_that_ask_at_once_share_one_native_object(monkeypatch):
+    """The object owns the handle: were two made, the one that is dropped would destroy it under the other."""
+    lib = _Library(bs.load())
+    monkeypatch.setattr(bs, "load", lambda: lib)
+    made, real = [], _bs_torch.Plan
+
+    def slow(*args):
+        made.append(real(*args))
+        time.sleep(0.2)  # every other thread gets to ask meanwhile
+        return made[-1]
+
+    monkeypatch.setattr(_bs_torch, "Plan", slow)
+    st, got = _stack(), []
+    threads = [threading.Thread(target=lambda: got.append(st.native())) for _ in range(4)]
+    [t.start() for t in threads]
+    [t.join() for t in threads]
+    assert len(made) == 1 and all(g is made[0] for g in got)
+    handle = st.handle
+    made.clear()
+    got.clear()
+    assert lib.destroyed == []
+    del st
+    assert lib.destroyed == [handle]
+    lib._lib.bs_stack_destroy(handle)
