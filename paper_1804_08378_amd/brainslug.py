@@ -480,7 +480,7 @@ def batch_stride_nhwc(t):
 
 
 # ---- convenience wrapper -----------------------------------------------------------------
-_native_lock = threading.Lock()  # held while a stack's native object is made
+_native_lock = threading.Lock()  # held while a stack's native object is made or its backward pass planned
 
 
 class Stack:
@@ -554,14 +554,26 @@ class Stack:
 
     def plan_backward(self):
         """Plan the backward pass (after `plan`; for the plan's memory layout)."""
+        with _native_lock:
+            self._plan_backward()
+        return self
+
+    def need_backward(self):
+        """Plan the backward pass unless it is planned: threads that come here at once plan it once (a second plan would take the
+        place of the one that is running)."""
+        if not self._bwd_planned:
+            with _native_lock:
+                if not self._bwd_planned:
+                    self._plan_backward()
+
+    def _plan_backward(self):
         bs_stack_plan_backward(self.handle)
-        self._bwd_planned = True
         self._bwd_workspace = None
         self._bwd_workspace_bytes = bs_stack_backward_workspace_bytes(self.handle)
         self.backward_reads_indices = bs_stack_backward_reads_indices(self.handle) == 1
         if self._native is not None:
             self._native.set_backward(self._bwd_workspace_bytes, self.backward_reads_indices)
-        return self
+        self._bwd_planned = True
 
     def backward(self, x, residuals, grad_out, need_input_grad=True, need_residual_grads=None, stream=None, indices=None):
         """Enqueue the backward pass; returns (grad_x or None, [grad_residual or None, ...]).
@@ -570,8 +582,7 @@ class Stack:
         `x` and `residuals` are the forward pass's operands, `grad_out` the gradient with respect
         to its output; all dense tensors of the stack's dtype in the plan's memory layout (the
         gradients come back in that layout)."""
-        if not self._bwd_planned:
-            self.plan_backward()
+        self.need_backward()
         if need_input_grad and need_residual_grads is None and stream is None:
             done = self.native().backward(x, residuals, grad_out, indices)
             if done is not None:
@@ -722,8 +733,7 @@ class Stack:
         None; batch strides in elements for `x`, `grad_out`, `grad_x` that are channel slices, 0 = dense).
         The library still checks strides, alignment, aliasing and the workspace."""
         import torch
-        if not self._bwd_planned:
-            self.plan_backward()
+        self.need_backward()
         n = self._bwd_workspace_bytes
         ptr = C.c_void_p * max(1, self.n_res)
         res = ptr(*[r.data_ptr() for r in residuals]) if residuals else None

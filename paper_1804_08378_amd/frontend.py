@@ -145,11 +145,10 @@ class _StackFunction(torch.autograd.Function):
         st = module.plan_for(x.shape, x.dtype, nhwc, keep_picks=True)
         mf = torch.channels_last if nhwc else torch.contiguous_format
         out = torch.empty(st.out_shape, dtype=x.dtype, device=x.device, memory_format=mf)
-        if not st._bwd_planned:
-            try:
-                st.plan_backward()
-            except bs.BrainSlugError:
-                pass  # the backward pass, if it comes to one, says so
+        try:
+            st.need_backward()
+        except bs.BrainSlugError:
+            pass  # the backward pass, if it comes to one, says so
         # the last max pooling's picks, where the backward pass reads them, are kept for it (saves recomputing them)
         wanted = not st._bwd_planned or st.backward_reads_indices
         picks = [torch.empty(sh, dtype=torch.int32, device=x.device, memory_format=mf) for sh in st.idx_shapes] if wanted else []

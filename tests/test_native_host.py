@@ -52,3 +52,29 @@ def test_threads_that_ask_at_once_share_one_native_object(monkeypatch):
     del st
     assert lib.destroyed == [handle]
     lib._lib.bs_stack_destroy(handle)
+
+
+def test_threads_that_need_the_backward_plan_at_once_plan_it_once(monkeypatch):
+    """Planning again frees the plan that another thread may be running."""
+    calls, real = [], bs.bs_stack_plan_backward
+
+    def slow(handle):
+        calls.append(handle)
+        time.sleep(0.2)
+        return real(handle)
+
+    monkeypatch.setattr(bs, "bs_stack_plan_backward", slow)
+    st = _stack()
+    native, x = st.native(), torch.zeros(SHAPE)
+
+    def first_call():
+        with pytest.raises(Exception):  # no device: what is looked at is who plans
+            st.backward(x, [], torch.zeros(1))
+
+    threads = [threading.Thread(target=first_call) for _ in range(4)]
+    [t.start() for t in threads]
+    [t.join() for t in threads]
+    assert len(calls) == 1 and st._bwd_planned and st.native() is native
+    st.plan_backward()  # asked for by name: planned anew
+    assert len(calls) == 2
+    st.close()
