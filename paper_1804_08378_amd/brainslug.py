@@ -495,10 +495,10 @@ class Stack:
         self.n_idx = bs_stack_num_index_outputs(self.handle)
         self.res_shapes = [bs_stack_residual_shape(self.handle, i) for i in range(self.n_res)]
         self.idx_shapes = [bs_stack_index_shape(self.handle, i) for i in range(self.n_idx)]
-        self._workspace = None
+        self._workspace = {}
         self._workspace_bytes = 0
         self._fast = None
-        self._bwd_workspace = None
+        self._bwd_workspace = {}
         self._bwd_planned = False
         self._native = None
         self.layout = BS_LAYOUT_NCHW
@@ -507,6 +507,7 @@ class Stack:
         if getattr(self, "_native", None) is not None:
             self._native.release()
             self._native = None
+        self._workspace, self._bwd_workspace = {}, {}
         if getattr(self, "handle", None) and bs_stack_destroy is not None:
             bs_stack_destroy(self.handle)
             self.handle = None
@@ -545,10 +546,10 @@ class Stack:
             self._native = None
         bs_stack_plan(self.handle, **opts)
         self.layout = int(opts.get("layout", BS_LAYOUT_NCHW))
-        self._workspace = None
+        self._workspace = {}
         self._fast = None
         self._workspace_bytes = bs_stack_workspace_bytes(self.handle)
-        self._bwd_workspace = None
+        self._bwd_workspace = {}
         self._bwd_planned = False
         return self
 
@@ -568,7 +569,7 @@ class Stack:
 
     def _plan_backward(self):
         bs_stack_plan_backward(self.handle)
-        self._bwd_workspace = None
+        self._bwd_workspace = {}
         self._bwd_workspace_bytes = bs_stack_backward_workspace_bytes(self.handle)
         self.backward_reads_indices = bs_stack_backward_reads_indices(self.handle) == 1
         if self._native is not None:
@@ -649,19 +650,15 @@ class Stack:
         if not n:
             return None
         dev = torch.device(device)
+        if dev.index is None and dev.type == "cuda":
+            dev = torch.device("cuda", torch.cuda.current_device())
         if stream is None:
             stream = torch.cuda.current_stream(dev).cuda_stream
         cache = self._bwd_workspace if backward else self._workspace
-        if cache is None:
-            cache = {}
-            if backward:
-                self._bwd_workspace = cache
-            else:
-                self._workspace = cache
-        key = (dev.index if dev.index is not None else torch.cuda.current_device(), int(stream or 0))
+        key = (dev.index, int(stream or 0))
         ws = cache.get(key)
-        if ws is None or ws.numel() < n:
-            ws = cache[key] = torch.empty(n, dtype=torch.uint8, device=dev)
+        if ws is None:  # the native calls' own buffer: one for both
+            ws = cache[key] = self.native().workspace(backward, dev, int(stream or 0))
         return ws
 
     def run(self, x, residuals=(), out=None, indices=None, stream=None):

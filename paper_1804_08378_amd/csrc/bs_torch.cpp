@@ -14,6 +14,7 @@
 #include <c10/core/impl/TorchDispatchModeTLS.h>
 #include <c10/hip/HIPStream.h>
 #include <c10/util/SmallVector.h>
+#include <torch/csrc/Device.h>
 #include <torch/csrc/Exceptions.h>
 #include <torch/csrc/autograd/custom_function.h>
 #include <torch/csrc/autograd/python_variable.h>
@@ -457,6 +458,20 @@ PyObject *plan_set_backward(PyObject *self, PyObject *args)
     Py_RETURN_NONE;
 }
 
+// workspace(backward?, device, raw stream) -> the buffer that calls on this stream hand intermediate tensors through, or None
+PyObject *plan_workspace(PyObject *self, PyObject *args)
+{
+    HANDLE_TH_ERRORS
+    int bwd;
+    PyObject *dev;
+    unsigned long long stream;
+    if (!PyArg_ParseTuple(args, "pO!K", &bwd, &THPDeviceType, &dev, &stream)) return nullptr;
+    const at::Tensor t = plan_of(self).workspace(bwd != 0, reinterpret_cast<THPDevice *>(dev)->device, reinterpret_cast<void *>(stream));
+    if (!t.defined()) Py_RETURN_NONE;
+    return THPVariable_Wrap(t);
+    END_HANDLE_TH_ERRORS
+}
+
 // release() -> handle: nothing runs through this object any more, and the caller destroys the handle (0: released before)
 PyObject *plan_release(PyObject *self, PyObject *) { return PyLong_FromVoidPtr(plan_of(self).release()); }
 
@@ -474,6 +489,7 @@ PyMethodDef plan_methods[] = {
      "(x, residuals, grad_out, indices or None) -> (grad_x, residual gradients) or None"},
     {"record", reinterpret_cast<PyCFunction>(reinterpret_cast<void (*)()>(plan_record)), METH_FASTCALL, "(x, residuals) -> out in the autograd graph, or None"},
     {"set_backward", plan_set_backward, METH_VARARGS, "(workspace bytes, reads picks)"},
+    {"workspace", plan_workspace, METH_VARARGS, "(backward, device, raw stream) -> buffer or None"},
     {"release", plan_release, METH_NOARGS, "-> handle"},
     {nullptr, nullptr, 0, nullptr}};
 

@@ -162,3 +162,20 @@ def test_threads_and_streams_have_their_own_workspaces():
     [t.start() for t in threads]
     [t.join() for t in threads]
     assert not wrong
+
+
+def test_a_second_call_holds_no_more_memory_than_the_first():
+    """The first call of a module plans and runs through Python, later ones natively: both use one workspace per direction."""
+    shape = (4, 8, 32, 32)
+    m = BrainSlugStack.from_layers([wl.maxpool(3, 1, 1), wl.bn_params(8, 3), wl.leaky_relu(0.1), wl.maxpool(5, 2, 2), wl.relu()], [""], max_steps_per_sequence=1).eval()
+    x = torch.randn(shape, device="cuda", requires_grad=True)
+    held = []
+    for _ in range(3):
+        m(x.detach())
+        torch.autograd.grad(m(x).sum(), x)
+        torch.cuda.synchronize()
+        held.append(torch.cuda.memory_allocated())
+    st = m.plan_for(x.shape, x.dtype, False, keep_picks=True)
+    assert st._workspace_bytes > 0 and st._bwd_workspace_bytes > 0
+    assert held[1] == held[0] and held[2] == held[0]
+    m.close()

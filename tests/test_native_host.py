@@ -78,3 +78,18 @@ def test_threads_that_need_the_backward_plan_at_once_plan_it_once(monkeypatch):
     st.plan_backward()  # asked for by name: planned anew
     assert len(calls) == 2
     st.close()
+
+
+def test_python_and_native_calls_share_one_workspace():
+    """Calls that go through Python (the first one, channel slices) and native ones on a stream use one buffer, forward and backward each."""
+    st = _stack([wl.maxpool(3, 1, 1), wl.leaky_relu(0.1), wl.avgpool(2, 2), wl.relu(), wl.maxpool(3, 1, 1)], max_steps_per_sequence=1).plan_backward()
+    assert st._workspace_bytes > 0 and st._bwd_workspace_bytes > 0
+    for backward, n in ((False, st._workspace_bytes), (True, st._bwd_workspace_bytes)):
+        a = st.workspace("cpu", 5, backward)
+        assert a.numel() == n and a.data_ptr() == st.native().workspace(backward, torch.device("cpu"), 5).data_ptr()
+        assert a.data_ptr() == st.workspace("cpu", 5, backward).data_ptr()
+        other = st.native().workspace(backward, torch.device("cpu"), 6)  # another stream, asked for by a native call first
+        assert other.data_ptr() != a.data_ptr() and st.workspace("cpu", 6, backward).data_ptr() == other.data_ptr()
+    st.plan(host_only=1)  # one sequence: nothing to hand over, nothing kept
+    assert st.workspace("cpu", 5) is None and not st._workspace and st.native().workspace(False, torch.device("cpu"), 5) is None
+    st.close()
