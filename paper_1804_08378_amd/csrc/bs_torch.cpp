@@ -73,7 +73,8 @@ struct Plan {
     bool bwd_planned = false, bwd_reads_picks = true;
     std::mutex mutex;
     // one workspace per (device, stream) and direction: runs on different streams may overlap
-    std::map<std::pair<int, void *>, at::Tensor> ws[2];
+    using Buffers = std::map<std::pair<int, void *>, at::Tensor>;
+    Buffers ws[2];
 
     ~Plan()
     {
@@ -82,21 +83,28 @@ struct Plan {
     // Closed or planned anew: the handle is the Python object's again, nothing runs here any more.
     void *release()
     {
+        Buffers old[2];
         std::lock_guard<std::mutex> lock(mutex);
         void *h = handle;
         handle = nullptr;
-        ws[0].clear();
-        ws[1].clear();
+        for (int i = 0; i < 2; ++i) old[i].swap(ws[i]);
         return h;
     }
+    // Nothing is allocated or freed under the mutex: the allocator may call into the interpreter, whose lock the thread that waits for the
+    // mutex may hold.
     at::Tensor workspace(bool bwd, const at::Device &dev, void *stream)
     {
         const uint64_t n = bwd ? bwd_ws_bytes : ws_bytes;
         if (!n) return {};
+        const Buffers::key_type key{dev.index(), stream};
+        {
+            std::lock_guard<std::mutex> lock(mutex);
+            const auto it = ws[bwd].find(key);
+            if (it != ws[bwd].end()) return it->second;
+        }
+        const at::Tensor t = at::empty({(int64_t)n}, at::TensorOptions().dtype(at::kByte).device(dev));
         std::lock_guard<std::mutex> lock(mutex);
-        at::Tensor &t = ws[bwd ? 1 : 0][{dev.index(), stream}];
-        if (!t.defined() || (uint64_t)t.numel() < n) t = at::empty({(int64_t)n}, at::TensorOptions().dtype(at::kByte).device(dev));
-        return t;
+        return ws[bwd].emplace(key, t).first->second;  // (another thread's, if it was faster)
     }
     at::TensorOptions options(const at::Tensor &like) const { return at::TensorOptions().dtype(dtype).device(like.device()); }
 };
@@ -142,7 +150,7 @@ void run_forward(Plan &p, const at::Tensor &x, const std::vector<at::Tensor> &re
     for (const at::Tensor &r : res) rp.push_back(r.data_ptr());
     for (const at::Tensor &t : picks) ip.push_back(static_cast<int32_t *>(t.data_ptr()));
     const int rc = p.run(p.handle, x.data_ptr(), 0, res.empty() ? nullptr : rp.data(), out.data_ptr(), 0, picks.empty() ? nullptr : ip.data(),
-                         ws.defined() ? ws.data_ptr() : nullptr, p.ws_bytes, stream);
+                         ws.defined() ? ws.data_ptr() : nullptr, ws.defined() ? (uint64_t)ws.numel() : 0, stream);
     if (rc != 0) throw CallFailed(rc, "bs_stack_run");
 }
 
@@ -166,7 +174,7 @@ void run_backward(Plan &p, const at::Tensor &x, const std::vector<at::Tensor> &r
     for (const at::Tensor &t : picks) ip.push_back(t.defined() ? static_cast<const int32_t *>(t.data_ptr()) : nullptr);
     const int rc = p.backward(p.handle, x.data_ptr(), 0, res.empty() ? nullptr : rp.data(), picks.empty() ? nullptr : ip.data(), dy.data_ptr(), dy_stride,
                               gx.defined() ? gx.data_ptr() : nullptr, 0, res.empty() ? nullptr : gp.data(), ws.defined() ? ws.data_ptr() : nullptr,
-                              p.bwd_ws_bytes, stream);
+                              ws.defined() ? (uint64_t)ws.numel() : 0, stream);
     if (rc != 0) throw CallFailed(rc, "bs_stack_backward");
 }
 
@@ -450,11 +458,14 @@ PyObject *plan_set_backward(PyObject *self, PyObject *args)
     int reads;
     if (!PyArg_ParseTuple(args, "Kp", &n, &reads)) return nullptr;
     Plan &p = plan_of(self);
-    std::lock_guard<std::mutex> lock(p.mutex);
-    p.bwd_ws_bytes = n;
-    p.bwd_planned = true;
-    p.bwd_reads_picks = reads != 0;
-    p.ws[1].clear();
+    {
+        Plan::Buffers old;
+        std::lock_guard<std::mutex> lock(p.mutex);
+        p.bwd_ws_bytes = n;
+        p.bwd_planned = true;
+        p.bwd_reads_picks = reads != 0;
+        old.swap(p.ws[1]);
+    }
     Py_RETURN_NONE;
 }
 

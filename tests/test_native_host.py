@@ -1,5 +1,7 @@
 """The native calls' object (csrc/bs_torch.cpp) without a GPU: who owns a stack's handle, and the buffers it keeps."""
 import ctypes as C
+import subprocess
+import sys
 import threading
 import time
 
@@ -93,3 +95,33 @@ def test_python_and_native_calls_share_one_workspace():
     st.plan(host_only=1)  # one sequence: nothing to hand over, nothing kept
     assert st.workspace("cpu", 5) is None and not st._workspace and st.native().workspace(False, torch.device("cpu"), 5) is None
     st.close()
+
+
+def test_nothing_is_allocated_while_another_thread_can_only_wait():
+    """An allocation may call into the interpreter (here: a dispatch mode that lets other threads run).  A thread that then closes or plans the
+    stack waits for the object with the interpreter's lock in its hand, so the allocation must not happen inside.  In a process of its own: the
+    mistake is a deadlock."""
+    code = """
+import threading, time, torch
+from torch.utils._python_dispatch import TorchDispatchMode
+from paper_1804_08378_amd import brainslug as bs, workloads as wl
+st = bs.Stack([wl.maxpool(3, 1, 1), wl.relu(), wl.maxpool(3, 1, 1)], (2, 8, 12, 12)).plan(host_only=1, max_steps_per_sequence=1)
+inside = threading.Event()
+class Slow(TorchDispatchMode):
+    def __torch_dispatch__(self, func, types, args=(), kwargs=None):
+        inside.set()
+        time.sleep(0.5)
+        return func(*args, **(kwargs or {}))
+native = st.native()
+def ask():
+    with Slow():
+        native.workspace(False, torch.device("cpu"), 3)
+t = threading.Thread(target=ask)
+t.start()
+inside.wait()
+st.close()
+t.join()
+print("done")
+"""
+    done = subprocess.run([sys.executable, "-c", code], cwd=bs.HERE + "/..", capture_output=True, text=True, timeout=90)
+    assert done.stdout.strip().endswith("done"), done.stderr[-2000:]
