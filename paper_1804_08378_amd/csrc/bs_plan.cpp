@@ -1769,19 +1769,29 @@ bs_status group_sequences(bs_stack *s, const bs_plan_options &o, const Limits &l
         if (!per_layer && o.max_steps_per_sequence != 1) {
             std::vector<SeqDraft> paired;
             for (size_t i = 0; i < drafts.size(); ++i) {
-                // runs of stacked blocks: up to ten in a sequence, longer runs in even parts of at most eight
+                // runs of stacked blocks: up to ten in a sequence, longer runs in parts of at most eight (and at least five) steps whose lengths differ by
+                // one at most; a run with a part that the kernel does not take runs in pairs
                 auto blocks = [&](size_t from, int32_t n) {
                     Sequence trial;
                     range_ops(SeqDraft{drafts[from].first_step, n}, trial.first_op, trial.n_ops);
                     return plan_blocks_nhwc(s, trial, o, lim);
                 };
                 if (o.max_steps_per_sequence == 0 && i + K_BLOCKS_NHWC_MIN <= drafts.size() && blocks(i, K_BLOCKS_NHWC_MIN)) {
-                    int32_t run = K_BLOCKS_NHWC_MIN;
+                    int32_t run = K_BLOCKS_NHWC_MIN, done = 0;
                     while (i + run < drafts.size() && blocks(i + run - 1, 2)) ++run;
-                    const int32_t parts = run <= K_BLOCKS_MAX ? 1 : (run + K_CHAIN_MAX - 1) / K_CHAIN_MAX, each = (run + parts - 1) / parts;
-                    for (int32_t done = 0; done < run; done += each) paired.push_back(SeqDraft{drafts[i + done].first_step, std::min(each, run - done)});
-                    i += (size_t)run - 1;
-                    continue;
+                    const int32_t parts = run <= K_BLOCKS_MAX ? 1 : (run + K_CHAIN_MAX - 1) / K_CHAIN_MAX;
+                    std::vector<SeqDraft> cut;
+                    for (int32_t p = 0; p < parts; ++p) {
+                        const int32_t n = run / parts + (p < run % parts ? 1 : 0);
+                        if (!blocks(i + done, n)) break;
+                        cut.push_back(SeqDraft{drafts[i + done].first_step, n});
+                        done += n;
+                    }
+                    if (done == run) {
+                        paired.insert(paired.end(), cut.begin(), cut.end());
+                        i += (size_t)run - 1;
+                        continue;
+                    }
                 }
                 if (i + 1 < drafts.size()) {
                     Sequence trial;

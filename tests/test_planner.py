@@ -191,6 +191,20 @@ def test_chains_of_identical_blocks_take_the_register_kernel():
     assert plan(_blocks(4), shape, lane_exchange=-1)["sequences"][0]["variant"] == bs.BS_VARIANT_LDS_TILE
 
 
+@pytest.mark.parametrize("layout", [bs.BS_LAYOUT_NHWC])
+def test_runs_of_blocks_of_every_length_are_cut_evenly(layout):
+    """Every number of blocks up to the most layers of a stack: sequences of the register kernel (row-major: two blocks and more,
+    channels-last: four) whose lengths differ by one at most, ten steps at most, and of more than one sequence eight."""
+    for n in range(1, 86):
+        steps = plan(_blocks(n), (1, 4, 13, 13), layout=layout)["sequences"]
+        lengths = [q["n_steps"] for q in steps]
+        assert sum(lengths) == n
+        if n < (4 if layout == bs.BS_LAYOUT_NHWC else 2):
+            continue
+        assert all(q["variant"] == bs.BS_VARIANT_ROWS_CHAIN for q in steps), n
+        assert max(lengths) - min(lengths) <= 1 and max(lengths) <= (10 if len(lengths) == 1 else 8), (n, lengths)
+
+
 def test_lds_budget_is_respected_and_no_fit_is_reported():
     layers, shape, _ = wl.build("halo_stress")
     for budget in (4096, 8192, 16384, 32768, 65536):
