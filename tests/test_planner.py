@@ -215,6 +215,21 @@ def test_lds_budget_is_respected_and_no_fit_is_reported():
     assert e.value.status == 6
 
 
+@pytest.mark.parametrize("shape,levels", [((4, 64, 56, 56), 4), ((1, 8, 7, 7), 10), ((2, 24, 30, 31), 12), ((1, 16, 64, 224), 10)])
+def test_lds_budget_of_channels_last_blocks(shape, levels):
+    """The kernel that hands channels to lanes through LDS is taken only where the budget holds its buffers; else pairs of blocks as strips."""
+    c = shape[1]
+    layers = [l for i in range(levels) for l in (wl.maxpool(3, 1, 1), wl.bn_params(c, i), wl.relu())]
+    full = max(q["lds_bytes"] for q in plan(layers, shape, layout=bs.BS_LAYOUT_NHWC)["sequences"])
+    assert 0 < full <= 65536
+    for budget in (1024, 8192, full - 1, full, 65536):
+        seqs = plan(layers, shape, layout=bs.BS_LAYOUT_NHWC, max_lds_bytes=budget)["sequences"]
+        assert all(q["lds_bytes"] <= budget for q in seqs), budget
+        names = {q["variant_name"] for q in seqs}
+        assert names == {"rows_chain"} if budget >= full else "strips" in names  # (fewer levels of a wide plane may still fit)
+        assert sum(q["n_steps"] for q in seqs) == levels
+
+
 def test_resource_example_ratio_is_k_squared():
     """Section 4.1's example: a non-overlapping 3x3 pooling needs 3*3 times the output's data
     as input."""
