@@ -409,6 +409,24 @@ def test_stacked_blocks_of_any_width(shape, levels, dtype):
         assert same.all(), (rc, np.argwhere(~same)[:4])
 
 
+def test_stacked_blocks_on_a_plane_of_more_than_four_gib():
+    """Row offsets beyond 2^32 bytes: the rows around that place and the plane's last ones, against the same blocks on a copy of those rows."""
+    h, w, levels, n = 5_000_000, 224, 2, 64
+    layers = sum(([wl.maxpool(3, 1, 1), wl.bn_params(1, 700 + i), wl.relu()] for i in range(levels)), [])
+    x = torch.randn((1, 1, h, w), device="cuda", generator=torch.Generator(device="cuda").manual_seed(3))
+    st = bs.Stack(layers, tuple(x.shape), "f32").plan()
+    assert [q["variant_name"] for q in st.info()["sequences"]] == ["rows_chain"]
+    out, _ = st.run(x)
+    wrap = 2 ** 32 // (4 * w)
+    small = bs.Stack(layers, (1, 1, n, w), "f32").plan()
+    for first in (0, wrap - h // 100, wrap - n // 2, wrap + 5, h - n):
+        ref, _ = small.run(x[:, :, first:first + n].clone())
+        inner = slice(0 if first == 0 else levels, n if first + n == h else n - levels)  # rows that need nothing beyond the copy
+        assert torch.equal(out[:, :, first:first + n][:, :, inner], ref[:, :, inner]), first
+    st.close()
+    small.close()
+
+
 @pytest.mark.parametrize("shape,levels", [((1, 8, 7, 7), 10), ((2, 3, 1, 2), 4), ((1, 5, 3, 3), 9), ((2, 24, 30, 31), 4), ((1, 16, 20, 63), 6), ((3, 40, 13, 13), 8),
                                           ((1, 16, 40, 126), 10), ((1, 12, 33, 127), 5), ((1, 8, 9, 128), 4), ((1, 33, 31, 129), 9), ((1, 8, 64, 224), 10),
                                           ((2, 24, 56, 56), 12)])
