@@ -715,9 +715,11 @@ void bwd_strip2_kernel(const BwdK k)
                 iat += irow;
             }
         }
+        // the last row is the next window row's first (a row above the plane has no cells: its keys stay below every cell's, a value of 0 among them)
+        const uint32_t up = hA + 2 >= 0 ? 32u : 0u;
 #pragma unroll
         for (int i = 0; i < NW * V; ++i) {
-            if constexpr (KEYS) km[R2][i] = km[R2][i].bumped(32u);  // the last row is the next window row's first
+            if constexpr (KEYS) km[R2][i] = km[R2][i].bumped(up);
             else code[R2][i] -= 6;
         }
 #pragma unroll

@@ -809,3 +809,25 @@ def test_picks_found_as_greatest_keys(shape, dtype):
             gx, _, stages = run_gpu(layers, x, [], dy, dtype, **opts)
             assert stages == 1
             _close(gx, ref, dtype, f"keys {shape} {dtype} s{s} p{p} {opts}")
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16", "f16"])
+@pytest.mark.parametrize("shape", [(2, 8, 13, 11), (1, 5, 4, 31), (1, 16, 33, 9)])
+def test_windows_of_averages_that_round_to_zero(shape, dtype):
+    """ReLU, average, maximum in one kernel on cells so small that every average rounds to 0 while the cells are positive: a window's
+    gradient goes to its first cell inside the plane all the same, also in the windows that begin above it."""
+    tiny = {"f32": 2.0 ** -149, "bf16": 2.0 ** -133, "f16": 2.0 ** -24}[dtype]
+    bn = wl.bn_params(shape[1], 51)
+    bn["beta"] = np.abs(bn["beta"]) + 2.0 + np.abs(bn["mean"] * bn["gamma"]) / np.sqrt(bn["var"] + bn["eps"])  # the ReLU behind it passes everything
+    bn["beta"] = bn["beta"].astype(np.float32)
+    layers = [wl.relu(), wl.avgpool(3, 1, 1, True), wl.maxpool(3, 2, 1), bn, wl.relu()]
+    rng = np.random.default_rng(11)
+    x = np.full(shape, -1.0, np.float32)
+    x[:, :, ::3, ::3] = tiny  # one in nine: no average reaches half the smallest value
+    dy = rng.integers(-8, 9, wl.output_shape(layers, shape)).astype(np.float32)
+    ref, _ = bw.backward_stack(layers, x, [], dy, dtype)
+    assert np.abs(ref[:, :, 0]).max() > 0.0
+    for opts in (dict(layout=bs.BS_LAYOUT_NHWC), dict()):
+        gx, _, stages = run_gpu(layers, x, [], dy, dtype, **opts)
+        assert stages == 1
+        _close(gx, ref, dtype, f"averages of 0, {shape} {dtype} {opts}")
