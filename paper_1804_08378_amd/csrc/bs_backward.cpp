@@ -248,7 +248,6 @@ extern "C" bs_status bs_stack_plan_backward(bs_stack *stack)
         const int32_t full = stack->dtype == BS_F32 ? 4 : 8;
         const size_t S = plan->stages.size();
         uint64_t off = 0;
-        bool last_room = false;  // the last stage has room for picks
         for (size_t j = 0; j < S && st == BS_OK; ++j) {
             BwdStage &g = plan->stages[j];
             const bool nhwc = stack->opts.layout == BS_LAYOUT_NHWC;
@@ -394,17 +393,14 @@ extern "C" bs_status bs_stack_plan_backward(bs_stack *stack)
                 g.g_off = off;
                 off += align256(numel(g.in_shape) * es);
             }
-            // (the cells of row-major planes record nothing; the plan's workspace keeps the size that callers know for such planes)
-            const bool room = is_max || (p.kind == OP_MAXPOOL && g.k.direct == K_DIRECT_CELLS);
-            last_room = room;
-            if (room) {
+            if (is_max) {
                 g.idx_off = off;
                 off += align256(numel(g.out_shape) * 4);
             }
             if (g.forward) plan->fwd_ws_bytes = std::max(plan->fwd_ws_bytes, g.forward->workspace_bytes);
         }
         if (st == BS_OK) {
-            if (plan->stages[S - 1].forward || last_room) {
+            if (plan->stages[S - 1].forward) {
                 plan->last_out_off = off;
                 off += align256(numel(plan->stages[S - 1].out_shape) * es);
             }

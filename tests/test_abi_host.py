@@ -179,9 +179,15 @@ def test_backward_stages_and_workspace():
     # 2 x 2 windows that tile the plane find their picks themselves, in both layouts
     assert _backward_plan([bn(0), wl.relu(), wl.maxpool(2, 2)], shape) == (1, 0)
     assert _backward_plan([bn(0), wl.relu(), wl.maxpool(2, 2)], shape, layout=bs.BS_LAYOUT_NHWC) == (1, 0)
-    # ... unless the rows are no whole vectors (float32: 4 per vector) or the plane is odd
+    # ... also where the rows are no whole vectors (float32: 4 per vector) or the plane is odd, in front of another stage as well
+    for odd in ((2, 8, 14, 14), (2, 8, 13, 15)):
+        assert _backward_plan([bn(0), wl.relu(), wl.maxpool(2, 2)], odd) == (1, 0)
+        assert _backward_plan([bn(0), wl.relu(), wl.maxpool(2, 2)], odd, layout=bs.BS_LAYOUT_NHWC) == (1, 0)
+        n_out = 2 * 8 * (odd[2] // 2) * (odd[3] // 2)
+        assert _backward_plan([bn(0), wl.relu(), wl.maxpool(2, 2), bn(1), wl.add()], odd) == (2, 2 * al(n_out * 4))
+    # ... but not with an Add in front on such rows
     n_out = 2 * 8 * 7 * 7
-    assert _backward_plan([bn(0), wl.relu(), wl.maxpool(2, 2)], (2, 8, 14, 14)) == (1, al(n_out * 4) + al(n_out * 4))
+    assert _backward_plan([bn(0), wl.add(), wl.maxpool(2, 2)], (2, 8, 14, 14)) == (1, al(n_out * 4) + al(n_out * 4))
     # overlapping 3 x 3 windows (padding 1, stride 1 or 2) on rows of whole vectors: the lanes of a row find the picks
     n_out = 2 * 8 * 8 * 8
     assert _backward_plan([bn(0), wl.relu(), wl.maxpool(3, 2, 1)], shape) == (1, 0)
