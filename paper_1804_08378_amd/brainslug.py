@@ -11,6 +11,7 @@ from __future__ import annotations
 import ctypes as C
 import os
 import threading
+import warnings
 
 import numpy as np
 
@@ -483,6 +484,56 @@ def batch_stride_nhwc(t):
 _native_lock = threading.Lock()  # held while a stack's native object is made or its backward pass planned
 
 
+_torch_module = None  # the native module, False: not there; None: not looked for yet
+
+
+def _torch_calls():
+    """The module with the native calls, or None where it is not built for the installed torch (its Python counterpart takes the calls).
+    Under the lock: it is looked for once."""
+    global _torch_module
+    if _torch_module is None:
+        import torch  # noqa: F401 (the module links against it)
+        from . import build
+        try:
+            if not build.torch_ext_fits():
+                raise ImportError("it is not built for " + build.torch_tag())
+            from . import _bs_torch
+            _bs_torch.set_error(BrainSlugError)
+            _torch_module = _bs_torch
+        except ImportError as e:
+            warnings.warn(f"the native calls are not used ({os.path.basename(build.TORCH_EXT)}: {e}): every call costs some microseconds more; "
+                          "run `python paper_1804_08378_amd/build.py`", RuntimeWarning, stacklevel=4)
+            _torch_module = False
+    return _torch_module or None
+
+
+class _PythonCalls:
+    """Stands where the native calls are not there: takes no call, keeps the workspaces."""
+
+    def __init__(self, workspace_bytes):
+        self._bytes, self._buffers = [workspace_bytes, 0], ({}, {})
+
+    def run(self, *operands):
+        return None
+
+    infer = backward = record = run
+
+    def set_backward(self, workspace_bytes, reads_indices):
+        self._bytes[1] = workspace_bytes
+        self._buffers[1].clear()
+
+    def workspace(self, backward, device, stream):
+        import torch
+        n, kept = self._bytes[bool(backward)], self._buffers[bool(backward)]
+        if n and (device, stream) not in kept:
+            kept[device, stream] = torch.empty(n, dtype=torch.uint8, device=device)
+        return kept.get((device, stream))
+
+    def release(self):
+        for kept in self._buffers:
+            kept.clear()
+
+
 class Stack:
     """A planned stack bound to torch tensors (device memory and streams only)."""
 
@@ -500,7 +551,7 @@ class Stack:
         self._fast = None
         self._bwd_workspace = {}
         self._bwd_planned = False
-        self._native = None
+        self._native, self._native_owns = None, False
         self.layout = BS_LAYOUT_NCHW
 
     def close(self):
@@ -514,31 +565,36 @@ class Stack:
 
     def __del__(self):
         # possibly while the interpreter shuts down and module globals are gone
-        if getattr(self, "_native", None) is not None:
+        if getattr(self, "_native", None) is not None and self._native_owns:
             self._native = self.handle = None  # graph nodes may still hold the handle: the last owner destroys it
         else:
             self.close()
 
     def native(self):
-        """The plan's native calls (`csrc/bs_torch.cpp`): every method takes the plain case -- dense torch tensors of the plan's
-        shapes, type, memory layout and device, torch's current stream -- and returns None for any other."""
+        """The plan's native calls (`csrc/bs_torch.cpp`; `_PythonCalls` where they are not built): every method takes the plain case -- dense
+        torch tensors of the plan's shapes, type, memory layout and device, torch's current stream -- and returns None for any other."""
         native = self._native
         if native is None:
-            import torch  # noqa: F401 (the module links against it)
-            from . import _bs_torch
             with _native_lock:  # one object per plan: it owns the handle, a second one would destroy it when it goes
+                module = _torch_calls()
                 native = self._native
                 if native is None:
-                    _bs_torch.set_error(BrainSlugError)
-                    lib = load()
-                    fns = tuple(C.cast(f, C.c_void_p).value for f in (lib.bs_stack_run_strided, lib.bs_stack_backward_strided, lib.bs_stack_destroy))
-                    code = (torch.float32, torch.bfloat16, torch.float16).index(self.torch_dtype())
-                    native = _bs_torch.Plan(fns, self.handle or 0, self.in_shape, self.out_shape, code, self.layout == BS_LAYOUT_NHWC,
-                                            self.res_shapes, self.idx_shapes, self._workspace_bytes)
+                    native = self._make_native(module)
                     if self._bwd_planned:
                         native.set_backward(self._bwd_workspace_bytes, self.backward_reads_indices)
                     self._native = native
         return native
+
+    def _make_native(self, module):
+        self._native_owns = module is not None
+        if module is None:
+            return _PythonCalls(self._workspace_bytes)
+        import torch
+        lib = load()
+        fns = tuple(C.cast(f, C.c_void_p).value for f in (lib.bs_stack_run_strided, lib.bs_stack_backward_strided, lib.bs_stack_destroy))
+        code = (torch.float32, torch.bfloat16, torch.float16).index(self.torch_dtype())
+        return module.Plan(fns, self.handle or 0, self.in_shape, self.out_shape, code, self.layout == BS_LAYOUT_NHWC, self.res_shapes,
+                           self.idx_shapes, self._workspace_bytes)
 
     def plan(self, **opts):
         if self._native is not None:  # bound to the plan that goes

@@ -3,6 +3,7 @@ from __future__ import annotations
 
 import os
 import subprocess
+import sys
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
@@ -29,10 +30,29 @@ def sources():
     return [os.path.join(CSRC, s) for s in SOURCES]
 
 
-def up_to_date() -> bool:
-    if not os.path.exists(LIB) or not os.path.exists(TORCH_EXT):
+def torch_tag() -> str:
+    """What the native calls are compiled for (the text stands in the built file); "" where torch is not installed."""
+    import importlib.metadata
+    import sysconfig
+    try:
+        return "bs_torch for torch %s, %s;" % (importlib.metadata.version("torch"), sysconfig.get_config_var("SOABI"))
+    except importlib.metadata.PackageNotFoundError:
+        return ""
+
+
+def torch_ext_fits() -> bool:
+    """Are the native calls there, and built for the installed torch and this Python?"""
+    tag = torch_tag()
+    if not tag or not os.path.exists(TORCH_EXT):
         return False
-    if os.path.getmtime(TORCH_EXT) < os.path.getmtime(os.path.join(CSRC, "bs_torch.cpp")):
+    with open(TORCH_EXT, "rb") as f:
+        return tag.encode() in f.read()
+
+
+def up_to_date() -> bool:
+    if not os.path.exists(LIB):
+        return False
+    if torch_tag() and (not torch_ext_fits() or os.path.getmtime(TORCH_EXT) < os.path.getmtime(os.path.join(CSRC, "bs_torch.cpp"))):
         return False
     t = os.path.getmtime(LIB)
     deps = sources() + [os.path.join(CSRC, h) for h in JIT_HEADERS + ["bs_internal.h", "bs_rows_tables.h", "bs_nhwc_device.h", "bs_bwd_device.h", "bs_strip_device.h", "bs_backward_keys.h"]]
@@ -70,12 +90,25 @@ def build_torch_ext() -> None:
     lib = os.path.join(os.path.dirname(torch.__file__), "lib")
     tmp = TORCH_EXT + ".tmp.%d" % os.getpid()
     cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-fvisibility=hidden", "-Wall", "-Wno-unused-parameter",
-           "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1", "-D_GLIBCXX_USE_CXX11_ABI=%d" % int(torch._C._GLIBCXX_USE_CXX11_ABI)]
+           "-DBS_TORCH_TAG=\"%s\"" % torch_tag(), "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1", "-D_GLIBCXX_USE_CXX11_ABI=%d" % int(torch._C._GLIBCXX_USE_CXX11_ABI)]
     for d in [*cpp_extension.include_paths(), "/opt/rocm/include", sysconfig.get_paths()["include"]]:
         cmd += ["-isystem", d]
     cmd += [os.path.join(CSRC, "bs_torch.cpp"), "-o", tmp, "-L" + lib, "-ltorch_python", "-ltorch_cpu", "-lc10_hip", "-lc10"]
     subprocess.run(cmd, check=True)
     os.replace(tmp, TORCH_EXT)
+
+
+def try_torch_ext() -> bool:
+    """The native calls are optional: the library needs no torch, and the binding's Python code takes every call without them.  A file that
+    cannot be built anew is removed, so that none for another torch or an older source stays."""
+    try:
+        build_torch_ext()
+        return True
+    except (ImportError, OSError, subprocess.CalledProcessError) as e:
+        if os.path.exists(TORCH_EXT):
+            os.remove(TORCH_EXT)
+        print("without the native calls (%s): torch calls go through ctypes: %s" % (os.path.basename(TORCH_EXT), e), file=sys.stderr)
+        return False
 
 
 def build(force: bool = True, verbose: bool = False) -> str:
@@ -100,7 +133,7 @@ def build(force: bool = True, verbose: bool = False) -> str:
 
     from concurrent.futures import ThreadPoolExecutor
     with ThreadPoolExecutor(max_workers=min(8, len(SOURCES) + 1)) as ex:
-        ext = ex.submit(build_torch_ext)
+        ext = ex.submit(try_torch_ext)
         objs = list(ex.map(compile_one, sources() + [embed]))
         ext.result()
     tmp = LIB + ".tmp.%d" % os.getpid()

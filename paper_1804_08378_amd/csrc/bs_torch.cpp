@@ -515,12 +515,13 @@ PyModuleDef module_def = {PyModuleDef_HEAD_INIT, "_bs_torch", nullptr, -1, modul
 
 }  // namespace
 
+// built_for: what the file was compiled for; read from the file before it is loaded
 extern "C" __attribute__((visibility("default"))) PyObject *PyInit__bs_torch(void)
 {
     PyObject *m = PyModule_Create(&module_def);
     if (!m) return nullptr;
     PyObject *t = PyType_FromSpec(&plan_spec);
-    if (!t || PyModule_AddObject(m, "Plan", t) != 0) {
+    if (!t || PyModule_AddStringConstant(m, "built_for", BS_TORCH_TAG) != 0 || PyModule_AddObject(m, "Plan", t) != 0) {
         Py_XDECREF(t);
         Py_DECREF(m);
         return nullptr;

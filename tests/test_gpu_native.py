@@ -179,3 +179,20 @@ def test_a_second_call_holds_no_more_memory_than_the_first():
     assert st._workspace_bytes > 0 and st._bwd_workspace_bytes > 0
     assert held[1] == held[0] and held[2] == held[0]
     m.close()
+
+
+def test_same_results_without_the_native_module(monkeypatch):
+    shape = (3, 8, 12, 14)
+    layers, x, res, dy = _operands("two", shape, "f32", False)
+
+    def results():
+        st = bs.Stack(layers, shape, "f32").plan(max_steps_per_sequence=1).plan_backward()
+        out, gx, gres = st.run(x, res)[0], *st.backward(x, res, dy)
+        m, xs = _module(layers), x.clone().requires_grad_()
+        got = [m(x, *res), m(x, *res), *[torch.autograd.grad(m(xs, *res), xs, dy)[0] for _ in range(2)]]
+        st.close()
+        return [out, gx, *gres, *got]
+
+    native = results()
+    monkeypatch.setattr(bs, "_torch_module", False)
+    assert all(torch.equal(a, b) for a, b in zip(native, results()))

@@ -10,6 +10,7 @@ import torch  # noqa: F401 (the native module links against it)
 
 from paper_1804_08378_amd import _bs_torch
 from paper_1804_08378_amd import brainslug as bs
+from paper_1804_08378_amd import build
 from paper_1804_08378_amd import workloads as wl
 
 SHAPE = (2, 8, 12, 12)
@@ -125,3 +126,39 @@ print("done")
 """
     done = subprocess.run([sys.executable, "-c", code], cwd=bs.HERE + "/..", capture_output=True, text=True, timeout=90)
     assert done.stdout.strip().endswith("done"), done.stderr[-2000:]
+
+
+def test_without_the_native_module_the_python_code_takes_every_call(monkeypatch):
+    lib = _Library(bs.load())
+    monkeypatch.setattr(bs, "load", lambda: lib)
+    monkeypatch.setattr(bs, "_torch_module", None)
+    monkeypatch.setattr(build, "TORCH_EXT", "/nonexistent/_bs_torch.so")
+    st = _stack([wl.maxpool(3, 1, 1), wl.leaky_relu(0.1), wl.avgpool(2, 2), wl.relu(), wl.maxpool(3, 1, 1)], max_steps_per_sequence=1)
+    with pytest.warns(RuntimeWarning, match="native calls"):
+        n = st.native()
+    assert n.run(None, []) is None and n.infer(None, []) is None and n.record(None, []) is None and n.backward(None, [], None, None) is None
+    st.plan_backward()
+    for backward, size in ((False, st._workspace_bytes), (True, st._bwd_workspace_bytes)):
+        a = st.workspace("cpu", 5, backward)
+        assert a.numel() == size and st.workspace("cpu", 5, backward) is a and st.workspace("cpu", 6, backward) is not a
+    st.plan(host_only=1)
+    assert st.workspace("cpu", 5) is None and st.native() is not n
+    handle = st.handle
+    del st
+    assert lib.destroyed == [handle]
+    lib._lib.bs_stack_destroy(handle)
+
+
+def test_native_module_is_built_for_one_torch_and_optional(monkeypatch, tmp_path, capsys):
+    assert build.torch_ext_fits() and build.up_to_date() and _bs_torch.built_for == build.torch_tag()
+    with monkeypatch.context() as m:
+        m.setattr(build, "torch_tag", lambda: "bs_torch for torch 0.0, none;")  # another torch than the file's
+        assert not build.torch_ext_fits() and not build.up_to_date()
+    with monkeypatch.context() as m:
+        m.setattr(build, "torch_tag", lambda: "")  # no torch: the library alone
+        assert build.up_to_date()
+    stale = tmp_path / "_bs_torch.so"
+    stale.write_bytes(b"older")
+    monkeypatch.setattr(build, "TORCH_EXT", str(stale))
+    monkeypatch.setenv("CXX", "false")
+    assert build.try_torch_ext() is False and not stale.exists() and "without the native calls" in capsys.readouterr().err
