@@ -290,6 +290,7 @@ struct NhwcK {
     EwOp pre[K_MAX_STREAM_EW], post[K_MAX_EW];
     PoolK pool;
     int32_t cached;   // element-wise sequences: 1: input read through the caches, 0: streamed
+    int32_t flat;     // element-wise sequences, C no whole number of vectors: 1: dense tensors run as vectors over the whole tensor
     int32_t C, H, W, Ho, Wo;
     uint32_t total;   // lanes with work: (output) pixels * channel vectors
     FastDiv div_cv;   // by channel vectors per pixel = C / vec

@@ -515,16 +515,19 @@ static bs_status launch_nhwc_t(const NhwcK &k, int32_t dtype, dim3 grid, dim3 bl
             }
         }
         if constexpr (VEC == 1) {
-            // dense: one run of elements (slices leave a gap behind every pixel: one element per lane)
-            if (!k.in_xp && !k.out_xp && k.total > 0 && (int64_t)k.div_cv.d == k.C && k.total % (uint32_t)k.C == 0) {
+            if (!k.flat || k.total == 0 || (int64_t)k.div_cv.d != k.C || k.total % (uint32_t)k.C != 0) return BS_ERR_UNSUPPORTED;
+            if (!k.in_xp && !k.out_xp) {  // dense: one run of elements, the plan's grid
                 constexpr int V = DT == DT_F32 ? 4 : 8;
-                const dim3 gf((uint32_t)(((uint64_t)k.total + 256 * V - 1) / (256 * V)));
                 const int32_t code = list_code(k.pre, k.n_pre);
-                if (code == BN_RELU) nhwc_stream_flat_kernel<DT, V, BN_RELU><<<gf, dim3(256), 0, st>>>(k);
-                else if (code == BN_ADD_RELU) nhwc_stream_flat_kernel<DT, V, BN_ADD_RELU><<<gf, dim3(256), 0, st>>>(k);
-                else nhwc_stream_flat_kernel<DT, V><<<gf, dim3(256), 0, st>>>(k);
+                if ((uint64_t)grid.x * block.x * V < k.total) return BS_ERR_UNSUPPORTED;
+                if (code == BN_RELU) nhwc_stream_flat_kernel<DT, V, BN_RELU><<<grid, block, 0, st>>>(k);
+                else if (code == BN_ADD_RELU) nhwc_stream_flat_kernel<DT, V, BN_ADD_RELU><<<grid, block, 0, st>>>(k);
+                else nhwc_stream_flat_kernel<DT, V><<<grid, block, 0, st>>>(k);
                 return BS_OK;
             }
+            const uint64_t per_group = (uint64_t)block.x * K_STREAM_U;
+            nhwc_stream_kernel<DT, VEC, K_STREAM_U><<<dim3((uint32_t)((k.total + per_group - 1) / per_group)), block, 0, st>>>(k);
+            return BS_OK;
         }
         nhwc_stream_kernel<DT, VEC, K_STREAM_U><<<grid, block, 0, st>>>(k);
         return BS_OK;

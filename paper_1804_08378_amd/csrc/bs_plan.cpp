@@ -683,7 +683,10 @@ static bs_status plan_nhwc(const bs_stack *s, Sequence &q, const bs_plan_options
     q.tile_rows = ohb;
     q.tile_cols = owb;
     q.threads = std::min(q.threads, 256);
-    const int64_t per_group = (int64_t)q.threads * (seen ? 1 : K_STREAM_U);
+    // Element-wise, channels that are no whole vectors: a dense tensor is one run of vectors; one element per lane for channel slices (they leave a gap
+    // behind every pixel; launch_nhwc sets that grid).  Both sides measured at nhwc_stream_flat_kernel.
+    k.flat = !seen && vec == 1 ? 1 : 0;
+    const int64_t per_group = (int64_t)q.threads * (seen ? 1 : k.flat ? vec_of(s) : K_STREAM_U);
     q.grid = ((int64_t)k.total + per_group - 1) / per_group;
     q.lds_bytes = 0;
     q.redundancy = !seen ? 1.0 : (double)bh * ((ohb - 1) * k.pool.sh + k.pool.kh) * bw * ((owb - 1) * k.pool.sw + k.pool.kw) /

@@ -922,6 +922,25 @@ def test_channels_last_elementwise_over_the_whole_tensor(shape, dtype):
         check(layers, x, res, dtype, f"channels-last, flat, {[l['kind'] for l in layers]}", layout=bs.BS_LAYOUT_NHWC)
 
 
+@pytest.mark.parametrize("dtype", ["f32", "bf16", "f16"])
+@pytest.mark.parametrize("threads", [64, 192, 512])
+def test_channels_last_elementwise_over_the_whole_tensor_in_any_work_group(threads, dtype):
+    """The same in work-groups of the caller's size, and on channel slices (one element per lane, a grid of its own)."""
+    n, c, h, w = shape = (2, 30, 29, 37)
+    layers = [wl.bn_params(c, 2), wl.relu()]
+    x = wl.activation(shape, 7, dtype)
+    check(layers, x, [], dtype, f"channels-last, flat, {threads} threads", layout=bs.BS_LAYOUT_NHWC, threads_per_group=threads)
+    ref, _, _ = bf.run_stack(layers, x, [], dtype)
+    wide = torch.zeros((n, 48, h, w), dtype=TORCH_DTYPE[dtype], device="cuda").contiguous(memory_format=torch.channels_last)
+    wide[:, 8:8 + c] = _dev(x, dtype)
+    dst = torch.zeros_like(wide)
+    st = bs.Stack(layers, shape, dtype).plan(layout=bs.BS_LAYOUT_NHWC, threads_per_group=threads)
+    bs.bs_stack_run_strided(st.handle, wide[:, 8:8 + c].data_ptr(), h * w * 48, [], dst[:, 8:8 + c].data_ptr(), h * w * 48, None, 0, 0,
+                            torch.cuda.current_stream().cuda_stream)
+    assert np.array_equal(dst[:, 8:8 + c].float().cpu().numpy(), ref) and not dst[:, :8].any() and not dst[:, 8 + c:].any()
+    st.close()
+
+
 @pytest.mark.parametrize("shape", NHWC_SHAPES)
 @pytest.mark.parametrize("dtype", ["f32", "bf16", "f16"])
 def test_channels_last_plans_match_the_oracle(shape, dtype):

@@ -413,6 +413,17 @@ def test_threads_per_group_is_honoured_by_the_register_kernels():
         assert q["threads_per_group"] == 256 and q["grid"] == base["grid"]
 
 
+@pytest.mark.parametrize("dtype,vec", [("f32", 4), ("bf16", 8), ("f16", 8)])
+def test_channels_last_elementwise_reports_the_grid_that_is_launched(dtype, vec):
+    """Channels that are no whole vectors: a lane takes one vector of the whole tensor; the work-group size is the caller's."""
+    shape = (10, 30, 193, 193)
+    n = int(np.prod(shape))
+    for threads in (0, 64, 128, 256):
+        q = plan([wl.bn_params(30, 1), wl.relu()], shape, dtype, layout=bs.BS_LAYOUT_NHWC, threads_per_group=threads)["sequences"][0]
+        assert q["variant_name"] == "nhwc_stream" and q["threads_per_group"] == (threads or 256)
+        assert q["grid"] == -(-n // ((threads or 256) * vec))
+
+
 @pytest.mark.parametrize("layers,shape,opts,reads", [
     ([wl.bn_params(8, 1), wl.relu(), wl.maxpool(3, 2, 1, True)], (2, 8, 30, 30), dict(layout=bs.BS_LAYOUT_NHWC), 0),   # strips find the picks
     ([wl.bn_params(8, 1), wl.relu(), wl.maxpool(3, 2, 1, True)], (2, 8, 32, 32), {}, 0),                               # so does the row-walking kernel
