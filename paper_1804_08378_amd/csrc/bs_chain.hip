@@ -17,15 +17,18 @@ std::string blocks_expr(const ChainK &k, int32_t dtype)
     return b;
 }
 
+// Most output rows of a chunk: the rows it reads, L above and below its own among them, span less than 4 GiB (of float32).
+int32_t blocks_most_rows(const ChainK &k) { return (int32_t)(0xffffffffll / (4ll * k.W)) - 2 * k.n_levels; }
+
 // What the kernel assumes about its argument block and launch: column tiles that fit a wave with an idle lane between two segments and
-// halos that hold the levels' reach, chunks that cover the plane, a grid that covers every (group of segments, chunk).
+// halos that hold the levels' reach, chunks that cover the plane and whose rows 32-bit offsets reach, a grid that covers every (group of segments, chunk).
 bool blocks_launchable(const ChainK &k, int64_t planes, int64_t grid, int32_t threads)
 {
     if (k.n_levels < 2 || k.n_levels > K_BLOCKS_MAX || k.W < 2 || k.H < 1 || k.tiles < 1 || k.rc < 1 || k.chunks < 1 || k.spw < 1) return false;
     const int32_t columns = k.tile_w + k.halo_w * (k.tiles < 3 ? k.tiles - 1 : 2);
     return k.tile_w % 2 == 0 && k.halo_w % 2 == 0 && k.halo_w >= k.n_levels && (int64_t)k.tiles * k.tile_w >= k.W && 2 * (k.pitch - 1) >= columns &&
            k.spw * k.pitch <= 65 && k.div_pitch.d == (uint32_t)k.pitch && k.div_chunks.d == (uint32_t)k.chunks &&
-           k.div_tiles.d == (uint32_t)k.tiles && k.div_c.d == (uint32_t)k.C && (int64_t)k.chunks * k.rc >= k.H && k.units == (uint64_t)(planes * k.tiles) &&
+           k.div_tiles.d == (uint32_t)k.tiles && k.div_c.d == (uint32_t)k.C && (int64_t)k.chunks * k.rc >= k.H && k.rc <= blocks_most_rows(k) && k.units == (uint64_t)(planes * k.tiles) &&
            threads >= 64 && threads <= 256 && threads % 64 == 0 &&
            grid * (threads / 64) >= (((int64_t)k.units + k.spw - 1) / k.spw) * k.chunks;
 }

@@ -137,21 +137,15 @@ __global__ __launch_bounds__(256, chain_waves(DT, RAGGED, L)) void pool_chain_ke
         }
     }
 
-    const size_t plane_at = (size_t)plane * (size_t)(k.H * k.W);
-    const char *inp = static_cast<const char *>(image_base<DT>(k.in, img, k.in_extra)) + (plane_at + (uint32_t)(col0 - beyond)) * ES;
-    char *outp = static_cast<char *>(image_base<DT>(k.out, img, k.out_extra)) + (plane_at + (uint32_t)col0) * ES;
     const uint32_t pitch = (uint32_t)k.W * ES;
-    // Bytes from the plane's first row to row r, the same for every lane: in 64 bits (a float32 plane may have more than 4 GiB), in scalar registers
-    // (left to the compiler it is a vector multiplication per lane).
-    auto row_at = [&](int32_t r) __attribute__((always_inline)) {
-        uint64_t at = (uint64_t)(uint32_t)r * pitch;
-        asm("" : "+s"(at));
-        return at;
-    };
 
     const int32_t o0 = chunk * k.rc, o1 = min(o0 + k.rc, k.H);  // output rows of the chunk
     const int32_t first = max(o0 - L, 0), last = o1 - 1 + L;  // input rows (those behind the plane: padding)
     const int32_t fast_from = max(first, L), fast_to = min(k.H - 1, last);  // input rows whose step has a real row on every level
+    // The first rows read and written; the others follow at 32-bit offsets (the rows of a chunk span less than 4 GiB, a float32 plane may have more).
+    const size_t plane_at = (size_t)plane * (size_t)(k.H * k.W);
+    const char *inp = static_cast<const char *>(image_base<DT>(k.in, img, k.in_extra)) + (plane_at + (size_t)first * (size_t)k.W + (uint32_t)(col0 - beyond)) * ES;
+    char *outp = static_cast<char *>(image_base<DT>(k.out, img, k.out_extra)) + (plane_at + (size_t)o0 * (size_t)k.W + (uint32_t)col0) * ES;
 
     float ring[L][3][2];  // row maxima of the three newest rows of level l (level 0: the input)
 #pragma unroll
@@ -162,7 +156,7 @@ __global__ __launch_bounds__(256, chain_waves(DT, RAGGED, L)) void pool_chain_ke
             for (int i = 0; i < 2; ++i) ring[l][p][i] = l == 0 ? -INFINITY : 0.0f;
 
     auto fetch = [&](int32_t h, ChainRow<DT> &r) __attribute__((always_inline)) {
-        const char *p = inp + row_at(min(max(h, 0), k.H - 1));
+        const char *p = inp + (uint32_t)(min(h, k.H - 1) - first) * pitch;
         __builtin_memcpy(r.w, RAGGED ? p : static_cast<const char *>(__builtin_assume_aligned(p, 2 * ES)), 2 * ES);
     };
     // one input row; P: its place in the rings.  EDGE: some levels' rows may not exist.
@@ -198,7 +192,7 @@ __global__ __launch_bounds__(256, chain_waves(DT, RAGGED, L)) void pool_chain_ke
             for (int i = 0; i < 2; ++i) v[i] = __builtin_fmaxf(__builtin_fmaf(v[i], a[i % PC], b[i % PC]), 0.0f);
             const int32_t r = h - L;
             if (stores && r >= o0 && (!EDGE || r < o1)) {
-                char *p = outp + row_at(r);
+                char *p = outp + (uint32_t)(r - o0) * pitch;
                 if (!RAGGED) {
                     store_elems<DT, 2, false>(p, 0, v);
                 } else {  // at any multiple of the element size

@@ -216,6 +216,7 @@ bs_status launch_xrows(const PoolRowsK &k, int32_t dtype, int64_t grid, int32_t 
 bs_status launch_xrows2(const PoolRows2K &k, int32_t dtype, int64_t grid, int32_t threads, void *stream);
 // blocks of 3 x 3 maximum, BatchNorm, ReLU (pool_chain_kernel): compiled in (else a run-time build) / launch it
 bool blocks_compiled(int32_t dtype);
+int32_t blocks_most_rows(const ChainK &k);
 bool blocks_launchable(const ChainK &k, int64_t planes, int64_t grid, int32_t threads);
 std::string blocks_expr(const ChainK &k, int32_t dtype);
 bs_status launch_blocks(const ChainK &k, int32_t dtype, int64_t grid, int32_t threads, void *stream);

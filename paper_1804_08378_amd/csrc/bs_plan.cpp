@@ -1200,6 +1200,7 @@ static void plan_blocks(const bs_stack *s, Sequence &q, const bs_plan_options &o
         }
     }
     if (o.tile_rows > 0) rc = std::min(o.tile_rows, k.H);
+    rc = std::min(rc, blocks_most_rows(k));
     k.chunks = (k.H + rc - 1) / rc;
     k.rc = (k.H + k.chunks - 1) / k.chunks;
     k.chunks = (k.H + k.rc - 1) / k.rc;

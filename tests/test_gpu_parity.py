@@ -410,20 +410,24 @@ def test_stacked_blocks_of_any_width(shape, levels, dtype):
 
 
 def test_stacked_blocks_on_a_plane_of_more_than_four_gib():
-    """Row offsets beyond 2^32 bytes: the rows around that place and the plane's last ones, against the same blocks on a copy of those rows."""
+    """Row offsets beyond 2^32 bytes: the rows around that place and the plane's last ones, against the same blocks on a copy of those rows;
+    chunks of the planner's choice and the longest ones there are (a caller asks for the whole plane)."""
     h, w, levels, n = 5_000_000, 224, 2, 64
     layers = sum(([wl.maxpool(3, 1, 1), wl.bn_params(1, 700 + i), wl.relu()] for i in range(levels)), [])
     x = torch.randn((1, 1, h, w), device="cuda", generator=torch.Generator(device="cuda").manual_seed(3))
-    st = bs.Stack(layers, tuple(x.shape), "f32").plan()
-    assert [q["variant_name"] for q in st.info()["sequences"]] == ["rows_chain"]
-    out, _ = st.run(x)
-    wrap = 2 ** 32 // (4 * w)
     small = bs.Stack(layers, (1, 1, n, w), "f32").plan()
-    for first in (0, wrap - h // 100, wrap - n // 2, wrap + 5, h - n):
-        ref, _ = small.run(x[:, :, first:first + n].clone())
-        inner = slice(0 if first == 0 else levels, n if first + n == h else n - levels)  # rows that need nothing beyond the copy
-        assert torch.equal(out[:, :, first:first + n][:, :, inner], ref[:, :, inner]), first
-    st.close()
+    wrap = 2 ** 32 // (4 * w)
+    for opts in ({}, dict(tile_rows=h)):
+        st = bs.Stack(layers, tuple(x.shape), "f32").plan(**opts)
+        q, = st.info()["sequences"]
+        assert q["variant_name"] == "rows_chain" and q["tile_rows"] == (h // 2 if opts else q["tile_rows"])
+        out, _ = st.run(x)
+        for first in (0, wrap - h // 100, wrap - n // 2, wrap + 5, h // 2 - n // 2, h - n):
+            ref, _ = small.run(x[:, :, first:first + n].clone())
+            inner = slice(0 if first == 0 else levels, n if first + n == h else n - levels)  # rows that need nothing beyond the copy
+            assert torch.equal(out[:, :, first:first + n][:, :, inner], ref[:, :, inner]), (opts, first)
+        del out
+        st.close()
     small.close()
 
 
