@@ -337,6 +337,7 @@ template <int DT, bool CL, int Q, int S, int P, int PRE, int POST, typename OFF>
 __global__ __launch_bounds__(256) void bwd_strip_kernel(const BwdK k)
 {
     static_assert(Q % S == 0 && (S == 1 || S == 2) && (P == 0 || P == 1), "compiled windows");
+    static_assert(PRE == 0 || PRE == -1, "BatchNorm, ReLU in front and nothing behind: bwd_keys_kernel");
     constexpr int OW0 = -((2 - P) / S);            // first window over the strip: q0 / S + OW0 = ceil((q0 + P - 2) / S)
     constexpr int NW = (Q + 1) / S + 1;            // windows over the strip
     constexpr int X0 = OW0 * S - P;                // their first column, from q0
@@ -406,7 +407,7 @@ __global__ __launch_bounds__(256) void bwd_strip_kernel(const BwdK k)
                     y[i] = ok[j] && c >= 0 && c < k.W ? y[i] : -INFINITY;
                 }
             }
-            row_maxima<V, S, NW, CW, dh, LEAD, ends_in_relu(PRE)>(y, lead, m[slot], code[slot]);
+            row_maxima<V, S, NW, CW, dh, LEAD, false>(y, lead, m[slot], code[slot]);
 #pragma unroll
             for (int i = 0; i < Q * V; ++i) {
                 t[slot][i] = d[(j * CW - X0) * V + i];

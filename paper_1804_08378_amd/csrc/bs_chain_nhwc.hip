@@ -176,7 +176,7 @@ __global__ __launch_bounds__(K_THREADS, VEC == 1 ? 2 : 4) void pool_chain_nhwc_k
     for (; h <= last; h += K_ROWS) pass(IntTag<1>{}, h);
 }
 
-template <int DT, int VEC, int L = 2>
+template <int DT, int VEC, int L = K_BLOCKS_NHWC_MIN>
 void launch_levels(const ChainNhwcK &k, dim3 grid, uint32_t bytes, hipStream_t st)
 {
     if constexpr (L <= K_BLOCKS_MAX) {
@@ -246,7 +246,7 @@ bs_status launch_chain_nhwc(const ChainNhwcK &k, int64_t images, int32_t dtype, 
     // what the kernel assumes: tiles, halos, lanes, buffers and vectors as chain_nhwc_geometry lays them out, offsets inside a row below 4 GiB,
     // channel slices that keep a vector's alignment
     const int32_t columns = k.tile_w + k.halo_w * (k.tiles < 3 ? k.tiles - 1 : 2);
-    if (k.n_levels < 2 || k.n_levels > K_BLOCKS_MAX || (k.vec != 1 && (k.vec != full || k.C % full != 0)) || k.W < 2 || k.H < 1 || k.rc < 1 ||
+    if (k.n_levels < K_BLOCKS_NHWC_MIN || k.n_levels > K_BLOCKS_MAX || (k.vec != 1 && (k.vec != full || k.C % full != 0)) || k.W < 2 || k.H < 1 || k.rc < 1 ||
         k.halo_w < k.n_levels || k.halo_w % 2 != 0 || k.tile_w % 2 != 0 || (int64_t)k.tiles * k.tile_w < k.W || 2 * (k.pitch - 1) < columns || k.cols != columns ||
         k.spw < 1 || k.spw * k.pitch > 65 || k.cg != 8 * k.spw || k.lp < k.cols || k.lp % 2 != 0 || chain_nhwc_lds_bytes(k) > 64 * 1024 ||
         (int64_t)k.chunks * k.rc < k.H || k.div_groups.d != (uint32_t)groups || k.div_tiles.d != (uint32_t)k.tiles || k.div_chunks.d != (uint32_t)k.chunks ||

@@ -262,6 +262,12 @@ struct ChainK {
     FastDiv div_chunks, div_pitch, div_tiles, div_c;
 };
 
+// Fewest channels-last blocks in one launch of pool_chain_nhwc_kernel (two and three run as strips).
+#if !defined(BS_BLOCKS_NHWC_MIN)
+#define BS_BLOCKS_NHWC_MIN 4
+#endif
+constexpr int K_BLOCKS_NHWC_MIN = BS_BLOCKS_NHWC_MIN;
+
 // ... of a channels-last tensor (pool_chain_nhwc_kernel): a work-group takes `cols` columns of `cg` channels, a segment is a channel.
 struct ChainNhwcK {
     const void *in;

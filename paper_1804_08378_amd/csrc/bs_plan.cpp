@@ -343,12 +343,6 @@ static bool plane_applicable(const bs_stack *s, int32_t first_op, int32_t n_ops)
 #define BS_CHAIN_MIN 2
 #endif
 
-// ... and the fewest blocks pool_chain_nhwc_kernel is used for (two and three run as strips).
-#if !defined(BS_BLOCKS_NHWC_MIN)
-#define BS_BLOCKS_NHWC_MIN 4
-#endif
-constexpr int32_t K_BLOCKS_NHWC_MIN = BS_BLOCKS_NHWC_MIN;
-
 static uint64_t seq_min_lds(const bs_stack *s, int32_t first_op, int32_t n_ops, int32_t threads)
 {
     if (count_pools(s, first_op, n_ops) == 0) return 0;
