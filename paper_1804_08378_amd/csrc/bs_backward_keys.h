@@ -7,8 +7,8 @@
 // a maximum of keys, a ReLU's derivative at the pick is "the maximum is above zero" (once per window instead of once per cell), and the
 // BatchNorm's derivative is one factor of the finished sum.  16-bit storage, channels-last: two channels per lane where their number is
 // even -- half the addresses and requests.
-// What bounds it: memory -- 231 MB of the ResNet stem 64 x 64 x 112 x 112 bfloat16 in 46 us = 5.0 TB/s (the kernel that compares and selects: 60 us, 36
-// vector instructions per cell); float32 94 us = 4.9 TB/s (98).  32 x 192 x 71 x 71 / 2 without padding binary16 38 -> 35 us.  Row-major rows that are no whole
+// What bounds it: memory -- 231 MB of the ResNet stem 64 x 64 x 112 x 112 bfloat16 in 46 us = 5.0 TB/s (269 MB with what is fetched twice; 26 vector
+// instructions per cell take 29 of the 46 us; the kernel that compares and selects: 60 us, 36 instructions); float32 94 us = 4.9 TB/s (98).  32 x 192 x 71 x 71 / 2 without padding binary16 38 -> 35 us.  Row-major rows that are no whole
 // vectors, 64 x 64 x 111 x 111: float32 145 -> 143, bfloat16 78 -> 76.5.  Strips of 8 columns measured 5 % slower, 2 10 % (large tensors).
 // Part of bs_backward_strip.hip (its lanes, places, loads and stores).
 #pragma once

@@ -4,7 +4,9 @@
 // step, because level l's row h - l needs level l - 1's rows up to h - l + 1, which that step has just produced.  Per level the lane
 // keeps three rows of *row maxima* (the maximum over each window's three columns), so a window's value is one three-operand maximum.
 //
-// What bounds it is instruction issue, so the step is written for few instructions: 3.5 per cell and level.
+// What bounds it is instruction issue at the two waves per SIMD that planes of this size give (ten levels: one vector instruction per 6.1 cycles in
+// float32, 5.3 in bfloat16), in float32 beside the latency of the loads (waves wait 36 % of their time; bfloat16 16 %), so the step is written for
+// few instructions: 3.5 per cell and level.
 //   Columns: the maximum of a lane's two columns and ReLU's zero is one three-operand instruction shared by two windows (a max
 //   pooling follows, so "not below zero" may be applied to the window instead of the cell); the neighbouring lane's edge column is
 //   an operand of the window's last maximum (data-parallel-primitive operand), not a move.
@@ -13,8 +15,8 @@
 //   zero scale and shift as well.  No masks in the loop; only the first level, which reads raw values, is padded with -inf.
 //   Rows: all lanes of a wave are at the same row (segments of a wave are different planes, the same chunk), so the passes whose rows
 //   exist on every level are a loop of their own without any test of them.
-// Measured, 64 x 64 x 56 x 56 float32 (102.8 MB), ten levels: 33.5 us in one launch (the kernel for other lists,
-// 14 instructions per cell and level, took 65 us in two); four levels 27.0 us = 3.8 TB/s.
+// Measured, us, 64 x 64 x 56 x 56 float32 (102.8 MB), calls back to back over tensors from memory / on one tensor that the last cache holds: ten levels
+// 32.5 / 27.8 in one launch (the kernel for other lists, 14 instructions per cell and level: 62.3 / 58.0 in two); four levels 26.6 / 18.9 (3.9 TB/s from memory).
 // Rounding to the storage type commutes with maximum and ReLU: a level's values are rounded after the next level's maximum.
 #pragma once
 #include "bs_xrows_device.h"

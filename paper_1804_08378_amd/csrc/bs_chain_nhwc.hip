@@ -5,10 +5,11 @@
 // channels: its threads fetch three rows at a time as vectors of channels, hand them to the lanes through LDS (one row of columns per
 // channel), and take the results back the same way.  Both buffers are double, so a pass of three rows has one barrier; the rows of the pass
 // after the next are on their way while a pass is worked on.
-// What bounds it: instruction issue of the levels, as in row-major; two steps per launch as strips read and write every plane between the
-// launches.  us, strips (two blocks a launch) -> this kernel, four / seven / ten blocks: 64 x 64 x 56 x 56 float32 50 / 86 / 107 -> 31 / 33 / 40,
-// bfloat16 35 / 63 / 84 -> 23 / 32 / 42; 16 x 248 x 159 x 30 float32 81 / 135 / 165 -> 42 / 46 / 60; 13 x 200 x 43 x 43 bfloat16 21 / 38 / 52 -> 15 / 24 / 35;
-// 35 x 72 x 13 x 13 float32 9.7 / 19 / 26 -> 8.2 / 14 / 19.
+// What bounds it: issue as in row-major, with 14 to 20 % more vector instructions for handing the channels over, LDS bank conflicts in four of ten of its
+// LDS cycles, and waiting for loads and barriers (35 % of the waves' time); two steps per launch as strips read and write every plane between
+// the launches.  us, strips (two blocks a launch) -> this kernel, four / seven / ten blocks, tensors from memory: 64 x 64 x 56 x 56 float32 48 / 87 / 108 -> 30 /
+// 31 / 38, bfloat16 35 / 63 / 83 -> 23 / 32 / 42; 16 x 248 x 159 x 30 float32 81 / 135 / 165 -> 42 / 45 / 54; 13 x 200 x 43 x 43 bfloat16 21 / 38 / 52 -> 16 / 25 / 35;
+// 35 x 72 x 13 x 13 float32 9.7 / 19 / 26 -> 8.3 / 14 / 19.
 #include <algorithm>
 
 #include "bs_chain_device.h"

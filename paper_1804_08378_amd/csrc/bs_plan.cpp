@@ -338,7 +338,7 @@ static bool direct_applicable(const bs_stack *s, int32_t first_op, int32_t n_ops
 static bool rows_applicable(const bs_stack *s, int32_t first_op, int32_t n_ops, Sequence *fill);
 static bool plane_applicable(const bs_stack *s, int32_t first_op, int32_t n_ops);
 // Fewest identical pooling blocks the chain kernels are used for.  Measured on 64 x 64 x 56 x 56, float32: one block 25 us
-// (one-level sliding-window kernel: 22 us), two blocks 26 us (two-level kernel: 34 us), four 27 us.
+// (one-level sliding-window kernel: 22 us), two blocks 26 us (two-level kernel: 34 us), four 27 us (tensors from memory).
 #if !defined(BS_CHAIN_MIN)
 #define BS_CHAIN_MIN 2
 #endif
@@ -1134,8 +1134,8 @@ static bool chain_applicable(const bs_stack *s, int32_t first_op, int32_t n_ops,
     const int32_t vec = xrows_vec(s->dtype);
     blocks = blocks && k.n_ew == 2 && k.ew[0][0].kind == OP_BN && k.ew[0][1].kind == OP_RELU;
     // Any width from two columns up to what a wave's 128-bit vectors cover (wider rows: not measured).  Against the kernel for other lists (rows of
-    // whole vectors) and the LDS tiles (other rows), us: 64 x 64 x 56 x 56 float32, two / ten levels 26.8 / 65 -> 26.3 / 33.5; 55 columns 52 / 153
-    // -> 30 / 38; 1 x 32 x 224 x 224 bfloat16 43 / 186 -> 6.3 / 14.3; 35 x 72 x 13 x 13 11.3 / 42 -> 4.4 / 10.7.
+    // whole vectors) and the LDS tiles (other rows), us: 64 x 64 x 56 x 56 float32, two / ten levels 26.8 / 62 -> 25.9 / 32.5; 55 columns 52 / 153
+    // -> 33 / 37; 1 x 32 x 224 x 224 bfloat16 43 / 186 -> 6.3 / 14.3; 35 x 72 x 13 x 13 11.3 / 42 -> 4.4 / 10.7.
     if (blocks && s->opts.lane_exchange >= 0 && k.W >= 2 && k.W <= 64 * vec && (blocks_compiled(s->dtype) || jit_allowed(s))) {
         b.n_levels = k.n_levels;
         b.H = k.H;
@@ -1176,8 +1176,8 @@ static void plan_blocks(const bs_stack *s, Sequence &q, const bs_plan_options &o
     // Rows per chunk.  A whole plane recomputes nothing (a chunk walks L rows above and below its own), more chunks give more waves.  Cycles of a
     // launch: rows walked x (7 L + 12) instructions x cycles per instruction of a wave, which depend on the waves of its SIMD (measured: one
     // 10, four 18), plus the bytes at 2600 per cycle.  Longer chunks unless shorter ones save 3 %; none below half a plane, or 20 rows, or the
-    // rows they recompute.  Measured (us, float32, rows of the chunks): 64 x 64 x 56 x 56, ten levels 56: 33.9, 28: 38.5; two levels 25.9, 28.0;
-    // 7 x 208 x 128 x 128, ten levels 128: 61, 64: 51, 43: 59, 32: 57; 6 x 86 x 104 x 104, ten levels 104: 35, 35: 24, 26: 26, 13: 32.
+    // rows they recompute.  Measured (us, float32, tensors from memory, rows of the chunks): 64 x 64 x 56 x 56, ten levels 56: 32.5, 28: 35.6; two levels 25.9, 27.8;
+    // 7 x 208 x 128 x 128, ten levels 128: 61, 64: 49, 43: 58, 32: 54; 6 x 86 x 104 x 104, ten levels 104: 37, 35: 25, 26: 26, 13: 30.
     const int64_t groups = ((int64_t)k.units + k.spw - 1) / k.spw;
     const double bytes = (double)planes * k.H * k.W * (s->dtype == BS_F32 ? 4 : 2);
     double best = 0.0;
@@ -1768,8 +1768,9 @@ bs_status group_sequences(bs_stack *s, const bs_plan_options &o, const Limits &l
         if (!per_layer && o.max_steps_per_sequence != 1) {
             std::vector<SeqDraft> paired;
             for (size_t i = 0; i < drafts.size(); ++i) {
-                // runs of stacked blocks: up to ten in a sequence, longer runs in parts of at most eight (and at least five) steps whose lengths differ by
-                // one at most; a run with a part that the kernel does not take runs in pairs
+                // Runs of stacked blocks: up to ten in a sequence, longer runs in parts of at most eight (and at least five) steps whose lengths differ by
+                // one at most; a run with a part that the kernel does not take runs in pairs.  Parts of at most eight / ten, us, 20 steps: 64 x 64 x 56 x 56 float32
+                // 83.5 / 72.7, bfloat16 92.5 / 81.5; 16 x 248 x 30 x 159 float32 156 / 142, bfloat16 160 / 167; 13 x 200 x 43 x 43 float32 59.6 / 61.1, 57 steps 169 / 176.
                 auto blocks = [&](size_t from, int32_t n) {
                     Sequence trial;
                     range_ops(SeqDraft{drafts[from].first_step, n}, trial.first_op, trial.n_ops);
@@ -1819,7 +1820,7 @@ bs_status group_sequences(bs_stack *s, const bs_plan_options &o, const Limits &l
         // lengths (8 steps run as 4 + 4 rather than 5 + 3).
         // Chains of identical blocks that the register kernels take are the exception: they have no LDS
         // traffic and measured fastest with as many levels as they are built for (pool_chain_kernel, 64 x 64 x 56 x 56,
-        // float32: 13.2 / 6.8 / 4.3 / 3.4 us per block with 2 / 4 / 7 / 10 levels).
+        // float32, tensors from memory: 13.0 / 6.7 / 4.2 / 3.3 us per block with 2 / 4 / 7 / 10 levels).
         int32_t cap = K_AUTO_STEPS;
         {
             std::vector<SeqDraft> longer;
@@ -1830,7 +1831,9 @@ bs_status group_sequences(bs_stack *s, const bs_plan_options &o, const Limits &l
                 all_chains = all_chains && (d.n_steps < BS_CHAIN_MIN || chain_applicable(s, fo, no, nullptr));
                 all_chains = all_chains && (d.n_steps >= BS_CHAIN_MIN || longer.size() > 1);
             }
-            // nine or ten steps are one sequence; longer stacks are cut into sequences of at most eight
+            // Nine or ten steps are one sequence; longer stacks are cut into sequences of at most eight, the most levels that the kernel for other lists has.
+            // At most eight / ten, us: 64 x 64 x 56 x 56 float32, 20 steps 66.6 / 54.8 (7 + 7 + 6 / 10 + 10), 30 steps 94 / 82; 16 x 248 x 30 x 159 bfloat16 141.7 /
+            // 141.6; 12 and 16 steps are the same two sequences either way.  Channels-last both are measured at pool_chain_nhwc_kernel's runs above.
             if (all_chains) cap = longer.size() == 1 ? K_BLOCKS_MAX : K_CHAIN_MAX;
         }
         bs_status fs = fill(cap, drafts);
