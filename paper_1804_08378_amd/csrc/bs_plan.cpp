@@ -1292,6 +1292,8 @@ static bool plan_blocks_nhwc(const bs_stack *s, Sequence &q, const bs_plan_optio
     k.C = (int32_t)s->in_shape[1];
     int64_t grid = 0;
     if (at != 0 || k.n_levels < 2 || (uint64_t)k.W * k.C * dtype_size(s->dtype) > 0x7fffffffull || !chain_nhwc_geometry(k, s->in_shape[0], s->dtype, lim.num_cus, &grid)) return false;
+    // (a tensor has less than 2^31 elements: with two rows in all, a row of any channel slice is within the 4 GiB that the kernel's offsets reach)
+    if (s->dtype == BS_F32 && s->in_shape[0] * k.H < 2) return false;
     if (chain_nhwc_lds_bytes(k) > lim.max_lds_bytes) return false;  // a smaller budget than the kernel's buffers need: strips, without LDS
     q.blocks_cl = k;
     q.variant = BS_VARIANT_ROWS_CHAIN;

@@ -164,6 +164,30 @@ def test_threads_and_streams_have_their_own_workspaces():
     assert not wrong
 
 
+def test_threads_whose_first_calls_coincide():
+    """A fresh stack run for the first time by four threads at once: one native object, the same results, the handle still there."""
+    shape = (4, 8, 24, 28)
+    for trial in range(5):
+        layers, x, res, _ = _operands("two", shape, "f32", True, seed=trial)
+        st = bs.Stack(layers, shape, "f32").plan(layout=bs.BS_LAYOUT_NHWC, max_steps_per_sequence=1)
+        torch.cuda.synchronize()
+        gate, outs, natives = threading.Barrier(4), [None] * 4, [None] * 4
+
+        def work(i):
+            with torch.cuda.stream(torch.cuda.Stream()):
+                gate.wait()
+                outs[i] = st.run(x, res)[0]
+                natives[i] = st._native
+                torch.cuda.current_stream().synchronize()
+
+        threads = [threading.Thread(target=work, args=(i,)) for i in range(4)]
+        [t.start() for t in threads]
+        [t.join() for t in threads]
+        ref = st.run(x, res)[0]
+        assert all(n is st._native for n in natives) and all(torch.equal(o, ref) for o in outs)
+        st.close()
+
+
 def test_a_second_call_holds_no_more_memory_than_the_first():
     """The first call of a module plans and runs through Python, later ones natively: both use one workspace per direction."""
     shape = (4, 8, 32, 32)

@@ -230,6 +230,15 @@ def test_lds_budget_of_channels_last_blocks(shape, levels):
         assert sum(q["n_steps"] for q in seqs) == levels
 
 
+def test_channels_last_blocks_on_a_single_row():
+    """One float32 row: a channel slice of a larger tensor may have 8 GiB in it, beyond the offsets of the kernel that exchanges channels
+    through LDS; 16-bit rows, and rows of which there are two, cannot."""
+    layers = [l for i in range(4) for l in (wl.maxpool(3, 1, 1), wl.bn_params(8, i), wl.relu())]
+    names = lambda shape, dtype: {q["variant_name"] for q in plan(layers, shape, dtype, layout=bs.BS_LAYOUT_NHWC)["sequences"]}
+    assert names((1, 8, 1, 64), "f32") == {"strips"}
+    assert names((1, 8, 2, 64), "f32") == names((2, 8, 1, 64), "f32") == names((1, 8, 1, 64), "bf16") == {"rows_chain"}
+
+
 def test_resource_example_ratio_is_k_squared():
     """Section 4.1's example: a non-overlapping 3x3 pooling needs 3*3 times the output's data
     as input."""
