@@ -35,9 +35,13 @@ def torch_tag() -> str:
     import importlib.metadata
     import sysconfig
     try:
-        return "bs_torch for torch %s, %s;" % (importlib.metadata.version("torch"), sysconfig.get_config_var("SOABI"))
+        version = importlib.metadata.version("torch")
     except importlib.metadata.PackageNotFoundError:
-        return ""
+        try:  # a torch that was not installed as a package
+            from torch import __version__ as version
+        except ImportError:
+            return ""
+    return "bs_torch for torch %s, %s;" % (version, sysconfig.get_config_var("SOABI"))
 
 
 def torch_ext_fits() -> bool:
