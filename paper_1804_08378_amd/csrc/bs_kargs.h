@@ -246,6 +246,7 @@ struct RowsChainK {
 
 // The same chain with 3 x 3 windows and BatchNorm, ReLU behind each of them (pool_chain_kernel).  A lane owns two columns; a segment is
 // a plane or, of planes too wide for a wave, a column tile of it with halo_w columns on each inner side.
+// Ten levels take 108 vector registers in float32 (131 with odd rows: three waves per SIMD); more were not measured.
 constexpr int K_BLOCKS_MAX = 10;
 struct ChainK {
     const void *in;
