@@ -286,13 +286,15 @@ class BrainSlugStack(nn.Module):
         where to write the result -- a tensor of the output's shape, dense in the input's memory
         format or a channel slice of such a tensor (a concatenation buffer); when it does not fit
         (shape, type, alignment) it is ignored and a new tensor is returned."""
-        if out is None and not self.training:
-            done = self._native_forward(x, residuals)
-            if done is not None:
-                return done
         if self.training:
             raise RuntimeError("BrainSlugStack implements inference-mode layers only (BatchNorm with running "
                                "statistics): call model.eval(); gradients still flow in that mode")
+        if self._bn_seen:
+            self.sync_parameters()
+        if out is None:
+            done = self._native_forward(x, residuals)
+            if done is not None:
+                return done
         if not x.is_cuda:
             raise RuntimeError("BrainSlugStack needs a tensor on the GPU")
         if x.dim() != 4:
@@ -304,8 +306,6 @@ class BrainSlugStack(nn.Module):
                 raise RuntimeError("residual operands must have the input's shape (no broadcasting)")
             flat = self.forward(x.contiguous().view(1, 1, 1, -1), *[r.contiguous().view(1, 1, 1, -1) for r in residuals])
             return flat.view(x.shape)
-        if self._bn_seen:
-            self.sync_parameters()
         if self.channels is not None and x.shape[1] != self.channels:
             raise RuntimeError(f"expected {self.channels} channels, got {x.shape[1]}")
         if torch.is_grad_enabled() and (x.requires_grad or any(r.requires_grad for r in residuals)):
@@ -351,8 +351,6 @@ class BrainSlugStack(nn.Module):
 
     def _native_forward(self, x, residuals):
         """The call through the plan's native binding where there is a plan and the operands are dense; else None."""
-        if self._bn_seen:
-            self.sync_parameters()
         record = torch.is_grad_enabled() and (x.requires_grad or any(r.requires_grad for r in residuals))
         try:
             st = self._plans.get((x.shape, x.dtype, not x.is_contiguous(), record))

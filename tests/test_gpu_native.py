@@ -220,3 +220,22 @@ def test_same_results_without_the_native_module(monkeypatch):
     native = results()
     monkeypatch.setattr(bs, "_torch_module", False)
     assert all(torch.equal(a, b) for a, b in zip(native, results()))
+
+
+def test_parameters_are_looked_at_once_per_call(monkeypatch):
+    """Whichever path takes the call: dense, a channel slice, a given output, recorded by autograd, not 4-D."""
+    bn = torch.nn.BatchNorm2d(8).cuda().eval()
+    m = BrainSlugStack([bn, torch.nn.ReLU()]).eval()
+    looks, real = [], m.sync_parameters
+    monkeypatch.setattr(m, "sync_parameters", lambda: (looks.append(1), real())[1])
+    wide = torch.randn(2, 24, 12, 16, device="cuda")
+    x = wide[:, 8:16].contiguous()
+    want = torch.relu(bn(x)).detach()
+    for call in (lambda: m(x), lambda: m(wide[:, 8:16]), lambda: m(x, out=torch.empty_like(x)), lambda: m(x.clone().requires_grad_()),
+                 lambda: m(wide.clone().requires_grad_()[:, 8:16])):
+        for _ in range(2):  # the first call plans
+            looks.clear()
+            assert torch.allclose(call(), want, atol=1e-5) and len(looks) == 1
+    with torch.no_grad():
+        bn.bias.add_(1.0)
+    assert torch.allclose(m(wide[:, 8:16]), torch.relu(bn(x)), atol=1e-5) and torch.allclose(m(x), torch.relu(bn(x)), atol=1e-5)
