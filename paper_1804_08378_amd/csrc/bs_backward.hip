@@ -97,13 +97,8 @@ BS_DEV int32_t ew_sweep_impl(const BwdK &k, const int32_t (&c)[R], const uint32_
                 // tables start at multiples of 8 floats and c[0], C are multiples of VEC: 128-bit loads
                 float sc[VEC], sh[VEC];
                 if constexpr (FLAT) {  // elements of the whole tensor: the channels go round
-                    int32_t ch = c[0];
-#pragma unroll
-                    for (int e = 0; e < VEC; ++e) {
-                        sc[e] = k.params[arg + ch];
-                        sh[e] = k.params[arg + k.C + ch];
-                        ch = ch + 1 == k.C ? 0 : ch + 1;
-                    }
+                    load_params_round<VEC>(k.params, (uint32_t)arg, (uint32_t)c[0], (uint32_t)k.C, sc);
+                    load_params_round<VEC>(k.params, (uint32_t)(arg + k.C), (uint32_t)c[0], (uint32_t)k.C, sh);
                 } else if constexpr (VEC % 4 == 0) {
 #pragma unroll
                     for (int q = 0; q < VEC / 4; ++q) {

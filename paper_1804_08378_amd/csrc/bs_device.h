@@ -277,6 +277,41 @@ BS_DEV void store_elems(void *base, uint32_t elem, const float (&v)[N])
     }
 }
 
+// Parameters of VEC consecutive channels from c0 (below C) on, which start again at 0 behind the last one: the table's VEC floats from c0 in 128-bit
+// loads at any multiple of four bytes, and in the lanes that go round the ones that end before it begins again.  Reads up to VEC - 1 floats beside the
+// table (the parameter buffer has K_PARAMS_SLACK floats at both ends).  One request per float instead, BatchNorm -> ReLU twice, 4 x 1001 x 31 x 31
+// bfloat16: see nhwc_stream_flat_kernel.
+template <int VEC>
+BS_DEV void load_params_round(const float *__restrict__ params, uint32_t table, uint32_t c0, uint32_t C, float (&v)[VEC])
+{
+    if (VEC > 1 && C >= (uint32_t)VEC) {  // the same for every lane
+        struct __attribute__((packed, aligned(4))) Four { float f[4]; };
+        static_assert(VEC == 1 || VEC % 4 == 0, "whole loads");
+        const float *p = params + (table + c0);
+#pragma unroll
+        for (int q = 0; q < VEC / 4; ++q) {
+            const Four t = *reinterpret_cast<const Four *>(p + 4 * q);
+#pragma unroll
+            for (int i = 0; i < 4; ++i) v[4 * q + i] = t.f[i];
+        }
+        if (c0 + VEC > C) {
+#pragma unroll
+            for (int q = 0; q < VEC / 4; ++q) {
+                const Four t = *reinterpret_cast<const Four *>(p + 4 * q - (int64_t)C);
+#pragma unroll
+                for (int i = 0; i < 4; ++i) v[4 * q + i] = c0 + 4 * q + i < C ? v[4 * q + i] : t.f[i];
+            }
+        }
+    } else {
+        uint32_t ch = c0;
+#pragma unroll
+        for (int i = 0; i < VEC; ++i) {
+            v[i] = params[table + ch];
+            ch = ch + 1 == C ? 0u : ch + 1;
+        }
+    }
+}
+
 // The same for one or two elements as non-temporal stores (whole cache lines of a wave, written once and not read again).
 struct NonTemporal {};
 template <int DT, int N>

@@ -503,22 +503,23 @@ bs_status upload_params(bs_stack *s)
     if (s->host_params.empty()) return BS_OK;
     const size_t bytes = s->host_params.size() * sizeof(float);
     float *d = nullptr;
-    hipError_t e = hipMalloc(reinterpret_cast<void **>(&d), bytes);
+    // (the slack at both ends is read beside the tables and never used)
+    hipError_t e = hipMalloc(reinterpret_cast<void **>(&d), bytes + 2 * K_PARAMS_SLACK * sizeof(float));
     if (e != hipSuccess) return hip_fail(e);
     // synchronous copy from pageable memory: complete when it returns
-    e = hipMemcpy(d, s->host_params.data(), bytes, hipMemcpyHostToDevice);
+    e = hipMemcpy(d + K_PARAMS_SLACK, s->host_params.data(), bytes, hipMemcpyHostToDevice);
     if (e != hipSuccess) {
         (void)hipFree(d);
         return hip_fail(e);
     }
-    s->dev_params = d;
+    s->dev_params = d + K_PARAMS_SLACK;
     return BS_OK;
 }
 
 void free_params(bs_stack *s)
 {
     if (s->dev_params) {
-        (void)hipFree(s->dev_params);
+        (void)hipFree(s->dev_params - K_PARAMS_SLACK);
         s->dev_params = nullptr;
     }
 }

@@ -37,13 +37,8 @@ BS_DEV void apply_ew_nhwc(float (&x)[U][VEC], uint32_t c0, const uint32_t (&off)
         if (kind == OP_BN) {
             float sc[VEC], sh[VEC];
             if constexpr (FLAT) {
-                uint32_t ch = c0;
-#pragma unroll
-                for (int i = 0; i < VEC; ++i) {
-                    sc[i] = params[(uint32_t)arg + ch];
-                    sh[i] = params[(uint32_t)(arg + C) + ch];
-                    ch = ch + 1 == (uint32_t)C ? 0u : ch + 1;
-                }
+                load_params_round<VEC>(params, (uint32_t)arg, c0, (uint32_t)C, sc);
+                load_params_round<VEC>(params, (uint32_t)(arg + C), c0, (uint32_t)C, sh);
             } else {
                 load_params<VEC>(params, (uint32_t)arg + c0, sc);
                 load_params<VEC>(params, (uint32_t)(arg + C) + c0, sh);
