@@ -79,15 +79,16 @@ BS_DEV int32_t ew_sweep_impl(const BwdK &k, const int32_t (&c)[R], const uint32_
 #pragma unroll
                 for (int e = 0; e < VEC; ++e) x[j][e] = round_store<DT>(x[j][e] + v[e]);
             }
-            // from here on the residual's gradient collects the same factors as the input's
+            // From here on the residual's gradient collects the same factors as the input's.  Selects: a branch around the writes kept the whole
+            // array in scratch memory (two Adds, 32 x 64 x 56 x 56 channels-last, us, branch / selects: float32 72 / 35, bfloat16 89 / 23).
 #pragma unroll
-            for (int n = 0; n < NR; ++n)
-                if (n == adds) {
+            for (int n = 0; n < NR; ++n) {
+                const bool here = n == adds;
 #pragma unroll
-                    for (int j = 0; j < R; ++j)
+                for (int j = 0; j < R; ++j)
 #pragma unroll
-                        for (int e = 0; e < VEC; ++e) r[n][j][e] = 1.0f;
-                }
+                    for (int e = 0; e < VEC; ++e) r[n][j][e] = here ? 1.0f : r[n][j][e];
+            }
             ++adds;
             return;
         }

@@ -11,14 +11,18 @@ BIN = "/opt/rocm/lib/llvm/bin"
 WAIT_STATES = 2  # between a vector instruction that writes a lane mask (VCC or a scalar pair) and a vector instruction that reads it
 
 
-def disassemble(obj: str, tmp: str) -> str:
-    """Assembly of the device code inside an object that build() made."""
+def device_code(obj: str, tmp: str) -> str:
+    """File with the device code inside an object that build() made."""
     bundle, code = os.path.join(tmp, "bundle"), os.path.join(tmp, "code")
     subprocess.run([f"{BIN}/llvm-objcopy", f"--dump-section=.hip_fatbin={bundle}", obj, os.path.join(tmp, "rest.o")], check=True)
     subprocess.run([f"{BIN}/clang-offload-bundler", "--type=o", "--unbundle", f"--input={bundle}",
                     "--targets=hipv4-amdgcn-amd-amdhsa--gfx950", f"--output={code}"], check=True)
-    return subprocess.run([f"{BIN}/llvm-objdump", "-d", "--no-show-raw-insn", "--no-leading-addr", code], check=True, capture_output=True,
-                          text=True).stdout
+    return code
+
+
+def disassemble(obj: str, tmp: str) -> str:
+    return subprocess.run([f"{BIN}/llvm-objdump", "-d", "--no-show-raw-insn", "--no-leading-addr", device_code(obj, tmp)], check=True,
+                          capture_output=True, text=True).stdout
 
 
 def mask_reads(lines):
@@ -58,6 +62,20 @@ def test_selects_wait_for_the_compares_that_write_their_masks(source, tmp_path):
             short.append((states, line))
     print(f"{source}: {pairs} compare-select pairs")
     assert not short, (len(short), short[:5])
+
+
+@pytest.mark.parametrize("source", ["bs_backward.hip", "bs_backward_strip.hip", "bs_chain.hip", "bs_chain_nhwc.hip", "bs_nhwc.hip", "bs_kernels.hip"])
+def test_kernels_keep_nothing_in_scratch_memory(source, tmp_path):
+    """The factors of up to four residual gradients, rings and row buffers are arrays that must become registers."""
+    build.build(force=False)
+    obj = os.path.join(build.HERE, "_build", source + ".o")
+    if not os.path.exists(obj) or not os.path.exists(BIN):
+        pytest.skip("needs the build's objects and the ROCm toolchain")
+    notes = subprocess.run([f"{BIN}/llvm-readelf", "--notes", device_code(obj, str(tmp_path))], check=True, capture_output=True, text=True).stdout
+    sizes = re.findall(r"\.name:\s+(_Z\w+).*?\.private_segment_fixed_size:\s+(\d+)", notes, re.S)
+    assert sizes
+    scratch = [(name, int(n)) for name, n in sizes if int(n)]
+    assert not scratch, (len(scratch), scratch[:5])
 
 
 def test_audit_builds_check_every_access_of_the_backward_strip_kernels():
