@@ -1258,7 +1258,8 @@ static void launch_stage(const BwdK &k, dim3 g, dim3 b, hipStream_t st)
         if (has_add) bwd_stage_kernel<DT, VEC, 3, 3, 1, 1, 1><<<g, b, 0, st>>>(k);
         else bwd_stage_kernel<DT, VEC, 3, 3, 1, 1, 1, 0><<<g, b, 0, st>>>(k);
     }
-    else bwd_stage_kernel<DT, VEC, 0, 0, 0, 0, 0><<<g, b, 0, st>>>(k);
+    else if (has_add) bwd_stage_kernel<DT, VEC, 0, 0, 0, 0, 0><<<g, b, 0, st>>>(k);
+    else bwd_stage_kernel<DT, VEC, 0, 0, 0, 0, 0, 0><<<g, b, 0, st>>>(k);
 }
 
 bs_status launch_backward_stage(const BwdK &k, int32_t dtype, int32_t vec, int64_t grid, int32_t threads, void *stream)

@@ -58,7 +58,9 @@ inline bool op_is_elementwise(int32_t k) { return k != OP_MAXPOOL && k != OP_AVG
 constexpr int K_MAX_LEVELS = 8;   // pooling operations in one LDS sequence
 constexpr int K_MAX_EW = 6;       // element-wise operations attached to one level
 constexpr int K_MAX_STREAM_EW = 16;
-constexpr int K_PARAMS_SLACK = 8; // floats that may be read in front of and behind the parameter tables (load_params_round)
+// Floats in front of and behind the parameter tables: load_params_round reads up to 7 there; 256 bytes, so that the tables begin at a cache line
+// (32 bytes: up to 7 % slower in small launches of other kernels).
+constexpr int K_PARAMS_SLACK = 64;
 constexpr int K_MAX_RES = 4;      // residual tensors one sequence can read
 constexpr int K_MAX_IDX = 4;      // index tensors one sequence can write
 constexpr int K_STREAM_U = 2;     // 128-bit vectors per lane in stream_kernel (measured on MI355X: 1 is 3..9 points of HBM peak slower, 4 is 1..3 slower with 16-bit storage)
