@@ -26,8 +26,9 @@
 namespace bs {
 
 // Element-wise only.  A work-group takes nthr * U consecutive vectors; lane t handles vectors
-// t, t + nthr, ...  CODE: the kinds of the list's operations as a compile-time code (apply_ew_nhwc), or -1.
-template <int DT, int VEC, int U, int CODE = -1>
+// t, t + nthr, ...  CODE: the kinds of the list's operations as a compile-time code (apply_ew_nhwc), or -1.  CACHED: the input is read
+// through the caches (NhwcK::cached); an instance each, as in stream_kernel.
+template <int DT, int VEC, int U, int CODE, bool CACHED>
 __global__ __launch_bounds__(512) void nhwc_stream_kernel(const NhwcK k)
 {
     const uint32_t nthr = blockDim.x;
@@ -47,13 +48,7 @@ __global__ __launch_bounds__(512) void nhwc_stream_kernel(const NhwcK k)
             i = valid[u] ? i : base % cvn;  // a vector of the same channels at the start of the tensor
             off[u] = i * VEC;
             pixel[u] = fdiv(i, k.div_cv);
-        }
-        if (k.cached) {  // the same for every lane
-#pragma unroll
-            for (int u = 0; u < U; ++u) raw[u] = load_raw<DT, VEC>(k.in, off[u] + pixel[u] * k.in_xp);
-        } else {
-#pragma unroll
-            for (int u = 0; u < U; ++u) raw[u] = load_raw<DT, VEC, true>(k.in, off[u] + pixel[u] * k.in_xp);
+            raw[u] = load_raw<DT, VEC, !CACHED>(k.in, off[u] + pixel[u] * k.in_xp);
         }
         float x[U][VEC];
 #pragma unroll
@@ -496,6 +491,13 @@ static void launch_block(const NhwcK &k, dim3 grid, dim3 block, hipStream_t st)
     else nhwc_pool_kernel<DT, VEC, KH, KW, SH, SW, OHB, OWB, false><<<grid, block, 0, st>>>(k);
 }
 
+template <int DT, int VEC, int CODE = -1>
+static void launch_stream_as(const NhwcK &k, dim3 grid, dim3 block, hipStream_t st)
+{
+    if (k.cached) nhwc_stream_kernel<DT, VEC, K_STREAM_U, CODE, true><<<grid, block, 0, st>>>(k);
+    else nhwc_stream_kernel<DT, VEC, K_STREAM_U, CODE, false><<<grid, block, 0, st>>>(k);
+}
+
 template <int DT, int VEC>
 static bs_status launch_nhwc_t(const NhwcK &k, int32_t dtype, dim3 grid, dim3 block, uint64_t lds_bytes, hipStream_t st)
 {
@@ -506,11 +508,11 @@ static bs_status launch_nhwc_t(const NhwcK &k, int32_t dtype, dim3 grid, dim3 bl
         if constexpr (VEC > 1) {
             const int32_t code = list_code(k.pre, k.n_pre);
             if (code == BN_RELU) {
-                nhwc_stream_kernel<DT, VEC, K_STREAM_U, BN_RELU><<<grid, block, 0, st>>>(k);
+                launch_stream_as<DT, VEC, BN_RELU>(k, grid, block, st);
                 return BS_OK;
             }
             if (code == BN_ADD_RELU) {
-                nhwc_stream_kernel<DT, VEC, K_STREAM_U, BN_ADD_RELU><<<grid, block, 0, st>>>(k);
+                launch_stream_as<DT, VEC, BN_ADD_RELU>(k, grid, block, st);
                 return BS_OK;
             }
         }
@@ -526,10 +528,10 @@ static bs_status launch_nhwc_t(const NhwcK &k, int32_t dtype, dim3 grid, dim3 bl
                 return BS_OK;
             }
             const uint64_t per_group = (uint64_t)block.x * K_STREAM_U;
-            nhwc_stream_kernel<DT, VEC, K_STREAM_U><<<dim3((uint32_t)((k.total + per_group - 1) / per_group)), block, 0, st>>>(k);
+            launch_stream_as<DT, VEC>(k, dim3((uint32_t)((k.total + per_group - 1) / per_group)), block, st);
             return BS_OK;
         }
-        nhwc_stream_kernel<DT, VEC, K_STREAM_U><<<grid, block, 0, st>>>(k);
+        launch_stream_as<DT, VEC>(k, grid, block, st);
         return BS_OK;
     }
     if (k.cv_group > 0) {
