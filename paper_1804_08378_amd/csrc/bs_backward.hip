@@ -98,8 +98,7 @@ BS_DEV int32_t ew_sweep_impl(const BwdK &k, const int32_t (&c)[R], const uint32_
                 // tables start at multiples of 8 floats and c[0], C are multiples of VEC: 128-bit loads
                 float sc[VEC], sh[VEC];
                 if constexpr (FLAT) {  // elements of the whole tensor: the channels go round
-                    load_params_round<VEC>(k.params, (uint32_t)arg, (uint32_t)c[0], (uint32_t)k.C, sc);
-                    load_params_round<VEC>(k.params, (uint32_t)(arg + k.C), (uint32_t)c[0], (uint32_t)k.C, sh);
+                    load_bn_round<VEC>(k.params, (uint32_t)arg, (uint32_t)c[0], (uint32_t)k.C, sc, sh);
                 } else if constexpr (VEC % 4 == 0) {
 #pragma unroll
                     for (int q = 0; q < VEC / 4; ++q) {
@@ -1133,9 +1132,10 @@ __global__ __launch_bounds__(256) void bwd_stage_nhwc_kernel(const BwdK k)
 }
 
 // An element-wise stage on dense channels-last tensors whose channels are no whole vectors: the tensor is one run of elements,
-// a lane takes VEC of them, each with the parameters of its own channel (from the caches); the elements behind the last whole
-// vector one at a time.  BatchNorm -> Add -> ReLU, one element per lane / this: 10 x 30 x 193 x 193 bfloat16 74 / 28 us (112 MB), float32
-// 75 / 37 (224 MB, 6 TB/s); BatchNorm -> ReLU 16 x 132 x 56 x 56 binary16 33 / 22 (40 MB: the 16 parameter requests per BatchNorm).
+// a lane takes VEC of them, each with the parameters of its own channel (from the caches, in 128-bit requests); the elements behind the last
+// whole vector one at a time.  us, one element per lane / a vector per lane, one request per parameter / this: BatchNorm -> Add -> ReLU
+// 10 x 30 x 193 x 193 bfloat16 72 / 27 / 22.8 (112 MB, 4.9 TB/s), float32 74 / 38 / 36.4 (224 MB, 6.1 TB/s); BatchNorm -> ReLU 16 x 132 x 56 x 56
+// binary16 32 / 22 / 9.2 (40 MB); BatchNorm -> ReLU twice 4 x 1001 x 63 x 63 bfloat16 94 / 113 / 26, float32 86 / 63 / 37.
 template <int DT, int VEC, int NR, int PRE>
 BS_DEV void ew_nhwc_flat(const BwdK &k, uint32_t off)
 {

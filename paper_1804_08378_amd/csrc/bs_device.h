@@ -277,36 +277,49 @@ BS_DEV void store_elems(void *base, uint32_t elem, const float (&v)[N])
     }
 }
 
-// Parameters of VEC consecutive channels from c0 (below C) on, which start again at 0 behind the last one: the table's VEC floats from c0 in 128-bit
-// loads at any multiple of four bytes, and in the lanes that go round the ones that end before it begins again.  Reads up to VEC - 1 floats beside the
-// table (the parameter buffer has K_PARAMS_SLACK floats at both ends).  One request per float instead, BatchNorm -> ReLU twice, 4 x 1001 x 31 x 31
-// bfloat16: see nhwc_stream_flat_kernel.
+// BatchNorm factors (table `table`) and offsets (C floats behind it) of VEC consecutive channels from c0 (below C) on, which start again at 0 behind the
+// last one: each table's VEC floats from c0 in 128-bit loads at any multiple of four bytes, and in the lanes that go round the ones that end before
+// it begins again; the branch stands behind the requests of both tables.  Reads up to VEC - 1 floats beside the tables (the parameter buffer
+// has K_PARAMS_SLACK floats at both ends).  Figures against one request per float: nhwc_stream_flat_kernel.
 template <int VEC>
-BS_DEV void load_params_round(const float *__restrict__ params, uint32_t table, uint32_t c0, uint32_t C, float (&v)[VEC])
+BS_DEV void load_bn_round(const float *__restrict__ params, uint32_t table, uint32_t c0, uint32_t C, float (&sc)[VEC], float (&sh)[VEC])
 {
     if (VEC > 1 && C >= (uint32_t)VEC) {  // the same for every lane
         struct __attribute__((packed, aligned(4))) Four { float f[4]; };
         static_assert(VEC == 1 || VEC % 4 == 0, "whole loads");
-        const float *p = params + (table + c0);
+        const Four *p = reinterpret_cast<const Four *>(params + (table + c0));
+        const Four *q = reinterpret_cast<const Four *>(params + (table + C + c0));
+        Four a[VEC / 4 + 1], b[VEC / 4 + 1];
 #pragma unroll
-        for (int q = 0; q < VEC / 4; ++q) {
-            const Four t = *reinterpret_cast<const Four *>(p + 4 * q);
+        for (int n = 0; n < VEC / 4; ++n) {
+            a[n] = p[n];
+            b[n] = q[n];
+        }
 #pragma unroll
-            for (int i = 0; i < 4; ++i) v[4 * q + i] = t.f[i];
+        for (int i = 0; i < VEC; ++i) {
+            sc[i] = a[i / 4].f[i % 4];
+            sh[i] = b[i / 4].f[i % 4];
         }
         if (c0 + VEC > C) {
+            p = reinterpret_cast<const Four *>(params + table + ((int64_t)c0 - C));
+            q = reinterpret_cast<const Four *>(params + (table + c0));
 #pragma unroll
-            for (int q = 0; q < VEC / 4; ++q) {
-                const Four t = *reinterpret_cast<const Four *>(p + 4 * q - (int64_t)C);
+            for (int n = 0; n < VEC / 4; ++n) {
+                a[n] = p[n];
+                b[n] = q[n];
+            }
 #pragma unroll
-                for (int i = 0; i < 4; ++i) v[4 * q + i] = c0 + 4 * q + i < C ? v[4 * q + i] : t.f[i];
+            for (int i = 0; i < VEC; ++i) {
+                sc[i] = c0 + i < C ? sc[i] : a[i / 4].f[i % 4];
+                sh[i] = c0 + i < C ? sh[i] : b[i / 4].f[i % 4];
             }
         }
     } else {
         uint32_t ch = c0;
 #pragma unroll
         for (int i = 0; i < VEC; ++i) {
-            v[i] = params[table + ch];
+            sc[i] = params[table + ch];
+            sh[i] = params[table + C + ch];
             ch = ch + 1 == C ? 0u : ch + 1;
         }
     }

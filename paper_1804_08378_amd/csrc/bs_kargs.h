@@ -49,6 +49,13 @@ constexpr int ew_code_kind(int code, int q)
     for (int i = 0; i < q; ++i) code /= K_EW_BASE;
     return code % K_EW_BASE;
 }
+// Position of the first operation of `kind` in the list, -1 without one.
+constexpr int ew_code_first(int code, int kind)
+{
+    for (int q = 0; code > 0; ++q, code /= K_EW_BASE)
+        if (code % K_EW_BASE == kind) return q;
+    return -1;
+}
 
 inline bool op_is_elementwise(int32_t k) { return k != OP_MAXPOOL && k != OP_AVGSUM; }
 
@@ -58,7 +65,7 @@ inline bool op_is_elementwise(int32_t k) { return k != OP_MAXPOOL && k != OP_AVG
 constexpr int K_MAX_LEVELS = 8;   // pooling operations in one LDS sequence
 constexpr int K_MAX_EW = 6;       // element-wise operations attached to one level
 constexpr int K_MAX_STREAM_EW = 16;
-// Floats in front of and behind the parameter tables: load_params_round reads up to 7 there; 256 bytes, so that the tables begin at a cache line
+// Floats in front of and behind the parameter tables: load_bn_round reads up to 7 there; 256 bytes, so that the tables begin at a cache line
 // (32 bytes: up to 7 % slower in small launches of other kernels).
 constexpr int K_PARAMS_SLACK = 64;
 constexpr int K_MAX_RES = 4;      // residual tensors one sequence can read

@@ -75,32 +75,32 @@ __global__ __launch_bounds__(512) void nhwc_stream_kernel(const NhwcK k)
 }
 
 // Element-wise only, dense tensors whose channels are no whole vectors: the tensor is one run of elements, a lane takes VEC of
-// them, each with its own channel's parameters (from the caches); the elements behind the last whole vector one at a time.
-// BatchNorm -> Add -> ReLU, one element per lane / this, us: 10 x 30 x 193 x 193 bfloat16 52 / 22, float32 50 / 24 (134 MB, 5.6 TB/s); BatchNorm ->
-// ReLU 16 x 132 x 56 x 56 binary16 24 / 22 (the parameter requests).
-template <int DT, int VEC, int CODE>
+// them, each with its own channel's parameters (from the caches, in 128-bit requests); the elements behind the last whole vector one at a time.
+// us, one element per lane / a vector per lane, one request per parameter / this: BatchNorm -> Add -> ReLU 10 x 30 x 193 x 193 bfloat16 51 / 21 /
+// 15.5, float32 49 / 24 / 21.8 (134 MB, 6.2 TB/s); BatchNorm -> ReLU 16 x 132 x 56 x 56 binary16 22 / 21 / 6.3 (26 MB: cached); BatchNorm -> ReLU
+// twice 4 x 1001 x 63 x 63 bfloat16 66 / 109 / 18.8, float32 64 / 60 / 23.  CACHED: an instance as in nhwc_stream_kernel (3 to 9 % of the small ones).
+template <int DT, int VEC, int CODE, bool CACHED>
 BS_DEV void stream_flat(const NhwcK &k, uint32_t off)
 {
     const uint32_t c0 = off - fdiv(off, k.div_cv) * k.div_cv.d;  // one element per vector in the plan: div_cv divides by C
     const uint32_t offs[1] = {off};
     float x[1][VEC];
-    if (k.cached) unpack<DT, VEC>(load_raw<DT, VEC>(k.in, off), x[0]);  // the same for every lane
-    else unpack<DT, VEC>(load_raw<DT, VEC, true>(k.in, off), x[0]);
+    unpack<DT, VEC>(load_raw<DT, VEC, !CACHED>(k.in, off), x[0]);
     apply_ew_nhwc<DT, VEC, 1, CODE, true>(x, c0, offs, k.pre, k.n_pre, k.params, k.C, k.res);
     store_elems<DT, VEC>(k.out, off, x[0]);
 }
 
-template <int DT, int VEC, int CODE = -1>
+template <int DT, int VEC, int CODE, bool CACHED>
 __global__ __launch_bounds__(512) void nhwc_stream_flat_kernel(const NhwcK k)
 {
     const uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i > (k.total - 1) / VEC) return;  // total = elements of the tensor
     const uint32_t off = i * VEC;
     if (k.total - off >= VEC) {
-        stream_flat<DT, VEC, CODE>(k, off);
+        stream_flat<DT, VEC, CODE, CACHED>(k, off);
     } else {
 #pragma clang loop unroll(disable)
-        for (uint32_t e = off; e < k.total; ++e) stream_flat<DT, 1, -1>(k, e);
+        for (uint32_t e = off; e < k.total; ++e) stream_flat<DT, 1, -1, CACHED>(k, e);
     }
 }
 
@@ -498,6 +498,13 @@ static void launch_stream_as(const NhwcK &k, dim3 grid, dim3 block, hipStream_t 
     else nhwc_stream_kernel<DT, VEC, K_STREAM_U, CODE, false><<<grid, block, 0, st>>>(k);
 }
 
+template <int DT, int VEC, int CODE = -1>
+static void launch_flat_as(const NhwcK &k, dim3 grid, dim3 block, hipStream_t st)
+{
+    if (k.cached) nhwc_stream_flat_kernel<DT, VEC, CODE, true><<<grid, block, 0, st>>>(k);
+    else nhwc_stream_flat_kernel<DT, VEC, CODE, false><<<grid, block, 0, st>>>(k);
+}
+
 template <int DT, int VEC>
 static bs_status launch_nhwc_t(const NhwcK &k, int32_t dtype, dim3 grid, dim3 block, uint64_t lds_bytes, hipStream_t st)
 {
@@ -522,9 +529,9 @@ static bs_status launch_nhwc_t(const NhwcK &k, int32_t dtype, dim3 grid, dim3 bl
                 constexpr int V = DT == DT_F32 ? 4 : 8;
                 const int32_t code = list_code(k.pre, k.n_pre);
                 if ((uint64_t)grid.x * block.x * V < k.total) return BS_ERR_UNSUPPORTED;
-                if (code == BN_RELU) nhwc_stream_flat_kernel<DT, V, BN_RELU><<<grid, block, 0, st>>>(k);
-                else if (code == BN_ADD_RELU) nhwc_stream_flat_kernel<DT, V, BN_ADD_RELU><<<grid, block, 0, st>>>(k);
-                else nhwc_stream_flat_kernel<DT, V><<<grid, block, 0, st>>>(k);
+                if (code == BN_RELU) launch_flat_as<DT, V, BN_RELU>(k, grid, block, st);
+                else if (code == BN_ADD_RELU) launch_flat_as<DT, V, BN_ADD_RELU>(k, grid, block, st);
+                else launch_flat_as<DT, V>(k, grid, block, st);
                 return BS_OK;
             }
             const uint64_t per_group = (uint64_t)block.x * K_STREAM_U;
