@@ -53,6 +53,7 @@ struct Sequence {
     PoolRows2K rows2{};
     RowsChainK chain{};
     ChainK blocks{};          // n_levels > 0: the chain as blocks of 3 x 3 maximum, BatchNorm, ReLU
+    ChainWindowK window{};    // n_levels > 0: the blocks as one window
     ChainNhwcK blocks_cl{};   // n_levels > 0: the same channels-last
     LdsSeqK lds{};
     NhwcK nhwc{};
@@ -220,6 +221,12 @@ int32_t blocks_most_rows(const ChainK &k);
 bool blocks_launchable(const ChainK &k, int64_t planes, int64_t grid, int32_t threads);
 std::string blocks_expr(const ChainK &k, int32_t dtype);
 bs_status launch_blocks(const ChainK &k, int32_t dtype, int64_t grid, int32_t threads, void *stream);
+// ... as one window (chain_window_kernel; binary16: a run-time build).  window_geometry: false if the kernel does not take the planes or its LDS is above max_lds
+bool window_geometry(ChainWindowK &k, int32_t dtype, const Limits &lim, int64_t *grid, int32_t *threads);
+uint64_t window_lds(const ChainWindowK &k);
+bool window_launchable(const ChainWindowK &k, int32_t dtype, int64_t planes, int64_t grid, int32_t threads);
+std::string window_expr(const ChainWindowK &k, int32_t dtype);
+bs_status launch_window(const ChainWindowK &k, int32_t dtype, int64_t grid, int32_t threads, void *stream);
 // ... channels-last (pool_chain_nhwc_kernel)
 bool chain_nhwc_geometry(ChainNhwcK &k, int64_t images, int32_t dtype, int32_t num_cus, int64_t *grid);
 uint64_t chain_nhwc_lds_bytes(const ChainNhwcK &k);

@@ -273,6 +273,24 @@ struct ChainK {
     FastDiv div_chunks, div_pitch, div_tiles, div_c;
 };
 
+// The same blocks as one window of (2 n_levels + 1)^2 cells (chain_window_kernel): scales above zero on every level but the last.
+constexpr int K_WINDOW_THREADS = 512;
+struct ChainWindowK {
+    const void *in;
+    void *out;
+    const float *params;
+    uint32_t in_extra, out_extra;  // as above
+    int32_t n_levels;
+    int32_t bn[K_BLOCKS_MAX];
+    int32_t C, H, W;
+    int32_t rc, chunks;            // output rows of a work-group, chunks per plane
+    int32_t ppg;                   // planes per work-group (1 where a plane has several chunks)
+    int32_t rows, pitch;           // rows of a plane or chunk in LDS, words from one of them to the next
+    int32_t row_slots;             // rows of a plane that the work-group's threads hold at a time, four columns each
+    uint32_t planes;
+    FastDiv div_chunks, div_c, div_plane_tasks, div_vecs, div_second;
+};
+
 // Fewest channels-last blocks in one launch of pool_chain_nhwc_kernel (two and three run as strips).
 #if !defined(BS_BLOCKS_NHWC_MIN)
 #define BS_BLOCKS_NHWC_MIN 4

@@ -747,6 +747,15 @@ bs_status launch_sequence(const bs_stack *s, const Sequence &q, const void *in, 
             if (ls != BS_OK) return ls;
             break;
         }
+        if (q.window.n_levels > 0) {
+            ChainWindowK k = q.window;
+            k.in = in; k.out = out; k.params = s->dev_params;
+            k.in_extra = in_extra; k.out_extra = out_extra;
+            if (!window_launchable(k, dtype, q.in_shape[0] * q.in_shape[1], q.grid, q.threads)) return BS_ERR_UNSUPPORTED;
+            const bs_status ls = q.jit ? launch_built(q, false, &k, sizeof k, stream) : launch_window(k, dtype, q.grid, q.threads, stream);
+            if (ls != BS_OK) return ls;
+            break;
+        }
         if (q.blocks.n_levels > 0) {
             ChainK k = q.blocks;
             k.in = in; k.out = out; k.params = s->dev_params;

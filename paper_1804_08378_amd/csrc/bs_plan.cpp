@@ -1220,13 +1220,59 @@ static void plan_blocks(const bs_stack *s, Sequence &q, const bs_plan_options &o
     q.redundancy = cells / ((double)k.H * k.W);
 }
 
+// Do the BatchNorms of all blocks but the last rise with their input, and by finite numbers?  Then the blocks are one window (chain_window_kernel).
+static bool blocks_rise(const bs_stack *s, const int32_t *bn, int32_t n_levels, int32_t C)
+{
+    for (int32_t l = 0; l + 1 < n_levels; ++l)
+        for (int32_t c = 0; c < C; ++c) {
+            const float scale = s->host_params[(size_t)bn[l] + c], shift = s->host_params[(size_t)bn[l] + C + c];
+            if (!(scale > 0.0f) || !std::isfinite(scale) || !std::isfinite(shift)) return false;
+        }
+    return true;
+}
+
+// The blocks as one window, where the plan leaves the kernel and its geometry to the planner and where that measured faster.  Level by level -> one
+// window, us: 64 x 64 x 56 x 56 float32 ten levels 28.5 -> 24.5; 17 x 64 x 149 x 149 float32 six levels 62.8 -> 48.4; 5 x 184 x 153 x 153 float32 three levels
+// 60.5 -> 38.6; 34 x 40 x 135 x 135 bfloat16 eight levels 83 -> 43; 16 x 232 x 46 x 140 binary16 eight levels 70.4 -> 30.3; 1 x 168 x 54 x 54 float32 nine levels
+// 12.9 -> 5.6.  16-bit storage with two and three levels stays level by level (three levels binary16 9 x 352 x 82 x 92 25.0 -> 29.7, bfloat16 102 x 32 x 147 x 46
+// 24.0 -> 26.1), and so does float32 with eight levels and more beyond the last cache, where a row is asked of the second-level cache
+// (8 + 2 levels) / 8 times (nine levels 7 x 472 x 86 x 86, 195 MB, 58.7 -> 65.7; below 128 MB 19 x 40 x 122 x 122 28.1 -> 23.6).
+static bool plan_window(const bs_stack *s, Sequence &q, const bs_plan_options &o, const Limits &lim)
+{
+    if (o.threads_per_group > 0 || o.tile_rows > 0 || o.tile_cols > 0 || o.planes_per_group > 0) return false;
+    if (lim.max_lds_bytes < 32 * 1024) return false;  // a caller's smaller budget: the kernel that needs no LDS
+    ChainWindowK k{};
+    const int32_t L = k.n_levels = q.blocks.n_levels;
+    std::copy(q.blocks.bn, q.blocks.bn + K_BLOCKS_MAX, k.bn);
+    k.C = (int32_t)q.in_shape[1];
+    k.H = q.blocks.H;
+    k.W = q.blocks.W;
+    k.planes = (uint32_t)(q.in_shape[0] * q.in_shape[1]);
+    const double bytes = 2.0 * (double)k.planes * k.H * k.W * (double)dtype_size(s->dtype);
+    if (s->dtype == BS_F32 ? L >= 8 && bytes > 128e6 : L < 4) return false;
+    if (!blocks_rise(s, k.bn, L, k.C) || !window_geometry(k, s->dtype, lim, &q.grid, &q.threads)) return false;
+    q.window = k;
+    q.vec = 4;
+    q.lds_bytes = window_lds(k);
+    q.tile_rows = k.rc;
+    q.tile_cols = k.W;
+    q.planes_per_group = k.ppg;
+    q.n_levels = L;
+    q.halo_rows = 2 * L;
+    q.halo_cols = 0;
+    double rows = 0;
+    for (int32_t a = 0; a < k.H; a += k.rc) rows += std::min(k.H, a + k.rc + L) - std::max(0, a - L);
+    q.redundancy = rows / k.H;
+    return true;
+}
+
 static void plan_chain(const bs_stack *s, Sequence &q, const bs_plan_options &o, const Limits &lim)
 {
     q.variant = BS_VARIANT_ROWS_CHAIN;
     q.n_idx = 0;
     chain_applicable(s, q.first_op, q.n_ops, &q);
     if (q.blocks.n_levels > 0) {
-        plan_blocks(s, q, o, lim);
+        if (!plan_window(s, q, o, lim)) plan_blocks(s, q, o, lim);
         return;
     }
     RowsChainK &k = q.chain;
@@ -1643,6 +1689,10 @@ static bool audit_lds(const Sequence &q)
 static const char *jit_names(const bs_stack *s, const Sequence &q, std::string (&expr)[2])
 {
     if (q.variant == BS_VARIANT_ROWS_CHAIN) {
+        if (q.window.n_levels > 0) {
+            expr[0] = expr[1] = window_expr(q.window, s->dtype);
+            return "bs_chain_window_device.h";
+        }
         if (q.blocks.n_levels > 0) {
             expr[0] = expr[1] = blocks_expr(q.blocks, s->dtype);
             return "bs_chain_device.h";

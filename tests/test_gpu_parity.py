@@ -409,6 +409,41 @@ def test_stacked_blocks_of_any_width(shape, levels, dtype):
         assert same.all(), (rc, np.argwhere(~same)[:4])
 
 
+@pytest.mark.parametrize("shape,levels", [((1, 3, 7, 8), 10), ((2, 2, 1, 9), 2), ((1, 2, 3, 64), 3), ((3, 5, 30, 31), 4), ((1, 2, 20, 63), 5), ((1, 2, 41, 126), 6),
+                                          ((1, 2, 33, 127), 7), ((1, 3, 200, 129), 8), ((2, 2, 224, 224), 9), ((1, 1, 95, 255), 10), ((5, 700, 9, 11), 4),
+                                          ((1, 3, 6, 4), 4), ((7, 3, 56, 56), 10)])
+@pytest.mark.parametrize("dtype", ["f32", "bf16", "f16"])
+def test_stacked_blocks_as_one_window(shape, levels, dtype):
+    """Blocks whose BatchNorms rise with their input (the last one's scales of any sign): one window of (2 levels + 1)^2 cells and the lists behind it, bit
+    for bit the levels' own results.  Rows of whole vectors and not, rows and planes smaller than the window, chunks of rows, several planes in a
+    work-group with some left over, zeros of both signs, infinities and (against the kernel that goes level by level) NaN."""
+    c = shape[1]
+    layers = []
+    for i in range(levels):
+        bn = wl.bn_params(c, 800 + i)
+        if i + 1 == levels:
+            bn["gamma"] = bn["gamma"] * np.where(np.arange(c) % 3 == 1, -1.0, 1.0).astype(np.float32)
+            bn["gamma"][0] = 0.0
+        layers += [wl.maxpool(3, 1, 1), bn, wl.relu()]
+    x = wl.activation(shape, 79, dtype)
+    x[:, :, ::2, 1::3] = 0.5
+    x[:, :, ::3, ::4] = -np.inf
+    x[:, :, 1::3, ::5] = -0.0
+    if shape[2] > 8:
+        x[0, -1, 5, 2] = np.inf
+    ref, _, _ = bf.run_stack(layers, x, [], dtype)
+    out, _, info = run_gpu(layers, x, [], dtype)
+    q, = info["sequences"]
+    window = dtype == "f32" or levels >= 4
+    assert q["variant_name"] == "rows_chain" and (q["lds_bytes"] > 0) == window  # (the kernel that goes level by level needs no LDS)
+    assert ((out == ref) | (np.isnan(out) & np.isnan(ref))).all()
+    x[:, :, 2::5, 3::7] = np.nan
+    out, _, _ = run_gpu(layers, x, [], dtype)
+    ref, _, info = run_gpu(layers, x, [], dtype, tile_rows=shape[2])
+    assert info["sequences"][0]["lds_bytes"] == 0
+    assert ((out == ref) | (np.isnan(out) & np.isnan(ref))).all()
+
+
 def test_stacked_blocks_on_a_plane_of_more_than_four_gib():
     """Row offsets beyond 2^32 bytes: the rows around that place and the plane's last ones, against the same blocks on a copy of those rows;
     chunks of the planner's choice and the longest ones there are (a caller asks for the whole plane)."""
