@@ -54,6 +54,7 @@ struct Sequence {
     RowsChainK chain{};
     ChainK blocks{};          // n_levels > 0: the chain as blocks of 3 x 3 maximum, BatchNorm, ReLU
     ChainWindowK window{};    // n_levels > 0: the blocks as one window
+    ChainWindowNhwcK window_cl{};  // n_levels > 0: channels-last blocks as one window
     ChainNhwcK blocks_cl{};   // n_levels > 0: the same channels-last
     LdsSeqK lds{};
     NhwcK nhwc{};
@@ -231,6 +232,10 @@ bs_status launch_window(const ChainWindowK &k, int32_t dtype, int64_t grid, int3
 bool chain_nhwc_geometry(ChainNhwcK &k, int64_t images, int32_t dtype, int32_t num_cus, int64_t *grid);
 uint64_t chain_nhwc_lds_bytes(const ChainNhwcK &k);
 bs_status launch_chain_nhwc(const ChainNhwcK &k, int64_t images, int32_t dtype, int64_t grid, void *stream);
+// ... channels-last as one window (chain_window_nhwc_kernel)
+bool window_nhwc_geometry(ChainWindowNhwcK &k, int64_t images, int32_t dtype, int64_t *grid, int32_t *threads);
+uint64_t window_nhwc_lds(const ChainWindowNhwcK &k);
+bs_status launch_window_nhwc(const ChainWindowNhwcK &k, int64_t images, int32_t dtype, int64_t grid, int32_t threads, void *stream);
 // the chain kernel for other lists and windows (always a run-time build)
 bool xrows_chain_buildable(const RowsChainK &k, int32_t vec);
 bool xrows_chain_launchable(const RowsChainK &k, int32_t dtype, int64_t grid, int32_t threads);

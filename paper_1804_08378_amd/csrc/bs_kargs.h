@@ -313,6 +313,21 @@ struct ChainNhwcK {
     FastDiv div_groups, div_tiles, div_chunks, div_pitch, div_cv, div_nv;
 };
 
+// ... as one window (chain_window_nhwc_kernel): a work-group takes eight rows, tile_w columns and `lanes` vectors of channels of an image.
+struct ChainWindowNhwcK {
+    const void *in;
+    void *out;
+    const float *params;
+    uint32_t in_xp, out_xp;
+    int32_t n_levels;
+    int32_t bn[K_BLOCKS_MAX];
+    int32_t C, H, W;
+    int32_t vec, lanes;            // channels of a vector (4 or 1), vectors of a work-group
+    int32_t tile_w, tiles, work;   // columns a work-group writes (a multiple of four where there are several tiles), tiles, columns it reads
+    int32_t row_words;             // words of a row in LDS: columns with n_levels beside them on both sides
+    FastDiv div_groups, div_tiles, div_bands, div_lanes;
+};
+
 // Channels-last (N, H, W, C in memory) sequences: element-wise only (pool.kind == 0, the list
 // in `pre`) or one pooling operation with element-wise operations before and after it.
 struct NhwcK {

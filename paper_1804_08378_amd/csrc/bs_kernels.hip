@@ -736,6 +736,17 @@ bs_status launch_sequence(const bs_stack *s, const Sequence &q, const void *in, 
         break;
     }
     case BS_VARIANT_ROWS_CHAIN: {
+        if (q.window_cl.n_levels > 0) {
+            ChainWindowNhwcK k = q.window_cl;
+            const uint32_t hw = (uint32_t)(q.in_shape[2] * q.in_shape[3]);  // a slice skips the larger tensor's other channels in every pixel
+            if (in_extra % hw != 0 || out_extra % hw != 0) return BS_ERR_UNSUPPORTED;
+            k.in = in; k.out = out; k.params = s->dev_params;
+            k.in_xp = in_extra / hw;
+            k.out_xp = out_extra / hw;
+            const bs_status ls = launch_window_nhwc(k, q.in_shape[0], dtype, q.grid, q.threads, stream);
+            if (ls != BS_OK) return ls;
+            break;
+        }
         if (q.blocks_cl.n_levels > 0) {
             ChainNhwcK k = q.blocks_cl;
             const uint32_t hw = (uint32_t)(q.in_shape[2] * q.in_shape[3]);  // a slice skips the larger tensor's other channels in every pixel

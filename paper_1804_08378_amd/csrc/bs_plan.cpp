@@ -1312,8 +1312,9 @@ static void plan_chain(const bs_stack *s, Sequence &q, const bs_plan_options &o,
     q.redundancy = rows_loaded / (double)k.H;
 }
 
-// Channels-last: blocks <max pooling 3 x 3 / 1 / 1 without index output, BatchNorm, ReLU> in one sequence (pool_chain_nhwc_kernel).
-static bool plan_blocks_nhwc(const bs_stack *s, Sequence &q, const bs_plan_options &o, const Limits &lim)
+// Channels-last: blocks <max pooling 3 x 3 / 1 / 1 without index output, BatchNorm, ReLU> in one sequence (chain_window_nhwc_kernel, pool_chain_nhwc_kernel).
+// kinds_only: are they such blocks, whatever LDS the kernels need?
+static bool plan_blocks_nhwc(const bs_stack *s, Sequence &q, const bs_plan_options &o, const Limits &lim, bool kinds_only = false)
 {
     if (o.lane_exchange < 0 || o.threads_per_group > 0 || o.tile_rows > 0 || o.tile_cols > 0 || o.planes_per_group > 0) return false;
     ChainNhwcK k{};
@@ -1340,7 +1341,37 @@ static bool plan_blocks_nhwc(const bs_stack *s, Sequence &q, const bs_plan_optio
     if (at != 0 || k.n_levels < 2 || (uint64_t)k.W * k.C * dtype_size(s->dtype) > 0x7fffffffull || !chain_nhwc_geometry(k, s->in_shape[0], s->dtype, lim.num_cus, &grid)) return false;
     // (a tensor has less than 2^31 elements: with two rows in all, a row of any channel slice is within the 4 GiB that the kernel's offsets reach)
     if (s->dtype == BS_F32 && s->in_shape[0] * k.H < 2) return false;
+    if (kinds_only) return true;
+    ChainWindowNhwcK w{};
+    w.n_levels = k.n_levels;
+    std::copy(k.bn, k.bn + K_BLOCKS_MAX, w.bn);
+    w.C = k.C;
+    w.H = k.H;
+    w.W = k.W;
+    int32_t threads = 0;
+    // As one window.  Level by level -> one window, us: 120 x 200 x 8 x 18 float32 eight levels 28.2 -> 12.7; 20 x 144 x 92 x 92 float32 four levels 61.9 -> 51.1;
+    // 3 x 240 x 102 x 102 bfloat16 ten levels 39.5 -> 24.9; 22 x 144 x 55 x 140 binary16 ten levels 119 -> 58; 99 x 56 x 41 x 41 binary16 eight levels 44.0 -> 22.7.
+    if (blocks_rise(s, k.bn, k.n_levels, k.C) && window_nhwc_geometry(w, s->in_shape[0], s->dtype, &grid, &threads) &&
+        window_nhwc_lds(w) <= lim.max_lds_bytes) {
+        q.window_cl = w;
+        q.variant = BS_VARIANT_ROWS_CHAIN;
+        q.threads = threads;
+        q.vec = w.vec;
+        q.grid = grid;
+        q.lds_bytes = window_nhwc_lds(w);
+        q.tile_rows = 8;
+        q.tile_cols = w.tile_w;
+        q.planes_per_group = w.lanes * w.vec;
+        q.n_levels = w.n_levels;
+        q.halo_rows = 2 * w.n_levels;
+        q.halo_cols = w.tiles > 1 ? 2 * w.n_levels : 0;
+        double read = 0;
+        for (int32_t a = 0; a < w.H; a += 8) read += std::min(w.H, a + 8 + w.n_levels) - std::max(0, a - w.n_levels);
+        q.redundancy = read / w.H * w.tiles * w.work / w.W;
+        return true;
+    }
     if (chain_nhwc_lds_bytes(k) > lim.max_lds_bytes) return false;  // a smaller budget than the kernel's buffers need: strips, without LDS
+    if (!chain_nhwc_geometry(k, s->in_shape[0], s->dtype, lim.num_cus, &grid)) return false;
     q.blocks_cl = k;
     q.variant = BS_VARIANT_ROWS_CHAIN;
     q.threads = 512;
@@ -1823,14 +1854,14 @@ bs_status group_sequences(bs_stack *s, const bs_plan_options &o, const Limits &l
                 // Runs of stacked blocks: up to ten in a sequence, longer runs in parts of at most eight (and at least five) steps whose lengths differ by
                 // one at most; a run with a part that the kernel does not take runs in pairs.  Parts of at most eight / ten, us, 20 steps: 64 x 64 x 56 x 56 float32
                 // 83.5 / 72.7, bfloat16 92.5 / 81.5; 16 x 248 x 30 x 159 float32 156 / 142, bfloat16 160 / 167; 13 x 200 x 43 x 43 float32 59.6 / 61.1, 57 steps 169 / 176.
-                auto blocks = [&](size_t from, int32_t n) {
+                auto blocks = [&](size_t from, int32_t n, bool kinds_only = false) {
                     Sequence trial;
                     range_ops(SeqDraft{drafts[from].first_step, n}, trial.first_op, trial.n_ops);
-                    return plan_blocks_nhwc(s, trial, o, lim);
+                    return plan_blocks_nhwc(s, trial, o, lim, kinds_only);
                 };
-                if (o.max_steps_per_sequence == 0 && i + K_BLOCKS_NHWC_MIN <= drafts.size() && blocks(i, K_BLOCKS_NHWC_MIN)) {
+                if (o.max_steps_per_sequence == 0 && i + K_BLOCKS_NHWC_MIN <= drafts.size() && blocks(i, K_BLOCKS_NHWC_MIN, true)) {
                     int32_t run = K_BLOCKS_NHWC_MIN, done = 0;
-                    while (i + run < drafts.size() && blocks(i + run - 1, 2)) ++run;
+                    while (i + run < drafts.size() && blocks(i + run - 1, 2, true)) ++run;
                     const int32_t parts = run <= K_BLOCKS_MAX ? 1 : (run + K_CHAIN_MAX - 1) / K_CHAIN_MAX;
                     std::vector<SeqDraft> cut;
                     for (int32_t p = 0; p < parts; ++p) {

@@ -502,6 +502,39 @@ def test_stacked_blocks_channels_last(shape, levels, dtype):
         st.close()
 
 
+@pytest.mark.parametrize("shape,levels", [((1, 8, 7, 7), 10), ((2, 4, 1, 2), 4), ((1, 5, 9, 30), 9), ((2, 24, 30, 31), 4), ((1, 16, 20, 63), 6), ((3, 72, 13, 13), 8),
+                                          ((1, 16, 40, 126), 10), ((1, 33, 31, 129), 9), ((1, 8, 24, 224), 10), ((2, 44, 57, 56), 5), ((2, 67, 17, 20), 7)])
+@pytest.mark.parametrize("dtype", ["f32", "bf16", "f16"])
+def test_stacked_blocks_as_one_window_channels_last(shape, levels, dtype):
+    """As row-major (test_stacked_blocks_as_one_window): channels that are whole vectors or not and leave lanes of a work-group without one, column tiles,
+    bands of rows with some left over; against the oracle and, with NaN, against the same blocks as strips."""
+    c = shape[1]
+    layers = []
+    for i in range(levels):
+        bn = wl.bn_params(c, 820 + i)
+        if i + 1 == levels:
+            bn["gamma"] = bn["gamma"] * np.where(np.arange(c) % 3 == 1, -1.0, 1.0).astype(np.float32)
+            bn["gamma"][0] = 0.0
+        layers += [wl.maxpool(3, 1, 1), bn, wl.relu()]
+    x = wl.activation(shape, 80, dtype)
+    x[:, :, ::2, 1::3] = 0.5
+    x[:, :, ::3, ::4] = -np.inf
+    x[:, :, 1::3, ::5] = -0.0
+    if shape[2] > 8:
+        x[0, -1, 5, 2] = np.inf
+    ref, _, _ = bf.run_stack(layers, x, [], dtype)
+    out, _, info = run_gpu(layers, x, [], dtype, layout=bs.BS_LAYOUT_NHWC)
+    q, = info["sequences"]
+    level_by_level = dtype == "f32" and c == 33  # one channel a lane and narrow column tiles
+    assert q["variant_name"] == "rows_chain" and (q["tile_rows"] == 8) != level_by_level
+    assert ((out == ref) | (np.isnan(out) & np.isnan(ref))).all()
+    x[:, :, 2::5, 3::7] = np.nan
+    out, _, _ = run_gpu(layers, x, [], dtype, layout=bs.BS_LAYOUT_NHWC)
+    ref, _, info = run_gpu(layers, x, [], dtype, layout=bs.BS_LAYOUT_NHWC, max_steps_per_sequence=2)
+    assert all(q["variant_name"] != "rows_chain" for q in info["sequences"])
+    assert ((out == ref) | (np.isnan(out) & np.isnan(ref))).all()
+
+
 # ------------------------------------------------------------------ run-time builds
 def _built_stacks(c):
     """Signatures with no instance compiled into the library."""
