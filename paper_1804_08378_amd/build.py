@@ -11,7 +11,7 @@ CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libbrainslug_hip.so")
 TORCH_EXT = os.path.join(HERE, "_bs_torch.so")  # the binding's native calls (csrc/bs_torch.cpp, host code only)
 SOURCES = ["bs_stack.cpp", "bs_plan.cpp", "bs_run.cpp", "bs_jit.cpp", "bs_trace.cpp", "bs_kernels.hip", "bs_lds.hip", "bs_rows.hip",
-           "bs_rows2.hip", "bs_xrows.hip", "bs_chain.hip", "bs_chain_window.hip", "bs_chain_nhwc.hip", "bs_chain_window_nhwc.hip", "bs_nhwc.hip", "bs_nhwc_tile.hip", "bs_nhwc_rows.hip", "bs_strip.hip", "bs_backward.cpp", "bs_backward.hip", "bs_backward_strip.hip", "bs_probe.hip"]
+           "bs_rows2.hip", "bs_xrows.hip", "bs_chain.hip", "bs_chain_window.hip", "bs_chain_nhwc.hip", "bs_chain_window_nhwc.hip", "bs_nhwc.hip", "bs_nhwc_tile.hip", "bs_nhwc_rows.hip", "bs_strip.hip", "bs_pool_band.hip", "bs_backward.cpp", "bs_backward.hip", "bs_backward_strip.hip", "bs_probe.hip"]
 # device headers whose text is embedded in the library for run-time (hipRTC) kernel builds
 JIT_HEADERS = ["bs_kargs.h", "bs_device.h", "bs_lds_device.h", "bs_rows_device.h", "bs_xrows_device.h", "bs_chain_device.h", "bs_chain_window_device.h"]
 

@@ -25,21 +25,6 @@ namespace bs {
 constexpr int K_WINDOW_ROWS = 8, K_WINDOW_COLUMNS = 4;
 constexpr int window_pad(int levels) { return (levels + 3) / 4 * 4; }  // columns of LDS between two rows: whole 128-bit reads
 
-// Maxima as instructions: the compiler would first make every operand canonical.  The kernel clears its waves' IEEE bit, so a signalling NaN is
-// left out as any other.
-BS_DEV float max2(float a, float b)
-{
-    float r;
-    asm("v_max_f32 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
-    return r;
-}
-BS_DEV float max3(float a, float b, float c)
-{
-    float r;
-    asm("v_max3_f32 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "v"(c));
-    return r;
-}
-
 // y[i] = maximum of x[i] .. x[i + 2 L], i < Q; x(i, v) gives V values beside each other, y(i, v) takes them.
 template <int L, int Q, int V, typename X, typename Y>
 BS_DEV void slide_max(X x, Y y)
@@ -173,7 +158,7 @@ __global__ __launch_bounds__(K_WINDOW_THREADS, 4) void chain_window_kernel(const
     constexpr bool WHOLE = REM == 0;
     extern __shared__ float4 lds_vectors[];
     float *const lds = reinterpret_cast<float *>(lds_vectors);
-    asm volatile("s_setreg_imm32_b32 hwreg(HW_REG_MODE, 9, 1), 0");  // IEEE bit: see max2
+    quiet_maxima();
 
     const uint32_t block = xcd_contiguous(blockIdx.x, gridDim.x);
     const uint32_t group = fdiv(block, k.div_chunks);

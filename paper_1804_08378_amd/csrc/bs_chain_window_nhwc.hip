@@ -29,7 +29,7 @@ __global__ __launch_bounds__(K_THREADS, 4) void chain_window_nhwc_kernel(const C
     constexpr uint32_t ES = DT == DT_F32 ? 4 : 2;
     extern __shared__ float4 lds_vectors[];
     float *const lds = reinterpret_cast<float *>(lds_vectors);
-    asm volatile("s_setreg_imm32_b32 hwreg(HW_REG_MODE, 9, 1), 0");  // IEEE bit: see max2
+    quiet_maxima();
 
     // work-group -> (image, band, column tile, channel group), the last one fastest: groups that share cache lines, bands that share rows on one XCD
     uint32_t b = xcd_contiguous(blockIdx.x, gridDim.x), a = fdiv(b, k.div_groups);

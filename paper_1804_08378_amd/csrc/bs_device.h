@@ -115,6 +115,23 @@ BS_DEV void round_store_all(float (&x)[N])
     }
 }
 
+// ------------------------------------------------------------ maxima
+// Maxima as instructions: the compiler would first make every operand canonical, one more instruction each.  A kernel that takes them of raw values
+// clears its waves' IEEE bit (quiet_maxima, its first statement): a signalling NaN is left out then as any other.
+BS_DEV void quiet_maxima() { asm volatile("s_setreg_imm32_b32 hwreg(HW_REG_MODE, 9, 1), 0"); }
+BS_DEV float max2(float a, float b)
+{
+    float r;
+    asm("v_max_f32 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
+    return r;
+}
+BS_DEV float max3(float a, float b, float c)
+{
+    float r;
+    asm("v_max3_f32 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "v"(c));
+    return r;
+}
+
 // ------------------------------------------------------------ strided images
 // The input and the output of a sequence may be channel slices of larger NCHW tensors: image n
 // then starts `extra` elements later than in a dense tensor for every image before it

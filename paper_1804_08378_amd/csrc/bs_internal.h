@@ -62,6 +62,9 @@ struct Sequence {
     StripK strip{};           // pooling sequences as strips (strip_grid > 0: planned); `variant`: the kernel without them
     StripK strip_plain{};     // the same for a call that asks for no index output: the list may run behind the maximum
     int64_t strip_grid = 0;
+    PoolBandK band[2]{};      // the strips' step as bands of rows through LDS, without / with picks (rows > 0: it exists and pays)
+    int64_t band_grid[2] = {0, 0};
+    int32_t band_threads[2] = {0, 0};
     bool strip_first = false; // they run wherever possible (else only where the kernel of `variant` takes no such slice)
     // run-time build (hipFunction_t) without / with index outputs; null = pre-compiled kernel
     int32_t jit = 0;
@@ -216,6 +219,9 @@ bool xrows_launchable(const PoolRowsK &k, int32_t dtype, int64_t grid, int32_t t
 bool xrows2_launchable(const PoolRows2K &k, int32_t dtype, int64_t grid, int32_t threads);
 bs_status launch_xrows(const PoolRowsK &k, int32_t dtype, int64_t grid, int32_t threads, void *stream);
 bs_status launch_xrows2(const PoolRows2K &k, int32_t dtype, int64_t grid, int32_t threads, void *stream);
+// one row-major pooling step as bands of rows through LDS (pool_band_kernel)
+bool pool_band_geometry(PoolBandK &b, const StripK &k, bool idx, int64_t planes, int32_t dtype, int32_t num_cus, int64_t *grid, int32_t *threads);
+bs_status launch_pool_band(const PoolBandK &b, int64_t planes, int32_t dtype, int64_t grid, int32_t threads, void *stream);
 // blocks of 3 x 3 maximum, BatchNorm, ReLU (pool_chain_kernel): compiled in (else a run-time build) / launch it
 bool blocks_compiled(int32_t dtype);
 int32_t blocks_most_rows(const ChainK &k);

@@ -414,6 +414,21 @@ constexpr int32_t strip_columns(bool nhwc, int32_t dtype, int32_t stride)
 }
 constexpr int64_t K_STRIP_LANES = 7 * 1024 * 64;
 
+// One pooling step on row-major planes by bands of rows through LDS (pool_band_kernel).
+struct PoolBandK {
+    const void *in;
+    void *out;
+    const float *params;
+    int32_t *idx;
+    uint32_t in_extra, out_extra;  // as in StreamK
+    uint64_t in_bytes;             // bytes from the input's first to its last element
+    int32_t bn;                    // BatchNorm's parameters; -1: a ReLU alone
+    int32_t C, H, W, Ho, Wo;
+    int32_t rows, bands;           // output rows of a work-group, work-groups per plane
+    int32_t kind, k, pad;          // pooling operation, window, padding (stride 2)
+    FastDiv div_bands, div_c, div_wo, div_runs;  // (runs of four outputs)
+};
+
 constexpr int K_DIRECT_CELLS = 2;  // BwdK::direct
 
 // Backward pass of one stage: element-wise operations followed by at most one pooling

@@ -577,6 +577,14 @@ static void launch_stream(const StreamK &k, dim3 grid, dim3 block, hipStream_t s
 static bs_status run_strips(const bs_stack *s, const Sequence &q, const void *in, void *out, uint32_t in_extra, uint32_t out_extra,
                             int32_t *idx, void *stream)
 {
+    const int w = idx ? 1 : 0;
+    if (q.band[w].rows > 0) {
+        PoolBandK b = q.band[w];
+        b.in = in; b.out = out; b.params = s->dev_params; b.idx = idx;
+        b.in_extra = in_extra;
+        b.out_extra = out_extra;
+        return launch_pool_band(b, q.in_shape[0] * q.in_shape[1], s->dtype, q.band_grid[w], q.band_threads[w], stream);
+    }
     StripK k = idx ? q.strip : q.strip_plain;
     k.in_xp = in_extra;
     k.out_xp = out_extra;

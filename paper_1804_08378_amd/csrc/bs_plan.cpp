@@ -544,7 +544,7 @@ static void copy_list(const EwOp *from, int32_t n, EwOp *to, int32_t &n_to)
 // max 2x2/2 on 32 x 64 x 111 x 111 binary16 35 -> 15, float32 45 -> 29; average 3x3/1 on 32 x 288 x 35 x 35 float32 45 -> 31, bfloat16
 // 38 -> 18; with indices 64 x 64 x 111 x 111 float32 112 -> 76; halo_stress's stack on 18 x 56 x 117 x 117 float32 42 -> 38, binary16
 // 37 -> 18.  No kernel is built for the tile plan then.
-static void plan_row_strips(const bs_stack *s, Sequence &q, const bs_plan_options &o)
+static void plan_row_strips(const bs_stack *s, Sequence &q, const bs_plan_options &o, const Limits &lim)
 {
     if (!strips_wanted(o) || o.force_variant != BS_VARIANT_AUTO || o.max_lds_bytes != 0 || o.jit == 1 || q.n_res > 0) return;
     StripK k{};
@@ -580,6 +580,11 @@ static void plan_row_strips(const bs_stack *s, Sequence &q, const bs_plan_option
     if (n == 2 && pools[0].kind == OP_MAXPOOL) move_behind_max(s, C, k.pre, k.n_pre, k.mid, k.n_mid);
     if (n == 2 && pools[1].kind == OP_MAXPOOL && pools[1].idx_slot < 0) move_behind_max(s, C, k.mid, k.n_mid, k.post, k.n_post);
     plan_strips(s, q, k, n == 2 ? &pools[0] : nullptr, pools[n - 1], H, W, Ho, Wo);
+    if (!q.strip_first || n == 2) return;
+    // as bands of rows
+    const int64_t planes = q.in_shape[0] * q.in_shape[1];
+    for (int w = 0; w < 2; ++w)
+        if (!pool_band_geometry(q.band[w], w ? q.strip : q.strip_plain, w != 0, planes, s->dtype, lim.num_cus, &q.band_grid[w], &q.band_threads[w])) q.band[w].rows = 0;
 }
 
 // Channels-last sequence: element-wise only, or one pooling step.
@@ -1968,7 +1973,7 @@ bs_status group_sequences(bs_stack *s, const bs_plan_options &o, const Limits &l
             st = plan_lds(s, q, o, lim);
         }
         if (st != BS_OK) return st;
-        if (!nhwc && q.variant == BS_VARIANT_LDS_TILE) plan_row_strips(s, q, o);
+        if (!nhwc && q.variant == BS_VARIANT_LDS_TILE) plan_row_strips(s, q, o, lim);
         if (!nhwc && !q.strip_first) st = prepare_jit(s, q, o.host_only != 0);
         if (st != BS_OK) return st;
         if (di + 1 < drafts.size()) {

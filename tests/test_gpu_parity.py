@@ -535,6 +535,29 @@ def test_stacked_blocks_as_one_window_channels_last(shape, levels, dtype):
     assert ((out == ref) | (np.isnan(out) & np.isnan(ref))).all()
 
 
+@pytest.mark.parametrize("shape", [(1, 3, 9, 9), (2, 5, 147, 147), (3, 7, 35, 17), (1, 2, 200, 223), (2, 300, 13, 15), (1, 1, 3, 5), (1, 9, 7, 1501), (5, 3, 31, 33),
+                                   (33, 16, 201, 203)])
+@pytest.mark.parametrize("dtype", ["f32", "bf16", "f16"])
+def test_row_major_poolings_as_bands(shape, dtype):
+    """One stride-2 pooling behind BatchNorm and ReLU on rows that are no whole vectors: bands of rows through LDS.  Windows that reach beyond the plane on
+    every side (padding, ceil mode), several bands and one, planes that begin at any address, the tensor's last vector; scales of both signs (then the strips)."""
+    c = shape[1]
+    x = wl.activation(shape, 81, dtype)
+    x[:, :, ::2, 1::3] = 0.5  # equal values inside windows
+    x[0, 0, -1, -1] = 9.0
+    large = x.size > 20 << 20  # (16-bit storage without picks takes the bands from here on)
+    for ceil in (False, True)[:1 if large else 2]:
+        for tail in ([wl.maxpool(3, 2)], [wl.maxpool(3, 2, 1)]) if large else ([wl.maxpool(2, 2)], [wl.maxpool(3, 2)], [wl.maxpool(3, 2, 1)], [wl.maxpool(3, 2, 0, True)], [wl.maxpool(3, 2, 1, True)], [wl.avgpool(2, 2)]):
+            tail = [dict(tail[0], ceil_mode=ceil)]
+            for head in ([wl.bn_params(c, 840), wl.relu()], [wl.relu()])[:1 if large else 2]:
+                check(head + tail, x, [], dtype, f"band/{shape}/{tail[0]['kind']}{tail[0]['k']}")
+    if large:
+        return
+    bn = wl.bn_params(c, 841)
+    bn["gamma"] = -bn["gamma"]
+    check([bn, wl.relu(), wl.maxpool(3, 2)], x, [], dtype, f"band/{shape}/falling")
+
+
 # ------------------------------------------------------------------ run-time builds
 def _built_stacks(c):
     """Signatures with no instance compiled into the library."""
