@@ -273,6 +273,11 @@ extern "C" bs_status bs_stack_plan_backward(bs_stack *stack)
                 // columns: 9 x 88 x 42 x 42 bfloat16 channels-last 6.3 / 5.6 (748 waves), float32 6.3 / 5.6; 11 x 104 x 20 x 20 6.0 / 5.0 (224 waves);
                 // 16 x 64 x 56 x 57 bfloat16 7.2 / 7.3 (1680 waves).
                 if (bwd_strip_keys(k) && numel(g.in_shape) / (uint64_t)g.vec / 4 / (2 * s) < 1024 * 64) q = 2;
+                // Two levels: strips of four on tensors whose lanes walk the shortest chunks or nearly so (a step of eight columns takes longer than the
+                // waves that are saved).  Forward and backward, us, eight / four columns: channels-last 3 x 32 x 41 x 41 float32 20.2 / 16.9, 64 x 252 x 23 x 23
+                // binary16 56.8 / 47.9, 5 x 120 x 120 x 120 bfloat16 45.4 / 45.5, halo_stress float32 160 / 195; row-major 7 x 184 x 11 x 7 bfloat16 22.4 / 18.9,
+                // 38 x 280 x 20 x 20 34.9 / 32.9, 4 x 208 x 95 x 95 binary16 44.2 / 48.1.
+                if (two && numel(g.in_shape) <= (nhwc ? 8u << 20 : 4u << 20) + (1u << 19)) q = 4;
                 k.strips = q;
                 k.cbs = (k.W + q - 1) / q;
                 const int64_t per_chunk = g.in_shape[0] * k.cbs * (k.C / g.vec), rows = (k.H + s - 1) / s;
@@ -346,8 +351,18 @@ extern "C" bs_status bs_stack_plan_backward(bs_stack *stack)
                     k.spw = 64 / k.cbs;
                     const int64_t planes = g.in_shape[0] * g.in_shape[1];
                     const int32_t rows = (k.H + 1) / 2;  // window rows of the max pooling that cover the plane's rows
+                    // Shorter chunks while the chip's three waves per SIMD are not all there: a wave walks its chunk and two window rows more.  Forward and backward,
+                    // us, chunks of at most 28 / by this rule: 3 x 68 x 29 x 12 float32 25.5 / 10.1, 17 x 384 x 52 x 52 82.6 / 74.5, 8 x 16 x 96 x 96 binary16 39 / 13.
                     int32_t rc = std::min(K_BWD_ROWS2_RC, rows);
-                    k.chunks = (rows + rc - 1) / rc;
+                    double best = 0.0;
+                    for (int32_t r = rc; r >= 1; --r) {
+                        const double waves = (double)planes * ((rows + r - 1) / r) / k.spw, cost = (r + 3) * std::max(1.0, waves / 3072);
+                        if (r == rc || cost < 0.95 * best) {
+                            best = cost;
+                            k.rc = r;
+                        }
+                    }
+                    k.chunks = (rows + k.rc - 1) / k.rc;
                     k.rc = (rows + k.chunks - 1) / k.chunks;
                     k.chunks = (rows + k.rc - 1) / k.rc;
                     k.units = (uint32_t)(planes * k.chunks);

@@ -754,12 +754,19 @@ void launch1(const BwdK &k, bool wide, int32_t pre, dim3 g, hipStream_t st)
     else bwd_strip_kernel<DT, CL, Q, S, P, -1, -1, uint32_t><<<g, 256, 0, st>>>(k);
 }
 
+template <int DT, bool CL, int Q>
+void launch2_compiled(const BwdK &k, bool wide, dim3 g, hipStream_t st)
+{
+    if (wide) bwd_strip2_kernel<DT, CL, Q, true, BN_RELU, BN_RELU, uint64_t><<<g, 256, 0, st>>>(k);
+    else bwd_strip2_kernel<DT, CL, Q, true, BN_RELU, BN_RELU, uint32_t><<<g, 256, 0, st>>>(k);
+}
+
 template <int DT, bool CL>
 void launch2(const BwdK &k, bool wide, bool compiled, dim3 g, hipStream_t st)
 {
     constexpr int Q = bwd_strip2_columns(CL, DT, true), QR = bwd_strip2_columns(CL, DT, false);
-    if (compiled && wide) bwd_strip2_kernel<DT, CL, Q, true, BN_RELU, BN_RELU, uint64_t><<<g, 256, 0, st>>>(k);
-    else if (compiled) bwd_strip2_kernel<DT, CL, Q, true, BN_RELU, BN_RELU, uint32_t><<<g, 256, 0, st>>>(k);
+    if (compiled && k.strips == Q) launch2_compiled<DT, CL, Q>(k, wide, g, st);
+    else if (compiled) launch2_compiled<DT, CL, 4>(k, wide, g, st);
     else if (wide) bwd_strip2_kernel<DT, CL, QR, false, -1, -1, uint64_t><<<g, 256, 0, st>>>(k);
     else bwd_strip2_kernel<DT, CL, QR, false, -1, -1, uint32_t><<<g, 256, 0, st>>>(k);
 }
@@ -791,7 +798,7 @@ bs_status launch_backward_strips(const BwdK &arg, int32_t dtype, int32_t vec, in
     const bool two = k.wave_rows == 2, nhwc = k.nhwc != 0;
     const bool compiled = two && bwd_strip2_compiled(k);
     const int32_t s = two ? 2 : p.sh, Q = k.strips;
-    if (Q != (two ? bwd_strip2_columns(nhwc, dtype, compiled) : K_BWD_STRIP_Q) && !(Q == 2 && bwd_strip_keys(k))) return BS_ERR_UNSUPPORTED;
+    if (Q != (two ? bwd_strip2_columns(nhwc, dtype, compiled) : K_BWD_STRIP_Q) && !(Q == 2 && bwd_strip_keys(k)) && !(Q == 4 && two)) return BS_ERR_UNSUPPORTED;
     // what the kernels assume: no Add; 3 x 3 windows; strips and chunks that cover the plane; the divisors of the lane numbering
     if (k.n_ew < 0 || k.n_post < 0 || k.n_ew + k.n_post > K_BWD_EW || threads != 256 || grid < 1) return BS_ERR_UNSUPPORTED;
     for (int32_t j = 0; j < k.n_ew + k.n_post; ++j)

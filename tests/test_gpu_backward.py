@@ -748,6 +748,32 @@ def test_gradients_of_channel_slices_are_read_and_written_in_place(shape, dtype,
         st.close()
 
 
+@pytest.mark.parametrize("shape,layout", [((160, 24, 49, 51), bs.BS_LAYOUT_NHWC), ((1100, 7, 33, 38), bs.BS_LAYOUT_NHWC), ((80, 32, 47, 43), bs.BS_LAYOUT_NCHW),
+                                          ((20, 5, 224, 222), bs.BS_LAYOUT_NCHW), ((40, 96, 56, 56), bs.BS_LAYOUT_NCHW)])
+@pytest.mark.parametrize("dtype", ["f32", "bf16", "f16"])
+def test_two_levels_in_small_and_large_tensors(shape, layout, dtype):
+    """The kernels of two pooling levels choose strips of four or eight columns, and chunks of rows, by the tensor's size: images of a large tensor have the gradients
+    that they have in a small one, bit for bit (every sum has one order)."""
+    c = shape[1]
+    layers = [wl.bn_params(c, 910), wl.relu(), wl.avgpool(3, 1, 1, True), wl.maxpool(3, 2, 1), wl.bn_params(c, 911), wl.relu()]
+    mf = torch.channels_last if layout == bs.BS_LAYOUT_NHWC else torch.contiguous_format
+    dt = {"f32": torch.float32, "bf16": torch.bfloat16, "f16": torch.float16}[dtype]
+    gen = torch.Generator(device="cuda").manual_seed(5)
+    x = torch.randn(shape, generator=gen, device="cuda").to(dt).contiguous(memory_format=mf)
+    got = []
+    for images in (shape[0], 2):
+        st = bs.Stack(layers, (images, *shape[1:]), dtype).plan(layout=layout)
+        st.plan_backward()
+        part = x[:images].contiguous(memory_format=mf)
+        y, _ = st.run(part)
+        if not got:
+            dy = torch.randn(tuple(y.shape), generator=gen, device="cuda").to(dt).contiguous(memory_format=mf)
+        gx, _ = st.backward(part, [], dy[:images].contiguous(memory_format=mf))
+        got.append(gx[:2].clone())
+        st.close()
+    assert torch.equal(got[0], got[1])
+
+
 def test_repeated_calls_give_identical_bits():
     """A gather has one summation order: two runs agree bit for bit (no atomics anywhere)."""
     layers = _stacks(6)["halo_stress"]
