@@ -12,8 +12,8 @@
 // run's first cells from below, of its last ones from above and of the cells that all windows share; the rows, those around its own among them,
 // are vector loads that the lanes of the neighbouring runs find in the cache.  (2) Through LDS, with one barrier, a lane does the same along Q
 // columns of a row, applies the lists and stores.  Values are float32 from the loads on.
-// What bounds it: vector instructions and LDS together (ten levels float32, 64 x 64 x 56 x 56: 8.0 M vector instructions = 61 % of the SIMDs' cycles, LDS 62 %;
-// 28.5 -> 24.5 us against level by level, 4.2 TB/s); with 16-bit storage the lists: 2.5 instructions a cell and level in bfloat16, 1.5 in binary16.
+// What bounds it: vector instructions and LDS together (ten levels float32, 64 x 64 x 56 x 56: 31.6 -> 20.8 us against level by level, tensors from memory, 4.9 TB/s;
+// with 8.0 M vector instructions and, before the lanes of a row were rounded up, both for 60 % of the cycles); with 16-bit storage the lists: 2.5 instructions a cell and level in bfloat16, 1.5 in binary16.
 // Tried: rows staged in LDS first (31.8: two more barriers and round trips), sixteen rows a lane (26 .. 30: half the lanes), packed 16-bit integers of the
 // same order for 16-bit storage (nine instructions a pair to convert there and back), eight columns a lane (float32 stores 32 bytes apart).
 #pragma once
@@ -123,28 +123,32 @@ BS_DEV void lds_read4(const float *p, float *w)
     w[0] = v.x; w[1] = v.y; w[2] = v.z; w[3] = v.w;
 }
 
-// Four columns, or a row's last ones: REM of them (at any multiple of the element size).
+// Four columns, or a row's last ones: REM of them (at any multiple of the element size).  Non-temporal: plain stores of whole vectors 64 x 64 x 56 x 56 float32
+// 26.6 us, these 20.9 (tensors from memory).
 template <int DT, int REM>
 BS_DEV void store_columns(char *at, const float (&u)[4], bool all)
 {
-    struct __attribute__((packed, aligned(2))) W1 { uint32_t a; };
-    struct __attribute__((packed, aligned(2))) W2 { uint32_t a, b; };
-    struct __attribute__((packed, aligned(2))) W4 { uint32_t a, b, c, d; };
-    if constexpr (DT == DT_F32) {
-        const uint32_t a = __float_as_uint(u[0]), b = __float_as_uint(u[1]), c = __float_as_uint(u[2]), d = __float_as_uint(u[3]);
-        if constexpr (REM == 0) *reinterpret_cast<uint4 *>(at) = make_uint4(a, b, c, d);
-        else if (all) *reinterpret_cast<W4 *>(at) = {a, b, c, d};
-        else {
-            if constexpr (REM & 2) *reinterpret_cast<W2 *>(at) = {a, b};
-            if constexpr (REM & 1) *reinterpret_cast<W1 *>(at + (REM & 2) * 4) = {REM & 2 ? c : a};
-        }
+    constexpr int ES = DT == DT_F32 ? 4 : 2, NW = DT == DT_F32 ? 4 : 2;
+    uint32_t w[NW];
+#pragma unroll
+    for (int i = 0; i < NW; ++i) {
+        if constexpr (DT == DT_F32) w[i] = __float_as_uint(u[i]);
+        else w[i] = pack2<DT>(u[2 * i], u[2 * i + 1]);
+    }
+    if (REM == 0 || all) {
+        store_words_nt<NW, REM == 0 ? 4 * ES : ES>(at, w);
     } else {
-        const uint32_t a = pack2<DT>(u[0], u[1]), b = pack2<DT>(u[2], u[3]);
-        if constexpr (REM == 0) *reinterpret_cast<uint2 *>(at) = make_uint2(a, b);
-        else if (all) *reinterpret_cast<W2 *>(at) = {a, b};
-        else {
-            if constexpr (REM & 2) *reinterpret_cast<W1 *>(at) = {a};
-            if constexpr (REM & 1) *reinterpret_cast<uint16_t *>(at + (REM & 2) * 2) = (uint16_t)(REM & 2 ? b : a);
+        if constexpr (REM & 2) {
+            uint32_t head[NW / 2];
+#pragma unroll
+            for (int i = 0; i < NW / 2; ++i) head[i] = w[i];
+            store_words_nt<NW / 2, ES>(at, head);
+        }
+        if constexpr (REM & 1) {
+            const uint32_t last = w[REM & 2 ? NW / 2 : 0];
+            char *const to = at + (REM & 2) * ES;
+            if constexpr (DT == DT_F32) store_words_nt<1, 4>(to, {last});
+            else __builtin_nontemporal_store((uint16_t)last, reinterpret_cast<uint16_t *>(to));
         }
     }
 }
@@ -179,7 +183,8 @@ __global__ __launch_bounds__(K_WINDOW_THREADS, 4) void chain_window_kernel(const
             in_plane = t - p * (int32_t)k.div_plane_tasks.d;
             at = (uint32_t)p * plane_bytes + (fdiv(plane0 + (uint32_t)p, k.div_c) - img0) * k.in_extra * ES;
         }
-        const int32_t slot = (int32_t)fdiv((uint32_t)in_plane, k.div_vecs), v = in_plane - slot * (int32_t)k.div_vecs.d;
+        const int32_t slot = (int32_t)fdiv((uint32_t)in_plane, k.div_lanes), v = in_plane - slot * (int32_t)k.div_lanes.d;
+        if (v >= k.vecs) continue;
         const int32_t col = WHOLE ? v * 4 : min(v * 4, k.W - 4), top = o0 + slot * QV - L - low;
         at += (uint32_t)col * ES;
         float *const to = lds + (p * k.rows + slot * QV) * k.pitch + PAD + v * 4;
@@ -232,7 +237,7 @@ __global__ __launch_bounds__(K_WINDOW_THREADS, 4) void chain_window_kernel(const
 
     // (2) thread -> (plane, row, run of Q columns).  The levels' parameters are requested in front of the barrier.
     const int32_t p = k.ppg > 1 ? min((int32_t)fdiv((uint32_t)tid, k.div_second), planes - 1) : 0, in_plane = tid - p * (int32_t)k.div_second.d;
-    const int32_t r_in = (int32_t)fdiv((uint32_t)in_plane, k.div_vecs), run = in_plane - r_in * (int32_t)k.div_vecs.d, col = run * Q;
+    const int32_t r_in = (int32_t)fdiv((uint32_t)in_plane, k.div_lanes), run = in_plane - r_in * (int32_t)k.div_lanes.d, col = run * Q;
     const uint32_t plane = plane0 + (uint32_t)p, img = k.ppg > 1 ? fdiv(plane, k.div_c) : img0, c = plane - img * (uint32_t)k.C;
     float sc[L], sh[L], zero = 0.0f;
 #pragma unroll
@@ -241,7 +246,7 @@ __global__ __launch_bounds__(K_WINDOW_THREADS, 4) void chain_window_kernel(const
         sh[l] = k.params[k.bn[l] + k.C + c];
     }
     __syncthreads();
-    if (r_in >= k.row_slots) return;
+    if (r_in >= k.row_slots || run >= k.vecs) return;
     // what the levels make of 0
 #pragma unroll
     for (int l = 0; l + 1 < L; ++l) zero = __builtin_fmaxf(round_store<DT>(__builtin_fmaf(zero, sc[l], sh[l])), 0.0f);

@@ -135,7 +135,7 @@ __global__ __launch_bounds__(K_THREADS, 4) void chain_window_nhwc_kernel(const C
                 float o[V];
 #pragma unroll
                 for (int e = 0; e < V; ++e) o[e] = u[i * V + e];
-                store_elems<DT, V, false>(at + (uint32_t)i * pout, 0, o);
+                store_elems<DT, V, false>(at + (uint32_t)i * pout, 0, o);  // (non-temporal: 66 x 40 x 81 x 81 float32 51 -> 70 us)
             }
         }
     };
@@ -203,8 +203,9 @@ bool window_nhwc_geometry(ChainWindowNhwcK &k, int64_t images, int32_t dtype, in
         k.work = work;
     }
     if (!found) return false;
-    // one channel a lane and narrow tiles: float32 is slower than level by level (ten levels 6 x 310 x 110 x 110 105 -> 147 us; binary16 3 x 318 x 141 x 141 128 -> 89)
-    if (dtype == BS_F32 && k.vec == 1 && best > 2.0) return false;
+    // one channel a lane and narrow tiles or few channels: float32 is slower than level by level (ten levels 6 x 310 x 110 x 110 105 -> 147 us, five levels
+    // 27 x 326 x 53 x 53 72 -> 99; rows of 32 columns, 14 x 345 x 160 x 32 150 -> 101; binary16 3 x 318 x 141 x 141 128 -> 89)
+    if (dtype == BS_F32 && k.vec == 1 && best > 1.3) return false;
     const int32_t columns = k.tiles == 1 ? (k.W + 3) / 4 * 4 + 2 * L : k.work, px = k.lanes * k.vec;
     k.row_words = (columns * px + 3) / 4 * 4;
     if (k.row_words % 64 == 0) k.row_words += 32;  // rows on other banks

@@ -342,7 +342,32 @@ BS_DEV void load_bn_round(const float *__restrict__ params, uint32_t table, uint
     }
 }
 
-// The same for one or two elements as non-temporal stores (whole cache lines of a wave, written once and not read again).
+// N words (1, 2, 4) as a non-temporal store at any multiple of A bytes.
+template <int N>
+struct WordsOf {
+    typedef uint32_t type __attribute__((ext_vector_type(N)));
+};
+template <>
+struct WordsOf<1> { using type = uint32_t; };
+template <typename E, int A>
+struct AtMultiplesOf {
+    typedef E type __attribute__((aligned(A)));
+};
+template <int N, int A>
+BS_DEV void store_words_nt(char *p, const uint32_t (&w)[N])
+{
+    using V = typename WordsOf<N>::type;
+    V v;
+    if constexpr (N == 1) {
+        v = w[0];
+    } else {
+#pragma unroll
+        for (int i = 0; i < N; ++i) v[i] = w[i];
+    }
+    __builtin_nontemporal_store(v, reinterpret_cast<typename AtMultiplesOf<V, A>::type *>(p));
+}
+
+// store_elems for one or two elements as non-temporal stores (whole cache lines of a wave, written once and not read again).
 struct NonTemporal {};
 template <int DT, int N>
 BS_DEV void store_elems(NonTemporal, void *p, const float *v)

@@ -287,8 +287,9 @@ struct ChainWindowK {
     int32_t ppg;                   // planes per work-group (1 where a plane has several chunks)
     int32_t rows, pitch;           // rows of a plane or chunk in LDS, words from one of them to the next
     int32_t row_slots;             // rows of a plane that the work-group's threads hold at a time, four columns each
+    int32_t vecs;                  // vectors of four columns of a row; div_lanes: the lanes they take
     uint32_t planes;
-    FastDiv div_chunks, div_c, div_plane_tasks, div_vecs, div_second;
+    FastDiv div_chunks, div_c, div_plane_tasks, div_lanes, div_second;
 };
 
 // Fewest channels-last blocks in one launch of pool_chain_nhwc_kernel (two and three run as strips).
@@ -426,6 +427,7 @@ struct PoolBandK {
     int32_t C, H, W, Ho, Wo;
     int32_t rows, bands;           // output rows of a work-group, work-groups per plane
     int32_t kind, k, pad;          // pooling operation, window, padding (stride 2)
+    int32_t streamed;              // 16-bit storage: 1: non-temporal stores
     FastDiv div_bands, div_c, div_wo, div_runs;  // (runs of four outputs)
 };
 

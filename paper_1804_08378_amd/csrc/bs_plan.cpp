@@ -1237,7 +1237,7 @@ static bool blocks_rise(const bs_stack *s, const int32_t *bn, int32_t n_levels, 
 }
 
 // The blocks as one window, where the plan leaves the kernel and its geometry to the planner and where that measured faster.  Level by level -> one
-// window, us: 64 x 64 x 56 x 56 float32 ten levels 28.5 -> 24.5; 17 x 64 x 149 x 149 float32 six levels 62.8 -> 48.4; 5 x 184 x 153 x 153 float32 three levels
+// window, us: 64 x 64 x 56 x 56 float32 ten levels 31.6 -> 20.8; 17 x 64 x 149 x 149 float32 six levels 62.8 -> 48.4; 5 x 184 x 153 x 153 float32 three levels
 // 60.5 -> 38.6; 34 x 40 x 135 x 135 bfloat16 eight levels 83 -> 43; 16 x 232 x 46 x 140 binary16 eight levels 70.4 -> 30.3; 1 x 168 x 54 x 54 float32 nine levels
 // 12.9 -> 5.6.  16-bit storage with two and three levels stays level by level (three levels binary16 9 x 352 x 82 x 92 25.0 -> 29.7, bfloat16 102 x 32 x 147 x 46
 // 24.0 -> 26.1), and so does float32 with eight levels and more beyond the last cache, where a row is asked of the second-level cache
@@ -1256,6 +1256,8 @@ static bool plan_window(const bs_stack *s, Sequence &q, const bs_plan_options &o
     const double bytes = 2.0 * (double)k.planes * k.H * k.W * (double)dtype_size(s->dtype);
     if (s->dtype == BS_F32 ? L >= 8 && bytes > 128e6 : L < 4) return false;
     if (!blocks_rise(s, k.bn, L, k.C) || !window_geometry(k, s->dtype, lim, &q.grid, &q.threads)) return false;
+    // two and three levels on large float32 planes that whole runs and lanes overshoot by more than 15 % (5 x 299 x 43 x 178, three levels, 20.9 -> 24.8)
+    if (s->dtype == BS_F32 && L <= 3 && k.H * (int64_t)k.W > 4000 && (double)k.chunks * k.rows * k.div_lanes.d * 4 > 1.15 * k.H * k.W) return false;
     q.window = k;
     q.vec = 4;
     q.lds_bytes = window_lds(k);
