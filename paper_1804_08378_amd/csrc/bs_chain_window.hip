@@ -65,6 +65,20 @@ bool window_geometry(ChainWindowK &k, int32_t dtype, const Limits &lim, int64_t 
     return true;
 }
 
+// A work-group's planes are reached through offsets of 32 bits: one plane each where the images of a channel slice lie further apart.
+static bool window_reaches(const ChainWindowK &k, int32_t dtype)
+{
+    return k.ppg == 1 || (uint64_t)k.ppg * ((uint64_t)k.H * k.W + k.in_extra) * (dtype == BS_F32 ? 4 : 2) <= 0xffffffffull;
+}
+void window_for_slices(ChainWindowK &k, int32_t dtype, int32_t threads, int64_t *grid)
+{
+    if (window_reaches(k, dtype)) return;
+    k.ppg = 1;
+    k.row_slots = threads / (int32_t)k.div_lanes.d;
+    k.div_second = make_fastdiv((uint32_t)k.row_slots * k.div_lanes.d);
+    *grid = (int64_t)k.planes * k.chunks;
+}
+
 // What the kernel assumes about its argument block and launch (window_geometry makes it so): rows of LDS that hold every run of columns with what
 // lies beside it and every run of rows, chunks of whole runs that cover the plane.
 bool window_launchable(const ChainWindowK &k, int32_t dtype, int64_t planes, int64_t grid, int32_t threads)
@@ -76,7 +90,7 @@ bool window_launchable(const ChainWindowK &k, int32_t dtype, int64_t planes, int
     const int32_t vecs = (k.W + 3) / 4, lanes = (int32_t)k.div_lanes.d;
     return k.vecs == vecs && lanes >= vecs && (int64_t)k.planes == planes && (int64_t)k.row_slots * lanes * k.ppg <= threads &&
            ((uint64_t)k.rows + 2 * L) * k.W * es <= 0xffffffffull &&
-           (k.ppg == 1 || (uint64_t)k.ppg * ((uint64_t)k.H * k.W + k.in_extra) * es <= 0xffffffffull) &&
+           window_reaches(k, dtype) &&
            k.pitch == vecs * 4 + window_pad(L) && k.rows == (k.rc + QV - 1) / QV * QV &&
            (k.chunks == 1 ? k.rc == k.H : k.rc == k.rows && k.ppg == 1) && (int64_t)k.chunks * k.rc >= k.H && (int64_t)(k.chunks - 1) * k.rc < k.H &&
            window_lds_bytes(k) <= 64 * 1024 && k.div_chunks.d == (uint32_t)k.chunks && k.div_c.d == (uint32_t)k.C &&

@@ -231,6 +231,7 @@ bs_status launch_blocks(const ChainK &k, int32_t dtype, int64_t grid, int32_t th
 // ... as one window (chain_window_kernel; binary16: a run-time build).  window_geometry: false if the kernel does not take the planes or its LDS is above max_lds
 bool window_geometry(ChainWindowK &k, int32_t dtype, const Limits &lim, int64_t *grid, int32_t *threads);
 uint64_t window_lds(const ChainWindowK &k);
+void window_for_slices(ChainWindowK &k, int32_t dtype, int32_t threads, int64_t *grid);
 bool window_launchable(const ChainWindowK &k, int32_t dtype, int64_t planes, int64_t grid, int32_t threads);
 std::string window_expr(const ChainWindowK &k, int32_t dtype);
 bs_status launch_window(const ChainWindowK &k, int32_t dtype, int64_t grid, int32_t threads, void *stream);

@@ -770,8 +770,11 @@ bs_status launch_sequence(const bs_stack *s, const Sequence &q, const void *in, 
             ChainWindowK k = q.window;
             k.in = in; k.out = out; k.params = s->dev_params;
             k.in_extra = in_extra; k.out_extra = out_extra;
-            if (!window_launchable(k, dtype, q.in_shape[0] * q.in_shape[1], q.grid, q.threads)) return BS_ERR_UNSUPPORTED;
-            const bs_status ls = q.jit ? launch_built(q, false, &k, sizeof k, stream) : launch_window(k, dtype, q.grid, q.threads, stream);
+            int64_t grid = q.grid;
+            window_for_slices(k, dtype, q.threads, &grid);
+            if (!window_launchable(k, dtype, q.in_shape[0] * q.in_shape[1], grid, q.threads)) return BS_ERR_UNSUPPORTED;
+            if (q.jit && !q.jit_fn[0]) return BS_ERR_NOT_PLANNED;
+            const bs_status ls = q.jit ? jit_launch(q.jit_fn[0], &k, sizeof k, grid, q.threads, q.lds_bytes, stream) : launch_window(k, dtype, grid, q.threads, stream);
             if (ls != BS_OK) return ls;
             break;
         }

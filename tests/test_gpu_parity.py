@@ -899,6 +899,56 @@ def _check_sliced(layers, x, res, dtype, label, **opts):
     return info
 
 
+@pytest.mark.parametrize("shape,levels", [((5, 24, 9, 11), 4), ((2, 8, 56, 56), 10), ((3, 40, 13, 7), 5), ((2, 8, 40, 129), 6), ((1, 16, 200, 30), 4)])
+@pytest.mark.parametrize("dtype", ["f32", "bf16", "f16"])
+def test_windows_and_bands_on_channel_slices(shape, levels, dtype):
+    """Stacked blocks as one window and poolings as bands of rows between channel slices of larger tensors: work-groups of several planes that span images,
+    several bands of rows, pixels that skip channels; against the oracle, nothing outside the slices touched."""
+    n, c, h, w = shape
+    blocks = []
+    for i in range(levels):
+        blocks += [wl.maxpool(3, 1, 1), wl.bn_params(c, 860 + i), wl.relu()]
+    x = wl.activation(shape, 82, dtype)
+    info = _check_sliced(blocks, x, [], dtype, f"window{shape}")
+    assert [(q["variant_name"], q["lds_bytes"] > 0) for q in info["sequences"]] == [("rows_chain", True)]
+    for tail in (wl.maxpool(2, 2), wl.maxpool(3, 2), wl.maxpool(3, 2, 1, True), wl.avgpool(2, 2)):
+        _check_sliced([wl.bn_params(c, 870), wl.relu(), tail], x, [], dtype, f"band{shape}{tail['kind']}{tail['k']}")
+    ref, _, _ = bf.run_stack(blocks, x, [], dtype)
+    st = bs.Stack(blocks, shape, dtype).plan(layout=bs.BS_LAYOUT_NHWC)
+    assert [(q["variant_name"], q["tile_rows"]) for q in st.info()["sequences"]] == [("rows_chain", 8)]
+    big_in, big_out = (torch.full((n, c + 16, h, w), v, dtype=TORCH_DTYPE[dtype], device="cuda").contiguous(memory_format=torch.channels_last)
+                       for v in (float("nan"), 4321.0))
+    rest = big_out[:, :8].clone()
+    big_in[:, 8:8 + c] = _dev(x, dtype)
+    xs, outs = big_in[:, 8:8 + c], big_out[:, 8:8 + c]
+    ws = st.workspace("cuda")
+    bs.bs_stack_run_strided(st.handle, xs.data_ptr(), bs.batch_stride_nhwc(xs), [], outs.data_ptr(), bs.batch_stride_nhwc(outs), None,
+                            ws.data_ptr() if ws is not None else 0, ws.numel() if ws is not None else 0, torch.cuda.current_stream().cuda_stream)
+    assert np.array_equal(outs.float().cpu().numpy(), ref)
+    assert torch.equal(big_out[:, :8], rest) and torch.equal(big_out[:, 8 + c:], rest)
+    st.close()
+
+
+@pytest.mark.parametrize("dtype", ["f32", "f16"])
+def test_window_of_small_planes_in_images_far_apart(dtype):
+    """Small planes share a work-group, whose offsets have 32 bits: images of a slice more than 4 GiB / planes apart, against the dense run."""
+    n, c, h, w, between = 2, 4096, 9, 11, 1_500_000 * (1 if dtype == "f32" else 2)
+    layers = sum(([wl.maxpool(3, 1, 1), wl.bn_params(c, 880 + i), wl.relu()] for i in range(4)), [])
+    st = bs.Stack(layers, (n, c, h, w), dtype).plan()
+    q, = st.info()["sequences"]
+    assert q["variant_name"] == "rows_chain" and 8 * between * h * w * (4 if dtype == "f32" else 2) > 2 ** 32 and q["grid"] == n * c // 8
+    x = torch.randn((n, c, h, w), device="cuda", generator=torch.Generator(device="cuda").manual_seed(5)).to(TORCH_DTYPE[dtype])
+    ref, _ = st.run(x)
+    big = torch.zeros((n, between, h, w), dtype=x.dtype, device="cuda")
+    big[:, :c] = x
+    ws = st.workspace("cuda")
+    out = torch.empty_like(ref)
+    bs.bs_stack_run_strided(st.handle, big.data_ptr(), between * h * w, [], out.data_ptr(), c * h * w, None, ws.data_ptr() if ws is not None else 0,
+                            ws.numel() if ws is not None else 0, torch.cuda.current_stream().cuda_stream)
+    assert torch.equal(out, ref)
+    st.close()
+
+
 @pytest.mark.parametrize("shape", [(2, 8, 12, 16), (3, 8, 9, 8), (2, 8, 33, 24), (3, 8, 13, 11)])
 @pytest.mark.parametrize("dtype", ["f32", "bf16", "f16"])
 def test_channel_slices_are_read_and_written_in_place(shape, dtype):
