@@ -123,10 +123,9 @@ BS_DEV void lds_read4(const float *p, float *w)
     w[0] = v.x; w[1] = v.y; w[2] = v.z; w[3] = v.w;
 }
 
-// Four columns, or a row's last ones: REM of them (at any multiple of the element size).  Non-temporal: plain stores of whole vectors 64 x 64 x 56 x 56 float32
-// 26.6 us, these 20.9 (tensors from memory).
-template <int DT, int REM>
-BS_DEV void store_columns(char *at, const float (&u)[4], bool all)
+// Four columns, or a row's last ones: REM of them (at any multiple of the element size).
+template <int DT, int REM, bool NT>
+BS_DEV void store_columns_as(char *at, const float (&u)[4], bool all)
 {
     constexpr int ES = DT == DT_F32 ? 4 : 2, NW = DT == DT_F32 ? 4 : 2;
     uint32_t w[NW];
@@ -136,20 +135,35 @@ BS_DEV void store_columns(char *at, const float (&u)[4], bool all)
         else w[i] = pack2<DT>(u[2 * i], u[2 * i + 1]);
     }
     if (REM == 0 || all) {
-        store_words_nt<NW, REM == 0 ? 4 * ES : ES>(at, w);
+        store_words<NW, REM == 0 ? 4 * ES : ES, NT>(at, w);
     } else {
         if constexpr (REM & 2) {
             uint32_t head[NW / 2];
 #pragma unroll
             for (int i = 0; i < NW / 2; ++i) head[i] = w[i];
-            store_words_nt<NW / 2, ES>(at, head);
+            store_words<NW / 2, ES, NT>(at, head);
         }
         if constexpr (REM & 1) {
             const uint32_t last = w[REM & 2 ? NW / 2 : 0];
             char *const to = at + (REM & 2) * ES;
-            if constexpr (DT == DT_F32) store_words_nt<1, 4>(to, {last});
-            else __builtin_nontemporal_store((uint16_t)last, reinterpret_cast<uint16_t *>(to));
+            if constexpr (DT == DT_F32) store_words<1, 4, NT>(to, {last});
+            else if constexpr (NT) __builtin_nontemporal_store((uint16_t)last, reinterpret_cast<uint16_t *>(to));
+            else *reinterpret_cast<uint16_t *>(to) = (uint16_t)last;
         }
+    }
+}
+
+// Past the caches unless a later launch reads them.  Plain / non-temporal, us, 64 x 64 x 56 x 56 float32: ten levels, tensors from memory 26.6 / 20.9; between
+// launches, 16 levels in four of them 93.5 / 107.6, 40 levels in five 113.7 / 137.0.
+template <int DT, int REM>
+BS_DEV void store_columns(char *at, const float (&u)[4], bool all, bool streamed)
+{
+    if (streamed) {  // (the same for every lane)
+        asm volatile("");  // else the compiler makes one plain store of the two
+        store_columns_as<DT, REM, true>(at, u, all);
+        asm volatile("");
+    } else {
+        store_columns_as<DT, REM, false>(at, u, all);
     }
 }
 
@@ -265,7 +279,7 @@ __global__ __launch_bounds__(K_WINDOW_THREADS, 4) void chain_window_kernel(const
         slide_max<L, Q, 1>([&](int i, float(&v)[1]) __attribute__((always_inline)) { v[0] = x[i]; },
                            [&](int i, const float(&v)[1]) __attribute__((always_inline)) { u[i] = v[0]; });
         window_lists<DT, L, Q>(u, sc, sh, zero);
-        store_columns<DT, REM>(outp + (uint32_t)row * row_bytes, u, col + 4 <= k.W);
+        store_columns<DT, REM>(outp + (uint32_t)row * row_bytes, u, col + 4 <= k.W, k.streamed != 0);
     }
 }
 

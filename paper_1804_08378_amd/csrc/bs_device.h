@@ -342,7 +342,7 @@ BS_DEV void load_bn_round(const float *__restrict__ params, uint32_t table, uint
     }
 }
 
-// N words (1, 2, 4) as a non-temporal store at any multiple of A bytes.
+// N words (1, 2, 4) at any multiple of A bytes, NT: as a non-temporal store.
 template <int N>
 struct WordsOf {
     typedef uint32_t type __attribute__((ext_vector_type(N)));
@@ -353,8 +353,8 @@ template <typename E, int A>
 struct AtMultiplesOf {
     typedef E type __attribute__((aligned(A)));
 };
-template <int N, int A>
-BS_DEV void store_words_nt(char *p, const uint32_t (&w)[N])
+template <int N, int A, bool NT>
+BS_DEV void store_words(char *p, const uint32_t (&w)[N])
 {
     using V = typename WordsOf<N>::type;
     V v;
@@ -364,7 +364,9 @@ BS_DEV void store_words_nt(char *p, const uint32_t (&w)[N])
 #pragma unroll
         for (int i = 0; i < N; ++i) v[i] = w[i];
     }
-    __builtin_nontemporal_store(v, reinterpret_cast<typename AtMultiplesOf<V, A>::type *>(p));
+    auto *const to = reinterpret_cast<typename AtMultiplesOf<V, A>::type *>(p);
+    if constexpr (NT) __builtin_nontemporal_store(v, to);
+    else *to = v;
 }
 
 // store_elems for one or two elements as non-temporal stores (whole cache lines of a wave, written once and not read again).

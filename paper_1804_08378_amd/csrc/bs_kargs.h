@@ -288,6 +288,7 @@ struct ChainWindowK {
     int32_t rows, pitch;           // rows of a plane or chunk in LDS, words from one of them to the next
     int32_t row_slots;             // rows of a plane that the work-group's threads hold at a time, four columns each
     int32_t vecs;                  // vectors of four columns of a row; div_lanes: the lanes they take
+    int32_t streamed;              // the output goes past the caches: no later sequence of the stack reads it
     uint32_t planes;
     FastDiv div_chunks, div_c, div_plane_tasks, div_lanes, div_second;
 };

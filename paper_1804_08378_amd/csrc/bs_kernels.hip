@@ -583,6 +583,7 @@ static bs_status run_strips(const bs_stack *s, const Sequence &q, const void *in
         b.in = in; b.out = out; b.params = s->dev_params; b.idx = idx;
         b.in_extra = in_extra;
         b.out_extra = out_extra;
+        b.streamed = b.streamed && &q == &s->seqs.back();  // (a later sequence finds its input in the caches)
         return launch_pool_band(b, q.in_shape[0] * q.in_shape[1], s->dtype, q.band_grid[w], q.band_threads[w], stream);
     }
     StripK k = idx ? q.strip : q.strip_plain;
@@ -770,6 +771,7 @@ bs_status launch_sequence(const bs_stack *s, const Sequence &q, const void *in, 
             ChainWindowK k = q.window;
             k.in = in; k.out = out; k.params = s->dev_params;
             k.in_extra = in_extra; k.out_extra = out_extra;
+            k.streamed = &q == &s->seqs.back();  // (a later sequence finds its input in the caches)
             int64_t grid = q.grid;
             window_for_slices(k, dtype, q.threads, &grid);
             if (!window_launchable(k, dtype, q.in_shape[0] * q.in_shape[1], grid, q.threads)) return BS_ERR_UNSUPPORTED;

@@ -196,7 +196,7 @@ __global__ __launch_bounds__(K_BAND_THREADS) void pool_band_kernel(const PoolBan
             const uint32_t lo = pack2<DT>(y[0], y[1]), hi = pack2<DT>(y[2], y[3]);
             if (ow + Q <= k.Wo) {
                 struct __attribute__((packed, aligned(2))) W2 { uint32_t a, b; };
-                if (k.streamed) store_words_nt<2, 2>(to, {lo, hi});  // (the same for every lane)
+                if (k.streamed) store_words<2, 2, true>(to, {lo, hi});  // (the same for every lane)
                 else *reinterpret_cast<W2 *>(to) = {lo, hi};
             } else {
                 const int32_t rest = k.Wo - ow;

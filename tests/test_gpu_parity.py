@@ -444,6 +444,16 @@ def test_stacked_blocks_as_one_window(shape, levels, dtype):
     assert ((out == ref) | (np.isnan(out) & np.isnan(ref))).all()
 
 
+@pytest.mark.parametrize("shape", [(1, 3, 9, 12), (2, 2, 41, 13), (1, 2, 17, 126), (3, 3, 10, 31)])
+@pytest.mark.parametrize("dtype", ["f32", "bf16", "f16"])
+def test_windows_in_several_launches(shape, dtype):
+    """Runs of blocks longer than a launch: the first one's output goes to the workspace through the caches, the last one's past them; every rest of a row's columns."""
+    layers = sum(([wl.maxpool(3, 1, 1), wl.bn_params(shape[1], 890 + i), wl.relu()] for i in range(8)), [])
+    x = wl.activation(shape, 83, dtype)
+    info = check(layers, x, [], dtype, f"two windows/{shape}", max_steps_per_sequence=4)
+    assert [(q["variant_name"], q["lds_bytes"] > 0) for q in info["sequences"]] == [("rows_chain", True)] * 2
+
+
 def test_stacked_blocks_on_a_plane_of_more_than_four_gib():
     """Row offsets beyond 2^32 bytes: the rows around that place and the plane's last ones, against the same blocks on a copy of those rows;
     chunks of the planner's choice and the longest ones there are (a caller asks for the whole plane)."""
