@@ -1,4 +1,5 @@
-// pool_chain_kernel: L blocks <max pooling 3 x 3 / 1 / 1, BatchNorm, ReLU> in registers -- the stacked blocks of Section 5.1.
+// pool_chain_kernel: L blocks <max pooling 3 x 3 / 1 / 1, BatchNorm, ReLU> in registers -- the stacked blocks of Section 5.1, where
+// they are not one window (chain_window_kernel: every BatchNorm but the last with scales above zero; the rules are at plan_window).
 //
 // A lane owns two columns of a plane and walks down a chunk of its rows; every new input row ripples through all L levels in the same
 // step, because level l's row h - l needs level l - 1's rows up to h - l + 1, which that step has just produced.  Per level the lane

@@ -1,4 +1,5 @@
-// pool_chain_nhwc_kernel: the blocks <max pooling 3 x 3 / 1 / 1, BatchNorm, ReLU> of pool_chain_kernel on channels-last tensors.
+// pool_chain_nhwc_kernel: the blocks <max pooling 3 x 3 / 1 / 1, BatchNorm, ReLU> of pool_chain_kernel on channels-last tensors,
+// where they are not one window (chain_window_nhwc_kernel).
 //
 // The levels are pool_chain_kernel's: a lane owns two columns of one channel, neighbouring columns are neighbouring lanes, rows ripple through
 // all levels in registers.  In memory the channels of a pixel lie together, so a work-group of eight waves takes the same columns of `cg`
