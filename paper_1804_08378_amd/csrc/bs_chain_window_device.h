@@ -4,8 +4,9 @@
 // A BatchNorm with a positive scale, a ReLU and the rounding to the storage type never decrease when their input increases (the rounded
 // fused multiply-add is monotone), so each commutes with the maximum of the next level, and L stacked 3 x 3 maxima are one maximum over
 // (2 L + 1) x (2 L + 1) cells (cells outside the plane are in neither).  The lists of all levels then run once, on the window's maximum.  The
-// ReLUs commute with what stands behind them as well: f(max(a, 0)) = max(f(a), f(0)), so a cell goes through the bare multiply-adds and meets
-// one maximum with C, which is what the levels make of 0.  The same bits as level by level, also for infinities and for NaN (left out by a
+// ReLUs commute with what stands behind them as well: f(max(a, 0)) = max(f(a), f(0)), so a cell goes through the bare multiply-adds of levels 1 .. L - 1 and
+// meets one maximum with C in front of the last.  C is the least that level 1's ReLU lets through, 0, behind levels 2 .. L - 1 (0 with two levels): the first BatchNorm
+// stands in front of that ReLU and has no part in it.  The same bits as level by level, also for windows without a cell above zero, for infinities and for NaN (left out by a
 // maximum; behind a ReLU zero): 1 instruction per cell and level in float32 instead of 3.5, and no level recomputes its rows and columns.
 //
 // A work-group takes ppg whole planes or a band of rows of one.  (1) A lane takes the window maxima down four columns for QV rows: maxima of the
@@ -261,9 +262,9 @@ __global__ __launch_bounds__(K_WINDOW_THREADS, 4) void chain_window_kernel(const
     }
     __syncthreads();
     if (r_in >= k.row_slots || run >= k.vecs) return;
-    // what the levels make of 0
+    // what the levels behind the first ReLU make of its 0
 #pragma unroll
-    for (int l = 0; l + 1 < L; ++l) zero = __builtin_fmaxf(round_store<DT>(__builtin_fmaf(zero, sc[l], sh[l])), 0.0f);
+    for (int l = 1; l + 1 < L; ++l) zero = __builtin_fmaxf(round_store<DT>(__builtin_fmaf(zero, sc[l], sh[l])), 0.0f);
     char *const outp = static_cast<char *>(image_base<DT>(k.out, img, k.out_extra)) + ((size_t)plane * k.H + (size_t)(uint32_t)o0) * row_bytes + (uint32_t)col * ES;
     for (int32_t row = r_in; row < here; row += k.row_slots) {
         const float *const from = lds + (p * k.rows + row) * k.pitch + col;

@@ -11,6 +11,7 @@ import pytest
 import torch
 
 from oracle import breadth_first as bf
+from oracle.layers import round_to
 from paper_1804_08378_amd import brainslug as bs
 from paper_1804_08378_amd import workloads as wl
 
@@ -442,6 +443,52 @@ def test_stacked_blocks_as_one_window(shape, levels, dtype):
     ref, _, info = run_gpu(layers, x, [], dtype, tile_rows=shape[2])
     assert info["sequences"][0]["lds_bytes"] == 0
     assert ((out == ref) | (np.isnan(out) & np.isnan(ref))).all()
+
+
+def _blocks_below_zero(shape, levels, dtype, values, seed):
+    """Blocks whose BatchNorms rise, the first one's shifts of both signs, on inputs with windows that hold nothing above zero: the ReLUs of the inner levels decide
+    there.  "shifted": N(-3, 1); "negative": every cell below zero, most of them close to it; "-inf", "nan": N(0, 1) around regions wider than the window, one at the
+    plane's corner, and the first plane as a whole."""
+    n, c, h, w = shape
+    layers = []
+    for i in range(levels):
+        bn = wl.bn_params(c, seed + i)
+        if i == 0:
+            bn["mean"] = np.zeros_like(bn["mean"])
+            bn["beta"] = np.where(np.arange(c) % 3 == 2, -0.5, 0.5).astype(np.float32)
+        layers += [wl.maxpool(3, 1, 1), bn, wl.relu()]
+    x = wl.activation(shape, seed + 50)
+    if values == "shifted":
+        x = x - 3.0
+    elif values == "negative":
+        x = -0.25 * np.abs(x) - np.float32(1e-3)
+    else:
+        nothing, wide = np.float32(values), 2 * levels + 3
+        x[:, ::2, :wide, :wide] = nothing
+        x[:, 1::2, h // 3:h // 3 + wide, w // 3:w // 3 + wide] = nothing
+        x[0, 0] = nothing
+    return layers, round_to(x, dtype)
+
+
+def _same_values(a, b):
+    return ((a == b) | (np.isnan(a) & np.isnan(b))).all()
+
+
+@pytest.mark.parametrize("values", ["shifted", "negative", "-inf", "nan"])
+@pytest.mark.parametrize("shape,levels", [((2, 4, 17, 20), 2), ((2, 4, 17, 21), 2), ((1, 5, 20, 63), 3), ((2, 4, 33, 56), 4), ((3, 5, 30, 34), 4), ((1, 4, 57, 127), 10), ((2, 4, 56, 56), 10),
+                                          ((5, 900, 9, 11), 4)])
+@pytest.mark.parametrize("dtype", ["f32", "bf16", "f16"])
+def test_stacked_blocks_as_one_window_below_zero(shape, levels, dtype, values):
+    """Windows without a cell above zero: bit for bit the levels' own results (NaN: against the kernel that goes level by level)."""
+    layers, x = _blocks_below_zero(shape, levels, dtype, values, 840)
+    out, _, info = run_gpu(layers, x, [], dtype)
+    assert [(q["variant_name"], q["lds_bytes"] > 0) for q in info["sequences"]] == [("rows_chain", dtype == "f32" or levels >= 4)]
+    if values == "nan":
+        ref, _, info = run_gpu(layers, x, [], dtype, tile_rows=shape[2])
+        assert info["sequences"][0]["lds_bytes"] == 0
+    else:
+        ref, _, _ = bf.run_stack(layers, x, [], dtype)
+    assert _same_values(out, ref), np.argwhere(out != ref)[:4]
 
 
 @pytest.mark.parametrize("shape", [(1, 3, 9, 12), (2, 2, 41, 13), (1, 2, 17, 126), (3, 3, 10, 31)])
