@@ -58,7 +58,7 @@ __global__ __launch_bounds__(K_THREADS, 4) void chain_window_nhwc_kernel(const C
             lds[r * k.row_words + (i < left ? i : k.W * px + i)] = -INFINITY;
         }
     }
-    // the levels' scales and shifts of the group's channels, what they make of 0
+    // the levels' scales and shifts of the group's channels, what the levels behind the first ReLU make of its 0
     float *const table = lds + K_STEP * k.row_words;
     if (tid < px) {
         const int32_t ch = min(c0 + tid, k.C - 1);
@@ -68,7 +68,7 @@ __global__ __launch_bounds__(K_THREADS, 4) void chain_window_nhwc_kernel(const C
             const float s = k.params[k.bn[l] + ch], h = k.params[k.bn[l] + k.C + ch];
             table[(2 * l) * px + tid] = s;
             table[(2 * l + 1) * px + tid] = h;
-            if (l + 1 < L) zero = __builtin_fmaxf(round_store<DT>(__builtin_fmaf(zero, s, h)), 0.0f);
+            if (l > 0 && l + 1 < L) zero = __builtin_fmaxf(round_store<DT>(__builtin_fmaf(zero, s, h)), 0.0f);
         }
         table[2 * L * px + tid] = zero;
     }

@@ -615,6 +615,22 @@ def test_row_major_poolings_as_bands(shape, dtype):
     check([bn, wl.relu(), wl.maxpool(3, 2)], x, [], dtype, f"band/{shape}/falling")
 
 
+@pytest.mark.parametrize("values", ["shifted", "negative", "-inf", "nan"])
+@pytest.mark.parametrize("shape,levels", [((2, 8, 17, 20), 4), ((2, 5, 30, 31), 4), ((1, 16, 57, 126), 10), ((1, 9, 56, 27), 10), ((1, 32, 33, 100), 6)])
+@pytest.mark.parametrize("dtype", ["f32", "bf16", "f16"])
+def test_stacked_blocks_as_one_window_below_zero_channels_last(shape, levels, dtype, values):
+    """As row-major: vectors of four channels and single ones, one column tile and several (NaN: against the same blocks as strips)."""
+    layers, x = _blocks_below_zero(shape, levels, dtype, values, 860)
+    out, _, info = run_gpu(layers, x, [], dtype, layout=bs.BS_LAYOUT_NHWC)
+    assert [(q["variant_name"], q["tile_rows"]) for q in info["sequences"]] == [("rows_chain", 8)]
+    if values == "nan":
+        ref, _, info = run_gpu(layers, x, [], dtype, layout=bs.BS_LAYOUT_NHWC, max_steps_per_sequence=2)
+        assert all(q["variant_name"] != "rows_chain" for q in info["sequences"])
+    else:
+        ref, _, _ = bf.run_stack(layers, x, [], dtype)
+    assert _same_values(out, ref), np.argwhere(out != ref)[:4]
+
+
 # ------------------------------------------------------------------ run-time builds
 def _built_stacks(c):
     """Signatures with no instance compiled into the library."""
