@@ -142,8 +142,9 @@ typedef enum bs_variant {
                                    kinds of element-wise operations behind it: rows ripple through all levels in registers
                                    (channels-last: 3 x 3 with BatchNorm, ReLU, four and more) */
     BS_VARIANT_STRIPS = 11,     /* one 3 x 3 (row-major also 2 x 2 / 2) pooling step, or a 3 x 3 / 1 / 1 step and a 3 x 3 maximum, both layouts:
-                                   a lane walks down a strip of output columns in registers, no LDS (chosen by the planner,
-                                   force_variant does not take it)                                                        */
+                                   a lane walks down a strip of output columns in registers, no LDS; some row-major steps
+                                   with stride 2 as bands of rows through LDS instead (bs_sequence_info: lds_bytes > 0)
+                                   (chosen by the planner, force_variant does not take it)                                */
     BS_VARIANT_NHWC_ROWS = 10   /* channels-last plans only: two 3 x 3 pooling steps (the first with stride 1, the second a
                                    maximum) on images at most 64 pixels wide: rows slide in registers, a lane = one pixel
                                    column x one channel vector, no LDS */
@@ -252,7 +253,8 @@ typedef struct bs_sequence_info {
     int32_t first_layer, n_layers;
     int32_t variant;                 /* bs_variant                                         */
     int32_t n_levels;                /* pooling operations inside (LDS hand-offs + 1)      */
-    int32_t tile_rows, tile_cols;    /* final-output tile per work-group (LDS variant); strips: per lane */
+    int32_t tile_rows, tile_cols;    /* final-output tile per work-group (LDS variants); strips without LDS: per lane.
+                                        Steps that run as bands with or without index outputs only: the call with them */
     int32_t planes_per_group;
     int32_t halo_rows, halo_cols;    /* input rows/cols an interior tile loads beyond tile*stride */
     int32_t threads_per_group;

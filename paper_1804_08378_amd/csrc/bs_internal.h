@@ -220,6 +220,7 @@ bool xrows2_launchable(const PoolRows2K &k, int32_t dtype, int64_t grid, int32_t
 bs_status launch_xrows(const PoolRowsK &k, int32_t dtype, int64_t grid, int32_t threads, void *stream);
 bs_status launch_xrows2(const PoolRows2K &k, int32_t dtype, int64_t grid, int32_t threads, void *stream);
 // one row-major pooling step as bands of rows through LDS (pool_band_kernel)
+uint64_t pool_band_lds(const PoolBandK &b, int32_t dtype);
 bool pool_band_geometry(PoolBandK &b, const StripK &k, bool idx, int64_t planes, int32_t dtype, int32_t num_cus, int64_t *grid, int32_t *threads);
 bs_status launch_pool_band(const PoolBandK &b, int64_t planes, int32_t dtype, int64_t grid, int32_t threads, void *stream);
 // blocks of 3 x 3 maximum, BatchNorm, ReLU (pool_chain_kernel): compiled in (else a run-time build) / launch it

@@ -2162,6 +2162,18 @@ bs_status bs_stack_sequence_info(const bs_stack *stack, int32_t sequence, bs_seq
         r.lds_bytes = 0;
         r.redundancy = (double)k.total * (k.rc * k.pool2.sh + r.halo_rows) * (qo * k.pool2.sw + r.halo_cols) /
                        ((double)q.in_shape[0] * q.in_shape[1] * q.in_shape[2] * q.in_shape[3]);
+        const int w = k.pool2.idx_slot >= 0 ? 1 : 0;  // the call that asks for every output
+        if (const PoolBandK &b = q.band[w]; b.rows > 0) {
+            r.tile_rows = b.rows;
+            r.tile_cols = b.Wo;
+            r.halo_cols = 0;
+            r.threads_per_group = q.band_threads[w];
+            r.grid = q.band_grid[w];
+            r.lds_bytes = pool_band_lds(b, stack->dtype);
+            double rows = 0;
+            for (int32_t a = 0; a < b.Ho; a += b.rows) rows += std::min((std::min(b.Ho, a + b.rows) - 1) * 2 - b.pad + b.k, b.H) - std::max(a * 2 - b.pad, 0);
+            r.redundancy = rows / b.H;
+        }
     }
     *info = r;
     return BS_OK;

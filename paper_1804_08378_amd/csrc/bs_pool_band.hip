@@ -227,6 +227,8 @@ int64_t band_bytes(const PoolBandK &k, int32_t rows, int32_t es)
 
 }  // namespace
 
+uint64_t pool_band_lds(const PoolBandK &b, int32_t dtype) { return (uint64_t)band_bytes(b, b.rows, dtype == BS_F32 ? 4 : 2); }
+
 // The strips' step as bands, if the kernel exists for it.
 bool pool_band_geometry(PoolBandK &b, const StripK &k, bool idx, int64_t planes, int32_t dtype, int32_t num_cus, int64_t *grid, int32_t *threads)
 {

@@ -592,8 +592,17 @@ def test_stacked_blocks_as_one_window_channels_last(shape, levels, dtype):
     assert ((out == ref) | (np.isnan(out) & np.isnan(ref))).all()
 
 
-@pytest.mark.parametrize("shape", [(1, 3, 9, 9), (2, 5, 147, 147), (3, 7, 35, 17), (1, 2, 200, 223), (2, 300, 13, 15), (1, 1, 3, 5), (1, 9, 7, 1501), (5, 3, 31, 33),
-                                   (33, 16, 201, 203)])
+def _runs_as_band(shape, dtype, tail):
+    """The planner's rule for a stride-2 step behind lists that rise, on rows that are no whole vectors."""
+    cells = shape[2] * shape[3]
+    if dtype == "f32":
+        return cells >= 200
+    return tail["k"] == (3, 3) and cells >= 600 and (tail.get("return_indices", False) or shape[0] * shape[1] * cells >= 20 << 20)
+
+
+# (13 x 15, 9 x 9, 3 x 5: below the rule's sizes, strips; 14 x 15, 25 x 25: the least odd-sized planes it takes; 16-bit storage without picks: from the last two on)
+@pytest.mark.parametrize("shape", [(1, 3, 9, 9), (2, 5, 147, 147), (3, 7, 35, 17), (1, 2, 200, 223), (2, 300, 13, 15), (2, 100, 14, 15), (2, 30, 25, 25), (1, 1, 3, 5), (1, 9, 7, 1501),
+                                   (5, 3, 31, 33), (3, 5, 41, 45), (7, 600, 79, 65), (33, 16, 201, 203)])
 @pytest.mark.parametrize("dtype", ["f32", "bf16", "f16"])
 def test_row_major_poolings_as_bands(shape, dtype):
     """One stride-2 pooling behind BatchNorm and ReLU on rows that are no whole vectors: bands of rows through LDS.  Windows that reach beyond the plane on
@@ -602,17 +611,46 @@ def test_row_major_poolings_as_bands(shape, dtype):
     x = wl.activation(shape, 81, dtype)
     x[:, :, ::2, 1::3] = 0.5  # equal values inside windows
     x[0, 0, -1, -1] = 9.0
-    large = x.size > 20 << 20  # (16-bit storage without picks takes the bands from here on)
-    for ceil in (False, True)[:1 if large else 2]:
-        for tail in ([wl.maxpool(3, 2)], [wl.maxpool(3, 2, 1)]) if large else ([wl.maxpool(2, 2)], [wl.maxpool(3, 2)], [wl.maxpool(3, 2, 1)], [wl.maxpool(3, 2, 0, True)], [wl.maxpool(3, 2, 1, True)], [wl.avgpool(2, 2)]):
-            tail = [dict(tail[0], ceil_mode=ceil)]
-            for head in ([wl.bn_params(c, 840), wl.relu()], [wl.relu()])[:1 if large else 2]:
-                check(head + tail, x, [], dtype, f"band/{shape}/{tail[0]['kind']}{tail[0]['k']}")
+    large = x.size > 20 << 20
+    tails = [wl.maxpool(3, 2), wl.maxpool(3, 2, 1)]
+    if not large:
+        tails += [wl.maxpool(2, 2), wl.maxpool(3, 2, 0, True), wl.maxpool(3, 2, 1, True), wl.avgpool(2, 2)]
+    for tail in tails:
+        for ceil in (False, True):
+            tail = dict(tail, ceil_mode=ceil)
+            for head in ([wl.bn_params(c, 840), wl.relu()], [wl.relu()]):
+                info = check(head + [tail], x, [], dtype, f"band/{shape}/{tail['kind']}{tail['k']}")
+                q, = info["sequences"]
+                if q["variant_name"] == "strips":
+                    whole = tail["kind"] != "avgpool" or (2 * q["out_shape"][2] <= shape[2] and 2 * q["out_shape"][3] <= shape[3])
+                    assert (q["lds_bytes"] > 0) == (whole and _runs_as_band(shape, dtype, tail)), (tail, q)
+                else:
+                    assert not _runs_as_band(shape, dtype, tail) or tail["kind"] == "avgpool", (tail, q)
     if large:
         return
     bn = wl.bn_params(c, 841)
     bn["gamma"] = -bn["gamma"]
-    check([bn, wl.relu(), wl.maxpool(3, 2)], x, [], dtype, f"band/{shape}/falling")
+    info = check([bn, wl.relu(), wl.maxpool(3, 2)], x, [], dtype, f"band/{shape}/falling")
+    assert [(q["variant_name"], q["lds_bytes"]) for q in info["sequences"]] == [("strips", 0)]
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f16"])
+def test_bands_of_16_bit_channel_slices_without_picks(dtype):
+    """16-bit storage without picks takes the bands on large tensors only: between channel slices of larger ones, against the dense run of the same kernel (which
+    test_row_major_poolings_as_bands compares with the oracle), nothing outside the slices touched."""
+    shape = n, c, h, w = (34, 16, 201, 203)  # (the images of a slice begin at multiples of 16 bytes)
+    gen = torch.Generator(device="cuda").manual_seed(7)
+    big = torch.randn((n, c + 16, h, w), generator=gen, device="cuda").to(TORCH_DTYPE[dtype])
+    for tail in (wl.maxpool(3, 2), wl.maxpool(3, 2, 1)):
+        st = bs.Stack([wl.bn_params(c, 842), wl.relu(), dict(tail, ceil_mode=True)], shape, dtype).plan()
+        assert [(q["variant_name"], q["lds_bytes"] > 0) for q in st.info()["sequences"]] == [("strips", True)]
+        ref, _ = st.run(big[:, 8:8 + c].contiguous())
+        out = torch.full((n, c + 16, *ref.shape[2:]), 4321.0, dtype=ref.dtype, device="cuda")
+        bs.bs_stack_run_strided(st.handle, big[:, 8:].data_ptr(), big.stride(0), [], out[:, 8:].data_ptr(), out.stride(0), None, 0, 0,
+                                torch.cuda.current_stream().cuda_stream)
+        assert torch.equal(out[:, 8:8 + c], ref)
+        assert bool((out[:, :8] == 4321.0).all()) and bool((out[:, 8 + c:] == 4321.0).all())
+        st.close()
 
 
 @pytest.mark.parametrize("values", ["shifted", "negative", "-inf", "nan"])
