@@ -428,7 +428,6 @@ struct PoolBandK {
     int32_t C, H, W, Ho, Wo;
     int32_t rows, bands;           // output rows of a work-group, work-groups per plane
     int32_t kind, k, pad;          // pooling operation, window, padding (stride 2)
-    int32_t streamed;              // 16-bit storage: 1: non-temporal stores
     FastDiv div_bands, div_c, div_wo, div_runs;  // (runs of four outputs)
 };
 

@@ -583,7 +583,6 @@ static bs_status run_strips(const bs_stack *s, const Sequence &q, const void *in
         b.in = in; b.out = out; b.params = s->dev_params; b.idx = idx;
         b.in_extra = in_extra;
         b.out_extra = out_extra;
-        b.streamed = b.streamed && &q == &s->seqs.back();  // (a later sequence finds its input in the caches)
         return launch_pool_band(b, q.in_shape[0] * q.in_shape[1], s->dtype, q.band_grid[w], q.band_threads[w], stream);
     }
     StripK k = idx ? q.strip : q.strip_plain;

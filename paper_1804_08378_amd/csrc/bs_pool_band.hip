@@ -4,8 +4,8 @@
 // The rows under a band of output rows are one run of memory whatever their length: a work-group fetches it as aligned 128-bit vectors, several of each
 // thread on their way at a time, to LDS as it lies in memory (lists in front of the pooling applied on the way), and a lane takes its window from there.
 // The strips it stands in for read their columns as vectors at whatever address they begin, a row pair of a lane in flight.  float32: a lane takes one output;
-// 16-bit storage: four, whose columns are words of two (one output a lane, nine 16-bit reads each: 26.4 us where four take 20.8).
-// What bounds it: memory (32 x 64 x 147 x 147 binary16 3 x 3 maximum 28.0 -> 20.8 us, 5.3 TB/s; 3 x 314 x 145 x 145 float32 27.8 -> 17.6, 5.6 TB/s).
+// 16-bit storage: four, whose columns are words of two (one output a lane, nine 16-bit reads each: 26.4 us where four took 20.8).
+// What bounds it: memory (32 x 64 x 147 x 147 binary16 3 x 3 maximum 28.0 -> 21.6 us, 5.1 TB/s; 3 x 314 x 145 x 145 float32 27.8 -> 17.6, 5.6 TB/s).
 #include <algorithm>
 
 #include "bs_internal.h"
@@ -195,9 +195,10 @@ __global__ __launch_bounds__(K_BAND_THREADS) void pool_band_kernel(const PoolBan
             for (int q = 0; q < Q; ++q) y[q] = round_store<DT>(y[q]);
             const uint32_t lo = pack2<DT>(y[0], y[1]), hi = pack2<DT>(y[2], y[3]);
             if (ow + Q <= k.Wo) {
+                // (Non-temporal stores gain nothing.  Plain / non-temporal, binary16, us, three inputs in turn: 32 x 64 x 147 x 147 21.9 / 20.9, 21 x 64 x 199 x 199 25.9 / 26.5,
+                // 64 x 96 x 75 x 75 17.1 / 17.5; eight inputs 22.7 / 23.8, 26.0 / 27.3, 19.5 / 20.5; with a reader behind each call 30.0 / 31.5, 35.6 / 40.2, 23.4 / 24.9.)
                 struct __attribute__((packed, aligned(2))) W2 { uint32_t a, b; };
-                if (k.streamed) store_words<2, 2, true>(to, {lo, hi});  // (the same for every lane)
-                else *reinterpret_cast<W2 *>(to) = {lo, hi};
+                *reinterpret_cast<W2 *>(to) = {lo, hi};
             } else {
                 const int32_t rest = k.Wo - ow;
                 struct __attribute__((packed, aligned(2))) W1 { uint32_t a; };
@@ -263,9 +264,6 @@ bool pool_band_geometry(PoolBandK &b, const StripK &k, bool idx, int64_t planes,
     b.div_c = make_fastdiv((uint32_t)b.C);
     b.div_wo = make_fastdiv((uint32_t)b.Wo);
     b.div_runs = make_fastdiv((uint32_t)((b.Wo + 3) / 4));
-    // 16-bit outputs past the caches behind inputs that the last cache does not keep.  Plain / non-temporal, us: 32 x 64 x 147 x 147 (88 MB) 21.7 / 20.8, 17 x 40 x 190 x 190
-    // (49 MB) 15.0 / 15.4; float32 13 x 64 x 189 x 155 (98 MB) 23.0 / 24.0
-    b.streamed = dtype != BS_F32 && planes * cells > 32 << 20;
     *threads = (int32_t)std::min<int64_t>(K_BAND_THREADS, std::max<int64_t>(64, (std::max<int64_t>(band_bytes(b, b.rows, es) / 32, dtype == BS_F32 ? b.rows * b.Wo / 2 : b.rows * ((b.Wo + 3) / 4)) + 63) / 64 * 64));
     *grid = planes * b.bands;
     return *grid <= 0x7fffffffll;
