@@ -30,7 +30,7 @@ bool window_geometry(ChainWindowK &k, int32_t dtype, const Limits &lim, int64_t 
         const int32_t up = (vecs + step - 1) / step * step;
         if (8 * (up - vecs) <= up) lanes = up;
     }
-    if (L < 2 || L > K_BLOCKS_MAX || k.W < 4 || k.H < 1 || k.planes < 1) return false;
+    if (L < window_fewest(dtype) || L > K_BLOCKS_MAX || k.W < 4 || k.H < 1 || k.planes < 1) return false;
     k.pitch = vecs * 4 + pad;
     const int64_t most = (int64_t)std::min<uint64_t>(lim.max_lds_bytes, 64 * 1024);
     // rows of the plane per work-group: up to 256 lanes of pass (1)
@@ -84,7 +84,7 @@ void window_for_slices(ChainWindowK &k, int32_t dtype, int32_t threads, int64_t 
 bool window_launchable(const ChainWindowK &k, int32_t dtype, int64_t planes, int64_t grid, int32_t threads)
 {
     const int32_t es = dtype == BS_F32 ? 4 : 2, L = k.n_levels, QV = K_WINDOW_ROWS;
-    if (L < 2 || L > K_BLOCKS_MAX || k.W < 4 || k.H < 1 || k.C < 1 || k.rc < 1 || k.chunks < 1 || k.ppg < 1 || k.row_slots < 1 || threads < 64 ||
+    if (L < window_fewest(dtype) || L > K_BLOCKS_MAX || k.W < 4 || k.H < 1 || k.C < 1 || k.rc < 1 || k.chunks < 1 || k.ppg < 1 || k.row_slots < 1 || threads < 64 ||
         threads > K_WINDOW_THREADS || threads % 64 != 0)
         return false;
     const int32_t vecs = (k.W + 3) / 4, lanes = (int32_t)k.div_lanes.d;
@@ -105,7 +105,7 @@ std::string window_expr(const ChainWindowK &k, int32_t dtype)
     return b;
 }
 
-template <int DT, int REM, int L = 2>
+template <int DT, int REM, int L = window_fewest(DT)>
 static void launch_levels(const ChainWindowK &k, dim3 grid, dim3 block, uint32_t lds, hipStream_t st)
 {
     if constexpr (L <= K_BLOCKS_MAX) {

@@ -173,6 +173,7 @@ BS_DEV void store_columns(char *at, const float (&u)[4], bool all, bool streamed
 template <int DT, int L, int REM>
 __global__ __launch_bounds__(K_WINDOW_THREADS, 4) void chain_window_kernel(const ChainWindowK k)
 {
+    static_assert(L >= window_fewest(DT), "fewer levels go level by level");
     constexpr int ES = DT == DT_F32 ? 4 : 2, PAD = window_pad(L), QV = K_WINDOW_ROWS, Q = K_WINDOW_COLUMNS;
     constexpr bool WHOLE = REM == 0;
     extern __shared__ float4 lds_vectors[];

@@ -275,6 +275,7 @@ struct ChainK {
 
 // The same blocks as one window of (2 n_levels + 1)^2 cells (chain_window_kernel): scales above zero on every level but the last.
 constexpr int K_WINDOW_THREADS = 512;
+constexpr int window_fewest(int dtype) { return dtype == 0 ? 2 : 4; }  // fewest levels: float32 / 16-bit storage
 struct ChainWindowK {
     const void *in;
     void *out;

@@ -1254,7 +1254,7 @@ static bool plan_window(const bs_stack *s, Sequence &q, const bs_plan_options &o
     k.W = q.blocks.W;
     k.planes = (uint32_t)(q.in_shape[0] * q.in_shape[1]);
     const double bytes = 2.0 * (double)k.planes * k.H * k.W * (double)dtype_size(s->dtype);
-    if (s->dtype == BS_F32 ? L >= 8 && bytes > 128e6 : L < 4) return false;
+    if (s->dtype == BS_F32 && L >= 8 && bytes > 128e6) return false;
     if (!blocks_rise(s, k.bn, L, k.C) || !window_geometry(k, s->dtype, lim, &q.grid, &q.threads)) return false;
     // two and three levels on large float32 planes that whole runs and lanes overshoot by more than 15 % (5 x 299 x 43 x 178, three levels, 20.9 -> 24.8)
     if (s->dtype == BS_F32 && L <= 3 && k.H * (int64_t)k.W > 4000 && (double)k.chunks * k.rows * k.div_lanes.d * 4 > 1.15 * k.H * k.W) return false;

@@ -1,5 +1,5 @@
-// pool_band_kernel: one pooling step with stride 2 (max 2 x 2, max 3 x 3 with and without padding and picks, average 2 x 2) and BatchNorm -> ReLU on
-// row-major planes whose rows are no whole vectors.
+// pool_band_kernel: one pooling step with stride 2 (max 3 x 3 with and without padding and picks, float32 also max 2 x 2 and average 2 x 2) and
+// BatchNorm -> ReLU on row-major planes whose rows are no whole vectors.
 //
 // The rows under a band of output rows are one run of memory whatever their length: a work-group fetches it as aligned 128-bit vectors, several of each
 // thread on their way at a time, to LDS as it lies in memory (lists in front of the pooling applied on the way), and a lane takes its window from there.
@@ -17,9 +17,11 @@ namespace {
 constexpr int K_BAND_THREADS = 256, K_BAND_BYTES = 16 * 1024;
 
 // MAX: maximum (else the average of four), K x K, padding P; IDX: with picks, the list in front; else a maximum's list stands behind it, an average's in front.
+// 16-bit storage: 3 x 3 maxima only (strips are as fast with 2 x 2 windows, pool_band_geometry).
 template <int DT, bool MAX, int K, int P, bool IDX>
 __global__ __launch_bounds__(K_BAND_THREADS) void pool_band_kernel(const PoolBandK k)
 {
+    static_assert(DT == DT_F32 || (MAX && K == 3), "16-bit storage: 3 x 3 maxima");
     constexpr int ES = DT == DT_F32 ? 4 : 2, VEC = 16 / ES, U = 4;
     constexpr bool PRE = IDX || !MAX;
     extern __shared__ uint4 lds_vectors[];
@@ -142,24 +144,16 @@ __global__ __launch_bounds__(K_BAND_THREADS) void pool_band_kernel(const PoolBan
                 for (int n = 0; n < NW; ++n) w[i][n] = __builtin_amdgcn_alignbit(x[n + 1], x[n], (at & 1) * 16);
             }
             float y[Q];
-            if constexpr (!MAX) {
-#pragma unroll
-                for (int q = 0; q < Q; ++q) {
-                    y[q] = 0.0f + run_element<DT>(w[0], 2 * q);
-#pragma unroll
-                    for (int i = 1; i < K * K; ++i) y[q] += run_element<DT>(w[i / K], 2 * q + i % K);
-                    y[q] *= 1.0f / (K * K);
-                }
-            } else if constexpr (!IDX) {
+            if constexpr (!IDX) {
                 float m[NC];
 #pragma unroll
                 for (int j = 0; j < NC; ++j) {
-                    m[j] = K == 2 ? max2(run_element<DT>(w[0], j), run_element<DT>(w[1], j)) : max3(run_element<DT>(w[0], j), run_element<DT>(w[1], j), run_element<DT>(w[K - 1], j));
+                    m[j] = max3(run_element<DT>(w[0], j), run_element<DT>(w[1], j), run_element<DT>(w[K - 1], j));
                     m[j] = (uint32_t)(col + j) < (uint32_t)k.W ? m[j] : -INFINITY;
                 }
 #pragma unroll
                 for (int q = 0; q < Q; ++q) {
-                    y[q] = K == 2 ? max2(m[2 * q], m[2 * q + 1]) : max3(m[2 * q], m[2 * q + 1], m[2 * q + K - 1]);
+                    y[q] = max3(m[2 * q], m[2 * q + 1], m[2 * q + K - 1]);
                     y[q] = __builtin_fmaxf(__builtin_fmaf(y[q], scale, shift), 0.0f);
                 }
             } else {
@@ -210,13 +204,13 @@ __global__ __launch_bounds__(K_BAND_THREADS) void pool_band_kernel(const PoolBan
 }
 
 template <int DT>
-bool launch_as(const PoolBandK &k, dim3 grid, dim3 block, uint32_t lds, hipStream_t st)
+void launch_as(const PoolBandK &k, dim3 grid, dim3 block, uint32_t lds, hipStream_t st)
 {
-    if (k.kind != OP_MAXPOOL) pool_band_kernel<DT, false, 2, 0, false><<<grid, block, lds, st>>>(k);
-    else if (k.k == 2) pool_band_kernel<DT, true, 2, 0, false><<<grid, block, lds, st>>>(k);
-    else if (k.idx) k.pad ? pool_band_kernel<DT, true, 3, 1, true><<<grid, block, lds, st>>>(k) : pool_band_kernel<DT, true, 3, 0, true><<<grid, block, lds, st>>>(k);
+    if constexpr (DT == DT_F32) {
+        if (k.k == 2) return k.kind != OP_MAXPOOL ? pool_band_kernel<DT, false, 2, 0, false><<<grid, block, lds, st>>>(k) : pool_band_kernel<DT, true, 2, 0, false><<<grid, block, lds, st>>>(k);
+    }
+    if (k.idx) k.pad ? pool_band_kernel<DT, true, 3, 1, true><<<grid, block, lds, st>>>(k) : pool_band_kernel<DT, true, 3, 0, true><<<grid, block, lds, st>>>(k);
     else k.pad ? pool_band_kernel<DT, true, 3, 1, false><<<grid, block, lds, st>>>(k) : pool_band_kernel<DT, true, 3, 0, false><<<grid, block, lds, st>>>(k);
-    return true;
 }
 
 // LDS of a band: its rows, what their first vector holds in front of them, 16 bytes in front and 32 behind.
@@ -274,8 +268,8 @@ bs_status launch_pool_band(const PoolBandK &b, int64_t planes, int32_t dtype, in
     const int32_t es = dtype == BS_F32 ? 4 : 2;
     PoolBandK k = b;
     const int64_t bytes = band_bytes(k, k.rows, es), images = planes / std::max(k.C, 1);
-    // what the kernel assumes: bands that cover the output, LDS for a band's run, a window per output with a cell in the plane
-    if (k.C < 1 || planes % k.C != 0 || k.H < 1 || k.W < 1 || k.Ho < 1 || k.Wo < 1 || k.rows < 1 || (int64_t)k.bands * k.rows < k.Ho || (int64_t)(k.bands - 1) * k.rows >= k.Ho ||
+    // what the kernel assumes: an instance for the step, bands that cover the output, LDS for a band's run, a window per output with a cell in the plane
+    if (!(k.kind == OP_MAXPOOL ? (k.k == 2 && k.pad == 0 && !k.idx) || (k.k == 3 && (k.pad == 0 || k.pad == 1)) : k.k == 2 && k.pad == 0) || (dtype != BS_F32 && k.k == 2) || k.C < 1 || planes % k.C != 0 || k.H < 1 || k.W < 1 || k.Ho < 1 || k.Wo < 1 || k.rows < 1 || (int64_t)k.bands * k.rows < k.Ho || (int64_t)(k.bands - 1) * k.rows >= k.Ho ||
         (k.Ho - 1) * 2 - k.pad >= k.H || (k.Wo - 1) * 2 - k.pad >= k.W || bytes > 64 * 1024 || grid_n != planes * k.bands || grid_n > 0x7fffffffll || threads < 64 ||
         threads > K_BAND_THREADS || threads % 64 != 0 || k.div_bands.d != (uint32_t)k.bands || k.div_c.d != (uint32_t)k.C || k.div_wo.d != (uint32_t)k.Wo || k.div_runs.d != (uint32_t)((k.Wo + 3) / 4) ||
         (k.kind != OP_MAXPOOL && (2 * k.Ho > k.H || 2 * k.Wo > k.W)) || (uint64_t)k.H * k.W > 0x7fffffffull)

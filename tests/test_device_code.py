@@ -64,7 +64,8 @@ def test_selects_wait_for_the_compares_that_write_their_masks(source, tmp_path):
     assert not short, (len(short), short[:5])
 
 
-@pytest.mark.parametrize("source", ["bs_backward.hip", "bs_backward_strip.hip", "bs_chain.hip", "bs_chain_nhwc.hip", "bs_nhwc.hip", "bs_kernels.hip"])
+@pytest.mark.parametrize("source", ["bs_backward.hip", "bs_backward_strip.hip", "bs_chain.hip", "bs_chain_nhwc.hip", "bs_nhwc.hip", "bs_kernels.hip", "bs_chain_window.hip",
+                                    "bs_chain_window_nhwc.hip", "bs_pool_band.hip"])
 def test_kernels_keep_nothing_in_scratch_memory(source, tmp_path):
     """The factors of up to four residual gradients, rings and row buffers are arrays that must become registers."""
     build.build(force=False)
@@ -76,6 +77,25 @@ def test_kernels_keep_nothing_in_scratch_memory(source, tmp_path):
     assert sizes
     scratch = [(name, int(n)) for name, n in sizes if int(n)]
     assert not scratch, (len(scratch), scratch[:5])
+
+
+@pytest.mark.parametrize("source,kernel,instances", [
+    # storage type, levels, columns of a row beyond whole vectors
+    ("bs_chain_window.hip", "chain_window_kernel", {(0, l, r) for l in range(2, 11) for r in range(4)} | {(1, l, r) for l in range(4, 11) for r in range(4)}),
+    # storage type, channels of a vector, levels
+    ("bs_chain_window_nhwc.hip", "chain_window_nhwc_kernel", {(d, v, l) for d in range(3) for v in (1, 4) for l in range(4, 11)}),
+    # storage type, maximum?, window, padding, picks?
+    ("bs_pool_band.hip", "pool_band_kernel", {(d, 1, 3, p, i) for d in range(3) for p in (0, 1) for i in (0, 1)} | {(0, m, 2, 0, 0) for m in (0, 1)}),
+])
+def test_only_instances_that_a_plan_reaches_are_compiled(source, kernel, instances, tmp_path):
+    """The planner's rules keep some types and sizes with other kernels: no machine code for those."""
+    build.build(force=False)
+    obj = os.path.join(build.HERE, "_build", source + ".o")
+    if not os.path.exists(obj) or not os.path.exists(BIN):
+        pytest.skip("needs the build's objects and the ROCm toolchain")
+    notes = subprocess.run([f"{BIN}/llvm-readelf", "--notes", device_code(obj, str(tmp_path))], check=True, capture_output=True, text=True).stdout
+    args = re.findall(r"\.name:\s+_Z\w*?" + kernel + r"I((?:L[ib]\d+E)+)E", notes)
+    assert len(args) == len(instances) and {tuple(int(v) for v in re.findall(r"L[ib](\d+)E", a)) for a in args} == instances
 
 
 def test_audit_builds_check_every_access_of_the_backward_strip_kernels():
