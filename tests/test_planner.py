@@ -230,6 +230,16 @@ def test_lds_budget_of_channels_last_blocks(shape, levels):
         assert sum(q["n_steps"] for q in seqs) == levels
 
 
+@pytest.mark.parametrize("shape,levels,dtype,window", [
+    ((44, 176, 57, 57), 6, "f32", False), ((44, 176, 57, 57), 7, "f32", True), ((44, 176, 57, 57), 6, "bf16", True), ((31, 176, 57, 57), 6, "f32", True),  # 17.7 M cells
+    ((444, 16, 56, 56), 4, "f32", False), ((94, 48, 64, 64), 4, "f32", False), ((94, 48, 63, 65), 4, "f32", True)])
+def test_channels_last_blocks_in_large_float32_tensors(shape, levels, dtype, window):
+    """Few levels on rows that need no column tiles, and enough of them to fill the chip: level by level, not as one window."""
+    layers = [l for i in range(levels) for l in (wl.maxpool(3, 1, 1), wl.bn_params(shape[1], i), wl.relu())]
+    q, = plan(layers, shape, dtype, layout=bs.BS_LAYOUT_NHWC)["sequences"]
+    assert q["variant_name"] == "rows_chain" and (q["tile_rows"] == 8) == window
+
+
 def test_channels_last_blocks_on_a_single_row():
     """One float32 row: a channel slice of a larger tensor may have 8 GiB in it, beyond the offsets of the kernel that exchanges channels
     through LDS; 16-bit rows, and rows of which there are two, cannot."""
