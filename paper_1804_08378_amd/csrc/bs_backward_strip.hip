@@ -712,6 +712,10 @@ void bwd_strip2_kernel(const BwdK k)
 #pragma unroll
                 for (int i = 0; i < Q * V; ++i)
                     v[i] = (d == 0 ? (hs[K0][i] + hs[K0 + 1][i]) + hs[N0][i] : (hs[K0 + 1][i] + hs[N0][i]) + hs[N0 + 1][i]) * T[d][i];
+                if constexpr (DT == DT_F16) {  // two roundings, as in round_store: merged with its conversion, a strip's last column alone was rounded once, so gradients depended on Q
+#pragma unroll
+                    for (int i = 0; i < Q * V; ++i) asm("" : "+v"(v[i]));
+                }
                 store_row<DT, CL, Q, OFF>(k, 45, iat, L.q0, k.W, pi, whole, v);
                 iat += irow;
             }

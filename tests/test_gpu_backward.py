@@ -774,6 +774,36 @@ def test_two_levels_in_small_and_large_tensors(shape, layout, dtype):
     assert torch.equal(got[0], got[1])
 
 
+@pytest.mark.parametrize("shape,layout", [((160, 24, 49, 51), bs.BS_LAYOUT_NHWC), ((1100, 7, 33, 38), bs.BS_LAYOUT_NHWC), ((80, 32, 47, 43), bs.BS_LAYOUT_NCHW)])
+@pytest.mark.parametrize("dtype", ["bf16", "f16"])
+def test_two_levels_round_alike_in_strips_of_any_width(shape, layout, dtype):
+    """All images of a large tensor (strips of eight columns) against the same images in quarters (strips of four): the gradients' last product and its conversion to
+    16 bits are two roundings in every column, also where an instruction exists that does both in one."""
+    c = shape[1]
+    layers = [wl.bn_params(c, 910), wl.relu(), wl.avgpool(3, 1, 1, True), wl.maxpool(3, 2, 1), wl.bn_params(c, 911), wl.relu()]
+    mf = torch.channels_last if layout == bs.BS_LAYOUT_NHWC else torch.contiguous_format
+    dt = torch.float16 if dtype == "f16" else torch.bfloat16
+    gen = torch.Generator(device="cuda").manual_seed(6)
+    x = torch.randn(shape, generator=gen, device="cuda").to(dt).contiguous(memory_format=mf)
+    dy = None
+
+    def gradient(part, images):
+        nonlocal dy
+        st = bs.Stack(layers, tuple(part.shape), dtype).plan(layout=layout)
+        st.plan_backward()
+        if dy is None:
+            dy = torch.randn(tuple(st.run(part)[0].shape), generator=gen, device="cuda").to(dt).contiguous(memory_format=mf)
+        gx = st.backward(part, [], dy[images].clone(memory_format=mf))[0].clone()
+        st.close()
+        return gx
+
+    whole = gradient(x, slice(None))
+    q = shape[0] // 4
+    for i in range(0, shape[0], q):
+        part = slice(i, i + q)
+        assert torch.equal(whole[part], gradient(x[part].clone(memory_format=mf), part)), i  # (clones begin at aligned addresses)
+
+
 def test_repeated_calls_give_identical_bits():
     """A gather has one summation order: two runs agree bit for bit (no atomics anywhere)."""
     layers = _stacks(6)["halo_stress"]
