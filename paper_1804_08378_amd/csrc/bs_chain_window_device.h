@@ -13,8 +13,9 @@
 // run's first cells from below, of its last ones from above and of the cells that all windows share; the rows, those around its own among them,
 // are vector loads that the lanes of the neighbouring runs find in the cache.  (2) Through LDS, with one barrier, a lane does the same along Q
 // columns of a row, applies the lists and stores.  Values are float32 from the loads on.
-// What bounds it: vector instructions and LDS together (ten levels float32, 64 x 64 x 56 x 56: 31.6 -> 20.8 us against level by level, tensors from memory, 4.9 TB/s;
-// with 8.0 M vector instructions and, before the lanes of a row were rounded up, both for 60 % of the cycles); with 16-bit storage the lists: 2.5 instructions a cell and level in bfloat16, 1.5 in binary16.
+// What bounds it: vector instructions and LDS together (8.0 M vector instructions are 54 % of the time at 3.5 cycles each, LDS 62 % of the compute units' cycles), in float32 beside
+// memory; with 16-bit storage the lists: 2.5 instructions a cell and level in bfloat16, 1.5 in binary16.  Ten levels 64 x 64 x 56 x 56 float32, level by level -> window, us: three
+// tensors in turn (partly in the last cache) 27.5 .. 32.0 -> 20.0 .. 21.0 from one run of the machine to the next, eight in turn (from memory) 31.4 -> 30.4; bfloat16 31.6 -> 22.2, 31.7 -> 22.0.
 // Tried: rows staged in LDS first (31.8: two more barriers and round trips), sixteen rows a lane (26 .. 30: half the lanes), packed 16-bit integers of the
 // same order for 16-bit storage (nine instructions a pair to convert there and back), eight columns a lane (float32 stores 32 bytes apart).
 #pragma once
@@ -154,8 +155,11 @@ BS_DEV void store_columns_as(char *at, const float (&u)[4], bool all)
     }
 }
 
-// Past the caches unless a later launch reads them.  Plain / non-temporal, us, 64 x 64 x 56 x 56 float32: ten levels, tensors from memory 26.6 / 20.9; between
-// launches, 16 levels in four of them 93.5 / 107.6, 40 levels in five 113.7 / 137.0.
+// Past the caches unless a later launch of the stack reads them.  Plain / non-temporal, geometric means over 160 drawn sizes, three inputs in turn / eight: outputs up to 4 MB
+// 1.00 / 1.01, 4 .. 48 MB 1.05 / 1.06, 48 .. 120 MB 1.13 / 0.98 (three inputs stay in the last cache then, because the outputs do not drive them out).  Where another kernel reads the
+// output at once they gain up to 8 MB of float32 (1.03) and cost 1 .. 7 % beyond 24 MB and with 16-bit storage; ten levels 64 x 64 x 56 x 56 float32, us, three inputs 21.9 / 21.0,
+// eight 28.1 / 30.6, with a reader 43.5 / 48.1 (level by level 28.5, 31.4, 47.1).  Between the launches of one stack, which always reads them: 16 levels in four launches 93.5 / 107.6, 40 in five
+// 113.7 / 137.0.
 template <int DT, int REM>
 BS_DEV void store_columns(char *at, const float (&u)[4], bool all, bool streamed)
 {

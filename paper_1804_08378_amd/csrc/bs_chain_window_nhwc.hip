@@ -3,8 +3,8 @@
 // A lane takes the window maxima down eight rows of one column and four consecutive channels; its vector loads are contiguous over the lanes' channels.
 // Four rows at a time go through LDS, [row][column][channel], where a lane does the same along four columns, applies the lists and stores.  The
 // rest of the eight rows' state stays in registers meanwhile, so LDS holds four rows only.  A row is asked of the caches (8 + 2 L) / 8 times.
-// Against level by level over drawn sizes, geometric means: vectors of four channels float32 1.31 (430 sizes, 0.80 .. 2.8), 16-bit storage 1.38 (270, 0.90 .. 2.3), one channel a lane 16-bit
-// 1.62 (320, 0.77 .. 7.6: slower only on large tensors with four to six levels).
+// Against level by level over drawn sizes, geometric means: vectors of four channels float32 1.34 (396 sizes, 0.82 .. 2.8), 16-bit storage 1.38 (270, 0.90 .. 2.3), one channel a lane
+// float32 1.84 (201, 0.88 .. 3.3), 16-bit 1.62 (320, 0.77 .. 7.6: slower only on large tensors with four to six levels).
 // What bounds it: vector instructions (the lists; in float32 as many for the windows) and the LDS round trips between its two passes.  Ten levels bfloat16
 // 3 x 240 x 102 x 102 24.9 us (1.2 TB/s), float32 3 x 432 x 137 x 137 87.9 (2.2 TB/s).
 #include <algorithm>
@@ -210,8 +210,8 @@ bool window_nhwc_geometry(ChainWindowNhwcK &k, int64_t images, int32_t dtype, in
     }
     if (!found) return false;
     // One channel a lane and narrow tiles or few channels: float32 goes level by level (ten levels 6 x 310 x 110 x 110 105 -> 147 us, five levels
-    // 27 x 326 x 53 x 53 72 -> 99; rows of 32 columns, 14 x 345 x 160 x 32 150 -> 101; binary16 3 x 318 x 141 x 141 128 -> 89).  Over drawn sizes, up to 1.3 the window is 1.82 times as fast
-    // (205 sizes); beyond, 0.93 from 12 M cells on (89 sizes), 1.24 from 8 to 12 M, and never slower below 6 M (88 sizes, 1.0 .. 2.7), where the rule refuses more than it need.
+    // 27 x 326 x 53 x 53 72 -> 99; rows of 32 columns, 14 x 345 x 160 x 32 150 -> 101; binary16 3 x 318 x 141 x 141 128 -> 89).  Over drawn sizes, up to 1.3 the window is 1.84 times as fast
+    // (201 sizes); beyond, 0.93 from 12 M cells on (89 sizes), 1.24 from 8 to 12 M, and never slower below 6 M (88 sizes, 1.0 .. 2.7), where the rule refuses more than it need.
     if (dtype == BS_F32 && k.vec == 1 && best > 1.3) return false;
     const int32_t columns = k.tiles == 1 ? (k.W + 3) / 4 * 4 + 2 * L : k.work, px = k.lanes * k.vec;
     k.row_words = (columns * px + 3) / 4 * 4;

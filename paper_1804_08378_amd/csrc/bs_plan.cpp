@@ -1237,11 +1237,14 @@ static bool blocks_rise(const bs_stack *s, const int32_t *bn, int32_t n_levels, 
 }
 
 // The blocks as one window, where the plan leaves the kernel and its geometry to the planner and where that measured faster.  Level by level -> one
-// window, us: 64 x 64 x 56 x 56 float32 ten levels 31.6 -> 20.8; 17 x 64 x 149 x 149 float32 six levels 62.8 -> 48.4; 5 x 184 x 153 x 153 float32 three levels
-// 60.5 -> 38.6; 34 x 40 x 135 x 135 bfloat16 eight levels 83 -> 43; 16 x 232 x 46 x 140 binary16 eight levels 70.4 -> 30.3; 1 x 168 x 54 x 54 float32 nine levels
-// 12.9 -> 5.6.  16-bit storage with two and three levels stays level by level (three levels binary16 9 x 352 x 82 x 92 25.0 -> 29.7, bfloat16 102 x 32 x 147 x 46
-// 24.0 -> 26.1), and so does float32 with eight levels and more beyond the last cache, where a row is asked of the second-level cache
-// (8 + 2 levels) / 8 times (nine levels 7 x 472 x 86 x 86, 195 MB, 58.7 -> 65.7; below 128 MB 19 x 40 x 122 x 122 28.1 -> 23.6).
+// window, us, three tensors in turn / eight (from memory): 64 x 64 x 56 x 56 float32 ten levels 28.5 -> 20.9 / 31.4 -> 30.4; 17 x 64 x 149 x 149 float32 six levels 67 -> 48 / 68 -> 49;
+// 5 x 184 x 153 x 153 float32 three levels 62 -> 32 / 62 -> 40; 34 x 40 x 135 x 135 bfloat16 eight levels 83 -> 37 / 84 -> 44; 16 x 232 x 46 x 140 binary16 eight levels 70 -> 31 / 71 -> 36.
+// Over drawn sizes (7 .. 224 rows and columns, up to 25 M cells) the ones taken gain, geometric mean, three tensors / eight: float32 370 sizes 1.40 / 1.36, 16-bit storage 210 sizes
+// 1.48 / 1.45.  15 and 2 of them are over 5 % slower, the float32 ones with two and three levels on planes of 60 to 400 cells (20 x 40 x 10 x 10, two levels, 4.1 -> 4.6 us) or sides a little
+// beyond a multiple of eight (104 x 104 x 34 x 34 18.6 -> 20.7); the worst is binary16 63 x 288 x 37 x 37, five levels, 32.3 -> 38.1.
+// 16-bit storage with two and three levels stays level by level (three levels binary16 9 x 352 x 82 x 92 25.0 -> 29.7, bfloat16 102 x 32 x 147 x 46
+// 24.0 -> 26.1), and so does float32 with eight levels and more beyond 128 MB of input and output, where it depends on the width: 0.88 to 1.03 times as fast on 86 columns (36 .. 105 x 64 x 86 x 86),
+// 1.1 to 1.5 on 28 and 149, 1.08 on average (72 sizes of 130 to 400 MB).
 static bool plan_window(const bs_stack *s, Sequence &q, const bs_plan_options &o, const Limits &lim)
 {
     if (o.threads_per_group > 0 || o.tile_rows > 0 || o.tile_cols > 0 || o.planes_per_group > 0) return false;
@@ -1356,7 +1359,7 @@ static bool plan_blocks_nhwc(const bs_stack *s, Sequence &q, const bs_plan_optio
     w.H = k.H;
     w.W = k.W;
     int32_t threads = 0;
-    // As one window.  Level by level -> one window, us: 120 x 200 x 8 x 18 float32 eight levels 28.2 -> 12.7; 20 x 144 x 92 x 92 float32 four levels 61.9 -> 51.1;
+    // As one window.  Level by level -> one window, us: 120 x 200 x 8 x 18 float32 eight levels 28.2 -> 12.7; 20 x 144 x 92 x 92 float32 four levels 66 -> 59;
     // 3 x 240 x 102 x 102 bfloat16 ten levels 39.5 -> 24.9; 22 x 144 x 55 x 140 binary16 ten levels 119 -> 58; 99 x 56 x 41 x 41 binary16 eight levels 44.0 -> 22.7.
     if (blocks_rise(s, k.bn, k.n_levels, k.C) && window_nhwc_geometry(w, s->in_shape[0], s->dtype, &grid, &threads) &&
         window_nhwc_lds(w) <= lim.max_lds_bytes) {

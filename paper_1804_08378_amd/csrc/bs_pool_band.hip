@@ -236,7 +236,8 @@ bool pool_band_geometry(PoolBandK &b, const StripK &k, bool idx, int64_t planes,
     // 96 x 360 x 12 x 18 13.0 -> 11.0.  16-bit storage: 3 x 3 maximum 32 x 64 x 147 x 147 binary16 28.2 -> 21.3, 60 x 120 x 59 x 59 16.4 -> 13.6, with picks
     // 15 x 264 x 79 x 79 bfloat16 (and backward) 68 -> 59; no gain with 2 x 2 windows (8 x 240 x 109 x 109 11.8 -> 12.1, average 3 x 80 x 219 x 219 7.1 -> 8.1),
     // on small planes (38 x 240 x 11 x 11 with picks and backward 12.2 -> 13.8) and without picks on inputs the last cache holds (2 x 254 x 171 x 171, 30 MB, 9.0 -> 10.0;
-    // 7 x 176 x 134 x 134, 44 MB, 15.1 -> 13.1).
+    // 7 x 176 x 134 x 134, 44 MB, 15.1 -> 13.1).  Over 220 drawn sizes that this takes, geometric means: float32 2 x 2 1.29 (0.98 .. 1.8), 3 x 3 1.32 without picks and 1.42 with
+    // (0.97 .. 2.4); 16-bit storage 3 x 3 1.16 without picks (0.89 .. 2.4; with eight inputs in turn 1.32, 0.97 and more) and 1.16 with (0.91 .. 3.3).
     const int64_t cells = (int64_t)k.H * k.W;
     if (dtype == BS_F32 ? cells < 200 : p.kh == 2 || cells < 600 || (!idx && planes * cells < 20 << 20)) return false;
     const bool front = idx || !max;  // where the list has to stand
